@@ -75,23 +75,6 @@ __device__ __forceinline__ intx4 signed_filter_sums(const QConvArgs &a, int cob,
 
 // ------------------------------------------------------------------------------------------------ layouts
 
-__global__ void __launch_bounds__(256) pack_u8_kernel(const unsigned char *nchw, unsigned char *blk, int C, int HW, int Cb,
-                                                      size_t total, int unpack)
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;   // index into the blocked tensor
-    if (i >= total) return;
-    const int c_in = (int)(i % Cb);
-    const size_t t = i / Cb;
-    const int pix = (int)(t % HW);
-    const size_t t2 = t / HW;          // n * nCb + cb
-    const int nCb = C / Cb;
-    const int cb = (int)(t2 % nCb);
-    const size_t n = t2 / nCb;
-    const size_t j = (n * C + (size_t)cb * Cb + c_in) * HW + pix;
-    if (unpack) const_cast<unsigned char *>(nchw)[j] = blk[i];
-    else blk[i] = nchw[j];
-}
-
 __global__ void __launch_bounds__(256) pack_filter_u8_kernel(const unsigned char *oihw, unsigned char *blk, int Co, int Ci,
                                                              int khw, int Cob, int Cib, size_t total)
 {
@@ -847,14 +830,6 @@ QConvArgs conv_args(const unsigned char *in, const unsigned char *filt, unsigned
 }
 
 }  // namespace
-
-hipError_t launch_pack_u8(const unsigned char *nchw, unsigned char *blk, int N, int C, int H, int W, int Cb, bool unpack,
-                          hipStream_t s)
-{
-    const size_t total = (size_t)N * C * H * W;
-    hipLaunchKernelGGL(pack_u8_kernel, dim3(blocks_for(total)), dim3(256), 0, s, nchw, blk, C, H * W, Cb, total, unpack ? 1 : 0);
-    return hipGetLastError();
-}
 
 hipError_t launch_pack_filter_u8(const unsigned char *oihw, unsigned char *blk, int Co, int Ci, int kh, int kw, int Cob,
                                  int Cib, hipStream_t s)

@@ -320,7 +320,7 @@ int small_unpack_u8(const unsigned char *blocked, unsigned char *nchw, int N, in
     const size_t n = elems(N, C, H, W);
     if (!n) return SMALL_ERR_SHAPE;
     if (overlap_bytes(nchw, n, blocked, n)) return SMALL_ERR_ALIAS;
-    return from_hip(launch_pack_u8(nchw, const_cast<unsigned char *>(blocked), N, C, H, W, Cb, true, as_stream(stream)));
+    return from_hip(launch_pack_u8(blocked, nchw, N, C, H, W, Cb, true, as_stream(stream)));
 }
 
 int small_pack_filter_u8(const unsigned char *oihw, unsigned char *blocked, int Co, int Ci, int kh, int kw, int Cob,

@@ -278,7 +278,8 @@ __device__ __forceinline__ int requant_clamped(int acc, const QuantParams &q, lo
     return min(max(r, q.lo), q.hi);
 }
 
-hipError_t launch_pack_u8(const unsigned char *nchw, unsigned char *blk, int N, int C, int H, int W, int Cb, bool unpack,
+// layout change of uint8 tensors (layout_u8.hip): plain -> blocked, or blocked -> plain with unpack
+hipError_t launch_pack_u8(const unsigned char *src, unsigned char *dst, int N, int C, int H, int W, int Cb, bool unpack,
                           hipStream_t s);
 hipError_t launch_pack_filter_u8(const unsigned char *oihw, unsigned char *blk, int Co, int Ci, int kh, int kw, int Cob,
                                  int Cib, hipStream_t s);

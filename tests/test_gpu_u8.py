@@ -53,6 +53,26 @@ def test_pack_unpack(shape, Cb):
     assert np.array_equal(g2.check().reshape(shape), x)
 
 
+@pytest.mark.parametrize("Cb", [1, 2, 3, 4, 8, 16])
+@pytest.mark.parametrize("N,H,W", [(1, 1, 1), (3, 1, 3), (2, 2, 2), (5, 3, 7), (2, 16, 16), (3, 13, 21), (1, 1, 1027)])
+def test_pack_unpack_words(N, H, W, Cb):
+    """Planes of 1 .. 3 pixels, a multiple of four and every remainder, several planes to a workgroup and several
+    workgroups to a plane: copies, so bit for bit; also from and to addresses that are no multiple of four."""
+    C = 2 * Cb
+    x = WL.u8_codes(_rng(9), (N, C, H, W))
+    for off in (0, 1):
+        src = torch.zeros(x.size + off, dtype=torch.uint8, device=DEV)
+        src[off:].copy_(dev8(x.reshape(-1)))
+        g = Guarded8(x.size + off)
+        S.small_pack_u8(src[off:], g.t[off:], N, C, H, W, Cb)
+        blk = g.check()[off:]
+        assert np.array_equal(blk, Q.pack(x, Cb))
+        src[off:].copy_(dev8(blk))
+        g2 = Guarded8(x.size + off)
+        S.small_unpack_u8(src[off:], g2.t[off:], N, C, H, W, Cb)
+        assert np.array_equal(g2.check()[off:].reshape(x.shape), x)
+
+
 @pytest.mark.parametrize("Co,Ci,kh,kw,Cob,Cib", [(32, 48, 3, 3, 16, 16), (8, 3, 3, 3, 8, 3), (16, 1, 10, 4, 16, 1), (16, 8, 1, 1, 16, 8)])
 def test_pack_filter(Co, Ci, kh, kw, Cob, Cib):
     w = WL.u8_codes(_rng(1), (Co, Ci, kh, kw))
