@@ -289,6 +289,11 @@ bool conv_u8_uses_mfma(const LayerGeom &g, const void *in, const void *filt, con
 // null: the kernels then take these sums themselves, with one more matrix instruction per filter operand.
 hipError_t launch_conv_u8(const unsigned char *in, const unsigned char *filt, unsigned char *out, const LayerGeom &g,
                           const QuantParams &q, const int *filt_sums, hipStream_t s);
+// ... windows of more than one pixel through LDS tiles (conv_u8_tile.hip), where conv_u8_uses_mfma holds; filt_sums must
+// be given unless q.zx is 128, q.amax > 0
+bool conv_u8_tile_eligible(const LayerGeom &g, const QuantParams &q, const int *filt_sums, const void *out);
+hipError_t launch_conv_u8_tile(const unsigned char *in, const unsigned char *filt, unsigned char *out, const LayerGeom &g,
+                               const QuantParams &q, const int *filt_sums, hipStream_t s);
 hipError_t launch_filter_sums_u8(const unsigned char *filt, int *sums, int Co, int Ci, int kh, int kw, int Cob, int Cib,
                                  hipStream_t s);
 // mode 0: depthwise (filt [C/Cb][kh][kw][Cb]), 1: max pooling, 2: average pooling (filt unused, may be null)

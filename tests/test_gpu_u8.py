@@ -125,6 +125,46 @@ def test_conv_matrix_core(case):
     assert ref.std() > 1.5 and len(np.unique(ref)) > 8
 
 
+TILE_CASES = [  # N, Ci, Co, H, W, kh, kw, stride, pad, zx, zw: windows through LDS tiles
+    (3, 48, 48, 13, 11, 3, 3, 1, (1, 1, 1, 1), 120, 131),      # three input blocks; tiles across images; ragged last tile
+    (11, 48, 240, 26, 7, 3, 3, 1, (1, 1, 1, 1), 128, 106),     # 128 x 16 tiles, fifteen channel blocks
+    (76, 112, 112, 10, 10, 3, 3, 1, (1, 1, 1, 1), 7, 128),     # 128 x 32 tiles, seven input and output blocks
+    (40, 80, 64, 9, 33, 3, 3, 1, (1, 1, 1, 1), 255, 3),        # two strips of 17 columns, the second one column short
+    (2, 272, 16, 19, 65, 3, 3, 1, (1, 1, 1, 1), 0, 255),       # three strips; one block per instruction, four taps
+    (3, 272, 96, 37, 19, 3, 3, 2, (1, 1, 1, 1), 99, 92),       # stride 2: 32-pixel tiles
+    (1, 160, 32, 68, 15, 3, 3, 2, (0, 1, 0, 1), 130, 128),     # ... padded below and on the right only
+    (1, 384, 240, 1, 1, 3, 3, 1, (1, 1, 1, 1), 5, 250),        # one pixel: eight of nine taps outside
+    (2, 64, 80, 6, 5, 2, 7, 1, (1, 0, 3, 6), 77, 140),         # wide window, uneven padding
+    (2, 32, 16, 9, 8, 5, 3, 3, (2, 2, 1, 1), 10, 20),          # stride 3, fifteen taps
+    (4, 96, 48, 9, 9, 3, 3, 1, (0, 0, 0, 0), 128, 128),        # no padding, no correction sums
+]
+
+
+@pytest.mark.parametrize("case", TILE_CASES)
+def test_conv_tiles(case):
+    """Windows larger than a pixel with the filter's sums given: staged rows and their padding, strips, tiles that cross
+    images, the chunks a matrix instruction combines, missing input and output blocks. Integer arithmetic: exact."""
+    N, Ci, Co, H, W, kh, kw, s, pad, zx, zw = case
+    r = _rng(21)
+    x, w = WL.u8_codes(r, (N, Ci, H, W)), WL.u8_codes(r, (Co, Ci, kh, kw))
+    q = _quant_for(Q.conv2d_acc(x, w, s, pad, zx, zw), zx, zw)
+    q.lo, q.hi = 3, 250
+    ref = Q.conv2d(x, w, s, pad, q)
+    _same(_conv(x, w, s, pad, q, 16, 16, with_sums=True), ref, f"conv u8 tiles {case}")
+    assert len(np.unique(ref)) > 8
+
+
+@pytest.mark.parametrize("N,Ci,Co,H,W,k", [(64, 48, 64, 40, 40, 3), (64, 48, 32, 40, 41, 3), (90, 96, 144, 20, 21, 3), (30, 80, 16, 60, 61, 3)])
+def test_conv_tiles_large_batch(N, Ci, Co, H, W, k):
+    """The large tiles (256 x 64, 256 x 32, 128 x 128, 256 x 16), which only large layers take; four images recomputed."""
+    r = _rng(22)
+    x, w = WL.u8_codes(r, (N, Ci, H, W)), WL.u8_codes(r, (Co, Ci, k, k))
+    q = _quant(Ci * k * k, 140, 119)
+    got = _conv(x, w, 1, (1, 1, 1, 1), q, 16, 16, with_sums=True)
+    for n in (0, 1, N // 2, N - 1):
+        _same(got[n:n + 1], Q.conv2d(x[n:n + 1], w, 1, (1, 1, 1, 1), q), f"conv u8 {Ci}->{Co} image {n}")
+
+
 @pytest.mark.parametrize("case", [
     (2, 3, 8, 9, 9, 3, 3, 2, (0, 1, 0, 1), 128, 128, 3, 8),        # first layer of the depthwise-separable CNN
     (2, 1, 16, 13, 10, 10, 4, 2, (4, 5, 1, 1), 5, 140, 1, 16),     # first layer of the audio CNN
