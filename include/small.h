@@ -79,7 +79,7 @@ int small_conv2d(const float *in, const float *filt, float *out, int N, int Ci, 
                  int kw, int stride, small_pad pad, int Cib, int Cob, void *stream);
 
 /* Host only, enqueues nothing: the name of the kernel small_conv2d launches for this shape (for example
- * "conv16_mfma<4,1,2,1>" = 4x1 wavefronts of 2x1 16x16 matrix-core tiles, or "conv_direct"), so that a
+ * "conv16_same<4,1,1,2,3,1,1>" = 4x1 wavefronts of 1x2 16x16 matrix-core tiles, or "conv_direct"), so that a
  * profile's per-kernel rows can be matched to layers. Returns NULL when the arguments are invalid. */
 const char *small_conv2d_kernel(int N, int Ci, int Co, int H, int W, int kh, int kw, int stride, small_pad pad,
                                 int Cib, int Cob);

@@ -44,7 +44,8 @@ __device__ __forceinline__ floatx4 epilogue4(floatx4 v, int epi, const float *re
 }
 
 // ---------------------------------------------------------------------------------------------
-// Matrix-core path, Cib = Cob = 16, any window / stride / padding.
+// Matrix-core path, Cib = Cob = 16, any window / stride / padding: what neither conv_same.hip nor conv_split.hip takes
+// (tensors of 2 GiB and more).
 //
 // Workgroup tile: TM = WAVES_M*WM*16 flattened output pixels x TN = WAVES_N*WN*16 output channels.
 // Reduction step ("k-step") = one (Ci block, tap y, tap x): 16 input channels.
@@ -588,6 +589,7 @@ const char *conv_kernel_name(const LayerGeom &g)
         if (g.Cib == 8 && g.kh == 1 && g.kw == 1) return "conv_small<8,1,1>";
         return "conv_small<0,0,0>";
     }
+    if (conv_split_eligible(g)) return conv_split_kernel_name(g);
     if (conv_pw_eligible(g)) return conv_pw_kernel_name(g);
     const int tile = pick_tile(g);
     if (conv_same_eligible(g))
@@ -672,6 +674,7 @@ hipError_t launch_conv(const float *in, const float *filt, float *out, const flo
         hipLaunchKernelGGL(conv_direct, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a, g.Cib, g.Cob, total);
         return hipGetLastError();
     }
+    if (conv_split_eligible(g)) return launch_conv_split(in, filt, out, a.res, g, epilogue, s, bn);
     if (conv_pw_eligible(g)) return launch_conv_pw(in, filt, out, a.res, g, epilogue, s, bn);
     const int tile = pick_tile(g);
     if (conv_same_eligible(g)) return launch_conv_same(in, filt, out, a.res, g, tile, epilogue, s, 0, 0, 0, bn);

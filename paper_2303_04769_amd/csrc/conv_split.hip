@@ -1,0 +1,204 @@
+// Convolution with the reduction split over the waves of a workgroup: layers with few output pixels and a long reduction,
+// and every window, stride and padding that conv_same.hip has no tiles for.
+//
+// Bound: streaming the filter (every value is used for a handful of pixels only) and, per workgroup, a chain of matrix
+// instructions. The tiled kernels give a layer of few pixels to a few workgroups that walk the whole reduction one step
+// after the other -- 512 channels on one 6 x 6 image are 16 workgroups of 96 steps on a chip of 256 compute units. Here a
+// wave owns WM x WN tiles of 16 output pixels x 16 output channels and takes every WAVES-th reduction step, a step being
+// one (input block, tap): the waves of a workgroup read neighbouring kilobytes of the filter, each keeps kAhead steps of
+// operands in flight in registers (no LDS and no barrier in the loop), and the partial sums meet in LDS at the end, in a
+// fixed order. A tap outside the image is an offset beyond the buffer descriptor, which reads zero.
+#include "small_internal.h"
+
+namespace small {
+namespace {
+
+constexpr int kAhead = 4;              // steps of operands in flight per wave
+
+struct SplitArgs {
+    const float *in, *filt, *res, *bn;
+    float *out;
+    int H, W, HoWo, Wo, M;
+    int nCib, nCob, taps, kw, stride, pt, pl, steps;
+    int n_groups;                      // pixel groups of 16
+    int epilogue;
+    unsigned in_bytes, filt_bytes;
+    FastDiv dHoWo, dWo, dTaps, dKw, dGroups;
+};
+
+// FastDiv without a branch (a division by one is the sum's second term)
+__device__ __forceinline__ int quotient(const FastDiv &f, int n)
+{
+    const unsigned all = f.d == 1 ? ~0u : 0u;
+    return (int)((__umulhi((unsigned)n, f.magic) + ((unsigned)n & all)) >> f.shift);
+}
+
+template <int WAVES, int WM, int WN>
+__global__ void __launch_bounds__(64 * WAVES) conv16_split(SplitArgs a)
+{
+    constexpr int T = WM * WN, CH = T == 1 ? 2 : 1;            // one tile: two accumulators, so that the chain is not serial
+    __shared__ floatx4 part[WAVES][T][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int p = lane & 15, q = lane >> 4;
+    // pixel groups fastest: the workgroups that read one output block's filter meet in one L2
+    const int wg = (int)xcd_contiguous(blockIdx.x, gridDim.x);
+    const int ct = quotient(a.dGroups, wg), grp = wg - ct * a.n_groups, cob0 = ct * WN;
+    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.in), 0, a.in_bytes, kRawBuffer);
+    const __amdgpu_buffer_rsrc_t flt = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.filt), 0, a.filt_bytes, kRawBuffer);
+    const int HW = a.H * a.W;
+    int ih0[WM], iw0[WM], org[WM];                             // window origin; this lane's quad at tap (0, 0) of block 0
+#pragma unroll
+    for (int i = 0; i < WM; ++i) {
+        const int m = min((grp * WM + i) * 16 + p, a.M - 1);
+        const int n = quotient(a.dHoWo, m), rem = m - n * a.HoWo, oh = quotient(a.dWo, rem), ow = rem - oh * a.Wo;
+        ih0[i] = oh * a.stride - a.pt;
+        iw0[i] = ow * a.stride - a.pl;
+        org[i] = (n * a.nCib * HW + ih0[i] * a.W + iw0[i]) * 64 + q * 16;
+    }
+    // matrix instruction r multiplies input channel 4q + r of the step's 16 (both operands): lane (p, q) holds the input
+    // quad of pixel p and, in instruction r, the filter value [4q + r][p]
+    unsigned f_lane[WN];
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+        f_lane[j] = cob0 + j < a.nCob ? (unsigned)((cob0 + j) * a.steps) * 1024u + (unsigned)(q * 64 + p) * 4u : kBeyond;
+
+    floatx4 x[kAhead][WM];
+    float w[kAhead][WN][4];
+    auto request = [&](int s, floatx4 (&xs)[WM], float (&ws)[WN][4]) __attribute__((always_inline)) {
+        const int sc = s < a.steps ? s : 0;
+        const int cib = quotient(a.dTaps, sc), tap = sc - cib * a.taps, y = quotient(a.dKw, tap), z = tap - y * a.kw;    // wave-uniform
+#pragma unroll
+        for (int i = 0; i < WM; ++i) {
+            const bool inside = ((unsigned)(ih0[i] + y) < (unsigned)a.H) & ((unsigned)(iw0[i] + z) < (unsigned)a.W) & (s < a.steps);
+            const unsigned at = (unsigned)(org[i] + (cib * HW + y * a.W + z) * 64);
+            xs[i] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(src, inside ? at : kBeyond, 0, 0));
+        }
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                ws[j][r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(flt, s < a.steps ? f_lane[j] + (unsigned)sc * 1024u + 64u * r : kBeyond, 0, 0));
+    };
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) request(wave + i * WAVES, x[i], w[i]);
+    floatx4 acc[WM][WN][CH];
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) acc[i][j][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int s = wave; s < a.steps; s += kAhead * WAVES) {
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            // (steps past the end multiply zeros by zeros)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int i = 0; i < WM; ++i)
+#pragma unroll
+                    for (int j = 0; j < WN; ++j)
+                        acc[i][j][r % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[k][j][r], x[k][i][r], acc[i][j][r % CH], 0, 0, 0);
+            request(s + (k + kAhead) * WAVES, x[k], w[k]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j) part[wave][i * WN + j][lane] = CH == 2 ? acc[i][j][0] + acc[i][j][CH - 1] : acc[i][j][0];
+    __syncthreads();
+    for (int t = wave; t < T; t += WAVES) {
+        floatx4 v = part[0][t][lane];
+#pragma unroll
+        for (int k = 1; k < WAVES; ++k) v += part[k][t][lane];
+        const int m = (grp * WM + t / WN) * 16 + p, cob = cob0 + t % WN;
+        if (m >= a.M || cob >= a.nCob) continue;
+        const int n = quotient(a.dHoWo, m), rem = m - n * a.HoWo;
+        const size_t o = ((size_t)(n * a.nCob + cob) * a.HoWo + rem) * 16 + q * 4;
+        if (a.epilogue & EPI_BN) {
+            const float *c = a.bn + cob * 16 + q * 4;
+            const floatx4 sc = *reinterpret_cast<const floatx4 *>(c), sh = *reinterpret_cast<const floatx4 *>(c + a.nCob * 16);
+            v.x = fmaf(v.x, sc.x, sh.x); v.y = fmaf(v.y, sc.y, sh.y); v.z = fmaf(v.z, sc.z, sh.z); v.w = fmaf(v.w, sc.w, sh.w);
+        }
+        if (a.epilogue & EPI_ADD) v += *reinterpret_cast<const floatx4 *>(a.res + o);
+        if (a.epilogue & EPI_RELU) {
+            v.x = v.x > 0.f ? v.x : 0.f; v.y = v.y > 0.f ? v.y : 0.f;
+            v.z = v.z > 0.f ? v.z : 0.f; v.w = v.w > 0.f ? v.w : 0.f;
+        }
+        *reinterpret_cast<floatx4 *>(a.out + o) = v;
+    }
+}
+
+struct Variant { int waves, wm, wn; const char *name; };
+constexpr Variant kVariants[] = {{16, 1, 1, "conv16_split<16,1,1>"}, {8, 1, 1, "conv16_split<8,1,1>"}, {4, 1, 1, "conv16_split<4,1,1>"},
+                                 {4, 2, 1, "conv16_split<4,2,1>"},   {4, 2, 2, "conv16_split<4,2,2>"}, {2, 2, 2, "conv16_split<2,2,2>"}};
+
+long split_steps(const LayerGeom &g) { return (long)(g.Ci / 16) * g.kh * g.kw; }
+long split_tiles(const LayerGeom &g) { return ((long)g.N * g.Ho * g.Wo + 15) / 16 * (g.Co / 16); }
+
+// Up to about five 16 x 16 tiles per compute unit every tile is a workgroup of its own, split the more ways the longer its
+// reduction and the fewer the workgroups; beyond, waves own more tiles (operands serve two of them) and split less. Sweep
+// over random layers, us: 96 tiles of 288 steps 10.4 / 15.9 / 11.9 with 16 / 8 / 4 waves; 90 tiles of 125 steps 7.8 / 7.2 /
+// 7.3; 999 tiles of 243 steps 28.1 / 25.9 / 24.7; 3006 tiles of 25 steps 15.6 with <4,1,1>, 11.3 with <4,2,2>; 13128 tiles of
+// 25 steps 44.5, 35.3, and 33.7 with <2,2,2>.
+int pick_variant(const LayerGeom &g)
+{
+    const long steps = split_steps(g), tiles = split_tiles(g), cus = device_cus();
+    if (2 * tiles <= 3 * cus) return steps >= 200 ? 0 : steps >= 64 ? 1 : 2;
+    if (2 * tiles <= 11 * cus) return 2;
+    if (g.Co == 16) return 3;
+    return tiles <= 24 * cus ? 4 : 5;
+}
+
+template <int WAVES, int WM, int WN>
+hipError_t run(const SplitArgs &a, hipStream_t s)
+{
+    const dim3 grid((unsigned)(a.n_groups * ((a.nCob + WN - 1) / WN)));
+    hipLaunchKernelGGL((conv16_split<WAVES, WM, WN>), grid, dim3(64 * WAVES), 0, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool conv_split_eligible(const LayerGeom &g)
+{
+    const long M = (long)g.N * g.Ho * g.Wo, steps = split_steps(g), tiles = split_tiles(g), cus = device_cus();
+    if (g.Cib != 16 || g.Cob != 16 || M >= (1L << 30) || tiles >= (1L << 30) || steps >= (1L << 20) ||
+        (size_t)g.N * g.Ci * g.H * g.W * 4 >= kBeyond || (size_t)g.Co * g.Ci * g.kh * g.kw * 4 >= kBeyond)
+        return false;
+    if (!conv_same_eligible(g)) return true;       // against the gather kernel of conv.hip: 0.96 to 12 times as fast
+    // Against the tiles of conv_same.hip (their us / here): up to one tile per compute unit from 6 steps on (189 tiles of 7
+    // steps 3.9 / 3.1, 96 of 288 36.0 / 10.4), up to two for reductions of 32 (510 of 45 7.7 / 5.0; but 288 of 18 4.6 / 4.5), up
+    // to four for 200 (999 of 243 45.7 / 24.7; but 912 of 144 19.5 / 21.5); above that they win (2090 of 45 13.3 / 12.8, 4032 of
+    // 63 21.3 / 25.5).
+    return tiles <= cus ? steps >= 6 : tiles <= 2 * cus ? steps >= 32 : tiles <= 4 * cus && steps >= 200;
+}
+
+const char *conv_split_kernel_name(const LayerGeom &g) { return kVariants[pick_variant(g)].name; }
+
+hipError_t launch_conv_split(const float *in, const float *filt, float *out, const float *res, const LayerGeom &g, int epilogue,
+                             hipStream_t s, const float *bn)
+{
+    SplitArgs a;
+    a.in = in; a.filt = filt; a.out = out; a.res = res; a.bn = bn;
+    a.H = g.H; a.W = g.W; a.Wo = g.Wo; a.HoWo = g.Ho * g.Wo; a.M = g.N * a.HoWo;
+    a.nCib = g.Ci / 16; a.nCob = g.Co / 16; a.taps = g.kh * g.kw; a.kw = g.kw;
+    a.stride = g.stride; a.pt = g.pt; a.pl = g.pl; a.steps = a.nCib * a.taps;
+    const int v = pick_variant(g);
+    a.n_groups = (a.M + 16 * kVariants[v].wm - 1) / (16 * kVariants[v].wm);
+    a.epilogue = epilogue;
+    a.in_bytes = (unsigned)((size_t)g.N * g.Ci * g.H * g.W * 4);
+    a.filt_bytes = (unsigned)((size_t)g.Co * g.Ci * a.taps * 4);
+    a.dHoWo = make_fastdiv(a.HoWo); a.dWo = make_fastdiv(a.Wo); a.dTaps = make_fastdiv(a.taps); a.dKw = make_fastdiv(a.kw);
+    a.dGroups = make_fastdiv(a.n_groups);
+    switch (v) {
+        case 0: return run<16, 1, 1>(a, s);
+        case 1: return run<8, 1, 1>(a, s);
+        case 2: return run<4, 1, 1>(a, s);
+        case 3: return run<4, 2, 1>(a, s);
+        case 4: return run<4, 2, 2>(a, s);
+        default: return run<2, 2, 2>(a, s);
+    }
+}
+
+}  // namespace small

@@ -205,6 +205,44 @@ def test_conv2d_first_layer_matrix_core(case):
     assert_close(got, O.conv2d(x, w, s, pad), Ci * kh * kw, f"first layer {case}, all {N} images")
 
 
+SPLIT_CASES = [  # N, Ci, Co, H, W, kh, kw, stride, pad, kernel: the reduction split over the waves of a workgroup
+    (1, 512, 48, 6, 6, 3, 3, 1, (1, 1, 1, 1), "16,1,1"),       # 288 steps, 36 pixels: a ragged third pixel group
+    (2, 80, 80, 6, 94, 5, 5, 2, (2, 2, 2, 2), "8,1,1"),        # 125 steps
+    (1, 96, 16, 1, 1, 3, 3, 1, (1, 1, 1, 1), "4,1,1"),         # one pixel, eight of nine taps outside
+    (5, 16, 32, 9, 7, 2, 2, 1, (1, 0, 0, 1), "4,1,1"),         # 4 steps: one per wave; a window without a middle
+    (3, 32, 48, 23, 11, 3, 3, 3, (2, 1, 0, 2), "4,1,1"),       # stride 3, uneven padding
+    (20, 16, 16, 68, 68, 3, 3, 2, (1, 1, 1, 1), "4,2,1"),      # one output block, many pixels
+    (12, 32, 48, 70, 70, 3, 3, 2, (1, 1, 1, 1), "4,2,2"),      # three output blocks: the last workgroup has one
+    (31, 16, 112, 59, 60, 3, 3, 2, (1, 1, 1, 1), "2,2,2"),     # seven output blocks; pixels end inside a group
+]
+
+
+@pytest.mark.parametrize("case", SPLIT_CASES)
+def test_conv2d_split_reduction(case):
+    N, Ci, Co, H, W, kh, kw, s, pad, variant = case
+    assert S.small_conv2d_kernel(N, Ci, Co, H, W, kh, kw, s, pad, 16, 16) == f"conv16_split<{variant}>", case
+    rng = np.random.default_rng(8100 + N + Ci)
+    x = (rng.random((N, Ci, H, W), dtype=np.float32) * 2 - 1).astype(np.float32)
+    w = (rng.random((Co, Ci, kh, kw), dtype=np.float32) * 2 - 1).astype(np.float32)
+    got = run_conv(x, w, s, pad)
+    assert_close(got, O.conv2d(x, w, s, pad), Ci * kh * kw, f"conv split {case}")
+
+
+def test_conv2d_split_reduction_infinities():
+    """An infinite filter value in the first step and an infinite input value reach the outputs that contain them and no
+    other: what a wave multiplies past its last step is zero by zero."""
+    rng = np.random.default_rng(8200)
+    x = (rng.random((1, 32, 5, 5), dtype=np.float32) + 1).astype(np.float32)
+    w = (rng.random((32, 32, 3, 3), dtype=np.float32) + 1).astype(np.float32)
+    w[3, 0, 0, 0] = np.inf
+    x[0, 17, 4, 4] = -np.inf
+    assert S.small_conv2d_kernel(1, 32, 32, 5, 5, 3, 3, 1, (0, 0, 0, 0), 16, 16).startswith("conv16_split")
+    got = run_conv(x, w, 1, (0, 0, 0, 0))
+    assert (got[0, 3].reshape(-1)[:8] == np.inf).all() and np.isnan(got[0, 3, 2, 2])
+    rest = np.delete(got[0], 3, axis=0)
+    assert (rest[:, 2, 2] == -np.inf).all() and np.isfinite(rest.reshape(31, 9)[:, :8]).all()
+
+
 def test_conv_identity_filter_is_exact():
     rng = np.random.default_rng(5)
     x = rng.standard_normal((2, 32, 10, 12)).astype(np.float32)
