@@ -194,7 +194,10 @@ int small_add_u8(const unsigned char *a, const unsigned char *b, unsigned char *
  * the pools have none (codes in, codes out, same scale). filt: blocked uint8 filter in the layout of
  * small_conv2d_u8 / small_dwconv2d_u8, filt_sums: optional, as for small_conv2d_u8. Layers run one after the other
  * through the entry points above, except that an in-place ReLU directly after a CONV / DWCONV / DENSE / ADD goes
- * into that layer's lower clamp (lo = max(lo, z): the same codes). Results are bit-exact.
+ * into that layer's lower clamp (lo = max(lo, z): the same codes), and that, up to two images per compute unit, three and
+ * more layers in a row whose tensors are small run as ONE launch, one image per workgroup (16-channel blocks; CONV,
+ * DWCONV, ADD, DENSE, AVGPOOL over the whole image; at most 64 KB per image's tensor and per filter): buffers written
+ * inside such a run that no later layer reads before rewriting them are then never written. Results are bit-exact.
  * small_network_workspace_u8: bytes of workspace (host only). small_network_run_u8: in_blocked [N][C0/Cb0][H0][W0][Cb0]
  * bytes with Cb0 = layers[0].Cib; out_blocked receives every write to SMALL_BUF_OUT; workspace 256-byte aligned. */
 typedef struct {

@@ -446,6 +446,99 @@ bool relu_follows_u8(const small_layer_u8 *L, int nL, int i)
     return r.q.zy >= 0 && r.q.zy <= hi;
 }
 
+// The lower clamp with an in-place ReLU behind the layer folded in (relu_follows_u8 holds).
+void fold_relu_u8(small_layer_u8 &l, const small_layer_u8 &relu)
+{
+    int &lo = l.op == SMALL_OP_ADD ? l.qa.lo : l.q.lo;
+    lo = lo > relu.q.zy ? lo : relu.q.zy;
+}
+
+// Whether buffer `id` is rewritten or never touched before anyone reads it in layers [from, nL). The caller's output
+// buffer is always read.
+bool dead_from_u8(const small_layer_u8 *L, int nL, int from, int id)
+{
+    if (id == SMALL_BUF_OUT) return false;
+    for (int j = from; j < nL; ++j) {
+        if (L[j].src == id || (L[j].op == SMALL_OP_ADD && L[j].src2 == id)) return false;
+        if (L[j].dst == id) return true;
+    }
+    return true;
+}
+
+// The longest image-resident run of a checked table from layer i on: its launch groups in g, how many in n_groups, the table's
+// layers it covers as the result (0: none of at least three groups). Every buffer it writes but the last layer's destination
+// is never written to memory, so nothing after the run may read it; nothing but the run's source may come from outside.
+int plan_resident_u8(const small_layer_u8 *L, int nL, int i, const ShapeU8 *shp_now, RU8Group *g, int &n_groups)
+{
+    ShapeU8 store[SMALL_MAX_SLOTS + 2] = {};
+    ShapeU8 *shp = store + 2;                                  // what the run itself holds
+    const int source = L[i].src;
+    shp[source] = shp_now[source];
+    bool written[SMALL_MAX_SLOTS + 2] = {};
+    int n = 0, covered = 0;
+    n_groups = 0;
+    for (int j = i; j < nL && n < kRU8MaxLayers; ++j) {
+        small_layer_u8 l = L[j];
+        const bool fold = (l.op == SMALL_OP_CONV || l.op == SMALL_OP_DWCONV || l.op == SMALL_OP_DENSE || l.op == SMALL_OP_ADD) &&
+                          relu_follows_u8(L, nL, j);
+        if (fold) fold_relu_u8(l, L[j + 1]);
+        if (!shp[l.src].set || l.Cib != 16 || (l.op != SMALL_OP_ADD && l.dst == l.src)) break;
+        const ShapeU8 si = shp[l.src];
+        RU8Group &d = g[n];
+        d = RU8Group{};
+        d.src = d.src2 = l.src + 2; d.dst = l.dst + 2;
+        d.Ci = l.Ci; d.Co = l.Co; d.Cob = l.Cob; d.H = si.H; d.W = si.W;
+        d.kh = l.kh; d.kw = l.kw; d.stride = l.stride; d.pt = l.pad.t; d.pl = l.pad.l;
+        d.filt = l.filt; d.sums = l.filt_sums;
+        int pb = l.pad.b, pr = l.pad.r;
+        if (l.op == SMALL_OP_CONV || l.op == SMALL_OP_DENSE) {
+            if (l.op == SMALL_OP_DENSE) { d.stride = 1; d.pt = d.pl = pb = pr = 0; }
+            d.kind = l.Cob == 16 ? RU8_CONV : RU8_DENSE;
+            if (d.kind == RU8_DENSE && (si.H != 1 || si.W != 1 || l.kh != 1 || l.kw != 1 || d.pt || d.pl || pb || pr)) break;
+            if (check_quant(&l.q, (long)l.Ci * l.kh * l.kw, d.q)) break;
+        } else if (l.op == SMALL_OP_DWCONV) {
+            d.kind = RU8_DW;
+            if (check_quant(&l.q, (long)l.kh * l.kw, d.q)) break;
+        } else if (l.op == SMALL_OP_ADD) {
+            if (!shp[l.src2].set || check_quant_add(&l.qa, d.qa)) break;
+            d.kind = RU8_ADD;
+            d.src2 = l.src2 + 2;
+            d.kh = d.kw = d.stride = 1; d.pt = d.pl = pb = pr = 0;
+        } else if (l.op == SMALL_OP_AVGPOOL && l.kh == si.H && l.kw == si.W && !l.pad.t && !l.pad.b && !l.pad.l && !l.pad.r) {
+            d.kind = RU8_AVG;
+            d.stride = 1;
+        } else {
+            break;
+        }
+        d.Ho = small_out_dim(si.H, d.kh, d.stride, d.pt, pb);
+        d.Wo = small_out_dim(si.W, d.kw, d.stride, d.pl, pr);
+        if (!resident_u8_takes(d) || !resident_u8_fits(g, n + 1)) break;
+        ++n;
+        shp[l.dst] = ShapeU8{l.Co, d.Ho, d.Wo, l.Cob, true};
+        written[l.dst + 2] = true;
+        if (fold) ++j;
+        // may the run end here?
+        bool closed = n >= 3;
+        for (int b = 0; closed && b < SMALL_MAX_SLOTS + 2; ++b)
+            if (written[b] && b != l.dst + 2 && !dead_from_u8(L, nL, j + 1, b - 2)) closed = false;
+        if (closed) { n_groups = n; covered = j + 1 - i; }
+        if (d.kind == RU8_DENSE) break;
+    }
+    return covered;
+}
+
+// When a run is worth it: up to two images per compute unit (us, layer by layer / one launch: audio CNN 41.4 / 28.5 at 100
+// images, 73.4 / 54.2 at 512, 103.6 / 101.8 at 1024; residual CNN 51.9 / 36.8, 98.5 / 73.4, 150 / 141; depthwise-separable CNN
+// 102 / 55, 150 / 114, 206 / 209), and layers of at most 1.5 million multiply-adds per image on average: a layer's fixed cost
+// falls from some 4 us to 1.2, its arithmetic on one compute unit runs at 0.6 multiply-adds per picosecond.
+bool resident_u8_batch(const RU8Group *g, int n, int N)
+{
+    double macs = 0;
+    for (int k = 0; k < n; ++k)
+        if (g[k].kind == RU8_CONV || g[k].kind == RU8_DENSE) macs += (double)g[k].Co * g[k].Ho * g[k].Wo * g[k].Ci * g[k].kh * g[k].kw;
+    return N <= 2 * device_cus() && macs <= 1.5e6 * n;
+}
+
 // run = false: shapes, parameters and workspace sizes only. Every layer is checked before the first one runs
 // (the caller walks twice).
 int walk_u8(const small_layer_u8 *L, int nL, int N, int C0, int H0, int W0, NetPlanU8 &plan, bool run, const unsigned char *in,
@@ -468,12 +561,28 @@ int walk_u8(const small_layer_u8 *L, int nL, int N, int C0, int H0, int W0, NetP
         if (!valid_buf(l.src) || !valid_buf(l.dst) || l.dst == SMALL_BUF_IN || !shp[l.src].set) return SMALL_ERR_LAYER;
         const ShapeU8 si = shp[l.src];
         if (l.Ci != si.C || l.Cib != si.Cb) return SMALL_ERR_LAYER;
+        if (run && l.Cib == 16) {
+            RU8Group groups[kRU8MaxLayers];
+            int n_groups = 0;
+            const int used = plan_resident_u8(L, nL, i, shp, groups, n_groups);
+            if (used) {
+                const RU8Group &last = groups[n_groups - 1];
+                const unsigned char *from = ptr(l.src);
+                unsigned char *to = ptr(last.dst - 2);
+                const size_t n_in = (size_t)N * si.C * si.H * si.W, n_out = (size_t)N * last.Co * last.Ho * last.Wo;
+                const bool aligned = ((uintptr_t)from & 15u) == 0 && (last.kind == RU8_DENSE || ((uintptr_t)to & 15u) == 0);
+                if (aligned && resident_u8_batch(groups, n_groups, N) && !overlap_bytes(from, n_in, to, n_out)) {
+                    if (int rc = from_hip(launch_resident_u8(groups, n_groups, from, to, N, s))) return rc;
+                    for (int k = 0; k < n_groups; ++k)
+                        shp[groups[k].dst - 2] = ShapeU8{groups[k].Co, groups[k].Ho, groups[k].Wo, groups[k].kind == RU8_DENSE ? groups[k].Cob : 16, true};
+                    i += used - 1;
+                    continue;
+                }
+            }
+        }
         const bool fold = (l.op == SMALL_OP_CONV || l.op == SMALL_OP_DWCONV || l.op == SMALL_OP_DENSE || l.op == SMALL_OP_ADD) &&
                           relu_follows_u8(L, nL, i);
-        if (fold) {
-            if (l.op == SMALL_OP_ADD) l.qa.lo = l.qa.lo > L[i + 1].q.zy ? l.qa.lo : L[i + 1].q.zy;
-            else l.q.lo = l.q.lo > L[i + 1].q.zy ? l.q.lo : L[i + 1].q.zy;
-        }
+        if (fold) fold_relu_u8(l, L[i + 1]);
         ShapeU8 so = ShapeU8{l.Co, si.H, si.W, l.Cob, true};
         int rc = SMALL_OK;
         LayerGeom g;

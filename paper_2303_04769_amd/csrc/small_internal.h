@@ -334,4 +334,23 @@ struct AddQuantParams { int za, zb, zy, mult_a, mult_b, shift, lo, hi; };
 hipError_t launch_add_u8(const unsigned char *a, const unsigned char *b, unsigned char *out, size_t n, const AddQuantParams &q,
                          hipStream_t s);
 
+// Image-resident runs of quantized layers (resident_u8.hip): one image per workgroup, every tensor in LDS. Kinds:
+// convolution or fully connected layer on 16-channel blocks in and out; depthwise 3x3; addition; average pooling over the
+// whole image; a fully connected layer with fewer than 16 outputs per block on a 1x1 image (only as the last one).
+enum : int { RU8_CONV = 0, RU8_DW = 1, RU8_ADD = 2, RU8_AVG = 3, RU8_DENSE = 4 };
+constexpr int kRU8MaxLayers = 36, kRU8Buffers = 10;
+struct RU8Group {
+    int kind, src, src2, dst;                 // buffers 0 .. kRU8Buffers - 1; images [C/16][H][W][16] in each
+    int Ci, Co, Cob, H, W, Ho, Wo, kh, kw, stride, pt, pl;
+    const unsigned char *filt;
+    const int *sums;                          // channel sums of the filter, or null
+    QuantParams q;
+    AddQuantParams qa;
+};
+size_t ru8_filter_bytes(const RU8Group &g);
+bool resident_u8_takes(const RU8Group &g);            // the layer by itself
+bool resident_u8_fits(const RU8Group *g, int n);      // LDS for the run
+// in: the first layer's source, out: the last one's result (16-byte aligned, out of a closing fully connected layer any)
+hipError_t launch_resident_u8(const RU8Group *g, int n, const unsigned char *in, unsigned char *out, int N, hipStream_t s);
+
 }  // namespace small

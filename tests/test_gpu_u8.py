@@ -618,3 +618,55 @@ def test_depthwise_extreme_scales(mult, shift):
     g = Guarded8(ref.size)
     S.small_dwconv2d_u8(dev8(Q.pack(x, 16)), dev8(Q.pack_dw_filter(w, 16)), g.t, 3, 32, 9, 20, 3, 3, 1, (1, 1, 1, 1), 16, q)
     _same(Q.unpack(g.check(), ref.shape, 16), ref, f"dw u8 scale {mult} / 2^{shift}")
+
+
+def _resident_table(C0, H, W, tail):
+    """Convolutions with odd windows, strides and paddings, a depthwise 5x3, a residual addition into a third buffer, and
+    one of the ends: a fully connected head, a tensor, a max pooling (which no image-resident run takes)."""
+    from workloads.nets import Layer, Network, OUT
+    L = [Layer("conv", C0, 32, H, W, 3, 3, 1, (1, 1, 1, 1), src=-1, dst=0, w=0)]
+    H1, W1 = L[0].Ho, L[0].Wo
+    L.append(Layer("relu", 32, 32, H1, W1, src=0, dst=0))
+    L.append(Layer("dw", 32, 32, H1, W1, 5, 3, 1, (2, 2, 1, 1), src=0, dst=1, w=1))
+    L.append(Layer("conv", 32, 32, H1, W1, 1, 1, 1, (0, 0, 0, 0), src=1, dst=2, w=2))
+    L.append(Layer("add", 32, 32, H1, W1, src=2, src2=0, dst=3))
+    L.append(Layer("relu", 32, 32, H1, W1, src=3, dst=3))
+    L.append(Layer("conv", 32, 80, H1, W1, 2, 3, 2, (1, 0, 0, 2), src=3, dst=1, w=3))
+    H2, W2 = L[-1].Ho, L[-1].Wo
+    L.append(Layer("dw", 80, 80, H2, W2, 3, 3, 2, (0, 1, 1, 1), src=1, dst=0, w=4))
+    H3, W3 = L[-1].Ho, L[-1].Wo
+    shapes = [((32, C0, 3, 3), 9 * C0), ((32, 1, 5, 3), 15), ((32, 32, 1, 1), 32), ((80, 32, 2, 3), 192), ((80, 1, 3, 3), 9)]
+    if tail == "head":
+        L.append(Layer("avgpool", 80, 80, H3, W3, H3, W3, 1, src=0, dst=1))
+        L.append(Layer("dense", 80, 11, 1, 1, 1, 1, 1, src=1, dst=OUT, w=5, Cob=11, Ho=1, Wo=1))
+        shapes.append(((11, 80, 1, 1), 80))
+    elif tail == "tensor":
+        L.append(Layer("conv", 80, 16, H3, W3, 1, 1, 1, (0, 0, 0, 0), src=0, dst=OUT, w=5))
+        shapes.append(((16, 80, 1, 1), 80))
+    else:                       # buffer 3, written inside the first run, is read again behind it
+        L.append(Layer("maxpool", 80, 80, H3, W3, 2, 2, 1, (0, 0, 0, 0), src=0, dst=1))
+        L.append(Layer("conv", 32, 16, H1, W1, 3, 3, 1, (1, 1, 1, 1), src=3, dst=OUT, w=5))
+        shapes.append(((16, 32, 3, 3), 288))
+    return Network("resident_" + tail, C0, H, W, L, shapes)
+
+
+@pytest.mark.parametrize("tail", ["head", "tensor", "reread"])
+@pytest.mark.parametrize("N,C0,H,W", [(1, 16, 7, 9), (3, 48, 13, 11), (515, 16, 9, 6), (300, 16, 25, 20)])
+def test_network_resident_runs(tail, N, C0, H, W):
+    """Image-resident runs and the layers beside them with zero points away from 128: images of one and of many pixel
+    groups, one image and several rounds of them, a batch past the rule's end; every image against the oracle."""
+    net = _resident_table(C0, H, W, tail)
+    x, ws, qs = WL.quantized_network_tensors(net, N, 77 + N)
+    r = _rng(31)
+    for q in qs:
+        if q is None:
+            continue
+        for k in ("zx", "zw", "za", "zb", "zy", "z"):
+            if k in q:
+                q[k] = int(r.integers(100, 156))
+    last = net.layers[-1]
+    idx = np.arange(N) if N < 100 else np.r_[0:6, N // 2:N // 2 + 6, N - 6:N]
+    ref = Q.run_network(net, x[idx], ws, qs)
+    got = _run_u8(net, x, ws, qs).reshape((N,) + ref.shape[1:])
+    _same(got[idx], ref, f"u8 resident {tail} {N}x{C0}x{H}x{W}")
+    assert len(np.unique(ref)) > 8 and last.dst == -2
