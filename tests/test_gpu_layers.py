@@ -205,6 +205,29 @@ def test_conv2d_first_layer_matrix_core(case):
     assert_close(got, O.conv2d(x, w, s, pad), Ci * kh * kw, f"first layer {case}, all {N} images")
 
 
+FIRST_LAYER_FEW_CASES = [  # N, Ci, Co, H, W, kh, kw, stride, pad: fewer than 16384 output pixels
+    (1, 3, 16, 32, 32, 3, 3, 1, (1, 1, 1, 1)),       # 1024 pixels: 16 workgroups of 64
+    (1, 3, 8, 96, 96, 3, 3, 2, (0, 1, 0, 1)),        # 8-channel output block
+    (3, 1, 64, 49, 10, 10, 4, 2, (4, 5, 1, 1)),      # four output blocks; 375 pixels: a ragged last group
+    (1, 3, 32, 1, 1, 3, 3, 1, (1, 1, 1, 1)),         # one pixel
+    (2, 8, 16, 7, 9, 1, 1, 1, (0, 0, 0, 0)),         # K = 8
+    (2, 5, 16, 11, 6, 2, 4, 1, (1, 0, 2, 1)),        # K = 40, five channels
+    (130, 3, 16, 11, 11, 3, 3, 1, (1, 1, 1, 1)),     # 15730 pixels: just below the limit
+]
+
+
+@pytest.mark.parametrize("case", FIRST_LAYER_FEW_CASES)
+def test_conv2d_first_layer_few_pixels(case):
+    N, Ci, Co, H, W, kh, kw, s, pad = case
+    name = S.small_conv2d_kernel(N, Ci, Co, H, W, kh, kw, s, pad, Ci, _blk(Co))
+    assert name.startswith("conv_first_mfma") and name.endswith(",1>"), (case, name)
+    rng = np.random.default_rng(4300 + N)
+    x = (rng.random((N, Ci, H, W), dtype=np.float32) * 2 - 1).astype(np.float32)
+    w = (rng.random((Co, Ci, kh, kw), dtype=np.float32) * 2 - 1).astype(np.float32)
+    got = run_conv(x, w, s, pad)
+    assert_close(got, O.conv2d(x, w, s, pad), Ci * kh * kw, f"first layer {case}")
+
+
 SPLIT_CASES = [  # N, Ci, Co, H, W, kh, kw, stride, pad, kernel: the reduction split over the waves of a workgroup
     (1, 512, 48, 6, 6, 3, 3, 1, (1, 1, 1, 1), "16,1,1"),       # 288 steps, 36 pixels: a ragged third pixel group
     (2, 80, 80, 6, 94, 5, 5, 2, (2, 2, 2, 2), "8,1,1"),        # 125 steps
