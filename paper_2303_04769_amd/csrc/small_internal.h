@@ -199,6 +199,13 @@ const char *conv_split_kernel_name(const LayerGeom &g);
 hipError_t launch_conv_split(const float *in, const float *filt, float *out, const float *res, const LayerGeom &g, int epilogue,
                              hipStream_t s, const float *bn = nullptr);
 
+// Windows of more than one pixel on the bf16 matrix cores, every value as a sum of three bf16 ones (conv_split3.hip).
+// 16-channel blocks, 16-byte aligned pointers, input and filter below 2 GiB.
+bool conv_split3_eligible(const LayerGeom &g);
+const char *conv_split3_kernel_name();
+hipError_t launch_conv_split3(const float *in, const float *filt, float *out, const float *res, const LayerGeom &g, int epilogue,
+                              hipStream_t s, const float *bn = nullptr);
+
 // Depthwise 3x3 (+ ReLU) followed by pointwise 1x1 (+ ReLU) in one launch, 16-channel blocks. dwpw_eligible looks
 // at what a layer table states (channels, blocks, windows, strides); dwpw_geom_ok at the image geometry.
 constexpr size_t kDwPwMaxLds = 160 * 1024;

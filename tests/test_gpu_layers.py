@@ -266,6 +266,57 @@ def test_conv2d_split_reduction_infinities():
     assert (rest[:, 2, 2] == -np.inf).all() and np.isfinite(rest.reshape(31, 9)[:, :8]).all()
 
 
+SPLIT3_CASES = [  # N, Ci, Co, H, W, kh, kw, pad: stride 1, at least 240 tiles of 128 pixels x 64 channels
+    (40, 32, 64, 28, 28, 3, 3, (1, 1, 1, 1)),        # one chunk of two input blocks
+    (21, 32, 112, 29, 31, 3, 3, (1, 1, 1, 1)),       # seven output blocks; two strips, the second a column short; ragged end
+    (640, 64, 64, 7, 7, 3, 3, (1, 1, 1, 1)),         # tiles over three images
+    (24, 16, 64, 37, 35, 5, 5, (2, 2, 2, 2)),        # one input block: two taps a step, the last step has one
+    (12, 48, 64, 53, 50, 2, 4, (1, 0, 0, 3)),        # an odd input block, a window without a middle, uneven padding
+    (40, 112, 64, 30, 30, 3, 3, (0, 0, 0, 0)),       # seven input blocks, no padding
+]
+
+
+@pytest.mark.parametrize("case", SPLIT3_CASES)
+@pytest.mark.parametrize("scale", [1.0, 1e18])
+def test_conv2d_three_part_products(case, scale):
+    N, Ci, Co, H, W, kh, kw, pad = case
+    assert S.small_conv2d_kernel(N, Ci, Co, H, W, kh, kw, 1, pad, 16, 16).startswith("conv16_split3"), case
+    rng = np.random.default_rng(8300 + N + Ci)
+    x = ((rng.random((N, Ci, H, W), dtype=np.float32) * 2 - 1) * np.float32(scale)).astype(np.float32)
+    w = (rng.random((Co, Ci, kh, kw), dtype=np.float32) * 2 - 1).astype(np.float32)
+    got = run_conv(x, w, 1, pad)
+    idx = np.r_[0, 1, N // 2, N - 1]
+    ref = O.conv2d(x[idx], w, 1, pad)
+    # K products of 24-bit operands, what the three parts drop (2^-26 of each) and the fp32 sums: below K 2^-24 of the largest
+    bound = Ci * kh * kw * 2.0 ** -24 * scale
+    assert np.isfinite(got).all() and np.abs(got[idx].astype(np.float64) - ref).max() <= bound + 2.0 ** -22 * np.abs(ref).max()
+
+
+def test_conv2d_three_part_products_infinities():
+    """Values without three parts: a workgroup that meets one computes its tile value by value. An infinity and a NaN in the
+    input, a filter value that rounds past the largest bf16, and the largest float."""
+    N, C, H = 40, 64, 28
+    rng = np.random.default_rng(8400)
+    x = (rng.random((N, C, H, H), dtype=np.float32) * 2 - 1).astype(np.float32)
+    w = (rng.random((C, C, 3, 3), dtype=np.float32) + np.float32(0.5)).astype(np.float32)
+    x[3, 5, 10, 11], x[7, 63, 0, 0], x[9, 0, 27, 27] = np.inf, np.nan, np.finfo(np.float32).max
+    clean = run_conv(np.nan_to_num(np.where(np.abs(x) > 2, 0, x), nan=0.0), w, 1, (1, 1, 1, 1))
+    got = run_conv(x, w, 1, (1, 1, 1, 1))
+    ref = O.conv2d(x[[3, 7, 9]], w, 1, (1, 1, 1, 1))
+    bad = ~np.isfinite(ref)
+    assert np.array_equal(np.isnan(got[[3, 7, 9]]), np.isnan(ref)) and np.array_equal(got[[3, 7, 9]] == np.inf, ref == np.inf)
+    assert bad[0].sum() == 9 * C and bad[1].sum() == 4 * C
+    ok = np.isfinite(ref) & (np.abs(ref) < 1e6)
+    assert np.abs(got[[3, 7, 9]][ok] - ref[ok]).max() <= 576 * 2.0 ** -23 * 1.5
+    rest = np.delete(np.arange(N), [3, 7, 9])
+    assert np.abs(got[rest] - clean[rest]).max() <= 576 * 2.0 ** -23 * 1.5
+    w[17, 3, 1, 1] = np.finfo(np.float32).max          # its bf16 is infinite
+    got = run_conv(clean_x := np.nan_to_num(np.where(np.abs(x) > 2, 0, x), nan=0.0), w, 1, (1, 1, 1, 1))
+    ref = O.conv2d(clean_x[[0]], w, 1, (1, 1, 1, 1))
+    both = np.isfinite(ref)
+    assert np.array_equal(np.isfinite(got[[0]]), both) and np.allclose(got[[0]][both], ref[both], rtol=1e-4, atol=1e-3)
+
+
 def test_conv_identity_filter_is_exact():
     rng = np.random.default_rng(5)
     x = rng.standard_normal((2, 32, 10, 12)).astype(np.float32)
