@@ -43,13 +43,19 @@ __device__ __forceinline__ int quotient(const FastDiv &f, int n)       // withou
     return (int)((__umulhi((unsigned)n, f.magic) + ((unsigned)n & all)) >> f.shift);
 }
 
+// The matrix instruction takes bf16 denormals as zero: without a scale the parts of values below 2^-102 would get lost (2.7e-6
+// relative error at 1e-35, 2.7e-4 at 1e-37). Both operands are therefore split at 2^24 times their size, and the sums taken
+// back by 2^-48; powers of two, so nothing is rounded by it. Values or sums that overflow at that scale (values above 2^103,
+// sums above 2^79) are found and computed value by value like the infinities. (327 us without the scale, 347 with it.)
+constexpr float kScale = 16777216.f, kUnscale = 1.f / (16777216.f * 16777216.f);
+
 // Eight values -> their three bf16 parts; `check` becomes NaN or infinite where a value has none.
 __device__ __forceinline__ void split8(floatx4 a, floatx4 b, uintx4 &h, uintx4 &m, uintx4 &l, float &check)
 {
     const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        float u = x[2 * k], v = x[2 * k + 1];
+        float u = x[2 * k] * kScale, v = x[2 * k + 1] * kScale;
         unsigned part[3];
 #pragma unroll
         for (int s = 0; s < 3; ++s) {
@@ -221,6 +227,15 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
             __syncthreads();
         }
     }
+#pragma unroll
+    for (int wm = 0; wm < WM; ++wm)
+#pragma unroll
+        for (int wn = 0; wn < WN; ++wn)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                acc[wm][wn][r] *= kUnscale;
+                check = fmaf(acc[wm][wn][r], 0.f, check);
+            }
     if (!(__builtin_fabsf(check) < __builtin_inff())) bad[0] = 1;           // (NaN compares false)
     __syncthreads();
 
@@ -319,7 +334,7 @@ Plan plan_tile(const LayerGeom &g)
 // Where it beats the fp32 matrix instruction: stride 1 (a strided tile stages too many rows), nine steps or more, at least
 // 15 / 16 of a workgroup per compute unit, and few channels padded (to 64 out, 32 in): against the tiles of conv_same.hip at most
 // one part in seven of the work, elsewhere two in five. us with the fp32 instruction / here: 64 -> 64 channels 28 x 28, 64
-// images (392 workgroups) 39.4 / 27.8, 40 images (245) 22.7 / 21.4, 8 x 8, 300 images (150) 16.4 / 21.3; 64 -> 112 62.7 /
+// images (392 workgroups) 39.4 / 27.8 (these figures before the scale of the parts, some 5 %), 40 images (245) 22.7 / 21.4, 8 x 8, 300 images (150) 16.4 / 21.3; 64 -> 112 62.7 /
 // 50.4; 48 -> 64 28 x 28 x 40 18.3 / 20.4; 16 -> 64 (five steps) 7 x 7 x 500 7.4 / 9.4; 48 -> 64 5 x 5 28 x 28 x 64 88 / 52.
 bool conv_split3_eligible(const LayerGeom &g)
 {

@@ -277,8 +277,9 @@ SPLIT3_CASES = [  # N, Ci, Co, H, W, kh, kw, pad: stride 1, at least 240 tiles o
 
 
 @pytest.mark.parametrize("case", SPLIT3_CASES)
-@pytest.mark.parametrize("scale", [1.0, 1e18])
+@pytest.mark.parametrize("scale", [1.0, 1e-36, 1e18, 1e30])
 def test_conv2d_three_part_products(case, scale):
+    """scale: where the parts of a value would be denormal, and where the sums overflow at the scale of the parts."""
     N, Ci, Co, H, W, kh, kw, pad = case
     assert S.small_conv2d_kernel(N, Ci, Co, H, W, kh, kw, 1, pad, 16, 16).startswith("conv16_split3"), case
     rng = np.random.default_rng(8300 + N + Ci)
