@@ -861,8 +861,10 @@ hipError_t launch_conv_u8(const unsigned char *in, const unsigned char *filt, un
     const QConvArgs a = conv_args(in, filt, out, g, q, filt_sums);
     if (conv_u8_uses_mfma(g, in, filt, out)) {
         const int corr = (q.zx != 128 && !filt_sums) ? 2 : (q.zw != 128 ? 1 : 0);
+        if (conv_u8_pw_eligible(g, q, filt_sums, out)) return launch_conv_u8_pw(in, filt, out, g, q, filt_sums, s);
         if (conv_u8_tile_eligible(g, q, filt_sums, out)) return launch_conv_u8_tile(in, filt, out, g, q, filt_sums, s);
-        // pointwise layers on 64 or 128 channels with enough pixels for a round of waves: the streaming kernel
+        // pointwise layers on 64 or 128 channels with enough pixels for a round of waves that the kernel above leaves (32 output
+        // channels, or no filter sums): the streaming kernel
         if (g.kh == 1 && g.kw == 1 && g.stride == 1 && g.pt == 0 && g.pl == 0 && g.Ho == g.H && g.Wo == g.W &&
             (a.nCib == 4 || a.nCib == 8) && a.nCob % 2 == 0 && (long)a.M >= 32L * 4 * device_cus()) {
             const int n_tiles = (a.M + 31) / 32;

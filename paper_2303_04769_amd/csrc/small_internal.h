@@ -309,6 +309,10 @@ hipError_t launch_conv_u8(const unsigned char *in, const unsigned char *filt, un
 bool conv_u8_tile_eligible(const LayerGeom &g, const QuantParams &q, const int *filt_sums, const void *out);
 hipError_t launch_conv_u8_tile(const unsigned char *in, const unsigned char *filt, unsigned char *out, const LayerGeom &g,
                                const QuantParams &q, const int *filt_sums, hipStream_t s);
+// ... pointwise on at most 256 channels with much output, every pixel read once for up to 40 output blocks (conv_u8_pw.hip)
+bool conv_u8_pw_eligible(const LayerGeom &g, const QuantParams &q, const int *filt_sums, const void *out);
+hipError_t launch_conv_u8_pw(const unsigned char *in, const unsigned char *filt, unsigned char *out, const LayerGeom &g,
+                             const QuantParams &q, const int *filt_sums, hipStream_t s);
 hipError_t launch_filter_sums_u8(const unsigned char *filt, int *sums, int Co, int Ci, int kh, int kw, int Cob, int Cib,
                                  hipStream_t s);
 // mode 0: depthwise (filt [C/Cb][kh][kw][Cb]), 1: max pooling, 2: average pooling (filt unused, may be null)

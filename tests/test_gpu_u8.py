@@ -165,6 +165,26 @@ def test_conv_tiles_large_batch(N, Ci, Co, H, W, k):
         _same(got[n:n + 1], Q.conv2d(x[n:n + 1], w, 1, (1, 1, 1, 1), q), f"conv u8 {Ci}->{Co} image {n}")
 
 
+@pytest.mark.parametrize("N,Ci,Co,H,W,s,zx,zw,sums", [
+    (11, 16, 48, 71, 73, 1, 7, 140, True),       # one input block; three output blocks of a group of four
+    (700, 64, 48, 14, 14, 1, 128, 130, False),   # one full matrix instruction; no sums needed; waves walk several tiles
+    (5, 80, 272, 31, 32, 1, 0, 255, True),       # two instructions, the second one block; output blocks in several shares
+    (9, 144, 160, 61, 59, 2, 250, 128, True),    # stride 2 on an odd image; three instructions; no pixel sums
+    (3, 256, 640, 29, 27, 1, 33, 99, True),      # the widest reduction; last pixel tile ragged
+])
+def test_conv_pointwise_walk(N, Ci, Co, H, W, s, zx, zw, sums):
+    """Pointwise layers with much output: shares of output blocks, missing blocks at both ends, tiles across images and beyond
+    the last pixel. Integer arithmetic: exact; the oracle recomputes three images."""
+    r = _rng(23)
+    x, w = WL.u8_codes(r, (N, Ci, H, W)), WL.u8_codes(r, (Co, Ci, 1, 1))
+    q = _quant_for(Q.conv2d_acc(x[:1], w, s, (0, 0, 0, 0), zx, zw), zx, zw)
+    got = _conv(x, w, s, (0, 0, 0, 0), q, 16, 16, with_sums=sums)
+    for n in (0, N // 2, N - 1):
+        ref = Q.conv2d(x[n:n + 1], w, s, (0, 0, 0, 0), q)
+        _same(got[n:n + 1], ref, f"conv u8 pointwise {Ci}->{Co} image {n}")
+        assert len(np.unique(ref)) > 8
+
+
 @pytest.mark.parametrize("case", [
     (2, 3, 8, 9, 9, 3, 3, 2, (0, 1, 0, 1), 128, 128, 3, 8),        # first layer of the depthwise-separable CNN
     (2, 1, 16, 13, 10, 10, 4, 2, (4, 5, 1, 1), 5, 140, 1, 16),     # first layer of the audio CNN
