@@ -2,9 +2,9 @@
 // window_dpp.hip. uint8 codes in and out, exact int32 sums, the library's requantization rule; HBM traffic is a
 // quarter of the fp32 layer's, so the bound is vector arithmetic, not memory.
 //
-// The mapping is window_dpp.hip's: a wave owns 16 neighbouring pixels of a strip of at most 7 rows of one plane
+// The mapping is window_dpp.hip's: a wave owns 16 neighbouring pixels of a strip of at most 5, 7 or 9 rows of one plane
 // (or several narrow planes side by side), lane = 16 q + l holding the four channels 4q .. 4q + 3 of pixel l --
-// one 32-bit word of the pixel's 16-byte block. Every lane requests its nine input words at once (buffer
+// one 32-bit word of the pixel's 16-byte block. Every lane requests its 7, 9 or 11 input words at once (buffer
 // addressing: lanes and rows outside the image read as the code zx); the left and right neighbours come from
 // lanes l - 1 and l + 1 by lane shifts of the words (zero is shifted in at a band's ends: lanes 0 and 15 produce no
 // output there, or the value is replaced). The sums are taken with four-byte signed dot products over the three
@@ -31,19 +31,18 @@ struct DppU8Args {
     QuantParams q;
 };
 
-// Output rows per strip (two more input rows prime the window). Strips of 13 rows, tried where they still leave two
-// waves for every SIMD, save a tenth of the vector work and measure 10-30 % slower: a wave is one serial chain from
-// its loads to its last row, and what hides it is the number of waves.
-constexpr int kStripRowsU8 = 7;
-constexpr int kStepsU8 = kStripRowsU8 + 2;
+// ROWS: output rows per strip (two more input rows prime the window), at most; a wave computes that many whatever its strip has.
+// Strips of 13 rows, tried where they still leave two waves for every SIMD, measured 10-30 % slower than 7: a wave is one
+// serial chain from its loads to its last row, and what hides it is the number of waves.
 
 // SEG 16: a band is 16 neighbouring pixels of one plane (14 outputs). SEG 8: rows of at most 7 pixels, two planes
 // side by side with a lane of padding on their left. SEG 0: rows of at most 5 pixels, floor(16 / W) planes back to
 // back without padding lanes (three planes of the audio CNN's 5-pixel rows instead of two): the neighbour a plane's
 // first and last pixel would take from the plane next to it is replaced by the code zx with a select.
-template <int SEG, bool HAS_ZB>
+template <int SEG, bool HAS_ZB, int ROWS>
 __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
 {
+    constexpr int kStepsU8 = ROWS + 2;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int unit = (int)blockIdx.x * 4 + wave;
@@ -78,7 +77,7 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
     const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(a.in), 0, a.bytes, kRawBuffer);
     const __amdgpu_buffer_rsrc_t dst = __builtin_amdgcn_make_buffer_rsrc(a.out, 0, a.bytes, kRawBuffer);
 
-    // the nine input words (codes), zx where there is no input
+    // the input words (codes), zx where there is no input
     const unsigned zx4 = (unsigned)a.q.zx * 0x01010101u;
     unsigned raw[kStepsU8];
 #pragma unroll
@@ -160,6 +159,39 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
     }
 }
 
+// Rows per strip: 7, unless strips of 5 or 9 leave clearly less to do. A wave costs about 180 + 52 rows vector instructions, also
+// for the rows that its strip lacks; up to two waves a SIMD the busiest one counts, beyond that their average. Measured (us, 7 -> the
+// one taken): 1024 images of 64 channels 25x5 11.0 -> 9.4 with 9 (three strips of 8 or 9 rows instead of four of 6 or 7), 2000 of 32
+// 5x9 5.6 -> 4.95 with 5, one of 64 48x48 3.4 -> 3.1 with 5 (fewer waves than SIMDs: the shorter chain). 7 stays where the
+// model's gain is below 8 %: 100 of 96 31x40 with zw != 128 11.8 against 12.5 with 9, which holds more registers; and 56, 28, 14
+// and 7 rows are whole strips of 7.
+int strip_rows(const LayerGeom &g, long planes_by_bands)
+{
+    const double simds = 4.0 * device_cus();
+    auto cost = [&](int rows) {
+        const double per_simd = (double)planes_by_bands * ((g.H + rows - 1) / rows) / simds;
+        return (per_simd <= 1 ? 1 : per_simd <= 2 ? 2 : per_simd) * (180 + 52 * rows);
+    };
+    const double c5 = cost(5), c7 = cost(7), c9 = cost(9);
+    if (c5 < c9) return c5 < 0.92 * c7 ? 5 : 7;
+    return c9 < 0.92 * c7 ? 9 : 7;
+}
+
+template <int ROWS>
+void go(const DppU8Args &a, int seg, hipStream_t s)
+{
+    const dim3 grid((unsigned)((a.n_units + 3) / 4)), block(256);
+    if (a.q.zw == 128) {
+        if (seg == 0) hipLaunchKernelGGL((dw16_dpp_u8<0, false, ROWS>), grid, block, 0, s, a);
+        else if (seg == 8) hipLaunchKernelGGL((dw16_dpp_u8<8, false, ROWS>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((dw16_dpp_u8<16, false, ROWS>), grid, block, 0, s, a);
+    } else {
+        if (seg == 0) hipLaunchKernelGGL((dw16_dpp_u8<0, true, ROWS>), grid, block, 0, s, a);
+        else if (seg == 8) hipLaunchKernelGGL((dw16_dpp_u8<8, true, ROWS>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((dw16_dpp_u8<16, true, ROWS>), grid, block, 0, s, a);
+    }
+}
+
 }  // namespace
 
 bool dw_dpp_u8_eligible(const LayerGeom &g, const QuantParams &q, const void *in, const void *filt, const void *out)
@@ -184,22 +216,16 @@ hipError_t launch_dw_dpp_u8(const unsigned char *in, const unsigned char *filt, 
     a.ppb = seg == 0 ? 16 / g.W : seg == 8 ? 2 : 1;
     a.nb = seg == 16 ? (g.W + 13) / 14 : 1;
     const long groups = (a.n_planes + a.ppb - 1) / a.ppb;
-    a.sp = (g.H + kStripRowsU8 - 1) / kStripRowsU8;
+    const int rows = strip_rows(g, groups * a.nb);
+    a.sp = (g.H + rows - 1) / rows;
     a.n_units = (int)(groups * a.sp * a.nb);
     a.by_nb = make_fastdiv(a.nb);
     a.by_sp = make_fastdiv(a.sp);
     a.by_nCb = make_fastdiv(a.nCb);
     a.by_W = make_fastdiv(g.W);
-    const dim3 grid((unsigned)((a.n_units + 3) / 4)), block(256);
-    if (q.zw == 128) {
-        if (seg == 0) hipLaunchKernelGGL((dw16_dpp_u8<0, false>), grid, block, 0, s, a);
-        else if (seg == 8) hipLaunchKernelGGL((dw16_dpp_u8<8, false>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((dw16_dpp_u8<16, false>), grid, block, 0, s, a);
-    } else {
-        if (seg == 0) hipLaunchKernelGGL((dw16_dpp_u8<0, true>), grid, block, 0, s, a);
-        else if (seg == 8) hipLaunchKernelGGL((dw16_dpp_u8<8, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((dw16_dpp_u8<16, true>), grid, block, 0, s, a);
-    }
+    if (rows == 5) go<5>(a, seg, s);
+    else if (rows == 9) go<9>(a, seg, s);
+    else go<7>(a, seg, s);
     return hipGetLastError();
 }
 

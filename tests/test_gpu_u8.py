@@ -627,6 +627,16 @@ def test_depthwise_lane_shift(case):
     _same(Q.unpack(g.check(), ref.shape, 16), ref, f"dw u8 lanes {case}")
 
 
+@pytest.mark.parametrize("case", [
+    (312, 256, 9, 7, 5, 128), (82, 256, 9, 15, 128, 131),                                  # strips of 9 rows
+    (64, 256, 14, 14, 250, 128), (64, 512, 7, 7, 1, 254), (256, 256, 13, 5, 128, 128),     # of 7, the last one strip of 7 and one of 6
+    (2, 32, 11, 5, 9, 130), (3, 48, 6, 6, 70, 128), (1, 16, 10, 29, 128, 90),              # few waves: of 5, cut to 3 and 4 rows
+])
+def test_depthwise_lane_shift_strips(case):
+    """Every strip length that a layer's size can choose, for one, two and several planes per band."""
+    test_depthwise_lane_shift(case)
+
+
 @pytest.mark.parametrize("mult,shift", [(1 << 20, 0), ((1 << 31) - 1, 0), (1, 31), (0, 5), ((1 << 31) - 1, 31), (3, 1)])
 def test_depthwise_extreme_scales(mult, shift):
     """Scales from 'everything saturates' to 'everything rounds to the zero point': whichever requantization path the
