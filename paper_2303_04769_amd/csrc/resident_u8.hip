@@ -22,7 +22,7 @@ typedef int intx4 __attribute__((ext_vector_type(4)));
 constexpr int kWaves = 16, kThreads = 64 * kWaves;
 constexpr int kMaxFilter = 65536, kFilterRegs = kMaxFilter / 16 / kThreads;
 
-// One layer, packed so that forty of them fit the kernel arguments.
+// One layer, packed so that kRU8MaxLayers of them fit the 4 KB of kernel arguments.
 struct RU8Layer {
     const unsigned char *filt;
     const int *sums;               // or null (zx = 128)
@@ -38,7 +38,8 @@ struct RU8Layer {
     int mult, amax;                // (add: mult_a, mult_b)
     unsigned magic, shift;         // division by Wo (average pooling: by the pixel count)
     int inv_unit, inv_taps;        // ceil(2^20 / d) of output blocks, and of taps
-    int inv_kw, pad_;
+    int inv_kw;
+    int sums_bytes;                // of the channel sums behind the filter in LDS (convolutions only)
 };
 struct RU8Args {
     const unsigned char *in;
@@ -49,6 +50,7 @@ struct RU8Args {
     int pads, table, filt0, filt1; // LDS byte offsets
     RU8Layer layer[kRU8MaxLayers];
 };
+static_assert(sizeof(RU8Args) <= 4096, "kernel arguments");
 
 __device__ __forceinline__ int quotient(unsigned magic, unsigned shift, int n)       // magic = 0: by one
 {
@@ -177,7 +179,7 @@ __global__ void __launch_bounds__(kThreads) resident_u8(RU8Args a)
     intx4 fr[kFilterRegs], sr;
     auto filter_request = [&](const RU8Layer &L) __attribute__((always_inline)) {
         const __amdgpu_buffer_rsrc_t f = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(L.filt), 0, L.filt_bytes, kRawBuffer);
-        const __amdgpu_buffer_rsrc_t s = __builtin_amdgcn_make_buffer_rsrc(const_cast<int *>(L.sums), 0, L.sums ? L.Co * 4 : 0, kRawBuffer);
+        const __amdgpu_buffer_rsrc_t s = __builtin_amdgcn_make_buffer_rsrc(const_cast<int *>(L.sums), 0, L.sums ? L.sums_bytes : 0, kRawBuffer);
 #pragma unroll
         for (int k = 0; k < kFilterRegs; ++k)
             if (k == 0 || k * kThreads * 16 < L.filt_bytes)
@@ -188,7 +190,7 @@ __global__ void __launch_bounds__(kThreads) resident_u8(RU8Args a)
 #pragma unroll
         for (int k = 0; k < kFilterRegs; ++k)
             if (k * kThreads * 16 < L.filt_bytes && (tid + k * kThreads) * 16 < L.filt_bytes) *reinterpret_cast<intx4 *>(lds + at + (tid + k * kThreads) * 16) = fr[k] ^ flip;
-        if (tid * 4 < L.Co) *reinterpret_cast<intx4 *>(lds + at + L.filt_bytes + tid * 16) = sr;
+        if (tid * 16 < L.sums_bytes) *reinterpret_cast<intx4 *>(lds + at + L.filt_bytes + tid * 16) = sr;
     };
     filter_request(a.layer[0]);
     filter_arrive(a.layer[0], a.filt0);
@@ -279,6 +281,9 @@ size_t ru8_chunks(const RU8Group &g)
     return g.kind == RU8_CONV ? (size_t)g.Ci / 16 * g.kh * g.kw : g.kind == RU8_DW ? (size_t)g.kh * g.kw : 0;
 }
 
+// what filter_arrive stages behind a layer's filter: the one statement of it, for the layout and for the kernel
+size_t ru8_sums_bytes(const RU8Group &g) { return g.kind == RU8_CONV ? (size_t)g.Co * 4 : 0; }
+
 struct Layout { int pads, table, filt0, filt1, at[kRU8Buffers]; size_t bytes; };
 
 bool lay_out(const RU8Group *g, int n, Layout &o)
@@ -291,7 +296,7 @@ bool lay_out(const RU8Group *g, int n, Layout &o)
     size[g[0].src] = (size_t)g[0].Ci * g[0].H * g[0].W;
     for (int i = 0; i < n; ++i) {
         entries += (ru8_chunks(g[i]) + 3) / 4 * 4;
-        const size_t f = (ru8_filter_bytes(g[i]) + 15) / 16 * 16 + (g[i].kind == RU8_CONV ? (size_t)g[i].Co * 4 : 0);
+        const size_t f = (ru8_filter_bytes(g[i]) + 15) / 16 * 16 + ru8_sums_bytes(g[i]);
         filt = f > filt ? f : filt;
         if (g[i].kind == RU8_DENSE) continue;
         const size_t b = (size_t)g[i].Co * g[i].Ho * g[i].Wo;
@@ -367,7 +372,8 @@ hipError_t launch_resident_u8(const RU8Group *g, int n, const unsigned char *in,
         d.table = entries | chunks << 16;
         entries += (chunks + 3) / 4 * 4;
         d.filt_bytes = (int)ru8_filter_bytes(l);
-        d.Co = l.kind == RU8_CONV || l.kind == RU8_DENSE ? l.Co : 0;
+        d.sums_bytes = (int)ru8_sums_bytes(l);
+        d.Co = l.kind == RU8_DENSE ? l.Co : 0;
         d.z = add ? l.qa.za | l.qa.zb << 8 | l.qa.zy << 16 | l.qa.shift << 24 : l.q.zx | l.q.zw << 8 | l.q.zy << 16 | l.q.shift << 24;
         // pixel groups of a unit: a filter operand serves that many, as long as every wave still has a unit
         const int groups = (l.Ho * l.Wo + 15) / 16, units = groups * (l.Co / 16);

@@ -700,3 +700,46 @@ def test_network_resident_runs(tail, N, C0, H, W):
     got = _run_u8(net, x, ws, qs).reshape((N,) + ref.shape[1:])
     _same(got[idx], ref, f"u8 resident {tail} {N}x{C0}x{H}x{W}")
     assert len(np.unique(ref)) > 8 and last.dst == -2
+
+
+def _shift_zero_points(qs, r):
+    for q in qs:
+        for k in ("zx", "zw", "za", "zb", "zy", "z"):
+            if q is not None and k in q:
+                q[k] = int(r.integers(100, 156))
+
+
+RESIDENT_HEAD_CASES = {  # layers before the fully connected one (op, Co, window), input channels, its outputs and their block
+    "conv": ([("conv", 16, 1), ("conv", 16, 7)], 16, 7, 4096, 8),                     # three layers, 64 KB: two images per workgroup
+    "conv_even": ([("conv", 16, 1), ("conv", 32, 1), ("conv", 16, 7)], 16, 7, 4096, 8),
+    "dw": ([("conv", 64, 1), ("dw", 64, 5)], 16, 5, 100, 10),
+    "avgpool_even": ([("conv", 16, 3), ("avgpool", 16, 4), ("conv", 32, 1)], 16, 6, 100, 10),
+    "ragged": ([("conv", 16, 1), ("dw", 16, 3)], 32, 3, 13, 13),                      # outputs no multiple of four
+}
+
+
+@pytest.mark.parametrize("N", [1, 37, 512])
+@pytest.mark.parametrize("case", sorted(RESIDENT_HEAD_CASES))
+def test_network_resident_head_has_the_largest_filter(case, N):
+    """A run whose closing fully connected layer needs the most LDS for its filter, in the first and in the second of the two
+    filter buffers, behind layers whose filter other waves still read while it arrives; 512 images: with 64 KB of filter a
+    workgroup takes two, and the buffers' roles change from one to the next where the layers are odd in number."""
+    from workloads.nets import Layer, Network, IN, OUT
+    before, C, H, Co, Cob = RESIDENT_HEAD_CASES[case]
+    layers, shapes, src, C0, H0 = [], [], IN, C, H
+    for i, (op, K, k) in enumerate(before):
+        w = None
+        if op != "avgpool":
+            w = len(shapes)
+            shapes.append(((K, 1 if op == "dw" else C, k, k), k * k * (1 if op == "dw" else C)))
+        layers.append(Layer(op, C, K, H, H, k, k, 1, (0, 0, 0, 0), src=src, dst=i % 2, w=w))
+        src, C, H = i % 2, K, H - k + 1
+    assert H == 1
+    layers.append(Layer("dense", C, Co, 1, 1, 1, 1, 1, src=src, dst=OUT, w=len(shapes), Cob=Cob, Ho=1, Wo=1))
+    shapes.append(((Co, C, 1, 1), C))
+    net = Network("resident_head_" + case, C0, H0, H0, layers, shapes)
+    x, ws, qs = WL.quantized_network_tensors(net, N, 990 + N)
+    _shift_zero_points(qs, _rng(32))
+    ref = Q.run_network(net, x, ws, qs)
+    _same(_run_u8(net, x, ws, qs), ref.reshape(N, Co, 1, 1), f"u8 resident head {case} {N}")
+    assert len(np.unique(ref)) > 8
