@@ -56,7 +56,11 @@ __device__ __forceinline__ int quotient(unsigned magic, unsigned shift, int n)  
 {
     return (int)((__umulhi((unsigned)n, magic) + (magic ? 0u : (unsigned)n)) >> shift);
 }
-__device__ __forceinline__ int short_div(int n, int inv) { return (n * inv) >> 20; }    // n < 4096, divisor <= 255
+// n / d by inv = ceil(2^20 / d): exact for n < 4096 and d <= 255 (chunks by taps), and for n below the units of a layer and d
+// its output blocks, as long as these are at most kMaxUnitBlocks and blocks x pixels at most 4096 (resident_u8_takes; with 1025
+// blocks of one pixel the quotient of unit 1024 would be 1)
+constexpr int kMaxUnitBlocks = 1024;
+__device__ __forceinline__ int short_div(int n, int inv) { return (n * inv) >> 20; }
 __device__ __forceinline__ unsigned pack4(const unsigned (&y)[4]) { return y[0] | y[1] << 8 | y[2] << 16 | y[3] << 24; }
 
 struct Requant { int amax, mult, shift, lo, hi; long bias; };
@@ -336,9 +340,10 @@ bool resident_u8_takes(const RU8Group &g)
     if (g.Ci % 16 || g.H > 255 || g.W > 255 || g.stride > 255 || (size_t)g.Ci * g.H * g.W > 65536) return false;
     if (g.kind == RU8_ADD || g.kind == RU8_AVG) return true;
     if (ru8_filter_bytes(g) > (size_t)kMaxFilter || ((uintptr_t)g.filt & 15u) || g.q.amax <= 0) return false;
-    if (g.kind == RU8_DW) return g.kh * g.kw <= 255 && g.kh < 64 && g.kw < 64 && (size_t)g.Ci * g.Ho * g.Wo <= 65536;
+    if (g.kind == RU8_DW)
+        return g.kh * g.kw <= 255 && g.kh < 64 && g.kw < 64 && (size_t)g.Ci * g.Ho * g.Wo <= 65536 && g.Ci / 16 <= kMaxUnitBlocks;
     if (g.kind == RU8_DENSE) return g.Cob < 16 && ru8_filter_bytes(g) % 16 == 0;
-    return g.Co % 16 == 0 && (size_t)g.Co * g.Ho * g.Wo <= 65536 && g.kh * g.kw <= 255 && g.kh < 64 && g.kw < 64 &&
+    return g.Co % 16 == 0 && (size_t)g.Co * g.Ho * g.Wo <= 65536 && g.Co / 16 <= kMaxUnitBlocks && g.kh * g.kw <= 255 && g.kh < 64 && g.kw < 64 &&
            (g.Ci / 16) * g.kh * g.kw < 4096 && (g.sums || g.q.zx == 128) && ((uintptr_t)g.sums & 15u) == 0;
 }
 

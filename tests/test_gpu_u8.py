@@ -743,3 +743,17 @@ def test_network_resident_head_has_the_largest_filter(case, N):
     ref = Q.run_network(net, x, ws, qs)
     _same(_run_u8(net, x, ws, qs), ref.reshape(N, Co, 1, 1), f"u8 resident head {case} {N}")
     assert len(np.unique(ref)) > 8
+
+
+@pytest.mark.parametrize("C", [16 * 1024, 16 * 1025])
+def test_network_resident_many_blocks(C):
+    """Depthwise layers of as many channel blocks as one run takes, and of one more (layer by layer)."""
+    from workloads.nets import Layer, Network, IN, OUT
+    net = Network("resident_blocks", C, 1, 1)
+    net.layers = [Layer("dw", C, C, 1, 1, 1, 1, 1, src=IN if i == 0 else i - 1, dst=OUT if i == 2 else i, w=i) for i in range(3)]
+    net.wshapes = [((C, 1, 1, 1), 1)] * 3
+    x, ws, qs = WL.quantized_network_tensors(net, 3, 71)
+    _shift_zero_points(qs, _rng(33))
+    ref = Q.run_network(net, x, ws, qs)
+    _same(_run_u8(net, x, ws, qs), ref, f"u8 resident {C} channels")
+    assert len(np.unique(ref)) > 8
