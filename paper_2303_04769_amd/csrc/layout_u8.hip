@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(256) pack_u8_words(const unsigned char *src, u
     const size_t base = (size_t)plane * HW * CB;                              // of the plane, in either layout
     const unsigned char *in = src + base + (UNPACK ? (size_t)pix * CB : (size_t)pix);
     unsigned char *out = dst + base + (UNPACK ? (size_t)pix : (size_t)pix * CB);
-    if (pix + 4 <= HW) {
+    if (HW - pix >= 4) {                                                       // (pix + 4 may pass 2^31)
         unsigned w[CB], o[CB];
 #pragma unroll
         for (int c = 0; c < CB; ++c) w[c] = load_word(UNPACK ? in + 4 * c : in + (size_t)c * HW);
@@ -118,7 +118,7 @@ __global__ void __launch_bounds__(256) pack_u8_kernel(const unsigned char *src, 
 template <int CB>
 void launch_words(const unsigned char *src, unsigned char *dst, long planes, int HW, bool unpack, hipStream_t s)
 {
-    const int groups = (HW + 3) / 4;
+    const int groups = (int)((HW + 3L) / 4);
     const int total = (int)(planes * groups);
     const dim3 grid((unsigned)((total + 255) / 256));
     if (unpack) hipLaunchKernelGGL((pack_u8_words<CB, true>), grid, dim3(256), 0, s, src, dst, HW, groups, make_fastdiv(groups), total);
@@ -135,7 +135,7 @@ hipError_t launch_pack_u8(const unsigned char *src, unsigned char *dst, int N, i
     const size_t total = (size_t)N * C * H * W;
     const int HW = H * W;
     const long planes = (long)N * (C / Cb);
-    if (planes * ((HW + 3) / 4) < (1L << 31) - 256) {
+    if (planes * ((HW + 3L) / 4) < (1L << 31) - 256) {
         switch (Cb) {
             case 1: launch_words<1>(src, dst, planes, HW, unpack, s); return hipGetLastError();
             case 3: launch_words<3>(src, dst, planes, HW, unpack, s); return hipGetLastError();

@@ -73,6 +73,17 @@ def test_pack_unpack_words(N, H, W, Cb):
         assert np.array_equal(g2.check()[off:].reshape(x.shape), x)
 
 
+@pytest.mark.parametrize("H,W", [(1, (1 << 31) - 1), (2, (1 << 30) - 1), (1, (1 << 31) - 3)])
+def test_pack_unpack_largest_plane(H, W):
+    """Planes whose pixel count plus a word passes 2^31, the largest the library takes. (One channel: a copy.)"""
+    n = H * W
+    x = torch.randint(0, 256, (n,), dtype=torch.uint8, device=DEV, generator=torch.Generator(DEV).manual_seed(n & 0xffff))
+    for move in (S.small_pack_u8, S.small_unpack_u8):
+        out = torch.zeros(n + 64, dtype=torch.uint8, device=DEV)
+        move(x, out[:n], 1, 1, H, W, 1)
+        assert torch.equal(out[:n], x) and int(out[n:].count_nonzero()) == 0
+
+
 @pytest.mark.parametrize("Co,Ci,kh,kw,Cob,Cib", [(32, 48, 3, 3, 16, 16), (8, 3, 3, 3, 8, 3), (16, 1, 10, 4, 16, 1), (16, 8, 1, 1, 16, 8)])
 def test_pack_filter(Co, Ci, kh, kw, Cob, Cib):
     w = WL.u8_codes(_rng(1), (Co, Ci, kh, kw))
