@@ -342,9 +342,11 @@ bool resident_u8_takes(const RU8Group &g)
     if (ru8_filter_bytes(g) > (size_t)kMaxFilter || ((uintptr_t)g.filt & 15u) || g.q.amax <= 0) return false;
     if (g.kind == RU8_DW)
         return g.kh * g.kw <= 255 && g.kh < 64 && g.kw < 64 && (size_t)g.Ci * g.Ho * g.Wo <= 65536 && g.Ci / 16 <= kMaxUnitBlocks;
+    // (channel sums at another address are refused by the layer's own call, also where they are not needed)
+    if ((uintptr_t)g.sums & 15u) return false;
     if (g.kind == RU8_DENSE) return g.Cob < 16 && ru8_filter_bytes(g) % 16 == 0;
     return g.Co % 16 == 0 && (size_t)g.Co * g.Ho * g.Wo <= 65536 && g.Co / 16 <= kMaxUnitBlocks && g.kh * g.kw <= 255 && g.kh < 64 && g.kw < 64 &&
-           (g.Ci / 16) * g.kh * g.kw < 4096 && (g.sums || g.q.zx == 128) && ((uintptr_t)g.sums & 15u) == 0;
+           (g.Ci / 16) * g.kh * g.kw < 4096 && (g.sums || g.q.zx == 128);
 }
 
 hipError_t launch_resident_u8(const RU8Group *g, int n, const unsigned char *in, unsigned char *out, int N, hipStream_t s)

@@ -539,6 +539,33 @@ bool resident_u8_batch(const RU8Group *g, int n, int N)
     return N <= 2 * device_cus() && macs <= 1.5e6 * n;
 }
 
+// Whether nothing that a run writes layer by layer overlaps anything else it touches: its source, its other buffers, any
+// filter or channel sums. Only then is one launch the same as the layers one after the other, and only then would none of
+// them be refused for an overlap (the layers' own calls decide that, so a run that fails here goes to them).
+template <class Ptr>
+bool disjoint_run_u8(const RU8Group *g, int n, int N, Ptr ptr)
+{
+    size_t written[kRU8Buffers] = {};                          // bytes of every buffer that the run writes, the largest tensor
+    for (int k = 0; k < n; ++k) {
+        const size_t b = (size_t)N * g[k].Co * g[k].Ho * g[k].Wo;
+        if (b > written[g[k].dst]) written[g[k].dst] = b;
+    }
+    if (g[n - 1].dst == g[0].src) return false;                // images of different sizes over each other
+    const size_t source = (size_t)N * g[0].Ci * g[0].H * g[0].W;
+    for (int d = 0; d < kRU8Buffers; ++d) {
+        if (!written[d]) continue;
+        const unsigned char *p = ptr(d - 2);
+        if (d != g[0].src && overlap_bytes(p, written[d], ptr(g[0].src - 2), source)) return false;
+        for (int e = 0; e < d; ++e)
+            if (written[e] && overlap_bytes(p, written[d], ptr(e - 2), written[e])) return false;
+        for (int k = 0; k < n; ++k) {
+            if (g[k].filt && overlap_bytes(p, written[d], g[k].filt, ru8_filter_bytes(g[k]))) return false;
+            if (g[k].sums && overlap_bytes(p, written[d], g[k].sums, (size_t)g[k].Co * sizeof(int))) return false;
+        }
+    }
+    return true;
+}
+
 // run = false: shapes, parameters and workspace sizes only. Every layer is checked before the first one runs
 // (the caller walks twice).
 int walk_u8(const small_layer_u8 *L, int nL, int N, int C0, int H0, int W0, NetPlanU8 &plan, bool run, const unsigned char *in,
@@ -569,9 +596,8 @@ int walk_u8(const small_layer_u8 *L, int nL, int N, int C0, int H0, int W0, NetP
                 const RU8Group &last = groups[n_groups - 1];
                 const unsigned char *from = ptr(l.src);
                 unsigned char *to = ptr(last.dst - 2);
-                const size_t n_in = (size_t)N * si.C * si.H * si.W, n_out = (size_t)N * last.Co * last.Ho * last.Wo;
                 const bool aligned = ((uintptr_t)from & 15u) == 0 && (last.kind == RU8_DENSE || ((uintptr_t)to & 15u) == 0);
-                if (aligned && resident_u8_batch(groups, n_groups, N) && !overlap_bytes(from, n_in, to, n_out)) {
+                if (aligned && resident_u8_batch(groups, n_groups, N) && disjoint_run_u8(groups, n_groups, N, ptr)) {
                     if (int rc = from_hip(launch_resident_u8(groups, n_groups, from, to, N, s))) return rc;
                     for (int k = 0; k < n_groups; ++k)
                         shp[groups[k].dst - 2] = ShapeU8{groups[k].Co, groups[k].Ho, groups[k].Wo, groups[k].kind == RU8_DENSE ? groups[k].Cob : 16, true};

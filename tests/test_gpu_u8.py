@@ -768,3 +768,38 @@ def test_network_resident_many_blocks(C):
     ref = Q.run_network(net, x, ws, qs)
     _same(_run_u8(net, x, ws, qs), ref, f"u8 resident {C} channels")
     assert len(np.unique(ref)) > 8
+
+
+def test_network_resident_output_over_a_filter():
+    """The output lies over the first layer's filter. Layer by layer that is well defined (the filter has been read when the last
+    layer writes), so it has to be in a table whose layers could be one launch; over the last layer's own filter or channel sums
+    it is refused, as by that layer's own call."""
+    from workloads.nets import Layer, Network, IN, OUT
+    N, C, H = 130, 64, 6
+    net = Network("resident_over", C, H, H)
+    net.layers = [Layer("conv", C, C, H, H, 3, 3, 1, (1, 1, 1, 1), src=IN, dst=0, w=0),
+                  Layer("dw", C, C, H, H, 3, 3, 1, (1, 1, 1, 1), src=0, dst=1, w=1),
+                  Layer("conv", C, C, H, H, 1, 1, 1, src=1, dst=OUT, w=2)]
+    net.wshapes = [((C, C, 3, 3), 9 * C), ((C, 1, 3, 3), 9), ((C, C, 1, 1), C)]
+    x, ws, qs = WL.quantized_network_tensors(net, N, 72)
+    _shift_zero_points(qs, _rng(34))
+    ref = Q.run_network(net, x, ws, qs)
+    pn = S.PackedNetworkU8(net, ws, qs, DEV)
+    xb = pn.pack_input(dev8(x))
+    mem = torch.zeros(ref.size, dtype=torch.uint8, device=DEV)
+    mem[4096:4096 + pn.filters[0].numel()].copy_(pn.filters[0])
+    pn.table[0].filt = mem.data_ptr() + 4096
+    pn.run(xb, mem, N)
+    torch.cuda.synchronize()
+    _same(Q.unpack(mem.cpu().numpy(), ref.shape, 16), ref, "u8 output over the first filter")
+    pn.table[0].filt = pn.filters[0].data_ptr()
+    out = torch.empty(ref.size, dtype=torch.uint8, device=DEV)
+    for field, keep in (("filt", pn.filters[2]), ("filt_sums", pn.sums[2])):
+        setattr(pn.table[2], field, out.data_ptr() + 256)
+        with pytest.raises(S.SmallError) as e:
+            pn.run(xb, out, N)
+        assert e.value.code == 4
+        setattr(pn.table[2], field, keep.data_ptr())
+    pn.run(xb, out, N)
+    torch.cuda.synchronize()
+    _same(Q.unpack(out.cpu().numpy(), ref.shape, 16), ref, "u8 apart")

@@ -53,3 +53,30 @@ def test_layers_that_are_taken(takes):
     assert takes(kind=DENSE, C_=64, Co=12, Cob=12) and takes(kind=ADD, C_=32, H=9, W=9) and takes(kind=AVG, C_=32, H=9, W=9)
     assert not takes(kind=CONV, C_=64, H=8, W=8, k=3, sums=None) and takes(kind=CONV, C_=64, H=8, W=8, k=3, sums=None, zx=128)
     assert not takes(kind=CONV, C_=64, H=8, W=8, k=3, sums=0x1004) and not takes(kind=CONV, C_=64, H=40, W=40, k=3)
+    assert not takes(kind=DENSE, C_=64, Co=12, Cob=12, sums=0x1004)
+
+
+def test_overlaps_are_refused_as_by_the_layers_own_calls():
+    """A first layer whose filter or channel sums lie in the buffer it writes, and an output that lies in the workspace: the
+    layer's own call refuses them, before anything is launched, and so does the table whose layers would be one launch. (Device
+    addresses that are never used: without the overlap the call gets as far as the launch, which has no device here.)"""
+    from paper_2303_04769_amd import binding as B
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the addresses are not real")
+    lib = B.load()
+    ws, out, inp, filt, sums = 0x100000, 0x800000, 0x400000, 0xa00000, 0xb00000
+
+    def run(filt0=filt, sums0=sums, out=out):
+        t = (B.small_layer_u8 * 3)()
+        for k, (src, dst) in enumerate([(-1, 0), (0, 1), (1, -2)]):
+            t[k].op, t[k].Ci, t[k].Co, t[k].Cib, t[k].Cob = B._OPS["conv"], 32, 32, 16, 16
+            t[k].kh = t[k].kw = t[k].stride = 1
+            t[k].src, t[k].dst = src, dst
+            t[k].filt, t[k].filt_sums = (filt0, sums0) if k == 0 else (filt + 4096 * k, sums + 4096 * k)
+            t[k].q = B.small_quant(100, 128, 128, 1 << 20, 30, 0, 255)
+        return lib.small_network_run_u8(t, 3, inp, out, ws, 1 << 16, 4, 32, 5, 5, None)
+
+    assert run() not in (0, 4)
+    assert run(filt0=ws + 64) == 4 and run(sums0=ws + 64) == 4 and run(filt0=ws + 4 * 32 * 25 - 16) == 4
+    assert run(filt0=ws + 0x8000) not in (0, 4)
