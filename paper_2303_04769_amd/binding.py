@@ -150,13 +150,12 @@ def _stream(stream):
 
 
 @functools.lru_cache(maxsize=1024)
-def _pad_record(t, b, l, r):
-    return small_pad(t, b, l, r)
+def _pad_record(*sides):
+    return small_pad(*sides)
 
 
 def _pad(pad):
-    t, b, l, r = pad
-    return _pad_record(int(t), int(b), int(l), int(r))       # (passed by value: nobody writes into a shared record)
+    return _pad_record(*map(int, pad))       # (sides left out are zero; passed by value: nobody writes into a shared record)
 
 
 def small_out_dim(i, k, stride, lo, hi):

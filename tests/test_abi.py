@@ -273,3 +273,15 @@ def test_batch_normalization_folds_into_the_convolution_before_it(lib):
     bad = _table([Layer("upsample", 32, 32, 10, 10, 2, 2, src=IN, dst=OUT)], 0)
     bad[0].kw = 0
     assert lib.small_network_workspace(bad, 1, 1, 32, 10, 10, C.byref(C.c_size_t())) == 7
+
+
+def test_padding_tuples():
+    """(t, b, l, r); sides left out at the end are zero, more than four are refused, any kind of integer is taken."""
+    from paper_2303_04769_amd import binding as B
+    import numpy as np
+    sides = lambda p: (p.t, p.b, p.l, p.r)
+    assert sides(B._pad((1, 2, 3, 4))) == (1, 2, 3, 4) and sides(B._pad(np.array([1, 0, 2, 0]))) == (1, 0, 2, 0)
+    assert sides(B._pad(())) == (0, 0, 0, 0) and sides(B._pad([1])) == (1, 0, 0, 0) and sides(B._pad((1, 1, 2))) == (1, 1, 2, 0)
+    with pytest.raises(TypeError):
+        B._pad((1, 1, 1, 1, 1))
+    assert B.small_conv2d_kernel(1, 16, 16, 8, 8, 3, 3, 1, (), 16, 16) == B.small_conv2d_kernel(1, 16, 16, 8, 8, 3, 3, 1, (0, 0, 0, 0), 16, 16)
