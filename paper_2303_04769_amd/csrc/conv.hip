@@ -431,6 +431,7 @@ struct FirstArgs {
     int Cib, Cob, K;
     int plain_input;      // the input is a plain [N][C][H][W] tensor (the network's own input): the layout change
                           // of the network boundary then happens in this kernel's gathers
+    int padded;           // some window reaches outside the image
     FastDiv div_HoWo, div_Wo;
     unsigned in_bytes, filt_bytes, out_bytes;       // each below 2 GiB
 };
@@ -491,6 +492,7 @@ __global__ void __launch_bounds__(256) conv_first_mfma(FirstArgs f)
     // the blocks with the gathered values in registers (a workgroup per output block would gather them again).
     float fb[WM][KT];
     unsigned o_at[WM];
+    int y_org[WM], x_org[WM], org_at[WM];                          // window origins (WM = 1: value_by_value needs them)
     const int image_bytes = 4 * a.H * a.W * cib, px_bytes = 4 * (f.plain_input ? 1 : cib);
 #pragma unroll
     for (int wm = 0; wm < WM; ++wm) {
@@ -500,6 +502,7 @@ __global__ void __launch_bounds__(256) conv_first_mfma(FirstArgs f)
         const int oy = f.div_Wo.div(rem), ox = rem - oy * a.Wo;
         const int iy0 = oy * a.stride - a.pt, ix0 = ox * a.stride - a.pl;
         const int org = n * image_bytes + (iy0 * a.W + ix0) * px_bytes;       // window origin, may lie before the image
+        y_org[wm] = iy0; x_org[wm] = ix0; org_at[wm] = org;
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
             const bool inside = (unsigned)(iy0 + kdy[t]) < (unsigned)a.H && (unsigned)(ix0 + kdx[t]) < (unsigned)a.W;
@@ -508,6 +511,18 @@ __global__ void __launch_bounds__(256) conv_first_mfma(FirstArgs f)
         // lane (p, q) holds output channels 4q .. 4q+3 of pixel p
         o_at[wm] = (m_own < a.M && 4 * q < f.Cob) ? (unsigned)(((n * a.nCob * a.HoWo + rem) * f.Cob + 4 * q) * 4) : kBeyond;
     }
+    // channels 4q .. 4q + 3 of pixel p, one product after the other
+    auto value_by_value = [&](int cob) {
+        floatx4 v = {0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < f.K; ++k) {
+            const int tap = k / cib, ci = k - tap * cib, dy = tap / kw, dx = tap - dy * kw;
+            if ((unsigned)(y_org[0] + dy) >= (unsigned)a.H || (unsigned)(x_org[0] + dx) >= (unsigned)a.W) continue;
+            const float x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(src, (unsigned)(org_at[0] + 4 * ((dy * a.W + dx) * cib + ci)), 0, 0));
+            const floatx4 w = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(flt, 4 * q < f.Cob ? (unsigned)(((cob * f.K + k) * f.Cob + 4 * q) * 4) : kBeyond, 0, 0));
+            v.x = fmaf(x, w.x, v.x); v.y = fmaf(x, w.y, v.y); v.z = fmaf(x, w.z, v.z); v.w = fmaf(x, w.w, v.w);
+        }
+        return v;
+    };
     const int o_block = 4 * a.HoWo * f.Cob;
     for (int cob = 0; cob < a.nCob; ++cob) {
         float fn[KT];
@@ -518,6 +533,11 @@ __global__ void __launch_bounds__(256) conv_first_mfma(FirstArgs f)
             acc[wm] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int t = 0; t < KT; ++t) acc[wm] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[t], fb[wm][t], acc[wm], 0, 0, 0);
+        }
+        if constexpr (WM == 1) {
+            // An infinite weight times the zero of a tap outside the image is NaN, but that tap does not count: sums that are
+            // NaN are taken again over the taps inside only.
+            if (f.padded && __any(__builtin_isunordered(acc[0].x, acc[0].y) | __builtin_isunordered(acc[0].z, acc[0].w))) acc[0] = value_by_value(cob);
         }
 #pragma unroll
         for (int wm = 0; wm < WM; ++wm) {
@@ -641,6 +661,7 @@ hipError_t launch_conv(const float *in, const float *filt, float *out, const flo
         f.c = a;
         f.Cib = g.Cib; f.Cob = g.Cob; f.K = g.Cib * g.kh * g.kw;
         f.plain_input = plain_input ? 1 : 0;
+        f.padded = g.pt > 0 || g.pl > 0 || (g.Ho - 1) * g.stride - g.pt + g.kh > g.H || (g.Wo - 1) * g.stride - g.pl + g.kw > g.W;
         f.div_HoWo = make_fastdiv(a.HoWo);
         f.div_Wo = make_fastdiv(g.Wo);
         const int kt = first_mfma_steps(g);

@@ -228,6 +228,25 @@ def test_conv2d_first_layer_few_pixels(case):
     assert_close(got, O.conv2d(x, w, s, pad), Ci * kh * kw, f"first layer {case}")
 
 
+@pytest.mark.parametrize("case", FIRST_LAYER_FEW_CASES)
+def test_conv2d_first_layer_few_pixels_infinite_weights(case):
+    """A tap outside the image does not count, whatever its weight: infinite and NaN weights at corners of the window, in one
+    channel each; an infinite input value reaches the outputs whose window holds it."""
+    N, Ci, Co, H, W, kh, kw, s, pad = case
+    rng = np.random.default_rng(4350 + N)
+    x = (rng.random((N, Ci, H, W), dtype=np.float32) + 1).astype(np.float32)
+    w = (rng.random((Co, Ci, kh, kw), dtype=np.float32) + 1).astype(np.float32)
+    w[1, 0, 0, 0], w[2, Ci - 1, kh - 1, kw - 1], w[Co - 1, 0, 0, kw - 1] = np.inf, np.nan, -np.inf
+    x[0, 0, 0, 0] = np.inf
+    got, ref = run_conv(x, w, s, pad), O.conv2d(x, w, s, pad)
+    ok = np.isfinite(ref)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[~ok], ref[~ok], equal_nan=True)
+    if (pad[0] or pad[2]) and H > 1:
+        assert ok[:, 1].any() and not ok[:, 1].all()
+    # sums of K positive products, every partial sum below the result: at most K roundings of 2^-24 of it
+    assert (np.abs(got[ok].astype(np.float64) - ref[ok]) <= Ci * kh * kw * 2.0 ** -23 * np.abs(ref[ok])).all()
+
+
 SPLIT_CASES = [  # N, Ci, Co, H, W, kh, kw, stride, pad, kernel: the reduction split over the waves of a workgroup
     (1, 512, 48, 6, 6, 3, 3, 1, (1, 1, 1, 1), "16,1,1"),       # 288 steps, 36 pixels: a ragged third pixel group
     (2, 80, 80, 6, 94, 5, 5, 2, (2, 2, 2, 2), "8,1,1"),        # 125 steps
