@@ -431,6 +431,7 @@ struct FirstArgs {
     int Cib, Cob, K;
     int plain_input;      // the input is a plain [N][C][H][W] tensor (the network's own input): the layout change
                           // of the network boundary then happens in this kernel's gathers
+    int share;            // output blocks of a workgroup
     int padded;           // some window reaches outside the image
     FastDiv div_HoWo, div_Wo;
     unsigned in_bytes, filt_bytes, out_bytes;       // each below 2 GiB
@@ -446,9 +447,11 @@ struct FirstArgs {
 // descriptor, which read zero and drop stores, instead of selects on the values. The kernel's time is the
 // output stream, address arithmetic and waiting, not matrix instructions: 1600 vector instructions per wave
 // with 64-bit addresses and selects, 500 this way (21 -> 16 us on that layer).
-// Layers of fewer than 16384 output pixels take one group per wave (WM = 1: four times the workgroups); a lane per
-// output value (conv_direct) took 6.5, 6.3 and 11.2 us for one image of the residual, the depthwise-separable and the
-// audio CNN, against 2.9, 4.6 and 2.8 us (audio CNN at 64 images 46.9 -> 31.5 us, at 128 65 -> 36.6).
+// Layers of fewer than 16384 output pixels take one group per wave (WM = 1: four times the workgroups) and deal the output
+// blocks out over the grid until there are two workgroups per compute unit (one or four: up to 1.3 times as long at 512 and
+// more channels). A lane per output value (conv_direct) took, in us, 5.9 for 3 -> 16 channels 32x32 (here 2.9), 6.1 for 3 -> 512
+// 9x9 (2.9; 8.9 with all blocks in one workgroup), 10.4 for 1 -> 64 10x4 49x10 (2.7), 3.8 for 8 -> 256 1x1 24x24 (2.5), one image
+// each; no size between 8 and 1024 channels and up to 13824 pixels was faster that way.
 template <int KT, int WM, int CIB, int KW>
 __global__ void __launch_bounds__(256) conv_first_mfma(FirstArgs f)
 {
@@ -483,8 +486,10 @@ __global__ void __launch_bounds__(256) conv_first_mfma(FirstArgs f)
             fa[t] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(flt, live ? f_at + (unsigned)(cob * f_block + t * f_step) : kBeyond, 0, 0));
         }
     };
+    // WM = 1 (few pixels): the workgroup's share of the output blocks; else all of them
+    const int cob0 = WM == 1 ? (int)blockIdx.y * f.share : 0, cob1 = WM == 1 ? min(cob0 + f.share, a.nCob) : a.nCob;
     float fa[KT];
-    filter_of(0, fa);
+    filter_of(cob0, fa);
 
     // All input values of the wave's WM pixel groups are requested before the first matrix instruction: a wave
     // has only a few hundred cycles of arithmetic, so the loads of one group after the other would each expose
@@ -524,9 +529,9 @@ __global__ void __launch_bounds__(256) conv_first_mfma(FirstArgs f)
         return v;
     };
     const int o_block = 4 * a.HoWo * f.Cob;
-    for (int cob = 0; cob < a.nCob; ++cob) {
+    for (int cob = cob0; cob < cob1; ++cob) {
         float fn[KT];
-        filter_of(cob + 1 < a.nCob ? cob + 1 : cob, fn);          // the next block's filter values, under way early
+        filter_of(cob + 1 < cob1 ? cob + 1 : cob, fn);          // the next block's filter values, under way early
         floatx4 acc[WM];
 #pragma unroll
         for (int wm = 0; wm < WM; ++wm) {
@@ -666,7 +671,11 @@ hipError_t launch_conv(const float *in, const float *filt, float *out, const flo
         f.div_Wo = make_fastdiv(g.Wo);
         const int kt = first_mfma_steps(g);
         const bool few = !use_small(g);
-        const dim3 grid((unsigned)(few ? (a.M + 63) / 64 : (a.M + 255) / 256));
+        const unsigned wgs = (unsigned)(few ? (a.M + 63) / 64 : (a.M + 255) / 256);
+        // (few pixels: the output blocks dealt out over the grid, up to two workgroups per compute unit)
+        const int splits = few ? min(a.nCob, max(1, 2 * device_cus() / (int)wgs)) : 1;
+        f.share = (a.nCob + splits - 1) / splits;
+        const dim3 grid(wgs, few ? (unsigned)((a.nCob + f.share - 1) / f.share) : 1u);
         f.in_bytes = (unsigned)((size_t)g.N * g.H * g.W * g.Ci * 4);
         f.out_bytes = (unsigned)((size_t)a.M * g.Co * 4);
         f.filt_bytes = (unsigned)((size_t)g.Co * f.K * 4);

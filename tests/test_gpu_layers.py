@@ -213,6 +213,9 @@ FIRST_LAYER_FEW_CASES = [  # N, Ci, Co, H, W, kh, kw, stride, pad: fewer than 16
     (2, 8, 16, 7, 9, 1, 1, 1, (0, 0, 0, 0)),         # K = 8
     (2, 5, 16, 11, 6, 2, 4, 1, (1, 0, 2, 1)),        # K = 40, five channels
     (130, 3, 16, 11, 11, 3, 3, 1, (1, 1, 1, 1)),     # 15730 pixels: just below the limit
+    (1, 3, 512, 9, 9, 3, 3, 1, (1, 1, 1, 1)),        # every output block a workgroup of its own
+    (24, 8, 1008, 24, 24, 1, 1, 1, (0, 0, 0, 0)),    # 63 output blocks in two shares, the second one short
+    (64, 1, 112, 49, 10, 10, 4, 2, (4, 5, 1, 1)),    # seven in four shares, the last one block
 ]
 
 
