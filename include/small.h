@@ -74,7 +74,8 @@ int small_pack_dw_filter(const float *c1hw, float *blocked, int C, int kh, int k
  *   out[n,co,oh,ow] = sum_{ci,y,x} in[n,ci,oh*stride+y-pad.t, ow*stride+x-pad.l] * filt[co,ci,y,x],
  * taps outside the input contribute 0. in: [N][Ci/Cib][H][W][Cib]; filt: blocked filter;
  * out: [N][Co/Cob][Ho][Wo][Cob]. Cib = Cob = 16 runs on the matrix cores (fp32 instructions, or, for large layers of
- * stride 1, bf16 ones on values in three parts: fp32 precision, errors no larger); any other
+ * stride 1, bf16 ones on values in three parts that hold all 24 bits: a product is then kept to 2^-24 of its size, and sums of
+ * more than one have smaller errors than with the fp32 instructions); any other
  * block sizes (<= 64) run a generic kernel. fp32 accumulation, summation order unspecified. */
 int small_conv2d(const float *in, const float *filt, float *out, int N, int Ci, int Co, int H, int W, int kh,
                  int kw, int stride, small_pad pad, int Cib, int Cob, void *stream);

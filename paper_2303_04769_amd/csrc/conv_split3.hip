@@ -1,12 +1,17 @@
 // fp32 convolution on the bf16 matrix cores, each value as the sum of three bf16 ones.
 //
-// A float has 24 significant bits, a bf16 eight: x = h + m + l with h, m, l the bf16 roundings of x, x - h and x - h - m, and
-// the products of two such sums that matter are hh, hm, mh, mm, hl and lh (what is dropped is below 2^-26 of a product).
-// bf16 products are exact and the matrix instruction adds them in fp32, 32 at a time, so a sum is rounded a few times per 32
-// products where the fp32 instruction rounds every 4: the error against 64 bits is 3.7e-7 of the largest output where it was
-// 4.3e-7 (64 channels, 56x56, 256 images). The bf16 instruction does
-// sixteen times the work of the fp32 one per cycle, six of them replace it: 2.7 times the matrix rate, of which
-// splitting (five and a half vector instructions per value, v_cvt_pk_bf16_f32 rounds two at once) and LDS traffic take
+// A float has 24 significant bits, a bf16 eight: x = h + m + l exactly, with h, m, l the bf16 roundings of x, x - h and
+// x - h - m (|m| up to 2^-8 of |x|, |l| up to 2^-17), and six of the nine products of two such sums are taken: hh, hm, mh, mm, hl
+// and lh. What is dropped, ml, lm and ll, is up to 2^-24 of a product, as much as rounding it to a float costs. bf16 products are
+// exact and the matrix instruction adds them in fp32, 32 at a time. The five small products have sums of their own, added to the
+// large ones' once at the end: their roundings are then 2^-8 of what they are in one sum, and the large products are rounded a
+// few times per 32 where the fp32 instruction rounds every 4. Error against 64 bits, 2-norm, fp32 instruction / here (64 channels
+// 3x3 28x28, 64 images): dense normal filters 4.2e-7 / 1.3e-7 (on rectified inputs 3.1e-7 / 1.0e-7), a tenth of the weights not
+// zero 1.4e-7 / 5.5e-8, two weights 3.0e-8 / 2.6e-8, one 2.53e-8 / 2.57e-8 (at most 1.9 instead of 1.0 x 2^-24 of the product: the
+// only kind of filter that loses). One sum for all six: 3.7e-7 (3.6e-7 rectified), 2.6e-7, 7.0e-8, 5.4e-8, 2 % faster; with ml and
+// lm too 2.53e-8 for one weight and the others unchanged, 11 to 15 % slower.
+// The bf16 instruction does sixteen times the work of the fp32 one per cycle, six of them replace it: 2.7 times the matrix rate,
+// of which splitting (five and a half vector instructions per value, v_cvt_pk_bf16_f32 rounds two at once) and LDS traffic take
 // their share. So every value is split once per workgroup: the tile scheme of conv_u8_tile.hip -- the input rows under TM
 // output pixels staged in LDS with their padding, an entry being the 8 channels of half a block, three planes h, m, l of
 // each; the filter by steps -- with one matrix instruction per (step, tile, product):
@@ -184,11 +189,11 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
         const int n = quotient(a.dHoWs, m), rem = m - n * a.HoWs, oh = quotient(a.dWs, rem);
         base[wm] = ((gb * 2 + half) * plane_e + (n * a.Hv + oh * a.stride - vr0) * a.Wv + (rem - oh * a.Ws) * a.stride) * 16;
     }
-    floatx4 acc[WM][WN];
+    floatx4 acc[WM][WN], low[WM][WN];                          // sums of hh; of all other products
 #pragma unroll
     for (int wm = 0; wm < WM; ++wm)
 #pragma unroll
-        for (int wn = 0; wn < WN; ++wn) acc[wm][wn] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int wn = 0; wn < WN; ++wn) acc[wm][wn] = low[wm][wn] = floatx4{0.f, 0.f, 0.f, 0.f};
     __syncthreads();
 
     // ---- reduction: the next step's filter and the next chunk's input are requested before the matrix instructions and
@@ -217,8 +222,10 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
 #pragma unroll
                 for (int wm = 0; wm < WM; ++wm)
 #pragma unroll
-                    for (int wn = 0; wn < WN; ++wn)
-                        acc[wm][wn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[wn][kPair[t][0]], fb[wm][kPair[t][1]], acc[wm][wn], 0, 0, 0);
+                    for (int wn = 0; wn < WN; ++wn) {
+                        floatx4 &c = t == 0 ? acc[wm][wn] : low[wm][wn];
+                        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[wn][kPair[t][0]], fb[wm][kPair[t][1]], c, 0, 0, 0);
+                    }
             if (end) break;
             f_store(buf ^ 1);
             if (last_st) {
@@ -234,7 +241,7 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
         for (int wn = 0; wn < WN; ++wn)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                acc[wm][wn][r] *= kUnscale;
+                acc[wm][wn][r] = (acc[wm][wn][r] + low[wm][wn][r]) * kUnscale;
                 check = fmaf(acc[wm][wn][r], 0.f, check);
             }
     if (!(__builtin_fabsf(check) < __builtin_inff())) bad[0] = 1;           // (NaN compares false)
@@ -283,10 +290,12 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
                 if ((unsigned)ih >= (unsigned)a.H || (unsigned)iw >= (unsigned)a.W) continue;
                 const float *x = a.in + (((size_t)n * a.nCib + cib) * a.H * a.W + (size_t)ih * a.W + iw) * 16;
                 const float *w = a.filt + (((size_t)cob * a.nCib + cib) * a.taps + tap) * 256 + q * 4;
+                floatx4 u = {0.f, 0.f, 0.f, 0.f};                  // (sixteen products first: a chain of all would lose more bits)
                 for (int c = 0; c < 16; ++c) {
                     const floatx4 wc = *reinterpret_cast<const floatx4 *>(w + c * 16);
-                    v.x = fmaf(x[c], wc.x, v.x); v.y = fmaf(x[c], wc.y, v.y); v.z = fmaf(x[c], wc.z, v.z); v.w = fmaf(x[c], wc.w, v.w);
+                    u.x = fmaf(x[c], wc.x, u.x); u.y = fmaf(x[c], wc.y, u.y); u.z = fmaf(x[c], wc.z, u.z); u.w = fmaf(x[c], wc.w, u.w);
                 }
+                v += u;
             }
         finish(v, cob, (((size_t)n * a.nCob + cob) * a.HoWo + oh * a.Wo + ow) * 16 + q * 4, q);
     }

@@ -310,9 +310,48 @@ def test_conv2d_three_part_products(case, scale):
     got = run_conv(x, w, 1, pad)
     idx = np.r_[0, 1, N // 2, N - 1]
     ref = O.conv2d(x[idx], w, 1, pad)
-    # K products of 24-bit operands, what the three parts drop (2^-26 of each) and the fp32 sums: below K 2^-24 of the largest
+    # K products of 24-bit operands, what the three parts drop (up to 2^-24 of each) and the fp32 sums: below K 2^-24 of the largest
     bound = Ci * kh * kw * 2.0 ** -24 * scale
     assert np.isfinite(got).all() and np.abs(got[idx].astype(np.float64) - ref).max() <= bound + 2.0 ** -22 * np.abs(ref).max()
+
+
+SPARSE_FILTERS = {  # worst error in 2^-24 of sum |x w|, or None; 2-norm error relative to the result's
+    "one": (2.1, 3.5e-8),       # one weight per output: the product's dropped part and the final rounding, 2^-24 each
+    "two": (3.1, 4.2e-8),       # two: one more rounding, of the large products' sum
+    "box": (None, 8e-8),        # 1/9 under one channel: ten roundings, fewer at full size; with all products in one sum 1.3e-7
+    "rectified": (None, 2.6e-7),      # dense weights, inputs >= 0: 3.1e-7 with the fp32 instruction, 3.6e-7 in one sum
+}
+
+
+@pytest.mark.parametrize("kind", sorted(SPARSE_FILTERS))
+@pytest.mark.parametrize("N,Ci,Co,H,W,k", [(64, 64, 64, 28, 28, 3), (24, 16, 64, 37, 35, 5)])
+def test_conv2d_three_part_products_precision(kind, N, Ci, Co, H, W, k):
+    """Filters of few weights, where every rounding of a small product at the size of a large one would show, and rectified
+    inputs, whose sums grow all the way."""
+    p = k // 2
+    assert S.small_conv2d_kernel(N, Ci, Co, H, W, k, k, 1, (p, p, p, p), 16, 16).startswith("conv16_split3")
+    rng = np.random.default_rng(8500 + N)
+    x = rng.standard_normal((N, Ci, H, W)).astype(np.float32)
+    dense = (rng.standard_normal((Co, Ci, k, k)) * np.sqrt(2 / (Ci * k * k))).astype(np.float32)
+    w = np.zeros_like(dense)
+    if kind == "box":
+        w[:, 3] = np.float32(1 / 9)
+    elif kind == "rectified":
+        w, x = dense, np.maximum(x, 0)
+    else:
+        w[:, 1, p, p] = dense[:, 1, p, p]
+        if kind == "two":
+            w[:, Ci - 1, 0, 0] = dense[:, Ci - 1, 0, 0]
+    got = run_conv(x, w, 1, (p, p, p, p))
+    idx = np.r_[0, 1, N // 2, N - 1]
+    xd, wd = torch.from_numpy(x[idx]).double(), torch.from_numpy(w).double()
+    ref = torch.nn.functional.conv2d(xd, wd, padding=p).numpy()
+    size = torch.nn.functional.conv2d(xd.abs(), wd.abs(), padding=p).numpy()
+    err = np.abs(got[idx] - ref)
+    worst, rel = SPARSE_FILTERS[kind]
+    if worst is not None:
+        assert (err <= worst * 2.0 ** -24 * size).all(), (err / np.maximum(size, 1e-30)).max() * 2 ** 24
+    assert np.linalg.norm(err) <= rel * np.linalg.norm(ref), np.linalg.norm(err) / np.linalg.norm(ref)
 
 
 def test_conv2d_three_part_products_infinities():
@@ -337,7 +376,11 @@ def test_conv2d_three_part_products_infinities():
     got = run_conv(clean_x := np.nan_to_num(np.where(np.abs(x) > 2, 0, x), nan=0.0), w, 1, (1, 1, 1, 1))
     ref = O.conv2d(clean_x[[0]], w, 1, (1, 1, 1, 1))
     both = np.isfinite(ref)
-    assert np.array_equal(np.isfinite(got[[0]]), both) and np.allclose(got[[0]][both], ref[both], rtol=1e-4, atol=1e-3)
+    assert np.array_equal(np.isfinite(got[[0]]), both)
+    # sums of sixteen products, then of these: at most 16 + 36 roundings, each at most 2^-24 of sum |x w|
+    size = O.conv2d(np.abs(clean_x[[0]]), np.abs(w), 1, (1, 1, 1, 1))
+    err = np.abs(got[[0]][both].astype(np.float64) - ref[both])
+    assert (err <= 52 * 2.0 ** -24 * size[both].astype(np.float64)).all()
 
 
 def test_conv_identity_filter_is_exact():
