@@ -44,8 +44,8 @@ __device__ __forceinline__ floatx4 epilogue4(floatx4 v, int epi, const float *re
 }
 
 // ---------------------------------------------------------------------------------------------
-// Matrix-core path, Cib = Cob = 16, any window / stride / padding: what neither conv_same.hip nor conv_split.hip takes
-// (tensors of 2 GiB and more).
+// Matrix-core path, Cib = Cob = 16, any window / stride / padding: what no other kernel takes, that is tensors of 2 GiB and
+// more, and short reductions under the windows that conv_same.hip has no tiles for (conv_split_eligible says where).
 //
 // Workgroup tile: TM = WAVES_M*WM*16 flattened output pixels x TN = WAVES_N*WN*16 output channels.
 // Reduction step ("k-step") = one (Ci block, tap y, tap x): 16 input channels.

@@ -1,5 +1,5 @@
 // Convolution with the reduction split over the waves of a workgroup: layers with few output pixels and a long reduction,
-// and every window, stride and padding that conv_same.hip has no tiles for.
+// and, unless their reduction is short, the windows, strides and paddings that conv_same.hip has no tiles for.
 //
 // Bound: streaming the filter (every value is used for a handful of pixels only) and, per workgroup, a chain of matrix
 // instructions. The tiled kernels give a layer of few pixels to a few workgroups that walk the whole reduction one step
@@ -166,12 +166,22 @@ bool conv_split_eligible(const LayerGeom &g)
     if (g.Cib != 16 || g.Cob != 16 || M >= (1L << 30) || tiles >= (1L << 30) || steps >= (1L << 20) ||
         (size_t)g.N * g.Ci * g.H * g.W * 4 >= kBeyond || (size_t)g.Co * g.Ci * g.kh * g.kw * 4 >= kBeyond)
         return false;
-    if (!conv_same_eligible(g)) return true;       // against the gather kernel of conv.hip: 0.96 to 12 times as fast
-    // Against the tiles of conv_same.hip (their us / here): up to one tile per compute unit from 6 steps on (189 tiles of 7
-    // steps 3.9 / 3.1, 96 of 288 36.0 / 10.4), up to two for reductions of 32 (510 of 45 7.7 / 5.0; but 288 of 18 4.6 / 4.5), up
-    // to four for 200 (999 of 243 45.7 / 24.7; but 912 of 144 19.5 / 21.5); above that they win (2090 of 45 13.3 / 12.8, 4032 of
+    if (!conv_same_eligible(g)) {
+        // Against the gather kernel of conv.hip, which spends a barrier per step but stages each input value once for a tile: the
+        // shorter the reduction, the fewer tiles per compute unit until it wins. 500 random layers, time here over time there, for
+        // few / many tiles: 4 steps 0.97 up to one tile a unit, 1.1 to 1.7 beyond (16 -> 32 channels 1x2 48x48 263 images 69 / 26 us,
+        // 16 -> 16 1x3 14x14 9633 images 190 / 58); 8 steps 0.78 to 0.96 / 0.93 to 1.24; 9 to 11 steps 0.70 to 1.0 / 1.04 to 1.33;
+        // 12 to 15 0.54 to 1.08 / 0.97 to 1.21; from 16 on 0.11 to 1.0, with many tiles 0.7 to 1.1 unless the last round of
+        // steps (2 waves, kAhead each) or of output blocks (two a tile) is too empty: 18 steps 0.93 to 1.23.
+        const double most = steps < 4 ? 0 : steps < 8 ? 1 : steps < 9 ? 2.5 : steps < 12 ? (g.Co == 16 ? 8 : 5.5) : 20;
+        const long nCob = g.Co / 16, done = (steps + 2 * kAhead - 1) / (2 * kAhead) * (2 * kAhead) * ((nCob + 1) / 2 * 2);
+        return tiles <= most * cus || (steps >= 16 && 100 * steps * nCob >= 78 * done);
+    }
+    // Against the tiles of conv_same.hip (their us / here): up to one tile per compute unit from 7 steps on (189 tiles of 7
+    // steps 3.9 / 3.1, 96 of 288 36.0 / 10.4; but 51 of 6 3.4 / 3.8), up to two for reductions of 32 (510 of 45 7.7 / 5.0; but 288
+    // of 18 4.6 / 4.5), up to four for 200 (999 of 243 45.7 / 24.7; but 912 of 144 19.5 / 21.5); above that they win (2090 of 45 13.3 / 12.8, 4032 of
     // 63 21.3 / 25.5).
-    return tiles <= cus ? steps >= 6 : tiles <= 2 * cus ? steps >= 32 : tiles <= 4 * cus && steps >= 200;
+    return tiles <= cus ? steps >= 7 : tiles <= 2 * cus ? steps >= 32 : tiles <= 4 * cus && steps >= 200;
 }
 
 const char *conv_split_kernel_name(const LayerGeom &g) { return kVariants[pick_variant(g)].name; }

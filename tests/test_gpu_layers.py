@@ -258,7 +258,7 @@ SPLIT_CASES = [  # N, Ci, Co, H, W, kh, kw, stride, pad, kernel: the reduction s
     (3, 32, 48, 23, 11, 3, 3, 3, (2, 1, 0, 2), "4,1,1"),       # stride 3, uneven padding
     (20, 16, 16, 68, 68, 3, 3, 2, (1, 1, 1, 1), "4,2,1"),      # one output block, many pixels
     (12, 32, 48, 70, 70, 3, 3, 2, (1, 1, 1, 1), "4,2,2"),      # three output blocks: the last workgroup has one
-    (31, 16, 112, 59, 60, 3, 3, 2, (1, 1, 1, 1), "2,2,2"),     # seven output blocks; pixels end inside a group
+    (31, 16, 112, 59, 60, 4, 4, 2, (1, 1, 1, 1), "2,2,2"),     # seven output blocks; pixels end inside a group
 ]
 
 
@@ -313,6 +313,32 @@ def test_conv2d_three_part_products(case, scale):
     # K products of 24-bit operands, what the three parts drop (up to 2^-24 of each) and the fp32 sums: below K 2^-24 of the largest
     bound = Ci * kh * kw * 2.0 ** -24 * scale
     assert np.isfinite(got).all() and np.abs(got[idx].astype(np.float64) - ref).max() <= bound + 2.0 ** -22 * np.abs(ref).max()
+
+
+GATHER_CASES = [  # N, Ci, Co, H, W, kh, kw, stride, pad, kernel: short reductions under windows that have no tiles of their own
+    (1, 16, 16, 5, 5, 1, 2, 1, (0, 0, 0, 0), "4,1,1,1"),       # 2 steps, 20 pixels of a tile of 64
+    (7, 16, 32, 19, 23, 1, 3, 1, (0, 0, 1, 1), "4,1,1,1"),     # tiles across images
+    (3, 16, 144, 39, 37, 3, 1, 2, (1, 1, 0, 0), "4,1,1,1"),    # nine output blocks
+    (40, 16, 16, 25, 27, 2, 2, 1, (1, 0, 0, 1), "4,1,2,1"),    # uneven padding, one output block
+    (9, 48, 96, 40, 41, 1, 2, 2, (0, 0, 0, 1), "4,1,1,2"),     # 6 steps on 27 tiles a compute unit
+    (15, 80, 240, 66, 65, 1, 3, 2, (0, 0, 0, 2), "4,1,1,2"),   # 15 steps; fifteen output blocks: the last tile has one
+    (31, 16, 112, 59, 60, 3, 3, 2, (1, 1, 1, 1), "4,1,1,1"),   # 9 steps: 19.0 us, with the reduction split 26.2
+    (20, 16, 96, 9, 16, 1, 2, 1, (0, 0, 0, 0), "2,2,1,1"),
+    (45, 32, 64, 86, 92, 3, 3, 3, (1, 1, 1, 1), "4,1,1,2"),    # 18 steps, 24 with the last round filled up
+]
+
+
+@pytest.mark.parametrize("case", GATHER_CASES)
+def test_conv2d_gather_kernel(case):
+    N, Ci, Co, H, W, kh, kw, s, pad, tile = case
+    assert S.small_conv2d_kernel(N, Ci, Co, H, W, kh, kw, s, pad, 16, 16) == f"conv16_mfma<{tile}>", case
+    rng = np.random.default_rng(8600 + N + Ci)
+    x = (rng.random((N, Ci, H, W), dtype=np.float32) * 2 - 1).astype(np.float32)
+    w = (rng.random((Co, Ci, kh, kw), dtype=np.float32) * 2 - 1).astype(np.float32)
+    got = run_conv(x, w, s, pad)
+    idx = np.unique(np.r_[0, N // 2, N - 1])
+    assert np.isfinite(got).all()
+    assert_close(got[idx], O.conv2d(x[idx], w, s, pad), Ci * kh * kw, f"conv gather {case}")
 
 
 SPARSE_FILTERS = {  # worst error in 2^-24 of sum |x w|, or None; 2-norm error relative to the result's
