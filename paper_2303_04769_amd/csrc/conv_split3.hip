@@ -342,19 +342,28 @@ Plan plan_tile(const LayerGeom &g)
 }  // namespace
 
 // Where it beats the fp32 matrix instruction: stride 1 (a strided tile stages too many rows), nine steps or more, at least
-// 15 / 16 of a workgroup per compute unit, and few channels padded (to 64 out, 32 in): against the tiles of conv_same.hip at most
-// one part in seven of the work, elsewhere two in five. us with the fp32 instruction / here: 64 -> 64 channels 28 x 28, 64
-// images (392 workgroups) 39.4 / 27.8 (these figures before the scale of the parts, some 5 %), 40 images (245) 22.7 / 21.4, 8 x 8, 300 images (150) 16.4 / 21.3; 64 -> 112 62.7 /
-// 50.4; 48 -> 64 28 x 28 x 40 18.3 / 20.4; 16 -> 64 (five steps) 7 x 7 x 500 7.4 / 9.4; 48 -> 64 5 x 5 28 x 28 x 64 88 / 52.
+// 15 / 16 of a workgroup per compute unit, and a time below the other kernels', from a model fitted to 1080 random layers of 150 to
+// 1600 workgroups (11 % and 13 % root mean square; of 560 taken then, 20 are slower by more than 3 %, two by more than 10). The
+// fullest compute unit counts, with a workgroup alone on it as 1.25; staging a chunk costs a step; work on padded channels, taps or
+// columns is done but does not count; an odd number of output blocks costs the other kernels an empty block, or conv_same.hip its
+// smaller tile (7 %). At full use the time is 0.62 of that of conv_same.hip's tiles and 0.495 of the others'. us with
+// the fp32 instruction / here: 64 -> 64 channels 56 x 56, 256 images (24.5 workgroups a unit) 454 / 355, 28 x 28, 64 images (1.53)
+// 41.5 / 31.7, 48 images (1.15; not taken) 29.7 / 30.1, 40 images (0.96) 24.7 / 24.8, 8 x 8, 300 images (0.59; not taken) 18.1 / 23.7;
+// 64 -> 112 28 x 28 x 64 66 / 58; 48 -> 64 28 x 28 x 40 (not taken) 20.1 / 23.6; 16 -> 64 (five steps; not taken) 7 x 7 x 500 9.0 /
+// 11.5; 48 -> 64 5 x 5 28 x 28 x 64 127 / 60; 256 -> 96 1 x 3 79 x 20 x 12 (1.16; not taken) 36 / 50.
 bool conv_split3_eligible(const LayerGeom &g)
 {
     if (g.stride != 1) return false;
     const Plan pl = plan_tile(g);
     if (!pl.ok || pl.n_chunks * pl.steps < 9) return false;
     const int nCib = g.Ci / 16, nCob = g.Co / 16, n_cot = (nCob + kNCT - 1) / kNCT;
-    const long wgs = ((long)g.N * pl.strips * g.Ho * pl.Ws + kTM - 1) / kTM * n_cot;
-    const double useful = (double)nCib * g.kh * g.kw * nCob / (2.0 * pl.n_chunks * pl.steps * n_cot * kNCT);
-    return wgs * 16 >= 15L * device_cus() && useful >= (conv_same_eligible(g) ? 0.86 : 0.6);
+    const long cus = device_cus(), wgs = ((long)g.N * pl.strips * g.Ho * pl.Ws + kTM - 1) / kTM * n_cot;
+    if (wgs * 16 < 15 * cus) return false;
+    const bool same = conv_same_eligible(g);
+    const double blocks = same ? nCob * (nCob % 2 ? 1.07 : 1.0) : (nCob + 1) / 2 * 2;
+    const double useful = nCib * g.kh * g.kw * blocks * g.Wo / (2.0 * pl.n_chunks * (pl.steps + 1) * n_cot * kNCT * pl.strips * pl.Ws);
+    const long most = (wgs + cus - 1) / cus;
+    return (same ? 0.62 : 0.495) * (most == 1 ? 1.25 : (double)most) * cus < wgs * useful;
 }
 
 const char *conv_split3_kernel_name() { return "conv16_split3<2,4,4,1>"; }

@@ -290,10 +290,10 @@ def test_conv2d_split_reduction_infinities():
 
 SPLIT3_CASES = [  # N, Ci, Co, H, W, kh, kw, pad: stride 1, at least 240 tiles of 128 pixels x 64 channels
     (40, 32, 64, 28, 28, 3, 3, (1, 1, 1, 1)),        # one chunk of two input blocks
-    (21, 32, 112, 29, 31, 3, 3, (1, 1, 1, 1)),       # seven output blocks; two strips, the second a column short; ragged end
+    (34, 32, 112, 29, 31, 3, 3, (1, 1, 1, 1)),       # seven output blocks; two strips, the second a column short; ragged end
     (640, 64, 64, 7, 7, 3, 3, (1, 1, 1, 1)),         # tiles over three images
     (24, 16, 64, 37, 35, 5, 5, (2, 2, 2, 2)),        # one input block: two taps a step, the last step has one
-    (12, 48, 64, 53, 50, 2, 4, (1, 0, 0, 3)),        # an odd input block, a window without a middle, uneven padding
+    (23, 48, 64, 53, 50, 2, 4, (1, 0, 0, 3)),        # an odd input block, a window without a middle, uneven padding
     (40, 112, 64, 30, 30, 3, 3, (0, 0, 0, 0)),       # seven input blocks, no padding
 ]
 
