@@ -68,33 +68,27 @@ __device__ __forceinline__ void to_channels(const unsigned (&o)[CB], unsigned (&
 // A lane owns four neighbouring pixels of one (image, channel block) plane: one word of four pixels per channel on the
 // plain side, 4 * CB contiguous bytes on the blocked side, the transposition between them in registers (byte permutes,
 // no LDS). The plain side is 256 contiguous bytes per wave and access; the CB accesses of either side are independent,
-// so a lane has its whole share of the tensor in flight at once. Where a plane's pixels are no multiple of four the
-// lane of the rest moves bytes.
+// so a lane has its whole share of the tensor in flight at once. Where a plane's pixels are no multiple of four its last lane
+// takes the last four, some of which the lane before it writes too, with the same bytes (moving the rest byte by byte took
+// that lane up to 48 memory round trips: 32 channels 63x1, 43 images 8.3 us, 2.8 this way). Planes of at least four pixels.
 template <int CB, bool UNPACK>
 __global__ void __launch_bounds__(256) pack_u8_words(const unsigned char *src, unsigned char *dst, int HW, int groups,
                                                      FastDiv div_groups, int total)
 {
     const int i = (int)(blockIdx.x * 256u + threadIdx.x);
     if (i >= total) return;
-    const int plane = div_groups.div(i), pix = (i - plane * groups) * 4;       // plane = n * nCb + cb
+    const int plane = div_groups.div(i), group = i - plane * groups;          // plane = n * nCb + cb
+    const int pix = group + 1 < groups ? group * 4 : HW - 4;
     const size_t base = (size_t)plane * HW * CB;                              // of the plane, in either layout
     const unsigned char *in = src + base + (UNPACK ? (size_t)pix * CB : (size_t)pix);
     unsigned char *out = dst + base + (UNPACK ? (size_t)pix : (size_t)pix * CB);
-    if (HW - pix >= 4) {                                                       // (pix + 4 may pass 2^31)
-        unsigned w[CB], o[CB];
+    unsigned w[CB], o[CB];
 #pragma unroll
-        for (int c = 0; c < CB; ++c) w[c] = load_word(UNPACK ? in + 4 * c : in + (size_t)c * HW);
-        if (UNPACK) to_channels<CB>(w, o);
-        else to_pixels<CB>(w, o);
+    for (int c = 0; c < CB; ++c) w[c] = load_word(UNPACK ? in + 4 * c : in + (size_t)c * HW);
+    if (UNPACK) to_channels<CB>(w, o);
+    else to_pixels<CB>(w, o);
 #pragma unroll
-        for (int c = 0; c < CB; ++c) store_word(UNPACK ? out + (size_t)c * HW : out + 4 * c, o[c]);
-    } else {
-        for (int j = 0; j < HW - pix; ++j)
-            for (int c = 0; c < CB; ++c) {
-                if (UNPACK) out[(size_t)c * HW + j] = in[j * CB + c];
-                else out[j * CB + c] = in[(size_t)c * HW + j];
-            }
-    }
+    for (int c = 0; c < CB; ++c) store_word(UNPACK ? out + (size_t)c * HW : out + 4 * c, o[c]);
 }
 
 // Any block size: one lane per byte of the blocked tensor.
@@ -127,15 +121,19 @@ void launch_words(const unsigned char *src, unsigned char *dst, long planes, int
 
 }  // namespace
 
-// The word kernel for the block sizes of the networks' inputs (1, 3) and of their tensors (4, 8, 16): 64 x 128 x 28 x 28
-// codes back to plain in 8.0 us a call, which is what enqueueing a call takes, against 18.9 us with a lane per byte.
+// The word kernel for the block sizes of the networks' inputs (1, 3) and of their tensors (4, 8, 16), a lane per byte for the
+// others, for planes of fewer than four pixels, and for small tensors in 16-byte blocks whose planes are small or no multiple of
+// four pixels, where sixteen scattered accesses in a row are the lane's time. Kernel us, a lane per byte / words: 64x128x28x28
+// packed 19.4 / 4.7, back 20.3 / 3.5; 256x3x32x32 in one block 3.9 / 2.3; 1x16x83x83 (not taken) 2.4 / 2.7; 3000 planes of 2x2
+// (not taken) 2.6 / 4.0; 300 thousand codes of 5x5 planes 2.9 / 3.1, a million 4.6 / 3.3; a million of 2x2 ones 4.6 / 4.1.
 hipError_t launch_pack_u8(const unsigned char *src, unsigned char *dst, int N, int C, int H, int W, int Cb, bool unpack,
                           hipStream_t s)
 {
     const size_t total = (size_t)N * C * H * W;
     const int HW = H * W;
     const long planes = (long)N * (C / Cb);
-    if (planes * ((HW + 3L) / 4) < (1L << 31) - 256) {
+    const bool scattered = Cb == 16 && total < (HW == 4 ? 800000u : 300000u) && (HW < 64 || HW % 4 != 0);
+    if (HW >= 4 && !scattered && planes * ((HW + 3L) / 4) < (1L << 31) - 256) {
         switch (Cb) {
             case 1: launch_words<1>(src, dst, planes, HW, unpack, s); return hipGetLastError();
             case 3: launch_words<3>(src, dst, planes, HW, unpack, s); return hipGetLastError();

@@ -54,7 +54,8 @@ def test_pack_unpack(shape, Cb):
 
 
 @pytest.mark.parametrize("Cb", [1, 2, 3, 4, 8, 16])
-@pytest.mark.parametrize("N,H,W", [(1, 1, 1), (3, 1, 3), (2, 2, 2), (5, 3, 7), (2, 16, 16), (3, 13, 21), (1, 1, 1027)])
+@pytest.mark.parametrize("N,H,W", [(1, 1, 1), (3, 1, 3), (2, 2, 2), (5, 3, 7), (2, 16, 16), (3, 13, 21), (1, 1, 1027),
+                                   (2100, 1, 5), (7000, 2, 2), (50, 13, 17), (60, 1, 163)])
 def test_pack_unpack_words(N, H, W, Cb):
     """Planes of 1 .. 3 pixels, a multiple of four and every remainder, several planes to a workgroup and several
     workgroups to a plane: copies, so bit for bit; also from and to addresses that are no multiple of four."""
