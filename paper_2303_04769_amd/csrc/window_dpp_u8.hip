@@ -159,22 +159,23 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
     }
 }
 
-// Rows per strip: 7, unless strips of 5 or 9 leave clearly less to do. A wave costs about 180 + 52 rows vector instructions, also
-// for the rows that its strip lacks; up to two waves a SIMD the busiest one counts, beyond that their average. Measured (us, 7 -> the
-// one taken): 1024 images of 64 channels 25x5 11.0 -> 9.4 with 9 (three strips of 8 or 9 rows instead of four of 6 or 7), 2000 of 32
-// 5x9 5.6 -> 4.95 with 5, one of 64 48x48 3.4 -> 3.1 with 5 (fewer waves than SIMDs: the shorter chain). 7 stays where the
-// model's gain is below 8 %: 100 of 96 31x40 with zw != 128 11.8 against 12.5 with 9, which holds more registers; and 56, 28, 14
-// and 7 rows are whole strips of 7.
+// Rows per strip: 7, unless strips of 5 or 9 leave less to do. A wave costs about 180 + 52 rows, also for the rows that its strip
+// lacks, and 4 % more with 9, which hold more registers; up to four waves a SIMD the busiest one counts, beyond that their
+// average. Over 500 random layers the kernel takes 0.943 of its time with strips of 7 alone (the best of the three each time:
+// 0.940); five take 3 to 5 % longer. us with 7 / with the one taken: 1024 images of 64 channels 25x5 11.3 / 10.7 with 9 (three
+// strips of 8 or 9 rows instead of four of 6 or 7), 2000 of 32 5x9 6.0 / 5.4 with 5, one of 64 48x48 3.9 / 3.6 with 5 (fewer
+// waves than SIMDs: the shorter chain); 7 stays for one of 512 86x86 (2.8 waves a SIMD; 6.7, 7.5 with 9's 2.2) and 100 of 96
+// 31x40 with zw != 128 (12.7, 13.4 with 5 or 9).
 int strip_rows(const LayerGeom &g, long planes_by_bands)
 {
     const double simds = 4.0 * device_cus();
     auto cost = [&](int rows) {
-        const double per_simd = (double)planes_by_bands * ((g.H + rows - 1) / rows) / simds;
-        return (per_simd <= 1 ? 1 : per_simd <= 2 ? 2 : per_simd) * (180 + 52 * rows);
+        const long waves = planes_by_bands * ((g.H + rows - 1) / rows), rounds = (waves + (long)simds - 1) / (long)simds;
+        return (rounds <= 4 ? (double)rounds : waves / simds) * (180 + 52 * rows) * (rows == 9 ? 1.04 : 1.0);
     };
     const double c5 = cost(5), c7 = cost(7), c9 = cost(9);
-    if (c5 < c9) return c5 < 0.92 * c7 ? 5 : 7;
-    return c9 < 0.92 * c7 ? 9 : 7;
+    if (c5 < c9) return c5 < 0.96 * c7 ? 5 : 7;
+    return c9 < 0.96 * c7 ? 9 : 7;
 }
 
 template <int ROWS>
