@@ -365,22 +365,45 @@ Plan plan_tile(const LayerGeom &g)
     return best;
 }
 
-// Where the register-only kernels of quant.hip stay the better ones (us there / here, measured):
-//   - reductions of at most 20 chunks, which their short form holds in registers whole: 16 channels 32 x 32 x 100 images
-//     5.3 / 6.6, 32 channels 16 x 16 x 100 images 4.0 / 4.9;
-//   - many small images of a multiple of 64 channels, where the rows staged around each image weigh most: 256 channels
-//     14 x 14 x 64 images 18.2 / 19.0, 512 channels 7 x 7 x 64 images 23.9 / 25.4;
-//   - strided layers whose rows only the smallest tile can stage, unless that fills the chip no more than twice: 48 -> 320
-//     channels 86 x 86 x 12 images 16.0 / 22.9, but 272 -> 96 channels 37 x 19 x 3 images 24.5 / 14.0.
-// Elsewhere, for instance: 128 channels 28 x 28 x 64 images 22.7 / 16.5, 64 channels 56 x 56 x 64 images 25.9 / 20.8, 240 -> 64
-// channels 57 x 57 x 5 images 28.1 / 14.9, 112 channels 10 x 10 x 76 images 11.6 / 7.5.
+// Where the register-only kernels of quant.hip stay the better ones: reductions of at most 20 chunks, which their short form
+// holds in registers whole (16 channels 32 x 32 x 100 images 5.3 us there, 6.6 here; 32 channels 16 x 16 x 100 4.0 / 4.9), and
+// where the two models below say so. They are fitted to 3300 measured pairs of layer and tile (us; 3 to 8 % root mean square for
+// the tiles, 7 to 13 for the kernels there), w being the workgroups of the fullest compute unit:
+//   here   3.0 + a w + phases (b + c w) + chunks (d + e w)       a phase: kTG steps; a chunk: input brought in and two barriers
+//   there  3.5 + a w + steps (b + c w) + d passes               a step: one matrix instruction of four 16-byte chunks per tile;
+//          a pass: every megabyte of input beyond four read once more, per window row and group of output blocks
+// On 900 fresh random layers the rule leaves 23 more than 3 % slower than there, eight of them by 10 to 31 % (rules on sizes alone
+// left 184, by up to 1.9 times: windows of two or three taps on many channels bring in a chunk for a single phase, and few channels out share it
+// with few others). us there / here: 128 channels 28 x 28 x 64 images 22.7 / 16.5, 64 channels 56 x 56 x 64 25.9 / 20.8, 240 -> 64
+// channels 57 x 57 x 5 28.1 / 14.9, 112 channels 10 x 10 x 76 11.6 / 7.5; not taken: 272 -> 128 2 x 2 14 x 14 x 102 19.3 / 35.3,
+// 512 -> 48 1 x 3 35 x 35 x 12 9.2 / 13.4, 128 -> 16 3 x 3 stride 2 47 x 91 x 14 6.7 / 8.8, 512 channels 7 x 7 x 64 23.9 / 25.4.
+struct Rate { double a, b, c, d, e; };
+constexpr Rate kHere[kNumTiles] = {{2.88, 0.43, 0.38, 0.34, 0.51}, {2.56, 0.47, 0.56, 0.20, 0.40}, {1.42, 0.33, 0.30, 0.43, 0.26},
+                                   {1.68, 0.51, 0.35, 0.35, 0.13}, {0.86, 0.32, 0.23, 0.43, 0.15}, {0.67, 0.34, 0.17, 0.48, 0.14},
+                                   {1.79, 0.39, 0.25, 0.68, 0.21}, {1.06, 0.31, 0.19, 0.52, 0.16}, {1.07, 0.38, 0.19, 0.67, 0.22},
+                                   {0.75, 0.25, 0.13, 0.56, 0.18}};
+// [input blocks a multiple of four][output blocks of a workgroup: 1, 2, 4]
+constexpr Rate kThere[2][3] = {{{0.74, 0.34, 0.093, 0.016, 0}, {1.10, 0.36, 0.110, 0.013, 0}, {1.97, 0.55, 0.091, 0.042, 0}},
+                               {{0.39, 0.086, 0.085, 0.054, 0}, {0.64, 0.062, 0.120, 0.043, 0}, {1.34, 0.060, 0.168, 0.052, 0}}};
+
 bool better_in_registers(const LayerGeom &g, const Plan &pl)
 {
-    const int nCib = g.Ci / 16, nCob = g.Co / 16;
-    const long M = (long)g.N * g.Ho * g.Wo, cus = device_cus();
-    if (nCib * g.kh * g.kw <= 20) return true;
-    if (nCib % 4 == 0 && g.Ho * g.Wo < 200 && ((M + 127) / 128) * ((nCob + 3) / 4) >= cus * 3 / 4) return true;
-    return pl.tile == 5 && ((M + 31) / 32) * ((nCob + 3) / 4) > 2 * cus;
+    const int nCib = g.Ci / 16, nCob = g.Co / 16, taps = g.kh * g.kw;
+    if (nCib * taps <= 20) return true;
+    const long cus = device_cus();
+    // workgroups of the fullest compute unit; many are as good as spread evenly
+    auto fullest = [&](long wgs) { return wgs < 4 * cus ? (double)((wgs + cus - 1) / cus) : (double)wgs / cus; };
+    const Tile &k = kTiles[pl.tile];
+    const int tm = 16 * k.wm * k.wvm, nct = k.wn * k.wvn;
+    const double w = fullest(((long)g.N * pl.strips * g.Ho * pl.Ws + tm - 1) / tm * ((nCob + nct - 1) / nct));
+    const Rate &h = kHere[pl.tile];
+    const double here = 3.0 + h.a * w + pl.n_chunks * (pl.phases * (h.b + h.c * w) + h.d + h.e * w);
+    const int wn = nCob % 4 == 0 ? 4 : nCob % 2 == 0 ? 2 : 1;
+    const double v = fullest(((long)g.N * g.Ho * g.Wo + 127) / 128 * (nCob / wn));
+    const Rate &t = kThere[nCib % 4 == 0][wn / 2];
+    const double mb = 1e-6 * (double)g.N * g.Ci * g.H * g.W - 4.0, passes = mb > 0 ? mb * (nCob / wn) * g.kh : 0.0;
+    const double there = 3.5 + t.a * v + (double)((nCib * taps + 3) / 4) * (t.b + t.c * v) + t.d * passes;
+    return here >= there;
 }
 
 }  // namespace

@@ -149,7 +149,10 @@ TILE_CASES = [  # N, Ci, Co, H, W, kh, kw, stride, pad, zx, zw: windows through 
     (2, 64, 80, 6, 5, 2, 7, 1, (1, 0, 3, 6), 77, 140),         # wide window, uneven padding
     (2, 32, 16, 9, 8, 5, 3, 3, (2, 2, 1, 1), 10, 20),          # stride 3, fifteen taps
     (4, 96, 48, 9, 9, 3, 3, 1, (0, 0, 0, 0), 128, 128),        # no padding, no correction sums
+    (1, 368, 240, 1, 1, 3, 3, 1, (1, 1, 1, 1), 5, 250),        # one pixel on a number of blocks that is no multiple of four
+    (2, 80, 80, 6, 5, 2, 7, 1, (1, 0, 3, 6), 77, 140),         # ... a wide window
 ]
+TILE_CASES_ELSEWHERE = [TILE_CASES[7], TILE_CASES[8]]          # the register kernels are faster there
 
 
 @pytest.mark.parametrize("case", TILE_CASES)
