@@ -32,14 +32,14 @@ struct RU8Layer {
     int taps;                      // taps | kw << 8 | window height << 16
     int src, src2, dst;            // LDS byte offsets
     int table;                     // first chunk-table entry | chunks << 16
-    int filt_bytes, Co;
+    int filt_bytes, sums_bytes;    // sums: the channel sums behind the filter in LDS (convolutions only)
     int z;                         // zx | zw << 8 | zy << 16 | shift << 24   (add: za, zb, zy, shift)
     int clamp;                     // lo | hi << 8 | pixel groups of a unit << 16 | Cob << 24
     int mult, amax;                // (add: mult_a, mult_b)
     unsigned magic, shift;         // division by Wo (average pooling: by the pixel count)
     int inv_unit, inv_taps;        // ceil(2^20 / d) of output blocks, and of taps
     int inv_kw;
-    int sums_bytes;                // of the channel sums behind the filter in LDS (convolutions only)
+    int Co;                        // outputs of a closing fully connected layer
 };
 struct RU8Args {
     const unsigned char *in;
