@@ -723,17 +723,11 @@ hipError_t launch_conv(const float *in, const float *filt, float *out, const flo
     if (conv_pw_eligible(g)) return launch_conv_pw(in, filt, out, a.res, g, epilogue, s, bn);
     const int tile = pick_tile(g);
     if (conv_same_eligible(g)) return launch_conv_same(in, filt, out, a.res, g, tile, epilogue, s, 0, 0, 0, bn);
-    switch (tile) {
-        case SAME_128x128: launch_mfma<2, 2, 4, 4>(a, s); break;
-        case SAME_64x128: launch_mfma<1, 4, 4, 2>(a, s); break;
-        case SAME_128x64: launch_mfma<2, 2, 4, 2>(a, s); break;
-        case SAME_64x64: launch_mfma<2, 2, 2, 2>(a, s); break;
-        case SAME_128x32: launch_mfma<4, 1, 2, 2>(a, s); break;
+    switch (tile) {                      // (the tiles that pick_tile returns)
         case SAME_64x32: launch_mfma<4, 1, 1, 2>(a, s); break;
         case SAME_128x16: launch_mfma<4, 1, 2, 1>(a, s); break;
         case SAME_32x64: launch_mfma<2, 2, 1, 2>(a, s); break;
         case SAME_32x32: launch_mfma<2, 2, 1, 1>(a, s); break;
-        case SAME_256x16: launch_mfma<4, 1, 4, 1>(a, s); break;
         default: launch_mfma<4, 1, 1, 1>(a, s); break;
     }
     return hipGetLastError();

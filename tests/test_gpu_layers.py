@@ -8,7 +8,7 @@ import torch
 
 import paper_2303_04769_amd as S
 from oracle import oracle as O
-from gpu_util import DEV, Guarded, assert_bits, assert_close, dev
+from gpu_util import CANARY, DEV, Guarded, assert_bits, assert_close, dev
 
 pytestmark = pytest.mark.gpu
 
@@ -339,6 +339,32 @@ def test_conv2d_gather_kernel(case):
     idx = np.unique(np.r_[0, N // 2, N - 1])
     assert np.isfinite(got).all()
     assert_close(got[idx], O.conv2d(x[idx], w, s, pad), Ci * kh * kw, f"conv gather {case}")
+
+
+@pytest.mark.parametrize("N,Ci,Co,H,W,k,tile", [
+    (4100, 16, 16, 128, 128, 3, "4,1,2,1"),      # input and output above 4 GiB
+    (2060, 64, 16, 90, 91, 3, "4,1,2,1"),        # the input alone; images that end inside a tile
+    (4100, 64, 64, 64, 64, 1, "2,2,1,2"),        # a pointwise layer
+    (2050, 16, 48, 128, 128, 5, "4,1,1,1"),      # a window without tiles of its own, from 2 GiB on
+])
+def test_conv2d_large_tensors(N, Ci, Co, H, W, k, tile):
+    """Byte offsets beyond 31 and 32 bits: the gather kernel, against the same images in three batches that the other kernels take."""
+    p = k // 2
+    args = (Ci, Co, H, W, k, k, 1, (p, p, p, p), 16, 16)
+    assert S.small_conv2d_kernel(N, *args) == f"conv16_mfma<{tile}>" and not S.small_conv2d_kernel(N // 3 + 1, *args).startswith("conv16_mfma")
+    g = torch.Generator(DEV).manual_seed(N)
+    x = torch.rand(N * Ci * H * W, device=DEV, generator=g) * 2 - 1
+    w = torch.rand(Co * Ci * k * k, device=DEV, generator=g) * 2 - 1
+    per_in, per_out = Ci * H * W, Co * H * W
+    out = torch.full((N * per_out + 64,), CANARY, device=DEV)
+    S.small_conv2d(x, w, out[:N * per_out], N, *args)
+    assert bool((out[N * per_out:] == CANARY).all())
+    for lo in range(0, N, N // 3 + 1):
+        n = min(N // 3 + 1, N - lo)
+        part = torch.empty(n * per_out, device=DEV)
+        S.small_conv2d(x[lo * per_in:(lo + n) * per_in], w, part, n, *args)
+        # two sums of K products of at most 1, each with at most K roundings of 2^-24 of the largest partial sum
+        assert float((out[lo * per_out:(lo + n) * per_out] - part).abs().max()) <= 2 * (Ci * k * k) ** 1.5 * 2.0 ** -24
 
 
 SPARSE_FILTERS = {  # worst error in 2^-24 of sum |x w|, or None; 2-norm error relative to the result's
