@@ -95,12 +95,12 @@ CONV_CASES = [  # N, Ci, Co, H, W, kh, kw, stride, pad
     (2, 16, 32, 32, 32, 3, 3, 2, (0, 1, 0, 1)),      # 'same' stride 2
     (3, 32, 32, 31, 31, 3, 3, 2, (1, 1, 1, 1)),      # stride 2, odd image, left / top padding
     (5, 48, 64, 20, 12, 3, 3, 2, (0, 1, 0, 1)),      # stride 2, non-square, three input-channel blocks
-    (2, 16, 32, 32, 32, 3, 3, 2, (1, 1, 1, 1)),      # stride 2 whose last tap stays inside the image: gather kernel
+    (2, 16, 32, 32, 32, 3, 3, 2, (1, 1, 1, 1)),      # stride 2 whose last tap stays inside the image
     (4, 64, 32, 15, 15, 1, 1, 2, (0, 0, 0, 0)),      # 1x1 stride 2, odd image, two planes per step
     (2, 16, 16, 9, 9, 1, 1, 3, (0, 0, 0, 0)),        # 1x1 stride 3
     (1, 32, 16, 7, 9, 5, 3, 2, (2, 2, 1, 1)),        # odd window
     (2, 16, 16, 6, 6, 3, 3, 1, (0, 0, 0, 0)),        # no padding
-    (4, 256, 128, 7, 7, 3, 3, 1, (1, 1, 1, 1)),      # tiles straddle images, 128-wide channel tile
+    (4, 256, 128, 7, 7, 3, 3, 1, (1, 1, 1, 1)),      # pixel groups straddle images, a long reduction
     (2, 1, 64, 49, 10, 10, 4, 2, (4, 5, 1, 1)),      # generic path: Ci = 1
     (2, 3, 16, 32, 32, 3, 3, 1, (1, 1, 1, 1)),       # generic path: Ci = 3
     (1, 3, 8, 96, 96, 3, 3, 2, (0, 1, 0, 1)),        # generic path: 8-channel output block
@@ -121,13 +121,44 @@ def test_conv2d(case):
 
 
 def test_conv2d_large_tiles():
-    """Enough pixels that the 128-pixel tiles are chosen (>= 256 workgroups) for every channel-tile width."""
+    """Layers that fill the chip several times over, whatever kernel takes them (SAME_TILE_CASES go by kernel and tile)."""
     rng = np.random.default_rng(77)
     for Ci, Co, N, H in [(32, 128, 18, 45), (16, 64, 10, 58), (16, 32, 9, 61), (16, 16, 9, 61)]:
         x = (rng.random((N, Ci, H, H), dtype=np.float32) * 2 - 1).astype(np.float32)
         w = (rng.random((Co, Ci, 3, 3), dtype=np.float32) * 2 - 1).astype(np.float32)
         got = run_conv(x, w, 1, (1, 1, 1, 1))
         assert_close(got, O.conv2d(x, w, 1, (1, 1, 1, 1)), Ci * 9, f"conv large {Ci}->{Co}")
+
+
+SAME_TILE_CASES = [  # N, Ci, Co, H, W, k, stride, pad, kernel: every tile that 3x3 and 1x1 layers have in conv_same.hip
+    (4, 16, 112, 25, 6, 3, 1, (1, 1, 1, 1), "conv16_same<4,1,1,1,3,1,1>"),        # 64 x 16; odd rows; tiles across images
+    (15, 16, 128, 23, 6, 3, 1, (1, 1, 1, 1), "conv16_same<4,1,1,2,3,1,1>"),       # 64 x 32
+    (6, 80, 144, 25, 27, 3, 1, (1, 1, 1, 1), "conv16_same<4,1,1,1,3,1,1>"),       # five input blocks, nine output blocks
+    (13, 16, 96, 19, 11, 3, 1, (1, 1, 1, 1), "conv16_same<2,2,1,1,3,1,1>"),       # 32 x 32; tiles across images, odd images
+    (11, 16, 16, 39, 41, 3, 1, (1, 1, 1, 1), "conv16_same<4,1,2,1,3,1,1>"),       # 128 x 16, one output block
+    (2, 16, 256, 13, 37, 3, 2, (1, 1, 1, 1), "conv16_same<4,1,1,1,3,1,2>"),       # stride 2, odd images
+    (226, 16, 64, 13, 5, 3, 2, (1, 1, 1, 1), "conv16_same<4,1,1,2,3,1,2>"),       # ... 21 output pixels an image
+    (54, 32, 16, 33, 55, 3, 2, (1, 1, 1, 1), "conv16_same<4,1,2,1,3,1,2>"),
+    (3, 80, 96, 59, 59, 3, 2, (1, 1, 1, 1), "conv16_same<2,2,1,1,3,1,2>"),
+    (46, 16, 240, 13, 14, 3, 1, (1, 1, 1, 1), "conv16_img<4,1,1,1,3,1,1>"),       # tiles end with the image: 182 pixels
+    (7, 16, 240, 37, 55, 3, 1, (1, 1, 1, 1), "conv16_img<4,1,1,2,3,1,1>"),        # fifteen output blocks under tiles of two
+    (5, 16, 32, 7, 3, 1, 3, (0, 0, 0, 0), "conv16_same<2,2,1,1,1,1,1>"),          # 1x1, one input block, stride 3
+    (2, 32, 48, 5, 37, 1, 2, (0, 0, 0, 0), "conv16_same<2,2,1,1,1,2,1>"),         # two planes a step, three output blocks
+    (5, 16, 80, 9, 3, 1, 2, (0, 0, 0, 0), "conv16_same<2,2,1,2,1,1,1>"),          # 32 x 64, five output blocks
+    (2, 64, 64, 3, 22, 1, 2, (0, 0, 0, 0), "conv16_same<2,2,1,2,1,2,1>"),
+    (2, 16, 16, 7, 16, 1, 1, (0, 0, 0, 0), "conv16_same<4,1,1,1,1,1,1>"),         # 64 x 16, 1x1
+    (2, 32, 16, 9, 12, 1, 2, (0, 0, 0, 0), "conv16_same<4,1,1,1,1,2,1>"),
+]
+
+
+@pytest.mark.parametrize("case", SAME_TILE_CASES)
+def test_conv2d_same_tiles(case):
+    N, Ci, Co, H, W, k, s, pad, kernel = case
+    assert S.small_conv2d_kernel(N, Ci, Co, H, W, k, k, s, pad, 16, 16) == kernel, case
+    rng = np.random.default_rng(8700 + N + Co)
+    x = (rng.random((N, Ci, H, W), dtype=np.float32) * 2 - 1).astype(np.float32)
+    w = (rng.random((Co, Ci, k, k), dtype=np.float32) * 2 - 1).astype(np.float32)
+    assert_close(run_conv(x, w, s, pad), O.conv2d(x, w, s, pad), Ci * k * k, f"conv tile {case}")
 
 
 PERSISTENT_CASES = [  # N, Ci, Co, H, W, k: enough images that a workgroup walks several of them
