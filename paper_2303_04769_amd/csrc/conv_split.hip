@@ -26,13 +26,6 @@ struct SplitArgs {
     FastDiv dHoWo, dWo, dTaps, dKw, dGroups;
 };
 
-// FastDiv without a branch (a division by one is the sum's second term)
-__device__ __forceinline__ int quotient(const FastDiv &f, int n)
-{
-    const unsigned all = f.d == 1 ? ~0u : 0u;
-    return (int)((__umulhi((unsigned)n, f.magic) + ((unsigned)n & all)) >> f.shift);
-}
-
 template <int WAVES, int WM, int WN>
 __global__ void __launch_bounds__(64 * WAVES) conv16_split(SplitArgs a)
 {

@@ -43,12 +43,6 @@ struct Split3Args {
     FastDiv dHoWs, dWs, dWv, dHv, dStrips, dCt, dkw;
 };
 
-__device__ __forceinline__ int quotient(const FastDiv &f, int n)       // without a branch
-{
-    const unsigned all = f.d == 1 ? ~0u : 0u;
-    return (int)((__umulhi((unsigned)n, f.magic) + ((unsigned)n & all)) >> f.shift);
-}
-
 // The matrix instruction takes bf16 denormals as zero: without a scale the parts of values below 2^-102 would get lost (2.7e-6
 // relative error at 1e-35, 2.7e-4 at 1e-37). Both operands are therefore split at 2^24 times their size, and the sums taken
 // back by 2^-48; powers of two, so nothing is rounded by it. Values or sums that overflow at that scale (values above 2^103,

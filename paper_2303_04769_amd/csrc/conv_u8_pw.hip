@@ -28,12 +28,6 @@ struct QPwArgs {
     QuantParams q;
 };
 
-__device__ __forceinline__ int quotient(const FastDiv &f, int n)       // without a branch
-{
-    const unsigned all = f.d == 1 ? ~0u : 0u;
-    return (int)((__umulhi((unsigned)n, f.magic) + ((unsigned)n & all)) >> f.shift);
-}
-
 // STEPS: matrix instructions of a reduction (four input blocks each); CORR: the pixel sums are needed (zw != 128)
 template <int STEPS, bool CORR>
 __global__ void __launch_bounds__(256) pw_u8_walk(QPwArgs a)

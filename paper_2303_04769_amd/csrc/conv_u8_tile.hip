@@ -49,13 +49,6 @@ struct QTileArgs {
     QuantParams q;
 };
 
-// FastDiv without a branch (a division by one is the sum's second term)
-__device__ __forceinline__ int quotient(const FastDiv &f, int n)
-{
-    const unsigned all = f.d == 1 ? ~0u : 0u;
-    return (int)((__umulhi((unsigned)n, f.magic) + ((unsigned)n & all)) >> f.shift);
-}
-
 template <int WM, int WN, int WVM, int WVN, int CORR>
 __global__ void __launch_bounds__(256, WM * WN >= 16 ? 2 : WM * WN >= 8 ? 3 : 4) conv_u8_tile(QTileArgs a)
 {

@@ -53,6 +53,14 @@ inline FastDiv make_fastdiv(int d)
     return f;
 }
 
+// The same on the device without a branch (a division by one is the sum's second term), for code whose loads must not be
+// separated by one.
+__device__ __forceinline__ int quotient(const FastDiv &f, int n)
+{
+    const unsigned all = f.d == 1 ? ~0u : 0u;
+    return (int)((__umulhi((unsigned)n, f.magic) + ((unsigned)n & all)) >> f.shift);
+}
+
 // Compute units of the current device (asked once; 256 -- an MI355X -- when no device can be asked, so that the
 // host-only planning calls give the same answers on a machine without a GPU). Launch shapes, tile choices and the
 // batch windows of image-resident runs are derived from it.
