@@ -17,7 +17,8 @@
 // each; the filter by steps -- with one matrix instruction per (step, tile, product):
 //   a step is one tap of two input blocks, or two taps of one block (a layer on 16 channels, or an odd last block that would
 //   leave half of the instruction empty); lane group g takes half g & 1 of the block's channels and block or tap g >> 1.
-// Infinities and NaN have no such sum (inf - inf): a workgroup that stages one computes its outputs value by value instead.
+// Infinities and NaN have no such sum (inf - inf): a workgroup that stages one computes its outputs with the fp32 instruction
+// instead, or, where it is a filter value, one by one.
 #include "small_internal.h"
 
 namespace small {
@@ -46,7 +47,7 @@ struct Split3Args {
 // The matrix instruction takes bf16 denormals as zero: without a scale the parts of values below 2^-102 would get lost (2.7e-6
 // relative error at 1e-35, 2.7e-4 at 1e-37). Both operands are therefore split at 2^24 times their size, and the sums taken
 // back by 2^-48; powers of two, so nothing is rounded by it. Values or sums that overflow at that scale (values above 2^103,
-// sums above 2^79) are found and computed value by value like the infinities. (327 us without the scale, 347 with it.)
+// sums above 2^79) are found and computed like the infinities. (327 us without the scale, 347 with it.)
 constexpr float kScale = 16777216.f, kUnscale = 1.f / (16777216.f * 16777216.f);
 
 // Eight values -> their three bf16 parts; `check` becomes NaN or infinite where a value has none.
@@ -93,7 +94,7 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
     const int bpc = 1 << a.l2bpc, planes = 2 * bpc;
     const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.in), 0, a.in_bytes, kRawBuffer);
     const __amdgpu_buffer_rsrc_t flt = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.filt), 0, a.filt_bytes, kRawBuffer);
-    float check = 0.f;
+    float check = 0.f, check_w = 0.f;                          // NaN or infinite: input, sums; filter
 
     // ---- filter: lane (p, g) brings 8 input channels (half g & 1 of a block) of output channel p, block or tap g >> 1
     const int half = g & 1, sub = g >> 1;
@@ -114,7 +115,7 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
 #pragma unroll
         for (int i = 0; i < FI; ++i) {
             uintx4 h, m, l;
-            split8(floatx4{fv[i][0], fv[i][1], fv[i][2], fv[i][3]}, floatx4{fv[i][4], fv[i][5], fv[i][6], fv[i][7]}, h, m, l, check);
+            split8(floatx4{fv[i][0], fv[i][1], fv[i][2], fv[i][3]}, floatx4{fv[i][4], fv[i][5], fv[i][6], fv[i][7]}, h, m, l, check_w);
             uintx4 *d = A + (buf * NCT + wave + 4 * i) * 3 * 64 + lane;
             d[0] = h; d[64] = m; d[128] = l;
         }
@@ -239,6 +240,7 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
                 check = fmaf(acc[wm][wn][r], 0.f, check);
             }
     if (!(__builtin_fabsf(check) < __builtin_inff())) bad[0] = 1;           // (NaN compares false)
+    if (!(__builtin_fabsf(check_w) < __builtin_inff())) bad[1] = 1;
     __syncthreads();
 
     auto finish = [&](floatx4 v, int cob, size_t o, int q) __attribute__((always_inline)) {
@@ -254,7 +256,60 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
         }
         *reinterpret_cast<floatx4 *>(a.out + o) = v;
     };
-    if (bad[0] == 0) {
+    if (bad[1] == 0) {
+        if (bad[0] != 0) {
+            // ---- some input or sum here is no finite sum of three parts: the fp32 matrix instruction, operands from memory, the
+            // next step's on their way (lane (p, g): input channels 4g .. 4g + 3 of its pixels, filter values [4g + r][p])
+            int ih0[WM], iw0[WM], at0[WM];
+#pragma unroll
+            for (int wm = 0; wm < WM; ++wm) {
+                const int m = min(m0 + (wave_m * WM + wm) * 16 + p, a.M - 1);
+                const int ns = quotient(a.dHoWs, m), rem = m - ns * a.HoWs, oh = quotient(a.dWs, rem);
+                const int n = quotient(a.dStrips, ns), ow = rem - oh * a.Ws + (ns - n * a.strips) * a.Ws;
+                ih0[wm] = oh * a.stride - a.pt;
+                iw0[wm] = ow * a.stride - a.pl;
+                at0[wm] = (n * a.nCib * a.H * a.W + ih0[wm] * a.W + iw0[wm]) * 64 + g * 16;
+            }
+            const int n_steps = a.nCib * a.taps;
+            floatx4 x[2][WM];
+            float w[2][WN][4];
+            auto request = [&](int s, floatx4 (&xs)[WM], float (&ws)[WN][4]) __attribute__((always_inline)) {
+                const int sc = min(s, n_steps - 1), cib = sc / a.taps, tap = sc - cib * a.taps, y = quotient(a.dkw, tap), z = tap - y * a.kw;
+#pragma unroll
+                for (int wm = 0; wm < WM; ++wm) {
+                    const bool inside = ((unsigned)(ih0[wm] + y) < (unsigned)a.H) & ((unsigned)(iw0[wm] + z) < (unsigned)a.W);
+                    const unsigned at = (unsigned)(at0[wm] + (cib * a.H * a.W + y * a.W + z) * 64);
+                    xs[wm] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(src, inside ? at : kBeyond, 0, 0));
+                }
+#pragma unroll
+                for (int wn = 0; wn < WN; ++wn) {
+                    const int cob = cob0 + wave_n * WN + wn;
+                    const unsigned at = cob < a.nCob ? (unsigned)((cob * n_steps + sc) * 1024 + (g * 64 + p) * 4) : kBeyond;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) ws[wn][r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(flt, at + 64u * r, 0, 0));
+                }
+            };
+#pragma unroll
+            for (int wm = 0; wm < WM; ++wm)
+#pragma unroll
+                for (int wn = 0; wn < WN; ++wn) acc[wm][wn] = floatx4{0.f, 0.f, 0.f, 0.f};
+            request(0, x[0], w[0]);
+            for (int s = 0; s < n_steps; s += 2) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    request(s + k + 1, x[k ^ 1], w[k ^ 1]);
+                    if (s + k < n_steps) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+#pragma unroll
+                            for (int wm = 0; wm < WM; ++wm)
+#pragma unroll
+                                for (int wn = 0; wn < WN; ++wn)
+                                    acc[wm][wn] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[k][wn][r], x[k][wm][r], acc[wm][wn], 0, 0, 0);
+                    }
+                }
+            }
+        }
 #pragma unroll
         for (int wm = 0; wm < WM; ++wm) {
             const int m = m0 + (wave_m * WM + wm) * 16 + p;
@@ -270,7 +325,8 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
         }
         return;
     }
-    // ---- some value here is no finite sum of three parts: plain fp32, four output channels at a time
+    // ---- some filter value is no finite sum of three parts. A tap outside the image does not count, whatever its weight (an
+    // infinite one times the zero read there would): plain fp32, four output channels at a time
     for (int it = tid; it < TM * NCT * 4; it += 256) {
         const int q = it & 3, m = m0 + (it >> 2) % TM, cob = cob0 + (it >> 2) / TM;
         if (m >= a.M || cob >= a.nCob) continue;

@@ -466,6 +466,28 @@ def test_conv2d_three_part_products_infinities():
     assert (err <= 52 * 2.0 ** -24 * size[both].astype(np.float64)).all()
 
 
+@pytest.mark.parametrize("case", SPLIT3_CASES)
+def test_conv2d_three_part_products_scattered_infinities(case):
+    """Tiles with an infinity or a NaN go by the fp32 instruction: strips, ragged ends, windows and padding once more. Outputs whose
+    window has none stay as exact as K + 1 roundings allow; in the last run a filter value is infinite too, which a tap in the
+    padding must not multiply."""
+    N, Ci, Co, H, W, kh, kw, pad = case
+    rng = np.random.default_rng(8450 + N)
+    x = (rng.random((N, Ci, H, W), dtype=np.float32) * 2 - 1).astype(np.float32)
+    w = (rng.random((Co, Ci, kh, kw), dtype=np.float32) * 2 - 1).astype(np.float32)
+    idx = np.unique(np.r_[0, 1, N // 2, N - 1])
+    x[idx, 3 % Ci, 0, 0], x[idx, Ci - 1, H - 1, W - 2], x[idx, 0, H // 2, W // 2] = np.inf, -np.inf, np.nan
+    size = O.conv2d(np.abs(np.nan_to_num(x[idx], nan=0, posinf=0, neginf=0)), np.abs(w), 1, pad)
+    for bad_weight in (False, True):
+        if bad_weight:
+            w[min(5, Co - 1), 0, 0, 0] = np.inf
+        got, ref = run_conv(x, w, 1, pad)[idx], O.conv2d(x[idx], w, 1, pad)
+        ok = np.isfinite(ref)
+        assert ok.mean() > 0.2 and not ok.all()
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[~ok], ref[~ok], equal_nan=True)
+        assert (np.abs(got[ok].astype(np.float64) - ref[ok]) <= (Ci * kh * kw + 1) * 2.0 ** -23 * size[ok]).all()
+
+
 def test_conv_identity_filter_is_exact():
     rng = np.random.default_rng(5)
     x = rng.standard_normal((2, 32, 10, 12)).astype(np.float32)
