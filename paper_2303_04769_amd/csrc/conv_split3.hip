@@ -49,23 +49,26 @@ struct Split3Args {
 // back by 2^-48; powers of two, so nothing is rounded by it. Values or sums that overflow at that scale (values above 2^103,
 // sums above 2^79) are found and computed like the infinities. (327 us without the scale, 347 with it.)
 constexpr float kScale = 16777216.f, kUnscale = 1.f / (16777216.f * 16777216.f);
+constexpr float kMost = 0x1.fep127f;   // the largest bf16: a scaled value above may round to an infinity
 
-// Eight values -> their three bf16 parts; `check` becomes NaN or infinite where a value has none.
-__device__ __forceinline__ void split8(floatx4 a, floatx4 b, uintx4 &h, uintx4 &m, uintx4 &l, float &check)
+// Eight values -> their three bf16 parts; `most` becomes their largest magnitude or NaN: a value has no parts if it is not below
+// kMost. (One instruction for two values, v_maximum3_f32; seen in the residuals behind the third part it took six.)
+__device__ __forceinline__ void split8(floatx4 a, floatx4 b, uintx4 &h, uintx4 &m, uintx4 &l, float &most)
 {
     const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         float u = x[2 * k] * kScale, v = x[2 * k + 1] * kScale;
+        most = __builtin_elementwise_maximum(most, __builtin_elementwise_maximum(__builtin_fabsf(u), __builtin_fabsf(v)));
         unsigned part[3];
 #pragma unroll
         for (int s = 0; s < 3; ++s) {
             const bf16x2 r = __builtin_convertvector(floatx2{u, v}, bf16x2);
             part[s] = __builtin_bit_cast(unsigned, r);
+            if (s == 2) break;
             u -= __builtin_bit_cast(float, part[s] << 16);
             v -= __builtin_bit_cast(float, part[s] & 0xffff0000u);
         }
-        check += u + v;
         h[k] = part[0]; m[k] = part[1]; l[k] = part[2];
     }
 }
@@ -94,7 +97,7 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
     const int bpc = 1 << a.l2bpc, planes = 2 * bpc;
     const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.in), 0, a.in_bytes, kRawBuffer);
     const __amdgpu_buffer_rsrc_t flt = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.filt), 0, a.filt_bytes, kRawBuffer);
-    float check = 0.f, check_w = 0.f;                          // NaN or infinite: input, sums; filter
+    float check = 0.f, most = 0.f, most_w = 0.f;               // NaN or infinite: sums; above kMost or NaN: input, filter
 
     // ---- filter: lane (p, g) brings 8 input channels (half g & 1 of a block) of output channel p, block or tap g >> 1
     const int half = g & 1, sub = g >> 1;
@@ -115,7 +118,7 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
 #pragma unroll
         for (int i = 0; i < FI; ++i) {
             uintx4 h, m, l;
-            split8(floatx4{fv[i][0], fv[i][1], fv[i][2], fv[i][3]}, floatx4{fv[i][4], fv[i][5], fv[i][6], fv[i][7]}, h, m, l, check_w);
+            split8(floatx4{fv[i][0], fv[i][1], fv[i][2], fv[i][3]}, floatx4{fv[i][4], fv[i][5], fv[i][6], fv[i][7]}, h, m, l, most_w);
             uintx4 *d = A + (buf * NCT + wave + 4 * i) * 3 * 64 + lane;
             d[0] = h; d[64] = m; d[128] = l;
         }
@@ -168,7 +171,7 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
         for (int k = 0; k < kRounds; ++k) {
             uintx4 h, m, l;
             asm volatile("" : "+v"(iv[k][0]), "+v"(iv[k][1]));     // (keeps the splitting, and its wait, from moving up to the loads)
-            split8(iv[k][0], iv[k][1], h, m, l, check);
+            split8(iv[k][0], iv[k][1], h, m, l, most);
             const int e = se + k * er, to = e < nE ? e : a.E;
             d[to] = h; d[planes * plane_e + to] = m; d[2 * planes * plane_e + to] = l;
         }
@@ -239,8 +242,8 @@ __global__ void __launch_bounds__(256, 2) conv16_split3(Split3Args a)
                 acc[wm][wn][r] = (acc[wm][wn][r] + low[wm][wn][r]) * kUnscale;
                 check = fmaf(acc[wm][wn][r], 0.f, check);
             }
-    if (!(__builtin_fabsf(check) < __builtin_inff())) bad[0] = 1;           // (NaN compares false)
-    if (!(__builtin_fabsf(check_w) < __builtin_inff())) bad[1] = 1;
+    if (!(__builtin_fabsf(check) < __builtin_inff()) || !(most <= kMost)) bad[0] = 1;           // (NaN compares false)
+    if (!(most_w <= kMost)) bad[1] = 1;
     __syncthreads();
 
     auto finish = [&](floatx4 v, int cob, size_t o, int q) __attribute__((always_inline)) {
