@@ -29,7 +29,7 @@ struct QPwArgs {
 };
 
 // STEPS: matrix instructions of a reduction (four input blocks each); CORR: the pixel sums are needed (zw != 128)
-template <int STEPS, bool CORR>
+template <int STEPS, bool CORR, bool HIGH>
 __global__ void __launch_bounds__(256) pw_u8_walk(QPwArgs a)
 {
     extern __shared__ intx4 lds[];
@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(256) pw_u8_walk(QPwArgs a)
         cst[c] = K * za * zb - za * sum;
     }
     __syncthreads();
-    const long bias = requant_bias(a.q);
+    const long addend = requant_addend<HIGH>(a.q);
     const intx4 ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
     for (int tile = wv; tile < a.n_tiles; tile += a.n_waves) {
         intx4 nxt[kWM][STEPS], fb[kWM][STEPS];
@@ -114,7 +114,7 @@ __global__ void __launch_bounds__(256) pw_u8_walk(QPwArgs a)
                 for (int i = 0; i < kWM; ++i) {
                     unsigned y[4];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) y[r] = (unsigned)requant_clamped(acc[i][r] - px[i], a.q, bias);
+                    for (int r = 0; r < 4; ++r) y[r] = (unsigned)requant_code<HIGH>(acc[i][r] - px[i], a.q, addend);
                     w[i][k] = y[0] | y[1] << 8 | y[2] << 16 | y[3] << 24;
                 }
             }
@@ -137,11 +137,17 @@ __global__ void __launch_bounds__(256) pw_u8_walk(QPwArgs a)
     }
 }
 
+template <int STEPS, bool HIGH>
+void go2(const QPwArgs &a, dim3 grid, size_t lds, hipStream_t s)
+{
+    if (a.q.zw != 128) hipLaunchKernelGGL((pw_u8_walk<STEPS, true, HIGH>), grid, dim3(256), lds, s, a);
+    else hipLaunchKernelGGL((pw_u8_walk<STEPS, false, HIGH>), grid, dim3(256), lds, s, a);
+}
 template <int STEPS>
 void go(const QPwArgs &a, dim3 grid, size_t lds, hipStream_t s)
 {
-    if (a.q.zw != 128) hipLaunchKernelGGL((pw_u8_walk<STEPS, true>), grid, dim3(256), lds, s, a);
-    else hipLaunchKernelGGL((pw_u8_walk<STEPS, false>), grid, dim3(256), lds, s, a);
+    if (a.q.mult32 >= 0) go2<STEPS, true>(a, grid, lds, s);
+    else go2<STEPS, false>(a, grid, lds, s);
 }
 
 }  // namespace

@@ -24,6 +24,8 @@
 // lives for some ten microseconds pays for every line of instructions it fetches.
 #include "small_internal.h"
 
+#include <type_traits>
+
 namespace small {
 namespace {
 
@@ -237,44 +239,49 @@ __global__ void __launch_bounds__(256, WM * WN >= 16 ? 2 : WM * WN >= 8 ? 3 : 4)
     // ---- zero-point correction of the pixel, requantization, store. Lane (p, g) has words of four channels (4g ..) of WM
     // pixels and WN blocks; four such words are transposed across the lane groups so that group g holds the whole 16-byte
     // block of the g-th one and a store instruction writes a kilobyte instead of a quarter.
-    const long bias = requant_bias(a.q);
-    auto word = [&](int wm, int wn) __attribute__((always_inline)) {
-        const unsigned px = use_s ? (unsigned)(zb * acc_s[wm][0]) : 0u;
-        unsigned y[4];
+    auto store = [&](auto high) __attribute__((always_inline)) {
+        constexpr bool HIGH = decltype(high)::value;
+        const long addend = requant_addend<HIGH>(a.q);
+        auto word = [&](int wm, int wn) __attribute__((always_inline)) {
+            const unsigned px = use_s ? (unsigned)(zb * acc_s[wm][0]) : 0u;
+            unsigned y[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) y[r] = (unsigned)requant_clamped((int)((unsigned)acc[wm][wn][r] - px), a.q, bias);
-        return y[0] | y[1] << 8 | y[2] << 16 | y[3] << 24;
-    };
-    // byte offset of (pixel wm of this lane, block wn) in the output, or kBeyond
-    const __amdgpu_buffer_rsrc_t dst = __builtin_amdgcn_make_buffer_rsrc(a.out, 0, a.out_bytes, kRawBuffer);
-    auto place = [&](int wm, int wn) __attribute__((always_inline)) {
-        const int m = m0 + (wave_m * WM + wm) * 16 + p, cob = cob0 + wave_n * WN + wn;
-        const int ns = quotient(a.dHoWs, min(m, a.M - 1)), rem = m - ns * a.HoWs, oh = quotient(a.dWs, rem);
-        const int n = quotient(a.dStrips, ns), ow = rem - oh * a.Ws + (ns - n * a.strips) * a.Ws;
-        const bool ok = (m < a.M) & (ow < a.Wo) & (cob < a.nCob);
-        return ok ? (unsigned)((n * a.nCob + cob) * a.HoWo + oh * a.Wo + ow) * 16u : kBeyond;
-    };
-    if constexpr (WM * WN % 4 == 0) {
+            for (int r = 0; r < 4; ++r) y[r] = (unsigned)requant_code<HIGH>((int)((unsigned)acc[wm][wn][r] - px), a.q, addend);
+            return y[0] | y[1] << 8 | y[2] << 16 | y[3] << 24;
+        };
+        // byte offset of (pixel wm of this lane, block wn) in the output, or kBeyond
+        const __amdgpu_buffer_rsrc_t dst = __builtin_amdgcn_make_buffer_rsrc(a.out, 0, a.out_bytes, kRawBuffer);
+        auto place = [&](int wm, int wn) __attribute__((always_inline)) {
+            const int m = m0 + (wave_m * WM + wm) * 16 + p, cob = cob0 + wave_n * WN + wn;
+            const int ns = quotient(a.dHoWs, min(m, a.M - 1)), rem = m - ns * a.HoWs, oh = quotient(a.dWs, rem);
+            const int n = quotient(a.dStrips, ns), ow = rem - oh * a.Ws + (ns - n * a.strips) * a.Ws;
+            const bool ok = (m < a.M) & (ow < a.Wo) & (cob < a.nCob);
+            return ok ? (unsigned)((n * a.nCob + cob) * a.HoWo + oh * a.Wo + ow) * 16u : kBeyond;
+        };
+        if constexpr (WM * WN % 4 == 0) {
 #pragma unroll
-        for (int c = 0; c < WM * WN / 4; ++c) {
-            unsigned w[4];
+            for (int c = 0; c < WM * WN / 4; ++c) {
+                unsigned w[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) w[k] = word((4 * c + k) / WN, (4 * c + k) % WN);
-            // (swap16: odd rows of 16 lanes of the first with even rows of the second; swap32: halves likewise)
-            auto t01 = __builtin_amdgcn_permlane16_swap(w[0], w[1], false, false);
-            auto t23 = __builtin_amdgcn_permlane16_swap(w[2], w[3], false, false);
-            auto e = __builtin_amdgcn_permlane32_swap(t01[0], t23[0], false, false);
-            auto o = __builtin_amdgcn_permlane32_swap(t01[1], t23[1], false, false);
-            const uintx4 v = {e[0], o[0], e[1], o[1]};
-            const int j = 4 * c + g;
-            __builtin_amdgcn_raw_buffer_store_b128(v, dst, place(WN == 4 ? c : j / WN, WN == 4 ? g : j % WN), 0, 0);
+                for (int k = 0; k < 4; ++k) w[k] = word((4 * c + k) / WN, (4 * c + k) % WN);
+                // (swap16: odd rows of 16 lanes of the first with even rows of the second; swap32: halves likewise)
+                auto t01 = __builtin_amdgcn_permlane16_swap(w[0], w[1], false, false);
+                auto t23 = __builtin_amdgcn_permlane16_swap(w[2], w[3], false, false);
+                auto e = __builtin_amdgcn_permlane32_swap(t01[0], t23[0], false, false);
+                auto o = __builtin_amdgcn_permlane32_swap(t01[1], t23[1], false, false);
+                const uintx4 v = {e[0], o[0], e[1], o[1]};
+                const int j = 4 * c + g;
+                __builtin_amdgcn_raw_buffer_store_b128(v, dst, place(WN == 4 ? c : j / WN, WN == 4 ? g : j % WN), 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int wm = 0; wm < WM; ++wm)
+#pragma unroll
+                for (int wn = 0; wn < WN; ++wn) __builtin_amdgcn_raw_buffer_store_b32(word(wm, wn), dst, place(wm, wn) + 4u * g, 0, 0);
         }
-    } else {
-#pragma unroll
-        for (int wm = 0; wm < WM; ++wm)
-#pragma unroll
-            for (int wn = 0; wn < WN; ++wn) __builtin_amdgcn_raw_buffer_store_b32(word(wm, wn), dst, place(wm, wn) + 4u * g, 0, 0);
-    }
+    };
+    if (a.q.mult32 >= 0) store(std::true_type());
+    else store(std::false_type());
 }
 
 // Tiles: pixel groups and blocks of a wave, waves along pixels and channels; cycles of a step of one workgroup alone on its

@@ -35,15 +35,15 @@ struct QConvArgs {
 
 // Zero-point corrections and requantization of a wave's accumulators, four consecutive output channels
 // (one 32-bit word of the blocked output) per lane and tile. acc_w: sum of the signed filter bytes per channel.
-template <int WM, int WN>
-__device__ __forceinline__ void store_tiles(const QConvArgs &a, const intx4 (&acc)[WM][WN], const intx4 (&acc_s)[WM],
+// FORM: of the requantization, 2 where q.mult32 >= 0, else 1 where q.amax > 0, else 0.
+template <int FORM, int WM, int WN>
+__device__ __forceinline__ void store_tiles_form(const QConvArgs &a, const intx4 (&acc)[WM][WN], const intx4 (&acc_s)[WM],
                                             const intx4 (&acc_w)[WN], int tile0, int cob0, int p, int g)
 {
     const int za = a.q.zx - 128, zb = a.q.zw - 128;
     const unsigned K = (unsigned)a.n_chunks * 16u;
     const unsigned kab = K * (unsigned)(za * zb);
-    const bool narrow = a.q.amax > 0;                  // (uniform) the five-instruction requantization applies
-    const long bias = requant_bias(a.q);
+    const long addend = requant_addend<FORM == 2>(a.q);
 #pragma unroll
     for (int wm = 0; wm < WM; ++wm) {
         const int m = tile0 + wm * 16 + p;
@@ -57,12 +57,21 @@ __device__ __forceinline__ void store_tiles(const QConvArgs &a, const intx4 (&ac
                 // wrap-around arithmetic: the true sum fits 32 bits, the partial terms need not
                 const unsigned v = (unsigned)acc[wm][wn][r] - (unsigned)zb * (unsigned)acc_s[wm][r] -
                                    (unsigned)za * (unsigned)acc_w[wn][r] + kab;
-                packed |= (unsigned)(narrow ? requant_clamped((int)v, a.q, bias) : requant((int)v, a.q)) << (8 * r);
+                packed |= (unsigned)(FORM ? requant_code<FORM == 2>((int)v, a.q, addend) : requant((int)v, a.q)) << (8 * r);
             }
             unsigned *o = reinterpret_cast<unsigned *>(a.out + (((size_t)n * a.nCob + cob0 + wn) * a.HoWo + pix) * 16 + g * 4);
             *o = packed;
         }
     }
+}
+
+template <int WM, int WN>
+__device__ __forceinline__ void store_tiles(const QConvArgs &a, const intx4 (&acc)[WM][WN], const intx4 (&acc_s)[WM],
+                                            const intx4 (&acc_w)[WN], int tile0, int cob0, int p, int g)
+{
+    if (a.q.mult32 >= 0) store_tiles_form<2>(a, acc, acc_s, acc_w, tile0, cob0, p, g);
+    else if (a.q.amax > 0) store_tiles_form<1>(a, acc, acc_s, acc_w, tile0, cob0, p, g);
+    else store_tiles_form<0>(a, acc, acc_s, acc_w, tile0, cob0, p, g);
 }
 
 // sum of the signed filter bytes of output channels 4g .. 4g+3 of block cob, from the caller's sums of codes

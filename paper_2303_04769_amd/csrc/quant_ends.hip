@@ -8,6 +8,8 @@
 // where a tap outside the image carries the code zx (its term is then zero) and K counts all taps.
 #include "small_internal.h"
 
+#include <type_traits>
+
 namespace small {
 
 namespace {
@@ -127,19 +129,24 @@ __global__ void __launch_bounds__(256) conv_first_u8(FirstU8Args a)
     const int base = K * a.q.zx * a.q.zw - a.q.zw * (int)sx;
     __syncthreads();                                     // the filter sums
 
-    const bool narrow = a.q.amax > 0;                    // (uniform) the five-instruction requantization applies
-    const long bias = requant_bias(a.q);
     unsigned packed[COB / 4];
 #pragma unroll
     for (int j = 0; j < COB / 4; ++j) packed[j] = 0;
+    auto codes = [&](auto form) __attribute__((always_inline)) {         // (the form of the requantization is uniform)
+        constexpr int FORM = decltype(form)::value;
+        const long addend = requant_addend<FORM == 2>(a.q);
 #pragma unroll
-    for (int co = 0; co < COB; ++co) {
-        unsigned dot = 0;
+        for (int co = 0; co < COB; ++co) {
+            unsigned dot = 0;
 #pragma unroll
-        for (int kd = 0; kd < KD; ++kd) dot = dot4(x[kd], wl[co * KD + kd], dot);
-        const int acc = (int)dot - a.q.zx * sw[co] + base;
-        packed[co / 4] |= (unsigned)(narrow ? requant_clamped(acc, a.q, bias) : requant(acc, a.q)) << (8 * (co % 4));
-    }
+            for (int kd = 0; kd < KD; ++kd) dot = dot4(x[kd], wl[co * KD + kd], dot);
+            const int acc = (int)dot - a.q.zx * sw[co] + base;
+            packed[co / 4] |= (unsigned)(FORM ? requant_code<FORM == 2>(acc, a.q, addend) : requant(acc, a.q)) << (8 * (co % 4));
+        }
+    };
+    if (a.q.mult32 >= 0) codes(std::integral_constant<int, 2>());
+    else if (a.q.amax > 0) codes(std::integral_constant<int, 1>());
+    else codes(std::integral_constant<int, 0>());
     if (live) {
         unsigned char *o = a.out + ((size_t)(n * a.nCob + cob) * a.HoWo + pix) * COB;
         if constexpr (COB == 16) *reinterpret_cast<uintx4 *>(o) = uintx4{packed[0], packed[1], packed[2], packed[3]};

@@ -14,6 +14,8 @@
 //     connected layer are plain vector code.
 #include "small_internal.h"
 
+#include <type_traits>
+
 namespace small {
 namespace {
 
@@ -63,9 +65,15 @@ constexpr int kMaxUnitBlocks = 1024;
 __device__ __forceinline__ int short_div(int n, int inv) { return (n * inv) >> 20; }
 __device__ __forceinline__ unsigned pack4(const unsigned (&y)[4]) { return y[0] | y[1] << 8 | y[2] << 16 | y[3] << 24; }
 
+// shift 32: mult is the layer's q.mult32 (small_internal.h)
 struct Requant { int amax, mult, shift, lo, hi; long bias; };
+__device__ __forceinline__ unsigned requant_high(int v, const Requant &q)
+{
+    return (unsigned)clamp_code((int)(((long)v * (long)q.mult + q.bias) >> 32), q.lo, q.hi);
+}
 __device__ __forceinline__ unsigned requant_signed(int v, const Requant &q)          // the code, unsigned
 {
+    if (q.shift == 32) return requant_high(v, q);
     const int c = min(max(v, -q.amax), q.amax);
     const int r = (int)(((long)c * (long)q.mult + q.bias) >> q.shift);
     return (unsigned)min(max(r, q.lo), q.hi);
@@ -131,18 +139,31 @@ __device__ __forceinline__ void conv_unit(char *lds, const RU8Layer &L, const Re
             if (zb != 0) acc_s[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(DW ? diag & ones : ones, fb, acc_s[i], 0, 0, 0);
         }
     }
+    if (zb != 0) {
 #pragma unroll
-    for (int i = 0; i < WM; ++i) {
-        const int m = (grp * WM + i) * 16 + p;
-        unsigned y[4];
+        for (int i = 0; i < WM; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            unsigned v = (unsigned)acc[i][r] - (unsigned)zb * (unsigned)acc_s[i][r];     // (without a diagonal all rows are the same)
-            if (DW) v -= (unsigned)za * (unsigned)acc_w[r];
-            y[r] = requant_signed((int)v, q);
-        }
-        if (m < P) *reinterpret_cast<unsigned *>(lds + L.dst + (cob * P + m) * 16 + 4 * g) = pack4(y) ^ 0x80808080u;
+            for (int r = 0; r < 4; ++r)                        // (without a diagonal all rows are the same)
+                acc[i][r] = (int)((unsigned)acc[i][r] - (unsigned)zb * (unsigned)acc_s[i][DW ? r : 0]);
     }
+    if (DW && za != 0) {
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[i][r] = (int)((unsigned)acc[i][r] - (unsigned)za * (unsigned)acc_w[r]);
+    }
+    auto store = [&](auto high) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < WM; ++i) {
+            const int m = (grp * WM + i) * 16 + p;
+            unsigned y[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) y[r] = decltype(high)::value ? requant_high(acc[i][r], q) : requant_signed(acc[i][r], q);
+            if (m < P) *reinterpret_cast<unsigned *>(lds + L.dst + (cob * P + m) * 16 + 4 * g) = pack4(y) ^ 0x80808080u;
+        }
+    };
+    if (q.shift == 32) store(std::true_type());
+    else store(std::false_type());
 }
 
 template <bool DW>
@@ -211,7 +232,7 @@ __global__ void __launch_bounds__(kThreads) resident_u8(RU8Args a)
             const int kind = L.kind_win & 255;
             const int zx = L.z & 255, zw = (L.z >> 8) & 255, pads = a.pads + 16 * l;
             Requant q;
-            q.amax = L.amax; q.mult = L.mult; q.shift = (L.z >> 24) & 31; q.lo = L.clamp & 255; q.hi = (L.clamp >> 8) & 255;
+            q.amax = L.amax; q.mult = L.mult; q.shift = (L.z >> 24) & 63; q.lo = L.clamp & 255; q.hi = (L.clamp >> 8) & 255;
             q.bias = (q.shift > 0 ? 1L << (q.shift - 1) : 0L) + ((long)((L.z >> 16) & 255) << q.shift);
             if (kind == RU8_CONV) {
                 conv_layer<false>(lds, L, q, wave, lane, zx, zw, filt, pads, a.table);
@@ -381,12 +402,12 @@ hipError_t launch_resident_u8(const RU8Group *g, int n, const unsigned char *in,
         d.filt_bytes = (int)ru8_filter_bytes(l);
         d.sums_bytes = (int)ru8_sums_bytes(l);
         d.Co = l.kind == RU8_DENSE ? l.Co : 0;
-        d.z = add ? l.qa.za | l.qa.zb << 8 | l.qa.zy << 16 | l.qa.shift << 24 : l.q.zx | l.q.zw << 8 | l.q.zy << 16 | l.q.shift << 24;
+        d.z = add ? l.qa.za | l.qa.zb << 8 | l.qa.zy << 16 | l.qa.shift << 24 : l.q.zx | l.q.zw << 8 | l.q.zy << 16 | (l.q.mult32 >= 0 ? 32 : l.q.shift) << 24;
         // pixel groups of a unit: a filter operand serves that many, as long as every wave still has a unit
         const int groups = (l.Ho * l.Wo + 15) / 16, units = groups * (l.Co / 16);
         const int wm = units >= 4 * kWaves ? 4 : units >= 2 * kWaves ? 2 : 1;
         d.clamp = (add ? l.qa.lo | l.qa.hi << 8 : l.q.lo | l.q.hi << 8) | wm << 16 | (l.kind == RU8_DENSE ? l.Cob : 0) << 24;
-        d.mult = add ? l.qa.mult_a : l.q.mult;
+        d.mult = add ? l.qa.mult_a : l.q.mult32 >= 0 ? l.q.mult32 : l.q.mult;
         d.amax = add ? l.qa.mult_b : l.q.amax;
         const FastDiv f = make_fastdiv(l.kind == RU8_AVG ? l.H * l.W : l.Wo > 0 ? l.Wo : 1);
         d.magic = f.magic; d.shift = f.shift;

@@ -295,7 +295,8 @@ int check_quant(const small_quant *q, long K, QuantParams &out)
         if (need > INT_MAX) amax = INT_MAX;
         else if (need * q->mult < ((__int128)((1LL << 31) - 1024) << q->shift)) amax = (int)need;
     }
-    out = QuantParams{q->zx, q->zw, q->zy, q->mult, q->shift, q->lo, q->hi, amax};
+    const long long m32 = (long long)q->mult << (32 - q->shift);
+    out = QuantParams{q->zx, q->zw, q->zy, q->mult, q->shift, q->lo, q->hi, amax, m32 < (1LL << 31) ? (int)m32 : -1};
     return SMALL_OK;
 }
 

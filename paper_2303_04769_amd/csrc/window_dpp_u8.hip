@@ -8,8 +8,8 @@
 // addressing: lanes and rows outside the image read as the code zx); the left and right neighbours come from
 // lanes l - 1 and l + 1 by lane shifts of the words (zero is shifted in at a band's ends: lanes 0 and 15 produce no
 // output there, or the value is replaced). The sums are taken with four-byte signed dot products over the three
-// taps of a window row (see the kernel), go through the requantization (the clamped 64-bit form: the host sends only
-// layers whose scale allows it) and into their byte of the output word.
+// taps of a window row (see the kernel), go through the requantization (HIGH: the form for scales below a half, else the
+// clamped one: the host sends only layers whose scale allows it) and into their byte of the output word.
 #include "small_internal.h"
 
 namespace small {
@@ -39,7 +39,7 @@ struct DppU8Args {
 // side by side with a lane of padding on their left. SEG 0: rows of at most 5 pixels, floor(16 / W) planes back to
 // back without padding lanes (three planes of the audio CNN's 5-pixel rows instead of two): the neighbour a plane's
 // first and last pixel would take from the plane next to it is replaced by the code zx with a select.
-template <int SEG, bool HAS_ZB, int ROWS>
+template <int SEG, bool HAS_ZB, int ROWS, bool HIGH>
 __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
 {
     constexpr int kStepsU8 = ROWS + 2;
@@ -122,7 +122,7 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
 #pragma unroll
         for (int c = 0; c < 4; ++c) cst[c] = za * cst[c] + 9 * za * zb;
     }
-    const long bias = requant_bias(a.q);
+    const long addend = requant_addend<HIGH>(a.q);
     const unsigned zxs = zx4 ^ flip;                        // the padding code as signed bytes
 
     unsigned tw[kStepsU8][4];                               // [input row][channel]: left, centre and right value
@@ -152,7 +152,7 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
             acc = __builtin_amdgcn_sdot4((int)tw[j - 1][c], (int)wt[1][c], acc, false);
             acc = __builtin_amdgcn_sdot4((int)tw[j][c], (int)wt[2][c], acc, false);
             if (HAS_ZB) acc += zb * (sx[j - 2][c] + sx[j - 1][c] + sx[j][c]);
-            y |= (unsigned)requant_clamped(acc, a.q, bias) << (8 * c);
+            y |= (unsigned)requant_code<HIGH>(acc, a.q, addend) << (8 * c);
         }
         const unsigned off = (col_out && j < n_in) ? at + (unsigned)((r0 + j - 2) * row_bytes) : kBeyond;
         __builtin_amdgcn_raw_buffer_store_b32(y, dst, off, 0, kNonTemporal);
@@ -178,19 +178,25 @@ int strip_rows(const LayerGeom &g, long planes_by_bands)
     return c9 < 0.96 * c7 ? 9 : 7;
 }
 
-template <int ROWS>
-void go(const DppU8Args &a, int seg, hipStream_t s)
+template <int ROWS, bool HIGH>
+void go2(const DppU8Args &a, int seg, hipStream_t s)
 {
     const dim3 grid((unsigned)((a.n_units + 3) / 4)), block(256);
     if (a.q.zw == 128) {
-        if (seg == 0) hipLaunchKernelGGL((dw16_dpp_u8<0, false, ROWS>), grid, block, 0, s, a);
-        else if (seg == 8) hipLaunchKernelGGL((dw16_dpp_u8<8, false, ROWS>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((dw16_dpp_u8<16, false, ROWS>), grid, block, 0, s, a);
+        if (seg == 0) hipLaunchKernelGGL((dw16_dpp_u8<0, false, ROWS, HIGH>), grid, block, 0, s, a);
+        else if (seg == 8) hipLaunchKernelGGL((dw16_dpp_u8<8, false, ROWS, HIGH>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((dw16_dpp_u8<16, false, ROWS, HIGH>), grid, block, 0, s, a);
     } else {
-        if (seg == 0) hipLaunchKernelGGL((dw16_dpp_u8<0, true, ROWS>), grid, block, 0, s, a);
-        else if (seg == 8) hipLaunchKernelGGL((dw16_dpp_u8<8, true, ROWS>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((dw16_dpp_u8<16, true, ROWS>), grid, block, 0, s, a);
+        if (seg == 0) hipLaunchKernelGGL((dw16_dpp_u8<0, true, ROWS, HIGH>), grid, block, 0, s, a);
+        else if (seg == 8) hipLaunchKernelGGL((dw16_dpp_u8<8, true, ROWS, HIGH>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((dw16_dpp_u8<16, true, ROWS, HIGH>), grid, block, 0, s, a);
     }
+}
+template <int ROWS>
+void go(const DppU8Args &a, int seg, hipStream_t s)
+{
+    if (a.q.mult32 >= 0) go2<ROWS, true>(a, seg, s);
+    else go2<ROWS, false>(a, seg, s);
 }
 
 }  // namespace

@@ -665,6 +665,42 @@ def test_depthwise_extreme_scales(mult, shift):
     _same(Q.unpack(g.check(), ref.shape, 16), ref, f"dw u8 scale {mult} / 2^{shift}")
 
 
+HALF_SCALES = [((1 << 30) - 1, 31), (1 << 30, 31), ((1 << 30) + 1, 31), (1, 1), (1, 2), (2, 2), ((1 << 29) - 1, 30), ((1 << 31) - 1, 31), (12345, 31)]
+
+
+@pytest.mark.parametrize("mult,shift", HALF_SCALES)
+def test_requantization_on_both_sides_of_a_half(mult, shift):
+    """The requantization takes the product's high word for scales below a half and shifts beyond: every kernel with a
+    requantization of its own, at zero points and codes that make the largest sums of either sign. Exact."""
+    r = _rng(33)
+    for zx, zw in ((0, 255), (255, 255), (131, 120)):
+        q = Q.Quant(zx=zx, zw=zw, zy=77, mult=mult, shift=shift, lo=3, hi=250)
+        for N, Ci, Co, H, W, k, s, sums, Cib, Cob in ((3, 64, 32, 11, 9, 3, 1, True, 16, 16), (2, 32, 16, 8, 8, 3, 1, False, 16, 16),
+                                                      (9, 64, 48, 31, 61, 1, 1, True, 16, 16), (2, 3, 16, 9, 9, 3, 1, False, 3, 16)):
+            x, w = WL.u8_codes(r, (N, Ci, H, W)), WL.u8_codes(r, (Co, Ci, k, k))
+            x[0], w[:8] = 255, np.where(np.arange(8) % 2, 255, 0).astype(np.uint8).reshape(8, 1, 1, 1)
+            pad = (k // 2,) * 4
+            _same(_conv(x, w, s, pad, q, Cib, Cob, with_sums=sums), Q.conv2d(x, w, s, pad, q), f"conv {Ci}->{Co} {k}x{k}, {mult} / 2^{shift}, {zx}, {zw}")
+        for s in (1, 2):
+            x, w = WL.u8_codes(r, (3, 32, 9, 20)), WL.u8_codes(r, (32, 1, 3, 3))
+            x[0], w[:8] = 255, np.where(np.arange(8) % 2, 255, 0).astype(np.uint8).reshape(8, 1, 1, 1)
+            ref = Q.dwconv2d(x, w, s, (1, 1, 1, 1), q)
+            g = Guarded8(ref.size)
+            S.small_dwconv2d_u8(dev8(Q.pack(x, 16)), dev8(Q.pack_dw_filter(w, 16)), g.t, 3, 32, 9, 20, 3, 3, s, (1, 1, 1, 1), 16, q)
+            _same(Q.unpack(g.check(), ref.shape, 16), ref, f"dw stride {s}, {mult} / 2^{shift}, {zx}, {zw}")
+
+
+@pytest.mark.parametrize("mult,shift", [(1 << 30, 31), (3, 2), ((1 << 30) - 1, 31)])
+def test_network_resident_scales_of_a_half_and_more(mult, shift):
+    """Layers of an image-resident run at such scales, others below beside them."""
+    net = _resident_table(16, 9, 7, "head")
+    x, ws, qs = WL.quantized_network_tensors(net, 5, 79)
+    _shift_zero_points(qs, _rng(34))
+    for i in (2, 3):
+        qs[i]["mult"], qs[i]["shift"] = mult, shift
+    _same(_run_u8(net, x, ws, qs), Q.run_network(net, x, ws, qs), f"u8 resident scale {mult} / 2^{shift}")
+
+
 def _resident_table(C0, H, W, tail):
     """Convolutions with odd windows, strides and paddings, a depthwise 5x3, a residual addition into a third buffer, and
     one of the ends: a fully connected head, a tensor, a max pooling (which no image-resident run takes)."""
