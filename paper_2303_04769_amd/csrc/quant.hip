@@ -35,6 +35,19 @@ struct QConvArgs {
 
 // Zero-point corrections and requantization of a wave's accumulators, four consecutive output channels
 // (one 32-bit word of the blocked output) per lane and tile. acc_w: sum of the signed filter bytes per channel.
+// The signed operand of 16 codes where m is all ones, the word `other` four times where m is zero.
+__device__ __forceinline__ intx4 signed_or(const intx4 v, int m, int other)
+{
+    const int flip = (int)0x80808080u & m, rest = other & ~m;
+    return (v & m) ^ (flip | rest);
+}
+
+// all ones for a pixel inside the image
+__device__ __forceinline__ int image_mask(int ih, int iw, const QConvArgs &a)
+{
+    return lane_mask(((unsigned)ih < (unsigned)a.H) & ((unsigned)iw < (unsigned)a.W));
+}
+
 // FORM: of the requantization, 2 where q.mult32 >= 0, else 1 where q.amax > 0, else 0.
 template <int FORM, int WM, int WN>
 __device__ __forceinline__ void store_tiles_form(const QConvArgs &a, const intx4 (&acc)[WM][WN], const intx4 (&acc_s)[WM],
@@ -207,11 +220,10 @@ __global__ void __launch_bounds__(256) conv_u8_mfma(QConvArgs a)
 #pragma unroll
         for (int wm = 0; wm < WM; ++wm) {
             const int ih = ih0[wm] + ky, iw = iw0[wm] + kx;
-            const bool inside = live && ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
+            const int alive = lane_mask(live), inside = alive & image_mask(ih, iw, a);
             // always a load from a valid address (no branch around it), then the choice
-            const intx4 v = in[inside ? img[wm] + (size_t)cib * HW + ih * a.W + iw : img[wm]];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) fb[wm][k] = live ? (inside ? v[k] ^ flip : zx4 ^ flip) : 0;
+            const intx4 v = in[img[wm] + (((size_t)cib * HW + ih * a.W + iw) & (size_t)(long)inside)];
+            fb[wm] = signed_or(v, inside, (zx4 ^ flip) & alive);
         }
         c += 4;
         kx += 4;
@@ -286,13 +298,13 @@ __global__ void __launch_bounds__(256) conv_u8_mfma_short(QConvArgs a)
     const intx4 zero = {0, 0, 0, 0};
 
     intx4 ra[STEPS][WN], rb[STEPS][WM];
-    bool live[STEPS], inside[STEPS][WM];
+    int live[STEPS], inside[STEPS][WM];                        // lane masks
 #pragma unroll
     for (int t = 0; t < STEPS; ++t) {
         // this lane group's chunk of step t: c = (cib * kh + ky) * kw + kx
         const int c_raw = 4 * t + g;
-        live[t] = c_raw < a.n_chunks;
-        const int c = live[t] ? c_raw : a.n_chunks - 1;
+        live[t] = lane_mask(c_raw < a.n_chunks);
+        const int c = min(c_raw, a.n_chunks - 1);
         const int cib = a.div_taps.div(c), tap = c - cib * a.kh * a.kw;
         const int ky = a.div_kw.div(tap), kx = tap - ky * a.kw;
 #pragma unroll
@@ -300,8 +312,8 @@ __global__ void __launch_bounds__(256) conv_u8_mfma_short(QConvArgs a)
 #pragma unroll
         for (int wm = 0; wm < WM; ++wm) {
             const int ih = ih0[wm] + ky, iw = iw0[wm] + kx;
-            inside[t][wm] = ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
-            rb[t][wm] = img[wm][inside[t][wm] ? cib * HW + ih * a.W + iw : 0];
+            inside[t][wm] = image_mask(ih, iw, a);
+            rb[t][wm] = img[wm][(cib * HW + ih * a.W + iw) & inside[t][wm]];
         }
     }
 
@@ -320,13 +332,11 @@ __global__ void __launch_bounds__(256) conv_u8_mfma_short(QConvArgs a)
         intx4 fa[WN], fb[WM];
 #pragma unroll
         for (int wn = 0; wn < WN; ++wn) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) fa[wn][k] = live[t] ? ra[t][wn][k] ^ flip : 0;
+            fa[wn] = signed_or(ra[t][wn], live[t], 0);
         }
 #pragma unroll
         for (int wm = 0; wm < WM; ++wm) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) fb[wm][k] = live[t] ? (inside[t][wm] ? rb[t][wm][k] ^ flip : pad) : 0;
+            fb[wm] = signed_or(rb[t][wm], live[t] & inside[t][wm], pad & live[t]);
         }
 #pragma unroll
         for (int wm = 0; wm < WM; ++wm) {
@@ -407,8 +417,8 @@ __global__ void __launch_bounds__(256) conv_u8_mfma4(QConvArgs a)
 #pragma unroll
         for (int wm = 0; wm < WM; ++wm) {
             const int ih = ih0[wm] + r_ky, iw = iw0[wm] + r_kx;
-            inside[wm] = ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
-            bp[wm] = img[wm] + (inside[wm] ? ih * a.W + iw : 0);
+            inside[wm] = image_mask(ih, iw, a);
+            bp[wm] = img[wm] + (inside[wm] & (ih * a.W + iw));
         }
         ap = filt + (size_t)r_tap * 16;
     };
@@ -447,8 +457,7 @@ __global__ void __launch_bounds__(256) conv_u8_mfma4(QConvArgs a)
                 for (int wn = 0; wn < WN; ++wn) fa[wn] = ra[d][wn] ^ flip;
 #pragma unroll
                 for (int wm = 0; wm < WM; ++wm) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) fb[wm][k] = rin[d][wm] ? rb[d][wm][k] ^ flip : pad;
+                    fb[wm] = signed_or(rb[d][wm], rin[d][wm], pad);
                 }
 #pragma unroll
                 for (int wm = 0; wm < WM; ++wm) {
@@ -672,15 +681,20 @@ __global__ void __launch_bounds__(256) dw3x3_u8(QDw3Args a)
         if (pix >= a.HoWo) break;
         const int oh = a.div_Wo.div(pix), ow = pix - oh * a.Wo;
         const int ih0 = oh * a.stride - a.pt, iw0 = ow * a.stride - a.pl;
+        int row[3], col[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            row[k] = lane_mask((unsigned)(ih0 + k) < (unsigned)a.H);
+            col[k] = lane_mask((unsigned)(iw0 + k) < (unsigned)a.W);
+        }
         unsigned x[9];
 #pragma unroll
         for (int ky = 0; ky < 3; ++ky)
 #pragma unroll
             for (int kx = 0; kx < 3; ++kx) {
-                const int ih = ih0 + ky, iw = iw0 + kx;
-                const bool inside = (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
-                const unsigned v = img[inside ? (ih * a.W + iw) * 4 : 0];
-                x[ky * 3 + kx] = inside ? v : zx4;
+                const int m = row[ky] & col[kx];
+                const unsigned v = img[((ih0 + ky) * a.W + iw0 + kx) * 4 & m];
+                x[ky * 3 + kx] = ((v ^ zx4) & (unsigned)m) ^ zx4;
             }
         unsigned packed = 0;
 #pragma unroll

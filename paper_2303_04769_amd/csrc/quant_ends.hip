@@ -99,6 +99,7 @@ __global__ void __launch_bounds__(256) conv_first_u8(FirstU8Args a)
 #pragma unroll
     for (int ky = 0; ky < KH; ++ky) {
         const bool row_in = (unsigned)(ih0 + ky) < (unsigned)a.H;
+        const unsigned row_out = ~(unsigned)lane_mask(row_in);
         unsigned r[NDW];
 #pragma unroll
         for (int d = 0; d < NDW; ++d) {
@@ -113,7 +114,8 @@ __global__ void __launch_bounds__(256) conv_first_u8(FirstU8Args a)
             }
             // (a row outside the image: zx in every byte of the window)
             const unsigned window = 4 * d + 4 <= NB ? 0xffffffffu : (NB > 4 * d ? (1u << (8 * (NB - 4 * d))) - 1u : 0u);
-            r[d] = row_in ? ((v & keep[d]) | fill[d]) : (zx4 & window);
+            // (v is zero there, and fill a part of it)
+            r[d] = (v & keep[d]) | fill[d] | (zx4 & window & row_out);
         }
         const int at = ky * NB;                    // the row's place in x, in bytes (a constant once unrolled)
 #pragma unroll

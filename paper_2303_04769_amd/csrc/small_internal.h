@@ -100,6 +100,17 @@ __device__ __forceinline__ floatx4 lane_shift(floatx4 v)
     const float x = v.x, y = v.y, z = v.z, w = v.w;      // (scalars first: the builtin takes values, not vector elements)
     return floatx4{lane_shift1<CTRL>(x), lane_shift1<CTRL>(y), lane_shift1<CTRL>(z), lane_shift1<CTRL>(w)};
 }
+// All ones where b holds, zero elsewhere, for choosing among the words of an operand with and / exclusive-or. The compiler makes
+// one v_cndmask_b32 per word of such a choice, and those, reading the same condition one behind the other, take the SIMD 16 cycles
+// each (measured; 4 with another instruction between them) where an and or an exclusive-or takes 2. (Opaque: it would turn
+// the mask back into a choice.)
+__device__ __forceinline__ int lane_mask(bool b)
+{
+    int m = b ? -1 : 0;
+    asm("" : "+v"(m));
+    return m;
+}
+
 // Buffer-descriptor addressing (raw buffers over a whole tensor): an offset at or beyond the descriptor's size reads
 // zeros and drops stores, which serves as a branch-free mask. kBeyond: an offset no tensor of less than 2 GiB reaches.
 constexpr unsigned kBeyond = 0x80000000u;

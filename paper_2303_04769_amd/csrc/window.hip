@@ -137,11 +137,11 @@ __global__ void __launch_bounds__(kBlock) window_lds16(const float *__restrict__
         const float *src = in + (size_t)plane * g.H * g.W * 16;
         for (int base = 0; base < items; base += kCopyBatch * kBlock) {
             floatx4 v[kCopyBatch];
-            bool ok[kCopyBatch];
+            int ok[kCopyBatch];
 #pragma unroll
             for (int k = 0; k < kCopyBatch; ++k) {
                 const int iy = iy0 + r, ix = (c >> 2) - g.pl;
-                ok[k] = iy >= 0 && iy < g.H && ix >= 0 && ix < g.W;
+                ok[k] = lane_mask(((unsigned)iy < (unsigned)g.H) & ((unsigned)ix < (unsigned)g.W));
                 const int iyc = min(max(iy, 0), g.H - 1), ixc = min(max(ix, 0), g.W - 1);
                 v[k] = ld4_stream(src + ((size_t)iyc * g.W + ixc) * 16 + (c & 3) * 4);
                 c += step_c; r += step_r;
@@ -150,7 +150,9 @@ __global__ void __launch_bounds__(kBlock) window_lds16(const float *__restrict__
 #pragma unroll
             for (int k = 0; k < kCopyBatch; ++k) {
                 const int f = base + k * kBlock + tid;
-                if (f < items) tile[f] = ok[k] ? v[k] : nv;
+                const uintx4 u = __builtin_bit_cast(uintx4, v[k]) & (unsigned)ok[k];
+                const unsigned rest = __builtin_bit_cast(unsigned, neutral) & ~(unsigned)ok[k];
+                if (f < items) tile[f] = __builtin_bit_cast(floatx4, OP == OP_MAX ? u | rest : u);
             }
         }
     }
