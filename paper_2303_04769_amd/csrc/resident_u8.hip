@@ -8,8 +8,10 @@
 //   - a tap outside the image is redirected to an entry of the layer's padding code, a chunk past the reduction's end to a
 //     zero entry: an address select instead of four selects of the value. Where chunk c = (input block, tap) of a layer lies
 //     relative to a pixel is tabled in LDS once per workgroup.
-//   - the next layer's filter (and the sums of its channels) is requested into registers before a layer is computed and
-//     written, sign-flipped, to the other of two LDS buffers behind it; filters are therefore at most 64 KB.
+//   - the next layer's filter (and the sums of its channels) is on its way into the other of two LDS buffers while a layer is
+//     computed, by the load unit: no registers (of which a thread has 128) and no copy behind the layer. Its bytes are made
+//     signed when they are read. (Through registers: audio CNN, 100 images 28.0 us, here 23.6; residual CNN, 256 images 39.0 and
+//     33.9.) Filters are at most 64 KB.
 //   - depthwise layers run on the matrix cores as well (conv_unit); additions, global average pooling and a closing fully
 //     connected layer are plain vector code.
 #include "small_internal.h"
@@ -22,7 +24,7 @@ namespace {
 typedef int intx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 16, kThreads = 64 * kWaves;
-constexpr int kMaxFilter = 65536, kFilterRegs = kMaxFilter / 16 / kThreads;
+constexpr int kMaxFilter = 65536;
 
 // One layer, packed so that kRU8MaxLayers of them fit the 4 KB of kernel arguments.
 struct RU8Layer {
@@ -53,6 +55,14 @@ struct RU8Args {
     RU8Layer layer[kRU8MaxLayers];
 };
 static_assert(sizeof(RU8Args) <= 4096, "kernel arguments");
+typedef const __attribute__((address_space(4))) RU8Args *RU8KernArgs;
+// all of a layer at once: field by field, where they are used, the scalar loads (some 250 cycles each) stand one behind the other
+__device__ __forceinline__ RU8Layer layer_at(RU8KernArgs ka, int l)
+{
+    RU8Layer L;
+    __builtin_memcpy(&L, (const __attribute__((address_space(4))) char *)&ka->layer[l], sizeof(L));
+    return L;
+}
 
 __device__ __forceinline__ int quotient(unsigned magic, unsigned shift, int n)       // magic = 0: by one
 {
@@ -118,25 +128,31 @@ __device__ __forceinline__ void conv_unit(char *lds, const RU8Layer &L, const Re
     intx4 diag;                                                // DW: 0xff in byte p of the operand
 #pragma unroll
     for (int k = 0; k < 4; ++k) diag[k] = (p >> 2) == k ? 255 << (8 * (p & 3)) : 0;
-#pragma unroll 2
+    // (one step at a time: two or three at once, their reads ahead of the first use, need more than a thread's 128 registers, and
+    // what is spilled costs more than the waiting: audio CNN, 100 images 25.2 us, here 23.6)
     for (int t = 0; t < chunks; t += 4) {
-        const int c = t + g;
-        const int e = tab[c];                                  // (padded to whole steps)
+        const int c = t + g, e = tab[c];                       // (padded to whole steps)
         intx4 fa;
-        if (DW) {
-            const int w = *reinterpret_cast<const unsigned char *>(fl + min(c, chunks - 1) * 16) * 0x01010101;
-            fa = intx4{w, w, w, w} & diag;
-        } else {
-            fa = *reinterpret_cast<const intx4 *>(fl + min(c, chunks - 1) * 256);
-        }
-        const int y = e & 63, x = (e >> 6) & 63, off = (e >> 12) * 16, outside = c < chunks ? pads : 0;
-        if (DW && za != 0) acc_w = __builtin_amdgcn_mfma_i32_16x16x64_i8(c < chunks ? fa : intx4{0, 0, 0, 0}, ones, acc_w, 0, 0, 0);
+        int w;
+        if (DW) w = *reinterpret_cast<const unsigned char *>(fl + min(c, chunks - 1) * 16);
+        else fa = *reinterpret_cast<const intx4 *>(fl + min(c, chunks - 1) * 256) ^ (int)0x80808080u;
+        const bool live = c < chunks;
+        const int y = e & 63, x = (e >> 6) & 63, off = (e >> 12) * 16, outside = live ? pads : 0;
+        intx4 fb[WM];
 #pragma unroll
         for (int i = 0; i < WM; ++i) {
-            const bool in = ((unsigned)(ih0[i] + y) < (unsigned)H) & ((unsigned)(iw0[i] + x) < (unsigned)W) & (c < chunks);
-            const intx4 fb = *reinterpret_cast<const intx4 *>(lds + (in ? base[i] + off : outside));
-            acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa, fb, acc[i], 0, 0, 0);
-            if (zb != 0) acc_s[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(DW ? diag & ones : ones, fb, acc_s[i], 0, 0, 0);
+            const bool in = ((unsigned)(ih0[i] + y) < (unsigned)H) & ((unsigned)(iw0[i] + x) < (unsigned)W) & live;
+            fb[i] = *reinterpret_cast<const intx4 *>(lds + (in ? base[i] + off : outside));
+        }
+        if (DW) {
+            const int v = (w ^ 128) * 0x01010101;
+            fa = intx4{v, v, v, v} & diag;
+            if (za != 0) acc_w = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa & lane_mask(live), ones, acc_w, 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < WM; ++i) {
+            acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa, fb[i], acc[i], 0, 0, 0);
+            if (zb != 0) acc_s[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(DW ? diag & ones : ones, fb[i], acc_s[i], 0, 0, 0);
         }
     }
     if (zb != 0) {
@@ -185,6 +201,7 @@ __global__ void __launch_bounds__(kThreads) resident_u8(RU8Args a)
     char *lds = reinterpret_cast<char *>(lds4);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int flip = (int)0x80808080u;
+    const RU8KernArgs ka = (RU8KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
 
     // ---- tables: the zero entry, every layer's padding entry, where its chunks lie
     if (tid == 0) lds4[0] = intx4{0, 0, 0, 0};
@@ -200,35 +217,30 @@ __global__ void __launch_bounds__(kThreads) resident_u8(RU8Args a)
         }
     }
 
-    // ---- the filter of a layer (and its channel sums behind it) on its way to LDS
-    intx4 fr[kFilterRegs], sr;
-    auto filter_request = [&](const RU8Layer &L) __attribute__((always_inline)) {
-        const __amdgpu_buffer_rsrc_t f = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(L.filt), 0, L.filt_bytes, kRawBuffer);
-        const __amdgpu_buffer_rsrc_t s = __builtin_amdgcn_make_buffer_rsrc(const_cast<int *>(L.sums), 0, L.sums ? L.sums_bytes : 0, kRawBuffer);
-#pragma unroll
-        for (int k = 0; k < kFilterRegs; ++k)
-            if (k == 0 || k * kThreads * 16 < L.filt_bytes)
-                fr[k] = __builtin_bit_cast(intx4, __builtin_amdgcn_raw_buffer_load_b128(f, (tid + k * kThreads) * 16, 0, 0));
-        sr = __builtin_bit_cast(intx4, __builtin_amdgcn_raw_buffer_load_b128(s, tid * 16, 0, 0));
+    // ---- the filter of a layer (and its channel sums behind it) into LDS, by the load unit: whole kilobytes of a wave, the last
+    // one's lanes beyond the end switched off
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)lds;
+    auto filter_request = [&](const RU8Layer &L, int at) __attribute__((always_inline)) {
+        for (int k = wave * 1024; k < L.filt_bytes; k += kThreads * 16)
+            if (k + lane * 16 < L.filt_bytes) dma16(L.filt, (unsigned)(k + lane * 16), lds0 + (unsigned)(at + k));
+        if (L.sums != nullptr)
+            for (int k = wave * 1024; k < L.sums_bytes; k += kThreads * 16)
+                if (k + lane * 16 < L.sums_bytes) dma16(L.sums, (unsigned)(k + lane * 16), lds0 + (unsigned)(at + L.filt_bytes + k));
     };
-    auto filter_arrive = [&](const RU8Layer &L, int at) __attribute__((always_inline)) {
-#pragma unroll
-        for (int k = 0; k < kFilterRegs; ++k)
-            if (k * kThreads * 16 < L.filt_bytes && (tid + k * kThreads) * 16 < L.filt_bytes) *reinterpret_cast<intx4 *>(lds + at + (tid + k * kThreads) * 16) = fr[k] ^ flip;
-        if (tid * 16 < L.sums_bytes) *reinterpret_cast<intx4 *>(lds + at + L.filt_bytes + tid * 16) = sr;
-    };
-    filter_request(a.layer[0]);
-    filter_arrive(a.layer[0], a.filt0);
+    filter_request(a.layer[0], a.filt0);
+    const intx4 first = reinterpret_cast<const intx4 *>(a.in + (size_t)blockIdx.x * a.in_bytes)[min(tid, a.in_bytes / 16 - 1)];
 
     int filt = a.filt0, other = a.filt1;
     for (int n = blockIdx.x; n < a.N; n += gridDim.x) {
         const intx4 *src = reinterpret_cast<const intx4 *>(a.in + (size_t)n * a.in_bytes);
-        for (int i = tid; i * 16 < a.in_bytes; i += kThreads) *reinterpret_cast<intx4 *>(lds + a.in_at + i * 16) = src[i] ^ flip;
+        for (int i = tid; i * 16 < a.in_bytes; i += kThreads)
+            *reinterpret_cast<intx4 *>(lds + a.in_at + i * 16) = (n == (int)blockIdx.x && i == tid ? first : src[i]) ^ flip;
+        wait_vmcnt<0>();
         __syncthreads();
         for (int l = 0; l < a.n_layers; ++l) {
-            const RU8Layer &L = a.layer[l];
-            const RU8Layer &next = a.layer[l + 1 < a.n_layers ? l + 1 : 0];
-            filter_request(next);
+            const RU8Layer L = layer_at(ka, l);
+            const RU8Layer next = layer_at(ka, l + 1 < a.n_layers ? l + 1 : 0);
+            filter_request(next, other);                       // (its buffer was last read before the barrier)
             const int kind = L.kind_win & 255;
             const int zx = L.z & 255, zw = (L.z >> 8) & 255, pads = a.pads + 16 * l;
             Requant q;
@@ -277,7 +289,7 @@ __global__ void __launch_bounds__(kThreads) resident_u8(RU8Args a)
                     int v = 0;
                     for (int i = lane; i < nB * 4; i += 64) {
                         const int x = *reinterpret_cast<const int *>(lds + L.src + i * 4);
-                        const int w = *reinterpret_cast<const int *>(lds + filt + ((cob * nB + (i >> 2)) * Cob + oi) * 16 + (i & 3) * 4);
+                        const int w = *reinterpret_cast<const int *>(lds + filt + ((cob * nB + (i >> 2)) * Cob + oi) * 16 + (i & 3) * 4) ^ flip;
                         v = __builtin_amdgcn_sdot4(x, w, v, false) - zb * __builtin_amdgcn_sdot4(x, 0x01010101, 0, false) -
                             za * __builtin_amdgcn_sdot4(w, 0x01010101, 0, false);
                     }
@@ -287,10 +299,10 @@ __global__ void __launch_bounds__(kThreads) resident_u8(RU8Args a)
                     if (lane == 0) a.out[(size_t)n * L.Co + o] = (unsigned char)requant_signed(v, q);
                 }
             }
-            filter_arrive(next, other);
             const int t = filt;
             filt = other;
             other = t;
+            wait_vmcnt<0>();                                   // this wave's part of the next filter has landed
             __syncthreads();
         }
         for (int i = tid; i * 16 < a.out_bytes; i += kThreads)
