@@ -1,4 +1,5 @@
-"""ctypes binding of libsmall_hip.so: same names and arguments as include/small.h.
+"""Binding of libsmall_hip.so: same names and arguments as include/small.h. ctypes, and for the single-layer calls, which
+are bound by their host time, an extension module in front of it (csrc/fastcall.cpp).
 
 Tensor arguments are torch CUDA tensors (float32, contiguous); only their device
 pointers cross the boundary. The stream is torch's current stream unless given.
@@ -12,6 +13,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsmall_hip.so")
+FASTCALL_PATH = os.path.join(_HERE, "_fastcall.so")
 
 OK = 0
 POOL_MAX, POOL_AVG = 0, 1
@@ -124,6 +126,23 @@ def load():
     return lib
 
 
+_fastcall = None
+
+
+def _fast():
+    """The calls of csrc/fastcall.cpp, of which each returns None for what it leaves to ctypes."""
+    global _fastcall
+    if _fastcall is None:
+        lib = load()
+        if not os.path.exists(FASTCALL_PATH):
+            from .build import build_fastcall
+            build_fastcall()
+        from . import _fastcall as module
+        module.bind(lib._handle, small_quant)
+        _fastcall = module
+    return _fastcall
+
+
 def strerror(code):
     return load().small_strerror(int(code)).decode()
 
@@ -163,11 +182,17 @@ def small_out_dim(i, k, stride, lo, hi):
 
 
 def small_pack(nchw, blocked, N, Cc, H, W, Cb, stream=None):
-    _check(load().small_pack(_ptr(nchw), _ptr(blocked), N, Cc, H, W, Cb, _stream(stream)), "small_pack")
+    rc = _fast().pack(nchw, blocked, N, Cc, H, W, Cb, stream)
+    if rc is None:
+        rc = load().small_pack(_ptr(nchw), _ptr(blocked), N, Cc, H, W, Cb, _stream(stream))
+    _check(rc, "small_pack")
 
 
 def small_unpack(blocked, nchw, N, Cc, H, W, Cb, stream=None):
-    _check(load().small_unpack(_ptr(blocked), _ptr(nchw), N, Cc, H, W, Cb, _stream(stream)), "small_unpack")
+    rc = _fast().unpack(blocked, nchw, N, Cc, H, W, Cb, stream)
+    if rc is None:
+        rc = load().small_unpack(_ptr(blocked), _ptr(nchw), N, Cc, H, W, Cb, _stream(stream))
+    _check(rc, "small_unpack")
 
 
 def small_pack_filter(oihw, blocked, Co, Ci, kh, kw, Cob, Cib, stream=None):
@@ -181,8 +206,11 @@ def small_pack_dw_filter(c1hw, blocked, Cc, kh, kw, Cb, stream=None):
 
 
 def small_conv2d(inp, filt, out, N, Ci, Co, H, W, kh, kw, stride, pad, Cib, Cob, stream=None):
-    _check(load().small_conv2d(_ptr(inp), _ptr(filt), _ptr(out), N, Ci, Co, H, W, kh, kw, stride, _pad(pad), Cib, Cob,
-                               _stream(stream)), "small_conv2d")
+    rc = _fast().conv2d(inp, filt, out, N, Ci, Co, H, W, kh, kw, stride, pad, Cib, Cob, stream)
+    if rc is None:
+        rc = load().small_conv2d(_ptr(inp), _ptr(filt), _ptr(out), N, Ci, Co, H, W, kh, kw, stride, _pad(pad), Cib, Cob,
+                                 _stream(stream))
+    _check(rc, "small_conv2d")
 
 
 def small_conv2d_kernel(N, Ci, Co, H, W, kh, kw, stride, pad, Cib, Cob):
@@ -191,25 +219,39 @@ def small_conv2d_kernel(N, Ci, Co, H, W, kh, kw, stride, pad, Cib, Cob):
 
 
 def small_dwconv2d(inp, filt, out, N, Cc, H, W, kh, kw, stride, pad, Cb, stream=None):
-    _check(load().small_dwconv2d(_ptr(inp), _ptr(filt), _ptr(out), N, Cc, H, W, kh, kw, stride, _pad(pad), Cb,
-                                 _stream(stream)), "small_dwconv2d")
+    rc = _fast().dwconv2d(inp, filt, out, N, Cc, H, W, kh, kw, stride, pad, Cb, stream)
+    if rc is None:
+        rc = load().small_dwconv2d(_ptr(inp), _ptr(filt), _ptr(out), N, Cc, H, W, kh, kw, stride, _pad(pad), Cb,
+                                   _stream(stream))
+    _check(rc, "small_dwconv2d")
 
 
 def small_pool2d(inp, out, N, Cc, H, W, kh, kw, stride, pad, Cb, mode, stream=None):
-    _check(load().small_pool2d(_ptr(inp), _ptr(out), N, Cc, H, W, kh, kw, stride, _pad(pad), Cb, mode,
-                               _stream(stream)), "small_pool2d")
+    rc = _fast().pool2d(inp, out, N, Cc, H, W, kh, kw, stride, pad, Cb, mode, stream)
+    if rc is None:
+        rc = load().small_pool2d(_ptr(inp), _ptr(out), N, Cc, H, W, kh, kw, stride, _pad(pad), Cb, mode, _stream(stream))
+    _check(rc, "small_pool2d")
 
 
 def small_relu(inp, out, n_elems, stream=None):
-    _check(load().small_relu(_ptr(inp), _ptr(out), n_elems, _stream(stream)), "small_relu")
+    rc = _fast().relu(inp, out, n_elems, stream)
+    if rc is None:
+        rc = load().small_relu(_ptr(inp), _ptr(out), n_elems, _stream(stream))
+    _check(rc, "small_relu")
 
 
 def small_add(a, b, out, n_elems, stream=None):
-    _check(load().small_add(_ptr(a), _ptr(b), _ptr(out), n_elems, _stream(stream)), "small_add")
+    rc = _fast().add(a, b, out, n_elems, stream)
+    if rc is None:
+        rc = load().small_add(_ptr(a), _ptr(b), _ptr(out), n_elems, _stream(stream))
+    _check(rc, "small_add")
 
 
 def small_dense(inp, filt, out, N, Ci, Co, Cib, Cob, stream=None):
-    _check(load().small_dense(_ptr(inp), _ptr(filt), _ptr(out), N, Ci, Co, Cib, Cob, _stream(stream)), "small_dense")
+    rc = _fast().dense(inp, filt, out, N, Ci, Co, Cib, Cob, stream)
+    if rc is None:
+        rc = load().small_dense(_ptr(inp), _ptr(filt), _ptr(out), N, Ci, Co, Cib, Cob, _stream(stream))
+    _check(rc, "small_dense")
 
 
 def small_batchnorm(inp, scale, shift, out, N, Cc, H, W, Cb, stream=None):
@@ -273,11 +315,17 @@ def _quant(q):
 
 
 def small_pack_u8(nchw, blocked, N, Cc, H, W, Cb, stream=None):
-    _check(load().small_pack_u8(_ptr8(nchw), _ptr8(blocked), N, Cc, H, W, Cb, _stream(stream)), "small_pack_u8")
+    rc = _fast().pack_u8(nchw, blocked, N, Cc, H, W, Cb, stream)
+    if rc is None:
+        rc = load().small_pack_u8(_ptr8(nchw), _ptr8(blocked), N, Cc, H, W, Cb, _stream(stream))
+    _check(rc, "small_pack_u8")
 
 
 def small_unpack_u8(blocked, nchw, N, Cc, H, W, Cb, stream=None):
-    _check(load().small_unpack_u8(_ptr8(blocked), _ptr8(nchw), N, Cc, H, W, Cb, _stream(stream)), "small_unpack_u8")
+    rc = _fast().unpack_u8(blocked, nchw, N, Cc, H, W, Cb, stream)
+    if rc is None:
+        rc = load().small_unpack_u8(_ptr8(blocked), _ptr8(nchw), N, Cc, H, W, Cb, _stream(stream))
+    _check(rc, "small_unpack_u8")
 
 
 def small_pack_filter_u8(oihw, blocked, Co, Ci, kh, kw, Cob, Cib, stream=None):
@@ -299,27 +347,42 @@ def small_filter_sums_u8(filt, sums, Co, Ci, kh, kw, Cob, Cib, stream=None):
 
 
 def small_conv2d_u8(inp, filt, out, N, Ci, Co, H, W, kh, kw, stride, pad, Cib, Cob, q, filt_sums=None, stream=None):
-    _check(load().small_conv2d_u8(_ptr8(inp), _ptr8(filt), _ptr8(out), N, Ci, Co, H, W, kh, kw, stride, _pad(pad), Cib, Cob,
-                                  _quant(q), _ptr32i(filt_sums), _stream(stream)), "small_conv2d_u8")
+    rc = _fast().conv2d_u8(inp, filt, out, N, Ci, Co, H, W, kh, kw, stride, pad, Cib, Cob, q, filt_sums, stream)
+    if rc is None:
+        rc = load().small_conv2d_u8(_ptr8(inp), _ptr8(filt), _ptr8(out), N, Ci, Co, H, W, kh, kw, stride, _pad(pad),
+                                    Cib, Cob, _quant(q), _ptr32i(filt_sums), _stream(stream))
+    _check(rc, "small_conv2d_u8")
 
 
 def small_dwconv2d_u8(inp, filt, out, N, Cc, H, W, kh, kw, stride, pad, Cb, q, stream=None):
-    _check(load().small_dwconv2d_u8(_ptr8(inp), _ptr8(filt), _ptr8(out), N, Cc, H, W, kh, kw, stride, _pad(pad), Cb,
-                                    _quant(q), _stream(stream)), "small_dwconv2d_u8")
+    rc = _fast().dwconv2d_u8(inp, filt, out, N, Cc, H, W, kh, kw, stride, pad, Cb, q, stream)
+    if rc is None:
+        rc = load().small_dwconv2d_u8(_ptr8(inp), _ptr8(filt), _ptr8(out), N, Cc, H, W, kh, kw, stride, _pad(pad), Cb,
+                                      _quant(q), _stream(stream))
+    _check(rc, "small_dwconv2d_u8")
 
 
 def small_dense_u8(inp, filt, out, N, Ci, Co, Cib, Cob, q, filt_sums=None, stream=None):
-    _check(load().small_dense_u8(_ptr8(inp), _ptr8(filt), _ptr8(out), N, Ci, Co, Cib, Cob, _quant(q), _ptr32i(filt_sums),
-                                 _stream(stream)), "small_dense_u8")
+    rc = _fast().dense_u8(inp, filt, out, N, Ci, Co, Cib, Cob, q, filt_sums, stream)
+    if rc is None:
+        rc = load().small_dense_u8(_ptr8(inp), _ptr8(filt), _ptr8(out), N, Ci, Co, Cib, Cob, _quant(q),
+                                   _ptr32i(filt_sums), _stream(stream))
+    _check(rc, "small_dense_u8")
 
 
 def small_pool2d_u8(inp, out, N, Cc, H, W, kh, kw, stride, pad, Cb, mode, stream=None):
-    _check(load().small_pool2d_u8(_ptr8(inp), _ptr8(out), N, Cc, H, W, kh, kw, stride, _pad(pad), Cb, mode,
-                                  _stream(stream)), "small_pool2d_u8")
+    rc = _fast().pool2d_u8(inp, out, N, Cc, H, W, kh, kw, stride, pad, Cb, mode, stream)
+    if rc is None:
+        rc = load().small_pool2d_u8(_ptr8(inp), _ptr8(out), N, Cc, H, W, kh, kw, stride, _pad(pad), Cb, mode,
+                                    _stream(stream))
+    _check(rc, "small_pool2d_u8")
 
 
 def small_relu_u8(inp, out, n, z, stream=None):
-    _check(load().small_relu_u8(_ptr8(inp), _ptr8(out), n, z, _stream(stream)), "small_relu_u8")
+    rc = _fast().relu_u8(inp, out, n, z, stream)
+    if rc is None:
+        rc = load().small_relu_u8(_ptr8(inp), _ptr8(out), n, z, _stream(stream))
+    _check(rc, "small_relu_u8")
 
 
 def make_layer_table(layers, filters):

@@ -6,6 +6,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsmall_hip.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")             # the single-layer calls from Python, in front of the ctypes binding
 PROBE_LIB = os.path.join(HERE, "libsmall_probe.so")       # the benchmark's matrix-rate probe, a library of its own
 SOURCES = ["elementwise.hip", "window.hip", "window_rows.hip", "window_dpp.hip", "window_dpp_u8.hip", "pool_dpp_u8.hip", "quant_ends.hip", "pool_dpp.hip", "conv.hip", "conv_same.hip", "conv_pw.hip", "conv_split.hip", "conv_split3.hip", "dwpw.hip", "dwpw_run.hip", "chain.hip", "resident.hip", "quant.hip", "conv_u8_tile.hip", "conv_u8_pw.hip", "layout_u8.hip", "resident_u8.hip", "table2.hip", "small_api.hip"]
 # packed fp32 VALU ops are switched off for every device translation unit
@@ -24,6 +25,25 @@ def _stale(target, deps):
         return True
     t = os.path.getmtime(target)
     return any(os.path.getmtime(d) > t for d in deps)
+
+
+def build_fastcall(force=False):
+    """Host code only, against torch's headers (its libraries are loaded before it)."""
+    src = os.path.join(CSRC, "fastcall.cpp")
+    if not (force or _stale(FASTCALL, [src, os.path.join(HERE, "..", "include", "small.h")])):
+        return
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+               os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    cmd += [a for d in include for a in ("-isystem", d)] + [src, "-o", FASTCALL, "-L" + os.path.join(root, "lib")]
+    out = subprocess.run(cmd + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], stdout=subprocess.PIPE,
+                         stderr=subprocess.STDOUT, text=True)
+    if out.returncode:
+        raise RuntimeError("g++ failed\nfastcall.cpp:\n" + out.stdout)
 
 
 def build_lib(force=False, verbose=False):
@@ -65,6 +85,7 @@ def build_lib(force=False, verbose=False):
                              stderr=subprocess.STDOUT, text=True)
         if out.returncode:
             raise RuntimeError("hipcc failed\nprobe.hip:\n" + out.stdout)
+    build_fastcall(force)
     return LIB
 
 

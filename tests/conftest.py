@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -28,3 +29,11 @@ def read_golden(name):
 @pytest.fixture(scope="session")
 def golden():
     return read_golden
+
+
+@pytest.fixture(autouse=True, scope="module")
+def _no_garbage_of_other_modules():
+    """Device memory that earlier tests' reference cycles still hold is freed here and not at some later allocation, between
+    two readings of torch's memory statistics for instance."""
+    gc.collect()
+    yield

@@ -1,0 +1,111 @@
+"""The extension in front of the ctypes binding: takes the plain calls, leaves everything else, refuses what ctypes' path refuses."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2303_04769_amd as S
+from paper_2303_04769_amd import binding as B
+
+Q = B.small_quant(128, 131, 128, 1 << 21, 31, 0, 255)
+F, U, I = torch.float32, torch.uint8, torch.int32
+CONV = (2, 16, 32, 5, 7, 3, 3, 1, (1, 1, 1, 1), 16, 16)
+DW = (2, 16, 5, 7, 3, 3, 1, (1, 1, 1, 1), 16)
+DENSE = (3, 32, 16, 16, 16)
+N_IN = 2 * 16 * 5 * 7
+# name: tensors (type, elements; the last one of the data is the result), the other arguments, place of the result
+CALLS = {
+    "pack": ([(F, N_IN), (F, N_IN)], (2, 16, 5, 7, 16), 1),
+    "unpack": ([(F, N_IN), (F, N_IN)], (2, 16, 5, 7, 16), 1),
+    "pack_u8": ([(U, N_IN), (U, N_IN)], (2, 16, 5, 7, 16), 1),
+    "unpack_u8": ([(U, N_IN), (U, N_IN)], (2, 16, 5, 7, 16), 1),
+    "conv2d": ([(F, N_IN), (F, 32 * 16 * 9), (F, 2 * N_IN)], CONV, 2),
+    "conv2d_u8": ([(U, N_IN), (U, 32 * 16 * 9), (U, 2 * N_IN)], CONV + (Q, (I, 32)), 2),
+    "dwconv2d": ([(F, N_IN), (F, 16 * 9), (F, N_IN)], DW, 2),
+    "dwconv2d_u8": ([(U, N_IN), (U, 16 * 9), (U, N_IN)], DW + (Q,), 2),
+    "pool2d": ([(F, N_IN), (F, N_IN)], DW + (S.POOL_MAX,), 1),
+    "pool2d_u8": ([(U, N_IN), (U, N_IN)], DW + (S.POOL_AVG,), 1),
+    "relu": ([(F, N_IN), (F, N_IN)], (N_IN,), 1),
+    "relu_u8": ([(U, N_IN), (U, N_IN)], (N_IN, 128), 1),
+    "add": ([(F, N_IN), (F, N_IN), (F, N_IN)], (N_IN,), 2),
+    "dense": ([(F, 96), (F, 512), (F, 48)], DENSE, 2),
+    "dense_u8": ([(U, 96), (U, 512), (U, 48)], DENSE + (Q, (I, 16)), 2),
+}
+
+
+def _tensor(spec, device, seed):
+    g = torch.Generator().manual_seed(seed)
+    t = torch.randn(spec[1], generator=g) if spec[0] == F else torch.randint(0, 256, (spec[1],), generator=g).to(spec[0])
+    return t.to(device)
+
+
+def _arguments(name, device):
+    tensors, rest, out = CALLS[name]
+    args = [_tensor(s, device, k) for k, s in enumerate(tensors)]
+    args += [_tensor(r, device, 9) if isinstance(r, tuple) and r and isinstance(r[0], torch.dtype) else r for r in rest]
+    return args, out
+
+
+def _forms(name, args):
+    """The same call in forms that are left to ctypes."""
+    ints = [k for k, a in enumerate(args) if type(a) is int]
+    yield "a number of another type", [np.int64(a) if k == ints[-1] else a for k, a in enumerate(args)]
+    for k, a in enumerate(args):
+        if isinstance(a, tuple):
+            yield "a padding in a list", [list(a) if j == k else b for j, b in enumerate(args)]
+            yield "a padding of five", [a + (1,) if j == k else b for j, b in enumerate(args)]
+        if isinstance(a, B.small_quant):
+            yield "a record of another type", [object() if j == k else b for j, b in enumerate(args)]
+    yield "a parameter", [torch.nn.Buffer(args[0]) if hasattr(torch.nn, "Buffer") else args[0].as_subclass(type("T", (torch.Tensor,), {}))] + args[1:]
+
+
+@pytest.mark.parametrize("name", sorted(CALLS))
+def test_only_plain_calls_are_taken(name):
+    """Without a GPU: tensors in host memory are refused as ever; a call in another form, with a stream or with an argument
+    too few is not looked at."""
+    args, _ = _arguments(name, "cpu")
+    fast = getattr(B._fast(), name)
+    with pytest.raises(TypeError, match="contiguous .* CUDA tensor"):
+        fast(*args, None)
+    with pytest.raises(TypeError, match="contiguous .* CUDA tensor"):
+        getattr(S, "small_" + name)(*args)
+    assert fast(*args, object()) is None and fast(*args) is None and fast(*args, None, None) is None
+    for what, other in _forms(name, args):
+        if what != "a parameter" or type(other[0]) not in (torch.Tensor, torch.nn.Parameter):
+            assert fast(*other, None) is None, what
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(CALLS))
+def test_both_routes_agree(name):
+    """The extension, the ctypes path (a stream given) and the keyword form: the same bytes; a type or stride it does not take is
+    refused; an error of the library has the same code on both routes; a side stream is taken as the current one."""
+    args, out = _arguments(name, "cuda:0")
+    call = getattr(S, "small_" + name)
+    want = None
+    for route in ("extension", "ctypes", "side"):
+        args[out] = torch.zeros_like(args[out])
+        if route == "extension":
+            assert getattr(B._fast(), name)(*args, None) == 0
+        elif route == "ctypes":
+            call(*args, stream=torch.cuda.current_stream())
+        else:
+            side = torch.cuda.Stream()
+            side.wait_stream(torch.cuda.current_stream())
+            with torch.cuda.stream(side):
+                call(*args)
+            torch.cuda.current_stream().wait_stream(side)
+        torch.cuda.synchronize()
+        got = args[out].cpu()
+        want = got if want is None else want
+        assert torch.equal(got, want) and got.float().abs().sum() > 0, route
+    wrong = list(args)
+    wrong[0] = torch.stack([args[0], args[0]], 1)[:, 0]
+    for bad in (wrong[0], args[0].double(), args[0].cpu()):
+        with pytest.raises(TypeError, match="contiguous .* CUDA tensor"):
+            call(*([bad] + args[1:]))
+    codes = []
+    for kw in ({}, {"stream": torch.cuda.current_stream()}):
+        with pytest.raises(S.SmallError) as e:
+            call(*([None] + args[1:]), **kw)
+        codes.append(e.value.code)
+    assert codes[0] == codes[1]
