@@ -93,18 +93,19 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
     // over all nine taps, those outside the image carrying the code zx. A dot product wants the three taps of one
     // window row of ONE channel in a word, the tensor has the four channels of one pixel in a word: per input row the
     // words of the left neighbour, the pixel and the right neighbour (lane shifts of the raw words: two per row, not
-    // eight) are transposed into four words [left, centre, right, 0], one per channel, with two byte permutes each;
+    // eight) are transposed into four words [left, centre, right, 0], one per channel, with six byte permutes;
     // every such word serves three output rows. The filter is transposed the same way once. Per output word: 2 lane
-    // shifts, 8 permutes and 12 dot products, where the float form of this kernel had 8 shifts, 4 conversions and 36
+    // shifts, 6 permutes and 12 dot products, where the float form of this kernel had 8 shifts, 4 conversions and 36
     // multiply-adds; with zw = 128 (b = 0) the sum of the window's codes is not needed at all.
     const unsigned flip = 0x80808080u;
     const int za = 128 - a.q.zx, zb = 128 - a.q.zw;
     auto channel_words = [&](unsigned left, unsigned mid, unsigned right, unsigned (&t)[4]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const unsigned lm = __builtin_amdgcn_perm(mid, left, 0x0c0c0000u | (unsigned)((4 + c) << 8) | (unsigned)c);
-            t[c] = __builtin_amdgcn_perm(right, lm, 0x0c000100u | (unsigned)((4 + c) << 16));
-        }
+        // (the two outer words' bytes in pairs first: six permutes)
+        const unsigned p01 = __builtin_amdgcn_perm(mid, left, 0x05010400u), p23 = __builtin_amdgcn_perm(mid, left, 0x07030602u);
+        t[0] = __builtin_amdgcn_perm(right, p01, 0x0c040100u);
+        t[1] = __builtin_amdgcn_perm(right, p01, 0x0c050302u);
+        t[2] = __builtin_amdgcn_perm(right, p23, 0x0c060100u);
+        t[3] = __builtin_amdgcn_perm(right, p23, 0x0c070302u);
     };
     unsigned wt[3][4];                                      // [window row][channel]: its three taps
     int cst[4];                                             // a sum w' + 9 a b per channel
@@ -151,7 +152,7 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
             int acc = __builtin_amdgcn_sdot4((int)tw[j - 2][c], (int)wt[0][c], cst[c], false);
             acc = __builtin_amdgcn_sdot4((int)tw[j - 1][c], (int)wt[1][c], acc, false);
             acc = __builtin_amdgcn_sdot4((int)tw[j][c], (int)wt[2][c], acc, false);
-            if (HAS_ZB) acc += zb * (sx[j - 2][c] + sx[j - 1][c] + sx[j][c]);
+            if (HAS_ZB) acc += __mul24(zb, sx[j - 2][c] + sx[j - 1][c] + sx[j][c]);      // (24 bits: one multiply-add)
             y |= (unsigned)requant_code<HIGH>(acc, a.q, addend) << (8 * c);
         }
         const unsigned off = (col_out && j < n_in) ? at + (unsigned)((r0 + j - 2) * row_bytes) : kBeyond;
