@@ -91,8 +91,7 @@ __device__ __forceinline__ unsigned requant_signed(int v, const Requant &q)     
 
 // A unit of a convolution or (DW) depthwise layer: one output block x WM groups of 16 pixels. A depthwise layer is the
 // convolution whose filter of a block has channel c's taps on the diagonal: the matrix cores are idle otherwise, and an output
-// word costs three matrix instructions and a third of the vector instructions of window_dpp_u8.hip's permutes and dot products
-// (which need the rows in registers to be worth it).
+// word costs three matrix instructions and a third of the vector instructions of byte permutes and dot products.
 template <int WM, bool DW>
 __device__ __forceinline__ void conv_unit(char *lds, const RU8Layer &L, const Requant &q, int u, int lane, int zx, int zw, int filt,
                                           int pads, int table)

@@ -652,6 +652,21 @@ def test_depthwise_lane_shift_strips(case):
     test_depthwise_lane_shift(case)
 
 
+@pytest.mark.parametrize("zw", [0, 1, 128, 255])
+@pytest.mark.parametrize("shape", [
+    (50, 16, 10, 5), (179, 16, 2, 7), (157, 16, 2, 8),             # strips of 3 rows: several, two and one plane per band
+    (193, 128, 4, 5), (513, 32, 4, 6), (257, 16, 4, 15),           # of 5
+    (126, 256, 13, 3), (51, 256, 13, 6), (205, 16, 13, 15),        # of 7
+    (212, 256, 8, 3), (341, 64, 8, 6), (171, 16, 16, 15),          # of 9
+    (1025, 256, 3, 6), (2049, 64, 33, 1), (17, 32, 5, 1),          # outputs of more than 4 MB, planes of one pixel a row
+])
+def test_depthwise_matrix_forms(shape, zw):
+    """Every strip length with every number of planes per band, the last image group not full, with the products by the
+    filter's zero point left out (128), once and twice (0, whose 128 is no signed byte): exact."""
+    N, C, H, W = shape
+    test_depthwise_lane_shift((N, C, H, W, (zw * 7 + H) % 256, zw))
+
+
 @pytest.mark.parametrize("mult,shift", [(1 << 20, 0), ((1 << 31) - 1, 0), (1, 31), (0, 5), ((1 << 31) - 1, 31), (3, 1)])
 def test_depthwise_extreme_scales(mult, shift):
     """Scales from 'everything saturates' to 'everything rounds to the zero point': whichever requantization path the
