@@ -313,7 +313,11 @@ template <bool HIGH>
 __device__ __forceinline__ int requant_code(int acc, const QuantParams &q, long addend)
 {
     if constexpr (!HIGH) return requant_clamped(acc, q, addend);
-    return clamp_code((int)(((long)acc * (long)q.mult32 + addend) >> 32), q.lo, q.hi);
+    // (a multiplier that the compiler has seen compared with zero makes two unsigned multiply-adds and two moves of this one: 128
+    // channels 3x3 28x28, 64 images 14.1 -> 13.6 us, 3 -> 32 channels stride 2 112x112 8.5 -> 8.2)
+    int mult = q.mult32;
+    asm("" : "+s"(mult));
+    return clamp_code((int)(((long)acc * (long)mult + addend) >> 32), q.lo, q.hi);
 }
 
 // For any layer.
