@@ -218,7 +218,7 @@ __global__ void __launch_bounds__(256, WM * WN >= 16 ? 2 : WM * WN >= 8 ? 3 : 4)
     // next chunk are requested before the matrix instructions and written over the current ones behind them.
     int f = 0;
     for (int ch = 0; ch < a.n_chunks; ++ch) {
-        in_load(ch + 1);
+        if (ch + 1 < a.n_chunks) in_load(ch + 1);          // (64 channels 56 x 56 x 64 images, one chunk: 17.1 -> 16.6 us)
         for (int ph = 0; ph < a.phases; ++ph, ++f) {
             const bool last_ph = ph + 1 == a.phases;
             f_load(last_ph ? ch + 1 : ch, last_ph ? 0 : ph + 1, f + 1 < a.F, f0);
