@@ -274,8 +274,7 @@ __global__ void __launch_bounds__(kThreads) resident_u8(RU8Args a)
                         for (int c = 0; c < 4; ++c) s[c] += (x >> (8 * c)) & 255u;
                     }
 #pragma unroll
-                    for (int d = 4; d < 64; d *= 2)
-                        for (int c = 0; c < 4; ++c) s[c] += __shfl_xor(s[c], d);
+                    for (int c = 0; c < 4; ++c) s[c] = add_quads(s[c]);
                     unsigned y[4];
 #pragma unroll
                     for (int c = 0; c < 4; ++c) y[c] = (unsigned)quotient(L.magic, L.shift, (int)(s[c] + (unsigned)HW / 2u));
@@ -292,8 +291,7 @@ __global__ void __launch_bounds__(kThreads) resident_u8(RU8Args a)
                         v = __builtin_amdgcn_sdot4(x, w, v, false) - zb * __builtin_amdgcn_sdot4(x, 0x01010101, 0, false) -
                             za * __builtin_amdgcn_sdot4(w, 0x01010101, 0, false);
                     }
-#pragma unroll
-                    for (int d = 1; d < 64; d *= 2) v += __shfl_xor(v, d);
+                    v = wave_sum(v);
                     v += nB * 16 * za * zb;
                     if (lane == 0) a.out[(size_t)n * L.Co + o] = (unsigned char)requant_signed(v, q);
                 }

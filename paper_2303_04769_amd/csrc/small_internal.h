@@ -61,6 +61,32 @@ __device__ __forceinline__ int quotient(const FastDiv &f, int n)
     return (int)((__umulhi((unsigned)n, f.magic) + ((unsigned)n & all)) >> f.shift);
 }
 
+// Sums across the lanes of a wave, in every lane: the additions of a butterfly over 32, 16, 8, 4, 2, 1 lanes apart, bit for bit,
+// by lane permutations of the vector unit. A step of shuffles is a trip through LDS, some 130 cycles, and every step waits for the
+// one before (the quantized image-resident networks, whose last two layers are such sums: audio CNN 100 images 23.8 -> 23.3 us).
+template <int CTRL>
+__device__ __forceinline__ int dpp_of(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
+template <typename T>
+__device__ __forceinline__ T add_quads(T v)                // over the lanes of equal (lane & 3): 32, 16, 8 and 4 apart
+{
+    static_assert(sizeof(T) == 4, "one register");
+    const unsigned a = __builtin_bit_cast(unsigned, v);
+    const auto h = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+    const T v32 = __builtin_bit_cast(T, (unsigned)h[0]) + __builtin_bit_cast(T, (unsigned)h[1]);
+    const unsigned b = __builtin_bit_cast(unsigned, v32);
+    const auto r = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    const T v16 = __builtin_bit_cast(T, (unsigned)r[0]) + __builtin_bit_cast(T, (unsigned)r[1]);
+    const T v8 = v16 + __builtin_bit_cast(T, dpp_of<0x128>(__builtin_bit_cast(int, v16)));       // row_ror:8
+    return v8 + __builtin_bit_cast(T, dpp_of<0x124>(__builtin_bit_cast(int, v8)));               // row_ror:4 (8 apart are equal)
+}
+template <typename T>
+__device__ __forceinline__ T wave_sum(T v)
+{
+    v = add_quads(v);
+    v += __builtin_bit_cast(T, dpp_of<0x4e>(__builtin_bit_cast(int, v)));                        // quad_perm [2, 3, 0, 1]
+    return v + __builtin_bit_cast(T, dpp_of<0xb1>(__builtin_bit_cast(int, v)));                  // quad_perm [1, 0, 3, 2]
+}
+
 // Compute units of the current device (asked once; 256 -- an MI355X -- when no device can be asked, so that the
 // host-only planning calls give the same answers on a machine without a GPU). Launch shapes, tile choices and the
 // batch windows of image-resident runs are derived from it.
