@@ -400,7 +400,7 @@ Plan plan_tile(const LayerGeom &g)
 // fullest compute unit counts, with a workgroup alone on it as 1.25; staging a chunk costs a step; work on padded channels, taps or
 // columns is done but does not count; an odd number of output blocks costs the other kernels an empty block, or conv_same.hip its
 // smaller tile (7 %). At full use the time is 0.62 of that of conv_same.hip's tiles and 0.495 of the others'. us with
-// the fp32 instruction / here: 64 -> 64 channels 56 x 56, 256 images (24.5 workgroups a unit) 454 / 355, 28 x 28, 64 images (1.53)
+// the fp32 instruction / here at the time of the fit (here 5 to 7 % less since, 333 us for the first): 64 -> 64 channels 56 x 56, 256 images (24.5 workgroups a unit) 454 / 355, 28 x 28, 64 images (1.53)
 // 41.5 / 31.7, 48 images (1.15; not taken) 29.7 / 30.1, 40 images (0.96) 24.7 / 24.8, 8 x 8, 300 images (0.59; not taken) 18.1 / 23.7;
 // 64 -> 112 28 x 28 x 64 66 / 58; 48 -> 64 28 x 28 x 40 (not taken) 20.1 / 23.6; 16 -> 64 (five steps; not taken) 7 x 7 x 500 9.0 /
 // 11.5; 48 -> 64 5 x 5 28 x 28 x 64 127 / 60; 256 -> 96 1 x 3 79 x 20 x 12 (1.16; not taken) 36 / 50.

@@ -17,7 +17,8 @@
 //     two barriers: with two buffers and one barrier half as many workgroups fit a compute unit and nothing covers a
 //     wave's waiting (128 channels 28 x 28 x 64 images: 23.5 us, 16.5 with one).
 //   - the code is free of branches around loads and LDS writes, and a wave's tile as large as the work allows: the time is
-//     issue slots and waiting, not matrix instructions (8.8 of 39 thousand cycles per SIMD on that layer).
+//     issue slots and waiting, not matrix instructions (8.8 of some 30 thousand cycles per SIMD on that layer, now 13.6 us; 15.2
+//     with zw != 128).
 // The correction sums of the zero points are those of quant.hip; the constant part (K a b and the filter's sums) is the
 // accumulators' initial value. Layers whose filter sums the caller did not give (zx != 128) and scales that need the wide
 // requantization stay with quant.hip: code that is rarely run would lie between the code that is, and a workgroup that
@@ -389,7 +390,8 @@ Plan plan_tile(const LayerGeom &g)
 
 // Where the register-only kernels of quant.hip stay the better ones: reductions of at most 20 chunks, which their short form
 // holds in registers whole (16 channels 32 x 32 x 100 images 5.3 us there, 6.6 here; 32 channels 16 x 16 x 100 4.0 / 4.9), and
-// where the two models below say so. They are fitted to 3300 measured pairs of layer and tile (us; 3 to 8 % root mean square for
+// where the two models below say so. They are fitted to 3300 measured pairs of layer and tile (us, before both
+// sides lost 3 to 12 % of their time by a shorter requantization; 3 to 8 % root mean square for
 // the tiles, 7 to 13 for the kernels there), w being the workgroups of the fullest compute unit:
 //   here   3.0 + a w + phases (b + c w) + chunks (d + e w)       a phase: kTG steps; a chunk: input brought in and two barriers
 //   there  3.5 + a w + steps (b + c w) + d passes               a step: one matrix instruction of four 16-byte chunks per tile;
