@@ -69,7 +69,7 @@ __device__ __forceinline__ FastDiv fastdiv_at(const __attribute__((address_space
     return r;
 }
 
-template <int WM, int WN, int WVM, int WVN, int CORR>
+template <int WM, int WN, int WVM, int WVN, int CORR, bool STREAM>
 __global__ void __launch_bounds__(256, WM * WN >= 16 ? 2 : WM * WN >= 8 ? 3 : 4) conv_u8_tile(QTileArgs a)
 {
     constexpr int TM = 16 * WM * WVM, NCT = WN * WVN;          // pixels, 16-channel blocks of a workgroup
@@ -294,7 +294,7 @@ __global__ void __launch_bounds__(256, WM * WN >= 16 ? 2 : WM * WN >= 8 ? 3 : 4)
                 auto o = __builtin_amdgcn_permlane32_swap(t01[1], t23[1], false, false);
                 const uintx4 v = {e[0], o[0], e[1], o[1]};
                 const int j = 4 * c + g;
-                __builtin_amdgcn_raw_buffer_store_b128(v, dst, place(WN == 4 ? c : j / WN, WN == 4 ? g : j % WN), 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(v, dst, place(WN == 4 ? c : j / WN, WN == 4 ? g : j % WN), 0, STREAM ? kNonTemporal : 0);
             }
         } else {
 #pragma unroll
@@ -463,10 +463,15 @@ hipError_t launch_conv_u8_tile(const unsigned char *in, const unsigned char *fil
     a.dStrips = make_fastdiv(a.strips); a.dCt = make_fastdiv(a.n_cot); a.dkw = make_fastdiv(a.kw);
     a.q = q;
     const dim3 grid((unsigned)((a.M + tm - 1) / tm * a.n_cot));
+    // Outputs of 4 MB and more are stored non-temporally: 0.94 to 1.0 of the time over 27 random layers (64 channels 56 x 56 x 64 images
+    // 16.6 -> 15.6 us, 128 channels 28 x 28 x 64 15.1 -> 14.8); smaller ones 0.97 to 1.06.
+    const bool stream = a.out_bytes >= (4u << 20);
 #define SMALL_TILE_CASE(I_, M_, N_, VM_, VN_)                                                   \
     case I_:                                                                                    \
-        if (corr == 0) return run<conv_u8_tile<M_, N_, VM_, VN_, 0>>(grid, pl.lds, s, a);       \
-        return run<conv_u8_tile<M_, N_, VM_, VN_, 1>>(grid, pl.lds, s, a);
+        if (!stream && corr == 0) return run<conv_u8_tile<M_, N_, VM_, VN_, 0, false>>(grid, pl.lds, s, a);  \
+        if (!stream) return run<conv_u8_tile<M_, N_, VM_, VN_, 1, false>>(grid, pl.lds, s, a);  \
+        if (corr == 0) return run<conv_u8_tile<M_, N_, VM_, VN_, 0, true>>(grid, pl.lds, s, a); \
+        return run<conv_u8_tile<M_, N_, VM_, VN_, 1, true>>(grid, pl.lds, s, a);
     switch (pl.tile) {
         SMALL_TILE_CASE(0, 4, 4, 4, 1)
         SMALL_TILE_CASE(1, 4, 4, 2, 2)

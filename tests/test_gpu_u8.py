@@ -200,6 +200,29 @@ def test_conv_pointwise_walk(N, Ci, Co, H, W, s, zx, zw, sums):
         assert len(np.unique(ref)) > 8
 
 
+@pytest.mark.parametrize("N,Ci,Co,H,W,zx,zw", [
+    (257, 16, 64, 29, 23, 7, 140), (257, 96, 112, 19, 23, 128, 128), (129, 144, 256, 19, 17, 3, 128), (65, 256, 176, 31, 31, 128, 99),
+])
+def test_conv_pointwise_walk_streamed(N, Ci, Co, H, W, zx, zw):
+    """Outputs of 10 MB and more, which are stored non-temporally: one to four instructions, with and without the sums."""
+    assert N * Co * H * W >= 10 << 20
+    test_conv_pointwise_walk(N, Ci, Co, H, W, 1, zx, zw, True)
+
+
+@pytest.mark.parametrize("N,Ci,Co,H,W,k", [(65, 64, 80, 31, 29, 3), (129, 48, 32, 33, 35, 3), (257, 128, 128, 13, 11, 3), (66, 48, 16, 64, 65, 5)])
+def test_conv_tiles_streamed(N, Ci, Co, H, W, k):
+    """Outputs of 4 MB and more through the LDS tiles, stored non-temporally."""
+    assert N * Co * H * W >= 4 << 20
+    p = k // 2
+    r = _rng(24)
+    x, w = WL.u8_codes(r, (N, Ci, H, W)), WL.u8_codes(r, (Co, Ci, k, k))
+    for zx, zw in ((140, 119), (128, 128)):
+        q = _quant(Ci * k * k, zx, zw)
+        got = _conv(x, w, 1, (p, p, p, p), q, 16, 16, with_sums=True)
+        for n in (0, N // 2, N - 1):
+            _same(got[n:n + 1], Q.conv2d(x[n:n + 1], w, 1, (p, p, p, p), q), f"conv u8 {Ci}->{Co} image {n}")
+
+
 @pytest.mark.parametrize("case", [
     (2, 3, 8, 9, 9, 3, 3, 2, (0, 1, 0, 1), 128, 128, 3, 8),        # first layer of the depthwise-separable CNN
     (2, 1, 16, 13, 10, 10, 4, 2, (4, 5, 1, 1), 5, 140, 1, 16),     # first layer of the audio CNN
