@@ -7,6 +7,8 @@ Every wrapper raises SmallError on a non-zero status. No arithmetic happens here
 """
 import ctypes as C
 import functools
+import importlib.util
+import logging
 import os
 
 import torch
@@ -129,17 +131,39 @@ def load():
 _fastcall = None
 
 
+class _Ctypes:
+    """Stands in for the extension where it can be neither loaded nor built: leaves every call to ctypes."""
+
+    def __getattr__(self, name):
+        return _left_to_ctypes
+
+
+def _left_to_ctypes(*_):
+    return None
+
+
+def _load_fastcall(lib):
+    if not os.path.exists(FASTCALL_PATH):
+        from .build import build_fastcall
+        build_fastcall()
+    spec = importlib.util.spec_from_file_location(__package__ + "._fastcall", FASTCALL_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    module.bind(lib._handle, small_quant)
+    return module
+
+
 def _fast():
-    """The calls of csrc/fastcall.cpp, of which each returns None for what it leaves to ctypes."""
+    """The calls of csrc/fastcall.cpp, of which each returns None for what it leaves to ctypes. Where there is no such module
+    (no compiler or no headers to build it with, a file that does not load) that is every call; looked for once."""
     global _fastcall
     if _fastcall is None:
         lib = load()
-        if not os.path.exists(FASTCALL_PATH):
-            from .build import build_fastcall
-            build_fastcall()
-        from . import _fastcall as module
-        module.bind(lib._handle, small_quant)
-        _fastcall = module
+        try:
+            _fastcall = _load_fastcall(lib)
+        except Exception as e:
+            logging.getLogger(__name__).warning("calls go through ctypes, some 1.5 us longer each: no extension module (%s)", e)
+            _fastcall = _Ctypes()
     return _fastcall
 
 

@@ -85,9 +85,15 @@ def build_lib(force=False, verbose=False):
                              stderr=subprocess.STDOUT, text=True)
         if out.returncode:
             raise RuntimeError("hipcc failed\nprobe.hip:\n" + out.stdout)
-    build_fastcall(force)
     return LIB
 
 
+def build_all(force=False, verbose=False):
+    """The libraries, and the extension, which the binding can do without."""
+    lib = build_lib(force, verbose)
+    build_fastcall(force)
+    return lib
+
+
 if __name__ == "__main__":
-    print(build_lib(force=True, verbose=True))
+    print(build_all(force=True, verbose=True))

@@ -74,6 +74,29 @@ def test_only_plain_calls_are_taken(name):
             assert fast(*other, None) is None, what
 
 
+@pytest.mark.parametrize("why", ["no compiler", "a file that does not load"])
+def test_calls_go_through_ctypes_where_there_is_no_extension(monkeypatch, tmp_path, why):
+    """Every call gets as far as ctypes' own look at the tensors, here in host memory; the extension is looked for once."""
+    from paper_2303_04769_amd import build
+    tries = []
+
+    def no_compiler(*args, **kwargs):
+        tries.append(args)
+        raise FileNotFoundError(2, "No such file or directory", "g++")
+    monkeypatch.setattr(build, "FASTCALL", str(tmp_path / "_fastcall.so"))
+    monkeypatch.setattr(B, "FASTCALL_PATH", str(tmp_path / "_fastcall.so"))
+    monkeypatch.setattr(B, "_fastcall", None)
+    monkeypatch.setattr(build.subprocess, "run", no_compiler)
+    if why != "no compiler":
+        (tmp_path / "_fastcall.so").write_bytes(b"not a shared object")
+    for name in sorted(CALLS):
+        args, _ = _arguments(name, "cpu")
+        assert getattr(B._fast(), name)(*args, None) is None
+        with pytest.raises(TypeError, match="contiguous .* CUDA tensor"):
+            getattr(S, "small_" + name)(*args)
+    assert len(tries) == (why == "no compiler")
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", sorted(CALLS))
 def test_both_routes_agree(name):
