@@ -15,7 +15,6 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsmall_hip.so")
-FASTCALL_PATH = os.path.join(_HERE, "_fastcall.so")
 
 OK = 0
 POOL_MAX, POOL_AVG = 0, 1
@@ -143,10 +142,10 @@ def _left_to_ctypes(*_):
 
 
 def _load_fastcall(lib):
-    if not os.path.exists(FASTCALL_PATH):
-        from .build import build_fastcall
-        build_fastcall()
-    spec = importlib.util.spec_from_file_location(__package__ + "._fastcall", FASTCALL_PATH)
+    from . import build
+    if not os.path.exists(build.FASTCALL):
+        build.build_fastcall()
+    spec = importlib.util.spec_from_file_location(__package__ + "._fastcall", build.FASTCALL)
     module = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(module)
     module.bind(lib._handle, small_quant)

@@ -1,12 +1,17 @@
 """Builds libsmall_hip.so in-tree with hipcc for gfx950 (cross-compiles without a GPU)."""
 import os
 import subprocess
+import sysconfig
+
+import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsmall_hip.so")
-FASTCALL = os.path.join(HERE, "_fastcall.so")             # the single-layer calls from Python, in front of the ctypes binding
+# The single-layer calls from Python, in front of the ctypes binding. It reads torch's tensors through its C++ headers: the name says
+# for which Python and which torch it was built, so that no other one loads it.
+FASTCALL = os.path.join(HERE, f"_fastcall.{sysconfig.get_config_var('SOABI')}.torch-{torch.__version__}.so")
 PROBE_LIB = os.path.join(HERE, "libsmall_probe.so")       # the benchmark's matrix-rate probe, a library of its own
 SOURCES = ["elementwise.hip", "window.hip", "window_rows.hip", "window_dpp.hip", "window_dpp_u8.hip", "pool_dpp_u8.hip", "quant_ends.hip", "pool_dpp.hip", "conv.hip", "conv_same.hip", "conv_pw.hip", "conv_split.hip", "conv_split3.hip", "dwpw.hip", "dwpw_run.hip", "chain.hip", "resident.hip", "quant.hip", "conv_u8_tile.hip", "conv_u8_pw.hip", "layout_u8.hip", "resident_u8.hip", "table2.hip", "small_api.hip"]
 # packed fp32 VALU ops are switched off for every device translation unit
@@ -32,8 +37,6 @@ def build_fastcall(force=False):
     src = os.path.join(CSRC, "fastcall.cpp")
     if not (force or _stale(FASTCALL, [src, os.path.join(HERE, "..", "include", "small.h")])):
         return
-    import sysconfig
-    import torch
     root = os.path.dirname(torch.__file__)
     include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
                os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"]]

@@ -1,4 +1,7 @@
 """The extension in front of the ctypes binding: takes the plain calls, leaves everything else, refuses what ctypes' path refuses."""
+import runpy
+import sysconfig
+
 import numpy as np
 import pytest
 import torch
@@ -84,7 +87,6 @@ def test_calls_go_through_ctypes_where_there_is_no_extension(monkeypatch, tmp_pa
         tries.append(args)
         raise FileNotFoundError(2, "No such file or directory", "g++")
     monkeypatch.setattr(build, "FASTCALL", str(tmp_path / "_fastcall.so"))
-    monkeypatch.setattr(B, "FASTCALL_PATH", str(tmp_path / "_fastcall.so"))
     monkeypatch.setattr(B, "_fastcall", None)
     monkeypatch.setattr(build.subprocess, "run", no_compiler)
     if why != "no compiler":
@@ -95,6 +97,18 @@ def test_calls_go_through_ctypes_where_there_is_no_extension(monkeypatch, tmp_pa
         with pytest.raises(TypeError, match="contiguous .* CUDA tensor"):
             getattr(S, "small_" + name)(*args)
     assert len(tries) == (why == "no compiler")
+
+
+def test_a_file_is_for_one_python_and_one_torch(monkeypatch):
+    """The extension reads tensors by torch's headers: one built for another torch or Python has another name and is not loaded."""
+    from paper_2303_04769_amd import build
+    path = lambda: runpy.run_path(build.__file__)["FASTCALL"]
+    assert path() == build.FASTCALL == B._fast().__file__
+    monkeypatch.setattr(torch, "__version__", "2.9.1+rocm6.4")
+    other = path()
+    monkeypatch.undo()
+    monkeypatch.setattr(sysconfig, "get_config_var", lambda name: "cpython-312-x86_64-linux-gnu")
+    assert len({build.FASTCALL, other, path()}) == 3
 
 
 @pytest.mark.gpu
