@@ -2,6 +2,7 @@
 import os
 import subprocess
 import sysconfig
+import threading
 
 import torch
 
@@ -42,11 +43,18 @@ def build_fastcall(force=False):
                os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"]]
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
-    cmd += [a for d in include for a in ("-isystem", d)] + [src, "-o", FASTCALL, "-L" + os.path.join(root, "lib")]
-    out = subprocess.run(cmd + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], stdout=subprocess.PIPE,
-                         stderr=subprocess.STDOUT, text=True)
-    if out.returncode:
-        raise RuntimeError("g++ failed\nfastcall.cpp:\n" + out.stdout)
+    # (written beside its place and moved there whole: another process may load it, or build it too, at the same time)
+    part = f"{FASTCALL[:-3]}.{os.getpid()}-{threading.get_ident()}.part.so"
+    cmd += [a for d in include for a in ("-isystem", d)] + [src, "-o", part, "-L" + os.path.join(root, "lib")]
+    try:
+        out = subprocess.run(cmd + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], stdout=subprocess.PIPE,
+                             stderr=subprocess.STDOUT, text=True)
+        if out.returncode:
+            raise RuntimeError("g++ failed\nfastcall.cpp:\n" + out.stdout)
+        os.replace(part, FASTCALL)
+    finally:
+        if os.path.exists(part):
+            os.remove(part)
 
 
 def build_lib(force=False, verbose=False):

@@ -111,6 +111,32 @@ def test_a_file_is_for_one_python_and_one_torch(monkeypatch):
     assert len({build.FASTCALL, other, path()}) == 3
 
 
+@pytest.mark.parametrize("fails", [False, True])
+def test_no_half_written_file_is_in_place(monkeypatch, tmp_path, fails):
+    """The compiler's output takes its place when it is whole; an earlier file stays until then, and for good if the build fails."""
+    from paper_2303_04769_amd import build
+    target = tmp_path / "_fastcall.so"
+    target.write_text("earlier")
+
+    def compiler(cmd, **kwargs):
+        out = cmd[cmd.index("-o") + 1]
+        with open(out, "w") as f:
+            f.write("half")
+            f.flush()
+            assert target.read_text() == "earlier"
+            f.write(" and half")
+        return build.subprocess.CompletedProcess(cmd, int(fails), "an error" if fails else "")
+    monkeypatch.setattr(build, "FASTCALL", str(target))
+    monkeypatch.setattr(build.subprocess, "run", compiler)
+    if fails:
+        with pytest.raises(RuntimeError, match="an error"):
+            build.build_fastcall(force=True)
+    else:
+        build.build_fastcall(force=True)
+    assert target.read_text() == ("earlier" if fails else "half and half")
+    assert [p.name for p in tmp_path.iterdir()] == ["_fastcall.so"]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", sorted(CALLS))
 def test_both_routes_agree(name):
