@@ -153,7 +153,8 @@ def _load_fastcall(lib):
 
 
 def _fast():
-    """The calls of csrc/fastcall.cpp, of which each returns None for what it leaves to ctypes. Where there is no such module
+    """The calls of csrc/fastcall.cpp, of which each returns None for what it leaves to ctypes (what can be seen here, a stream given,
+    does not get there: the look costs 0.1 us for a ReLU, 0.2 for a convolution). Where there is no such module
     (no compiler or no headers to build it with, a file that does not load) that is every call; looked for once."""
     global _fastcall
     if _fastcall is None:
@@ -205,14 +206,14 @@ def small_out_dim(i, k, stride, lo, hi):
 
 
 def small_pack(nchw, blocked, N, Cc, H, W, Cb, stream=None):
-    rc = _fast().pack(nchw, blocked, N, Cc, H, W, Cb, stream)
+    rc = _fast().pack(nchw, blocked, N, Cc, H, W, Cb, None) if stream is None else None
     if rc is None:
         rc = load().small_pack(_ptr(nchw), _ptr(blocked), N, Cc, H, W, Cb, _stream(stream))
     _check(rc, "small_pack")
 
 
 def small_unpack(blocked, nchw, N, Cc, H, W, Cb, stream=None):
-    rc = _fast().unpack(blocked, nchw, N, Cc, H, W, Cb, stream)
+    rc = _fast().unpack(blocked, nchw, N, Cc, H, W, Cb, None) if stream is None else None
     if rc is None:
         rc = load().small_unpack(_ptr(blocked), _ptr(nchw), N, Cc, H, W, Cb, _stream(stream))
     _check(rc, "small_unpack")
@@ -229,7 +230,7 @@ def small_pack_dw_filter(c1hw, blocked, Cc, kh, kw, Cb, stream=None):
 
 
 def small_conv2d(inp, filt, out, N, Ci, Co, H, W, kh, kw, stride, pad, Cib, Cob, stream=None):
-    rc = _fast().conv2d(inp, filt, out, N, Ci, Co, H, W, kh, kw, stride, pad, Cib, Cob, stream)
+    rc = _fast().conv2d(inp, filt, out, N, Ci, Co, H, W, kh, kw, stride, pad, Cib, Cob, None) if stream is None else None
     if rc is None:
         rc = load().small_conv2d(_ptr(inp), _ptr(filt), _ptr(out), N, Ci, Co, H, W, kh, kw, stride, _pad(pad), Cib, Cob,
                                  _stream(stream))
@@ -242,7 +243,7 @@ def small_conv2d_kernel(N, Ci, Co, H, W, kh, kw, stride, pad, Cib, Cob):
 
 
 def small_dwconv2d(inp, filt, out, N, Cc, H, W, kh, kw, stride, pad, Cb, stream=None):
-    rc = _fast().dwconv2d(inp, filt, out, N, Cc, H, W, kh, kw, stride, pad, Cb, stream)
+    rc = _fast().dwconv2d(inp, filt, out, N, Cc, H, W, kh, kw, stride, pad, Cb, None) if stream is None else None
     if rc is None:
         rc = load().small_dwconv2d(_ptr(inp), _ptr(filt), _ptr(out), N, Cc, H, W, kh, kw, stride, _pad(pad), Cb,
                                    _stream(stream))
@@ -250,28 +251,28 @@ def small_dwconv2d(inp, filt, out, N, Cc, H, W, kh, kw, stride, pad, Cb, stream=
 
 
 def small_pool2d(inp, out, N, Cc, H, W, kh, kw, stride, pad, Cb, mode, stream=None):
-    rc = _fast().pool2d(inp, out, N, Cc, H, W, kh, kw, stride, pad, Cb, mode, stream)
+    rc = _fast().pool2d(inp, out, N, Cc, H, W, kh, kw, stride, pad, Cb, mode, None) if stream is None else None
     if rc is None:
         rc = load().small_pool2d(_ptr(inp), _ptr(out), N, Cc, H, W, kh, kw, stride, _pad(pad), Cb, mode, _stream(stream))
     _check(rc, "small_pool2d")
 
 
 def small_relu(inp, out, n_elems, stream=None):
-    rc = _fast().relu(inp, out, n_elems, stream)
+    rc = _fast().relu(inp, out, n_elems, None) if stream is None else None
     if rc is None:
         rc = load().small_relu(_ptr(inp), _ptr(out), n_elems, _stream(stream))
     _check(rc, "small_relu")
 
 
 def small_add(a, b, out, n_elems, stream=None):
-    rc = _fast().add(a, b, out, n_elems, stream)
+    rc = _fast().add(a, b, out, n_elems, None) if stream is None else None
     if rc is None:
         rc = load().small_add(_ptr(a), _ptr(b), _ptr(out), n_elems, _stream(stream))
     _check(rc, "small_add")
 
 
 def small_dense(inp, filt, out, N, Ci, Co, Cib, Cob, stream=None):
-    rc = _fast().dense(inp, filt, out, N, Ci, Co, Cib, Cob, stream)
+    rc = _fast().dense(inp, filt, out, N, Ci, Co, Cib, Cob, None) if stream is None else None
     if rc is None:
         rc = load().small_dense(_ptr(inp), _ptr(filt), _ptr(out), N, Ci, Co, Cib, Cob, _stream(stream))
     _check(rc, "small_dense")
@@ -338,14 +339,14 @@ def _quant(q):
 
 
 def small_pack_u8(nchw, blocked, N, Cc, H, W, Cb, stream=None):
-    rc = _fast().pack_u8(nchw, blocked, N, Cc, H, W, Cb, stream)
+    rc = _fast().pack_u8(nchw, blocked, N, Cc, H, W, Cb, None) if stream is None else None
     if rc is None:
         rc = load().small_pack_u8(_ptr8(nchw), _ptr8(blocked), N, Cc, H, W, Cb, _stream(stream))
     _check(rc, "small_pack_u8")
 
 
 def small_unpack_u8(blocked, nchw, N, Cc, H, W, Cb, stream=None):
-    rc = _fast().unpack_u8(blocked, nchw, N, Cc, H, W, Cb, stream)
+    rc = _fast().unpack_u8(blocked, nchw, N, Cc, H, W, Cb, None) if stream is None else None
     if rc is None:
         rc = load().small_unpack_u8(_ptr8(blocked), _ptr8(nchw), N, Cc, H, W, Cb, _stream(stream))
     _check(rc, "small_unpack_u8")
@@ -370,7 +371,7 @@ def small_filter_sums_u8(filt, sums, Co, Ci, kh, kw, Cob, Cib, stream=None):
 
 
 def small_conv2d_u8(inp, filt, out, N, Ci, Co, H, W, kh, kw, stride, pad, Cib, Cob, q, filt_sums=None, stream=None):
-    rc = _fast().conv2d_u8(inp, filt, out, N, Ci, Co, H, W, kh, kw, stride, pad, Cib, Cob, q, filt_sums, stream)
+    rc = _fast().conv2d_u8(inp, filt, out, N, Ci, Co, H, W, kh, kw, stride, pad, Cib, Cob, q, filt_sums, None) if stream is None else None
     if rc is None:
         rc = load().small_conv2d_u8(_ptr8(inp), _ptr8(filt), _ptr8(out), N, Ci, Co, H, W, kh, kw, stride, _pad(pad),
                                     Cib, Cob, _quant(q), _ptr32i(filt_sums), _stream(stream))
@@ -378,7 +379,7 @@ def small_conv2d_u8(inp, filt, out, N, Ci, Co, H, W, kh, kw, stride, pad, Cib, C
 
 
 def small_dwconv2d_u8(inp, filt, out, N, Cc, H, W, kh, kw, stride, pad, Cb, q, stream=None):
-    rc = _fast().dwconv2d_u8(inp, filt, out, N, Cc, H, W, kh, kw, stride, pad, Cb, q, stream)
+    rc = _fast().dwconv2d_u8(inp, filt, out, N, Cc, H, W, kh, kw, stride, pad, Cb, q, None) if stream is None else None
     if rc is None:
         rc = load().small_dwconv2d_u8(_ptr8(inp), _ptr8(filt), _ptr8(out), N, Cc, H, W, kh, kw, stride, _pad(pad), Cb,
                                       _quant(q), _stream(stream))
@@ -386,7 +387,7 @@ def small_dwconv2d_u8(inp, filt, out, N, Cc, H, W, kh, kw, stride, pad, Cb, q, s
 
 
 def small_dense_u8(inp, filt, out, N, Ci, Co, Cib, Cob, q, filt_sums=None, stream=None):
-    rc = _fast().dense_u8(inp, filt, out, N, Ci, Co, Cib, Cob, q, filt_sums, stream)
+    rc = _fast().dense_u8(inp, filt, out, N, Ci, Co, Cib, Cob, q, filt_sums, None) if stream is None else None
     if rc is None:
         rc = load().small_dense_u8(_ptr8(inp), _ptr8(filt), _ptr8(out), N, Ci, Co, Cib, Cob, _quant(q),
                                    _ptr32i(filt_sums), _stream(stream))
@@ -394,7 +395,7 @@ def small_dense_u8(inp, filt, out, N, Ci, Co, Cib, Cob, q, filt_sums=None, strea
 
 
 def small_pool2d_u8(inp, out, N, Cc, H, W, kh, kw, stride, pad, Cb, mode, stream=None):
-    rc = _fast().pool2d_u8(inp, out, N, Cc, H, W, kh, kw, stride, pad, Cb, mode, stream)
+    rc = _fast().pool2d_u8(inp, out, N, Cc, H, W, kh, kw, stride, pad, Cb, mode, None) if stream is None else None
     if rc is None:
         rc = load().small_pool2d_u8(_ptr8(inp), _ptr8(out), N, Cc, H, W, kh, kw, stride, _pad(pad), Cb, mode,
                                     _stream(stream))
@@ -402,7 +403,7 @@ def small_pool2d_u8(inp, out, N, Cc, H, W, kh, kw, stride, pad, Cb, mode, stream
 
 
 def small_relu_u8(inp, out, n, z, stream=None):
-    rc = _fast().relu_u8(inp, out, n, z, stream)
+    rc = _fast().relu_u8(inp, out, n, z, None) if stream is None else None
     if rc is None:
         rc = load().small_relu_u8(_ptr8(inp), _ptr8(out), n, z, _stream(stream))
     _check(rc, "small_relu_u8")

@@ -99,6 +99,17 @@ def test_calls_go_through_ctypes_where_there_is_no_extension(monkeypatch, tmp_pa
     assert len(tries) == (why == "no compiler")
 
 
+def test_a_call_with_a_stream_goes_straight_to_ctypes(monkeypatch):
+    class Untouched:
+        def __getattr__(self, name):
+            raise AssertionError(name)
+    monkeypatch.setattr(B, "_fastcall", Untouched())
+    for name in sorted(CALLS):
+        args, _ = _arguments(name, "cpu")
+        with pytest.raises(TypeError, match="contiguous .* CUDA tensor"):
+            getattr(S, "small_" + name)(*args, stream=object())
+
+
 def test_a_file_is_for_one_python_and_one_torch(monkeypatch):
     """The extension reads tensors by torch's headers: one built for another torch or Python has another name and is not loaded."""
     from paper_2303_04769_amd import build
