@@ -398,7 +398,8 @@ int small_pool2d_u8(const unsigned char *in, unsigned char *out, int N, int C, i
     if ((long)kh * kw * 255L >= (1L << 31)) return SMALL_ERR_SHAPE;
     if (!in || !out) return SMALL_ERR_NULL;
     if (overlap_bytes(in, ni, out, no)) return SMALL_ERR_ALIAS;
-    const QuantParams none = {0, 0, 0, 0, 0, 0, 255, 0};
+    constexpr QuantParams none = {0, 0, 0, 0, 0, 0, 255, 0};
+    static_assert(none.mult32 < 0, "no scale, no form of the requantization");
     return from_hip(launch_window_u8(in, nullptr, out, g, mode == SMALL_POOL_MAX ? 1 : 2, none, as_stream(stream)));
 }
 

@@ -303,7 +303,8 @@ hipError_t launch_group_conv(const float *in, const float *filt, float *out, con
 // y = clamp(zy + ((int64)acc * mult + 2^(shift-1)) >> shift, lo, hi) (no rounding term when shift == 0).
 // amax: host-derived clamp of the sum that makes the 32-bit requantization path exact (0 = not available).
 // mult32: mult * 2^(32 - shift) where that is below 2^31, that is for scales below a half (-1 = not so).
-struct QuantParams { int zx, zw, zy, mult, shift, lo, hi, amax, mult32; };
+struct QuantParams { int zx, zw, zy, mult, shift, lo, hi, amax, mult32 = -1; };
+static_assert(sizeof(QuantParams) == 9 * sizeof(int), "tests/test_u8_routes.py and tests/test_resident_u8_rules.py mirror this record");
 // q.amax > 0: sums beyond +-amax saturate the output anyway (|amax * mult / 2^shift| >= 512) and within it the
 // scaled value fits 32 bits, so one clamp of the sum replaces 64-bit compares and selects after the product
 // (the host derives amax; 0 = scale too large for that, take the wide path). Same codes either way. bias = 2^(shift-1) +

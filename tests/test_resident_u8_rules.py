@@ -4,8 +4,8 @@ import ctypes as C
 import pytest
 
 
-class Quant(C.Structure):
-    _fields_ = [(n, C.c_int) for n in ("zx", "zw", "zy", "mult", "shift", "lo", "hi", "amax")]
+class Quant(C.Structure):          # QuantParams
+    _fields_ = [(n, C.c_int) for n in ("zx", "zw", "zy", "mult", "shift", "lo", "hi", "amax", "mult32")]
 
 
 class AddQuant(C.Structure):
@@ -32,7 +32,7 @@ def takes():
 def _group(kind, C_, H=1, W=1, Co=None, k=1, sums=0x1000, filt=0x1000, Cob=16, zx=100):
     g = Group(kind=kind, src=0, src2=0, dst=1, Ci=C_, Co=Co or C_, Cob=Cob, H=H, W=W, Ho=H, Wo=W, kh=k, kw=k, stride=1, pt=k // 2,
               pl=k // 2, filt=filt, sums=sums)
-    g.q = Quant(zx, 128, 128, 1 << 20, 30, 0, 255, 1000)
+    g.q = Quant(zx, 128, 128, 1 << 20, 30, 0, 255, 1000, 1 << 22)
     return g
 
 

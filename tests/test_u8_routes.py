@@ -14,7 +14,7 @@ def tiles():
     def call(N, Ci, Co, H, W, kh, kw, s, pad, sums=0x1000, out=0x1000, zx=100, amax=1000):
         Ho, Wo = (H + pad[0] + pad[1] - kh) // s + 1, (W + pad[2] + pad[3] - kw) // s + 1
         geom = (C.c_int * 14)(N, H, W, Ho, Wo, Ci, Co, 16, 16, kh, kw, s, pad[0], pad[2])
-        quant = (C.c_int * 8)(zx, 128, 128, 1 << 20, 30, 0, 255, amax)
+        quant = (C.c_int * 9)(zx, 128, 128, 1 << 20, 30, 0, 255, amax, 1 << 22)          # QuantParams
         return f(geom, quant, C.c_void_p(sums), C.c_void_p(out))
     return call
 
