@@ -69,6 +69,7 @@ __device__ __forceinline__ FastDiv fastdiv_at(const __attribute__((address_space
     return r;
 }
 
+// STREAM: see streams()
 template <int WM, int WN, int WVM, int WVN, int CORR, bool STREAM>
 __global__ void __launch_bounds__(256, WM * WN >= 16 ? 2 : WM * WN >= 8 ? 3 : 4) conv_u8_tile(QTileArgs a)
 {
@@ -77,6 +78,7 @@ __global__ void __launch_bounds__(256, WM * WN >= 16 ? 2 : WM * WN >= 8 ? 3 : 4)
     constexpr int ROUNDS = tile_rounds(TM);
     static_assert(WVM * WVN == 4, "four waves");
     constexpr bool use_s = CORR == 1;
+    static_assert(!STREAM || WM * WN % 4 == 0, "words of a block are not streamed");
 
     extern __shared__ intx4 lds[];
     int *tapoff = reinterpret_cast<int *>(lds);
@@ -430,6 +432,14 @@ bool better_in_registers(const LayerGeom &g, const Plan &pl)
     return here >= there;
 }
 
+// Outputs of 4 MB and more are stored non-temporally: 0.94 to 1.0 of the time over 27 random layers (64 channels 56 x 56 x 64 images
+// 16.6 -> 15.6 us, 128 channels 28 x 28 x 64 15.1 -> 14.8); smaller ones 0.97 to 1.06. That is by the tiles whose waves write whole
+// 16-byte blocks; the two smallest ones (5 and 9), which write a word of a block per lane, store through the cache.
+bool streams(const Tile &t, const LayerGeom &g)
+{
+    return t.wm * t.wn % 4 == 0 && (size_t)g.N * g.Co * g.Ho * g.Wo >= (4u << 20);
+}
+
 }  // namespace
 
 bool conv_u8_tile_eligible(const LayerGeom &g, const QuantParams &q, const int *filt_sums, const void *out)
@@ -437,6 +447,12 @@ bool conv_u8_tile_eligible(const LayerGeom &g, const QuantParams &q, const int *
     if (((uintptr_t)out & 15u) != 0 || q.amax <= 0 || (!filt_sums && q.zx != 128)) return false;
     const Plan pl = plan_tile(g);
     return pl.tile >= 0 && !better_in_registers(g, pl);
+}
+
+TileForm conv_u8_tile_form(const LayerGeom &g)
+{
+    const Plan pl = plan_tile(g);
+    return {pl.tile, pl.tile >= 0 && streams(kTiles[pl.tile], g)};
 }
 
 hipError_t launch_conv_u8_tile(const unsigned char *in, const unsigned char *filt, unsigned char *out, const LayerGeom &g,
@@ -463,15 +479,13 @@ hipError_t launch_conv_u8_tile(const unsigned char *in, const unsigned char *fil
     a.dStrips = make_fastdiv(a.strips); a.dCt = make_fastdiv(a.n_cot); a.dkw = make_fastdiv(a.kw);
     a.q = q;
     const dim3 grid((unsigned)((a.M + tm - 1) / tm * a.n_cot));
-    // Outputs of 4 MB and more are stored non-temporally: 0.94 to 1.0 of the time over 27 random layers (64 channels 56 x 56 x 64 images
-    // 16.6 -> 15.6 us, 128 channels 28 x 28 x 64 15.1 -> 14.8); smaller ones 0.97 to 1.06.
-    const bool stream = a.out_bytes >= (4u << 20);
+    const bool stream = streams(t, g);
 #define SMALL_TILE_CASE(I_, M_, N_, VM_, VN_)                                                   \
     case I_:                                                                                    \
         if (!stream && corr == 0) return run<conv_u8_tile<M_, N_, VM_, VN_, 0, false>>(grid, pl.lds, s, a);  \
         if (!stream) return run<conv_u8_tile<M_, N_, VM_, VN_, 1, false>>(grid, pl.lds, s, a);  \
-        if (corr == 0) return run<conv_u8_tile<M_, N_, VM_, VN_, 0, true>>(grid, pl.lds, s, a); \
-        return run<conv_u8_tile<M_, N_, VM_, VN_, 1, true>>(grid, pl.lds, s, a);
+        if (corr == 0) return run<conv_u8_tile<M_, N_, VM_, VN_, 0, M_ * N_ % 4 == 0>>(grid, pl.lds, s, a); \
+        return run<conv_u8_tile<M_, N_, VM_, VN_, 1, M_ * N_ % 4 == 0>>(grid, pl.lds, s, a);
     switch (pl.tile) {
         SMALL_TILE_CASE(0, 4, 4, 4, 1)
         SMALL_TILE_CASE(1, 4, 4, 2, 2)

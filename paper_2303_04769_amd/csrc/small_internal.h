@@ -381,6 +381,8 @@ hipError_t launch_conv_u8(const unsigned char *in, const unsigned char *filt, un
 // ... windows of more than one pixel through LDS tiles (conv_u8_tile.hip), where conv_u8_uses_mfma holds; filt_sums must
 // be given unless q.zx is 128, q.amax > 0
 bool conv_u8_tile_eligible(const LayerGeom &g, const QuantParams &q, const int *filt_sums, const void *out);
+struct TileForm { int tile; bool stream; };            // which tile (-1: none has room), and whether its output is stored non-temporally
+TileForm conv_u8_tile_form(const LayerGeom &g);
 hipError_t launch_conv_u8_tile(const unsigned char *in, const unsigned char *filt, unsigned char *out, const LayerGeom &g,
                                const QuantParams &q, const int *filt_sums, hipStream_t s);
 // ... pointwise on at most 256 channels with much output, every pixel read once for up to 40 output blocks (conv_u8_pw.hip)

@@ -209,9 +209,17 @@ def test_conv_pointwise_walk_streamed(N, Ci, Co, H, W, zx, zw):
     test_conv_pointwise_walk(N, Ci, Co, H, W, 1, zx, zw, True)
 
 
-@pytest.mark.parametrize("N,Ci,Co,H,W,k", [(65, 64, 80, 31, 29, 3), (129, 48, 32, 33, 35, 3), (257, 128, 128, 13, 11, 3), (66, 48, 16, 64, 65, 5)])
+STREAMED_TILE_CASES = {        # tile: N, Ci, Co, H, W, k
+    0: (56, 96, 48, 45, 39, 2), 1: (220, 48, 96, 4, 69, 3), 2: (182, 48, 128, 4, 53, 3), 3: (110, 64, 208, 4, 62, 3), 4: (143, 64, 144, 6, 34, 5),
+    6: (65, 64, 80, 31, 29, 3), 7: (926, 48, 32, 4, 38, 3), 8: (745, 16, 16, 16, 25, 5),
+}
+
+
+@pytest.mark.parametrize("N,Ci,Co,H,W,k", list(STREAMED_TILE_CASES.values()) +
+                         [(129, 48, 32, 33, 35, 3), (257, 128, 128, 13, 11, 3), (66, 48, 16, 64, 65, 5)])
 def test_conv_tiles_streamed(N, Ci, Co, H, W, k):
-    """Outputs of 4 MB and more through the LDS tiles, stored non-temporally."""
+    """Outputs of 4 MB and more through the LDS tiles: every tile that stores them non-temporally (the last case is one of a tile
+    that does not)."""
     assert N * Co * H * W >= 4 << 20
     p = k // 2
     r = _rng(24)

@@ -19,6 +19,23 @@ def tiles():
     return call
 
 
+@pytest.fixture(scope="module")
+def tile_form():
+    """(tile, streamed) of a layer that conv_u8_tile takes."""
+    from paper_2303_04769_amd import binding
+
+    class Form(C.Structure):
+        _fields_ = [("tile", C.c_int), ("stream", C.c_bool)]
+    f = binding.load()["_ZN5small17conv_u8_tile_formERKNS_9LayerGeomE"]
+    f.restype = Form
+
+    def call(N, Ci, Co, H, W, kh, kw, s, pad, *_):
+        Ho, Wo = (H + pad[0] + pad[1] - kh) // s + 1, (W + pad[2] + pad[3] - kw) // s + 1
+        form = f((C.c_int * 14)(N, H, W, Ho, Wo, Ci, Co, 16, 16, kh, kw, s, pad[0], pad[2]))
+        return form.tile, form.stream, N * Co * Ho * Wo
+    return call
+
+
 P1 = (1, 1, 1, 1)
 
 
@@ -46,3 +63,20 @@ def test_parity_cases_reach_the_tile_kernel(tiles):
     from test_gpu_u8 import TILE_CASES, TILE_CASES_ELSEWHERE
     for case in TILE_CASES:
         assert tiles(*case[:9]) == (case not in TILE_CASES_ELSEWHERE), case
+
+
+def test_streamed_tiles(tile_form, tiles):
+    """Outputs of 4 MB and more are streamed, but by tiles 5 and 9, which write words of a block; the parity test of streamed
+    outputs reaches every one that does."""
+    import random
+    from test_gpu_u8 import STREAMED_TILE_CASES
+    rng = random.Random(3)
+    for _ in range(4000):
+        H, W, k = rng.randrange(1, 60), rng.randrange(1, 60), rng.choice([2, 3, 5])
+        layer = (int(2 ** rng.uniform(0, 13)), 16 * rng.randrange(1, 20), 16 * rng.randrange(1, 20), H + k, W + k, k, k, 1, (k // 2,) * 4)
+        tile, stream, out_bytes = tile_form(*layer)
+        assert stream == (tile not in (-1, 5, 9) and out_bytes >= 4 << 20), (layer, tile)
+    assert sorted(STREAMED_TILE_CASES) == [0, 1, 2, 3, 4, 6, 7, 8]
+    for tile, (N, Ci, Co, H, W, k) in STREAMED_TILE_CASES.items():
+        layer = (N, Ci, Co, H, W, k, k, 1, (k // 2,) * 4)
+        assert tiles(*layer) and tile_form(*layer)[:2] == (tile, True), tile
