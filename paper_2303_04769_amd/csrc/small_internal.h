@@ -414,6 +414,8 @@ bool pool_dpp_u8_eligible(const LayerGeom &g, int mode, const void *in, const vo
 hipError_t launch_pool_dpp_u8(const unsigned char *in, unsigned char *out, const LayerGeom &g, hipStream_t s);
 // quantized depthwise 3x3, stride 1, padding 1, 16-byte blocks, 4-byte aligned pointers (window_dpp_u8.hip)
 bool dw_dpp_u8_eligible(const LayerGeom &g, const QuantParams &q, const void *in, const void *filt, const void *out);
+struct DwForm { long waves; int rows; bool fold; };      // of the launch: strips of that many rows; strips, not images, side by side
+DwForm dw_dpp_u8_form(const LayerGeom &g);
 hipError_t launch_dw_dpp_u8(const unsigned char *in, const unsigned char *filt, unsigned char *out, const LayerGeom &g,
                             const QuantParams &q, hipStream_t s);
 // y = clamp(zy + floor(((a - za) mult_a + (b - zb) mult_b + 2^(shift-1)) / 2^shift), lo, hi); out may be a or b

@@ -24,12 +24,13 @@ struct DppU8Args {
     int n_planes;          // N * nCb
     int nb;                // bands per row
     int sp;                // row strips per plane
-    int n_units;           // image groups * nCb * sp * nb: one per wave
-    int ppb;               // planes per band of 16 lanes
+    int n_units;           // image groups * nCb * sp * nb (FOLD: strip groups * nCb): one per wave
+    int ppb;               // planes (FOLD: strips) per band of 16 lanes
     unsigned bytes;        // of the input = of the output tensor (< 2^31)
     FastDiv by_nb, by_sp, by_nCb, by_W;
     int cached;            // CACHED (of HIGH only): stores through the cache, not non-temporal
     QuantParams q;
+    int nz;                // NZ where that is kAnyNZ
 };
 
 // ROWS: output rows per strip (two more input rows prime the window), at most; a wave computes that many whatever its strip has.
@@ -56,8 +57,10 @@ typedef int intx4 __attribute__((ext_vector_type(4)));
 // (about 0.05 us a wave): the smallest layers take as long as with dot products. Over 500 random layers with all of this and the
 // rules for rows and stores below, and the requantization by the high word: 0.80 of the time before, none longer.
 // The filter operand serves all pixels of the wave: planes side by side in a band (SEG 0, 8) are of one channel block and of
-// consecutive images.
-template <int SEG, int NZ, int ROWS, bool HIGH, bool CACHED>
+// consecutive images. FOLD: of too few images for that, a band takes strips instead, those of one channel block's planes in order,
+// and each lane has its own rows.
+constexpr int kAnyNZ = -1;
+template <int SEG, int NZ, int ROWS, bool HIGH, bool CACHED, bool FOLD>
 __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
 {
     constexpr int kSteps = ROWS + 2;
@@ -67,11 +70,11 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
     if (unit >= a.n_units) return;
     const int l = lane & 15, q = lane >> 4;
 
-    const int t = a.by_nb.div(unit), band = unit - t * a.nb;
-    const int pg = a.by_sp.div(t), strip = t - pg * a.sp;
-    const int r0 = strip * ROWS, r1 = min(r0 + ROWS, a.H);                             // output rows r0 .. r1 - 1
-    const int n_in = r1 - r0 + 2;
-    const int ig = a.by_nCb.div(pg), cb = pg - ig * a.nCb;                             // images ig * ppb .., channel block
+    const int t = FOLD ? unit : a.by_nb.div(unit), band = FOLD ? 0 : unit - t * a.nb;
+    const int pg = FOLD ? unit : a.by_sp.div(t);
+    const int strip = FOLD ? 0 : t - pg * a.sp;
+    int r0 = strip * ROWS, r1 = min(r0 + ROWS, a.H);                                   // output rows r0 .. r1 - 1
+    const int ig = a.by_nCb.div(pg), cb = pg - ig * a.nCb;                             // images (strips) ig * ppb .., channel block
 
     int image, x;
     bool lane_used = true;
@@ -87,6 +90,13 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
         x = l - pi * a.W;
         lane_used = pi < a.ppb;
     }
+    if (FOLD) {
+        const int slot = image;
+        image = a.by_sp.div(slot);
+        r0 = (slot - image * a.sp) * ROWS;
+        r1 = min(r0 + ROWS, a.H);
+    }
+    const int n_in = r1 - r0 + 2;
     const int plane = image * a.nCb + cb;
     const bool col_in = lane_used & (x >= 0) & (x < a.W) & (plane < a.n_planes);
     const bool col_out = col_in & (SEG != 16 || (l >= 1 && l <= 14));
@@ -120,7 +130,8 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
         for (int k = 0; k < 3; ++k) w[r][k] = (int)((taps[3 * r + k] ^ flip) & mine);
         w[r][3] = 0;
     }
-    const int zw4 = (int)((unsigned)((NZ == 2 ? zb / 2 : zb) & 255) * 0x01010101u & mine);
+    const int nz = NZ == kAnyNZ ? a.nz : NZ;
+    const int zw4 = (int)((unsigned)((nz == 2 ? zb / 2 : zb) & 255) * 0x01010101u & mine);
     const intx4 wz = {zw4, zw4, zw4, 0};
     intx4 cst = {0, 0, 0, 0};
     if (za != 0) {
@@ -151,9 +162,10 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
 #pragma unroll
         for (int r = 0; r < 3; ++r) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[r], row[j - 2 + r], acc, 0, 0, 0);
 #pragma unroll
-        for (int z = 0; z < NZ; ++z)
+        for (int z = 0; z < (NZ == kAnyNZ ? 2 : NZ); ++z)
+            if (NZ != kAnyNZ || z < nz)
 #pragma unroll
-            for (int r = 0; r < 3; ++r) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(wz, row[j - 2 + r], acc, 0, 0, 0);
+                for (int r = 0; r < 3; ++r) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(wz, row[j - 2 + r], acc, 0, 0, 0);
         unsigned y = 0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) y |= (unsigned)requant_code<HIGH>(acc[c], a.q, addend) << (8 * c);
@@ -162,31 +174,59 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
     }
 }
 
+// How a layer is cut: bands of rows (SEG), strips of rows, and what the lanes of a band hold. Images (fold = false) leave lanes idle
+// where there are fewer of them than a band holds planes, 15 of 16 for one image of one-pixel rows; strips do not, but a lane's own
+// rows cost vector compares. So strips where images fill at most half of the lanes and their shortest strips make more waves than the
+// chip has SIMDs. us by images / by strips: one image of 4096 channels 600x1 17.4 / 4.1, 512 2000x2 7.9 / 4.2, 4096 64x5 4.2 / 3.3, 16
+// 30000x7 5.1 / 4.2, eight images of 512 300x1 4.4 / 3.5; below that line 0.87 to 1.06 of the time: 128 channels 40x4 2.70 / 2.85. (With
+// planes of any channel block side by side, which dot products by the vector unit allowed: 7.0 for the first, 5.7 for the second.)
+struct Plan { int seg, ppb, nb, rows, sp; bool fold; long units; };
+
 // Rows per strip: a wave costs about as much as 5 rows and its rows, also those that its strip lacks; up to eight waves a SIMD
 // the busiest one counts, beyond that their average, and one more wave's time passes before and after. Over 500 random layers the
 // rows taken cost 0.4 % more than the best of 3, 5, 7 and 9 each time; 3 alone 5 %, 5 6 %, 7 9 %, 9 15 %, 13 26 % (13 is the best
 // for one layer in ten, by 0.3 % of the whole). us with 7 / with the one taken: one image of 128 channels 2x2 2.77 / 2.41 with 3,
 // 8 of 96 7x7 3.22 / 2.83 with 3, 16 of 64 13x4 3.49 / 2.88 with 3.
-int strip_rows(const LayerGeom &g, long planes_by_bands)
+Plan plan_dw(const LayerGeom &g)
 {
+    Plan pl;
+    pl.seg = g.W <= 5 ? 0 : g.W <= 7 ? 8 : 16;
+    pl.ppb = pl.seg == 0 ? 16 / g.W : pl.seg == 8 ? 2 : 1;
+    pl.nb = pl.seg == 16 ? (g.W + 13) / 14 : 1;
+    pl.fold = false;
+    const long nCb = g.Ci / 16;
     const double simds = 4.0 * device_cus();
+    auto units = [&](int rows) {
+        const long sp = (g.H + rows - 1) / rows;
+        return pl.fold ? (g.N * sp + pl.ppb - 1) / pl.ppb * nCb : ((long)g.N + pl.ppb - 1) / pl.ppb * nCb * sp * pl.nb;
+    };
+    pl.fold = 2 * g.N <= pl.ppb && units(3) > simds;
     auto cost = [&](int rows) {
-        const long waves = planes_by_bands * ((g.H + rows - 1) / rows), rounds = (waves + (long)simds - 1) / (long)simds;
+        const long waves = units(rows), rounds = (waves + (long)simds - 1) / (long)simds;
         return ((rounds <= 8 ? (double)rounds : waves / simds) + 1) * (5 + rows);
     };
-    int best = 3;
+    pl.rows = 3;
     for (int rows = 5; rows <= 9; rows += 2)
-        if (cost(rows) < cost(best)) best = rows;
-    return best;
+        if (cost(rows) < cost(pl.rows)) pl.rows = rows;
+    pl.sp = (g.H + pl.rows - 1) / pl.rows;
+    pl.units = units(pl.rows);
+    return pl;
 }
 
 template <int ROWS, bool HIGH, bool CACHED, int NZ>
 void go3(const DppU8Args &a, int seg, hipStream_t s)
 {
     const dim3 grid((unsigned)((a.n_units + 3) / 4)), block(256);
-    if (seg == 0) hipLaunchKernelGGL((dw16_dpp_u8<0, NZ, ROWS, HIGH, CACHED>), grid, block, 0, s, a);
-    else if (seg == 8) hipLaunchKernelGGL((dw16_dpp_u8<8, NZ, ROWS, HIGH, CACHED>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((dw16_dpp_u8<16, NZ, ROWS, HIGH, CACHED>), grid, block, 0, s, a);
+    if (seg == 0) hipLaunchKernelGGL((dw16_dpp_u8<0, NZ, ROWS, HIGH, CACHED, false>), grid, block, 0, s, a);
+    else if (seg == 8) hipLaunchKernelGGL((dw16_dpp_u8<8, NZ, ROWS, HIGH, CACHED, false>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((dw16_dpp_u8<16, NZ, ROWS, HIGH, CACHED, false>), grid, block, 0, s, a);
+}
+template <int ROWS, bool HIGH>
+void go_fold(const DppU8Args &a, int seg, hipStream_t s)
+{
+    const dim3 grid((unsigned)((a.n_units + 3) / 4)), block(256);
+    if (seg == 0) hipLaunchKernelGGL((dw16_dpp_u8<0, kAnyNZ, ROWS, HIGH, true, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((dw16_dpp_u8<8, kAnyNZ, ROWS, HIGH, true, true>), grid, block, 0, s, a);
 }
 template <int ROWS, bool HIGH, bool CACHED>
 void go2(const DppU8Args &a, int seg, hipStream_t s)
@@ -196,9 +236,11 @@ void go2(const DppU8Args &a, int seg, hipStream_t s)
     else go3<ROWS, HIGH, CACHED, 1>(a, seg, s);
 }
 template <int ROWS>
-void go(const DppU8Args &a, int seg, hipStream_t s)
+void go(const DppU8Args &a, int seg, bool fold, hipStream_t s)
 {
-    if (a.q.mult32 < 0) go2<ROWS, false, false>(a, seg, s);
+    if (fold && a.q.mult32 < 0) go_fold<ROWS, false>(a, seg, s);
+    else if (fold) go_fold<ROWS, true>(a, seg, s);
+    else if (a.q.mult32 < 0) go2<ROWS, false, false>(a, seg, s);
     else if (a.cached) go2<ROWS, true, true>(a, seg, s);
     else go2<ROWS, true, false>(a, seg, s);
 }
@@ -214,34 +256,37 @@ bool dw_dpp_u8_eligible(const LayerGeom &g, const QuantParams &q, const void *in
     return (size_t)g.N * g.Ci * g.H * g.W < ((size_t)1 << 31);
 }
 
+DwForm dw_dpp_u8_form(const LayerGeom &g)
+{
+    const Plan pl = plan_dw(g);
+    return {pl.units, pl.rows, pl.fold};
+}
+
 hipError_t launch_dw_dpp_u8(const unsigned char *in, const unsigned char *filt, unsigned char *out, const LayerGeom &g,
                             const QuantParams &q, hipStream_t s)
 {
-    DppU8Args a;
+    DppU8Args a = {};
     a.in = in; a.filt = filt; a.out = out;
     a.H = g.H; a.W = g.W; a.nCb = g.Ci / 16;
     a.n_planes = g.N * a.nCb;
     a.bytes = (unsigned)((size_t)g.N * g.Ci * g.H * g.W);
     a.q = q;
-    const int seg = g.W <= 5 ? 0 : g.W <= 7 ? 8 : 16;
-    a.ppb = seg == 0 ? 16 / g.W : seg == 8 ? 2 : 1;
-    a.nb = seg == 16 ? (g.W + 13) / 14 : 1;
+    const Plan pl = plan_dw(g);
+    a.ppb = pl.ppb; a.nb = pl.nb; a.sp = pl.sp;
+    a.n_units = (int)pl.units;
+    a.nz = q.zw == 128 ? 0 : q.zw == 0 ? 2 : 1;
     // Outputs of less than 4 MB stay in the cache, 3 to 6 % faster on average; past that the non-temporal stores are (8 to 16 MB: 8 %),
     // except to planes of one pixel a row, which a wave writes in pieces of 16 bytes at as many images: half a cache line each
     // (2000 images of 64 channels 86x1: 22.5 us non-temporal, 13.7). (A branch on it at each store costs 4 to 8 %.)
     a.cached = a.bytes < (4u << 20) || g.W == 1;
-    const long groups = ((long)g.N + a.ppb - 1) / a.ppb * a.nCb;
-    const int rows = strip_rows(g, groups * a.nb);
-    a.sp = (g.H + rows - 1) / rows;
-    a.n_units = (int)(groups * a.sp * a.nb);
     a.by_nb = make_fastdiv(a.nb);
     a.by_sp = make_fastdiv(a.sp);
     a.by_nCb = make_fastdiv(a.nCb);
     a.by_W = make_fastdiv(g.W);
-    if (rows == 3) go<3>(a, seg, s);
-    else if (rows == 5) go<5>(a, seg, s);
-    else if (rows == 7) go<7>(a, seg, s);
-    else go<9>(a, seg, s);
+    if (pl.rows == 3) go<3>(a, pl.seg, pl.fold, s);
+    else if (pl.rows == 5) go<5>(a, pl.seg, pl.fold, s);
+    else if (pl.rows == 7) go<7>(a, pl.seg, pl.fold, s);
+    else go<9>(a, pl.seg, pl.fold, s);
     return hipGetLastError();
 }
 

@@ -698,6 +698,36 @@ def test_depthwise_matrix_forms(shape, zw):
     test_depthwise_lane_shift((N, C, H, W, (zw * 7 + H) % 256, zw))
 
 
+FOLDED_DW_CASES = [  # N, C, H, W: strips of a plane side by side
+    (1, 16, 3100, 1), (8, 64, 770, 1), (1, 4096, 13, 1), (3, 528, 101, 2), (4, 2064, 25, 2), (2, 16, 3077, 3), (1, 1040, 49, 4), (1, 8192, 7, 6),  # of 3 rows
+    (1, 1024, 49, 7), (3, 5600, 16, 2), (1, 5520, 19, 5), (1, 5872, 13, 6), (1, 16, 30001, 7),     # 3, 5
+    (1, 7088, 61, 3), (1, 4752, 55, 5), (1, 4880, 37, 6), (1, 1520, 127, 7),                       # 7
+    (7, 5568, 34, 1), (2, 5872, 37, 3), (1, 4352, 44, 6), (1, 4128, 49, 7),                        # 9
+]
+
+
+@pytest.mark.parametrize("zw", [0, 1, 128, 255])
+@pytest.mark.parametrize("shape", FOLDED_DW_CASES)
+def test_depthwise_strips_side_by_side(shape, zw):
+    """Narrow planes of few images: every number of pixels a row with strips of every length, the last strip and the last band not
+    full, several images in a band: exact."""
+    N, C, H, W = shape
+    test_depthwise_lane_shift((N, C, H, W, (zw * 7 + H) % 256, zw))
+    _dw_scale_above_a_half(shape, 130, zw)
+
+
+def _dw_scale_above_a_half(shape, zx, zw):
+    """A scale of a half and a little: the other form of the requantization."""
+    N, C, H, W = shape
+    r = _rng(35)
+    x, w = WL.u8_codes(r, (N, C, H, W)), WL.u8_codes(r, (C, 1, 3, 3))
+    q = Q.Quant(zx=zx, zw=zw, zy=77, mult=(1 << 30) + 1, shift=31, lo=3, hi=250)
+    ref = Q.dwconv2d(x, w, 1, (1, 1, 1, 1), q)
+    g = Guarded8(ref.size)
+    S.small_dwconv2d_u8(dev8(Q.pack(x, 16)), dev8(Q.pack_dw_filter(w, 16)), g.t, N, C, H, W, 3, 3, 1, (1, 1, 1, 1), 16, q)
+    _same(Q.unpack(g.check(), ref.shape, 16), ref, f"dw u8 {shape}, {zx}, {zw}, a scale above a half")
+
+
 @pytest.mark.parametrize("mult,shift", [(1 << 20, 0), ((1 << 31) - 1, 0), (1, 31), (0, 5), ((1 << 31) - 1, 31), (3, 1)])
 def test_depthwise_extreme_scales(mult, shift):
     """Scales from 'everything saturates' to 'everything rounds to the zero point': whichever requantization path the

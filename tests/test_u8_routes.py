@@ -80,3 +80,39 @@ def test_streamed_tiles(tile_form, tiles):
     for tile, (N, Ci, Co, H, W, k) in STREAMED_TILE_CASES.items():
         layer = (N, Ci, Co, H, W, k, k, 1, (k // 2,) * 4)
         assert tiles(*layer) and tile_form(*layer)[:2] == (tile, True), tile
+
+
+@pytest.fixture(scope="module")
+def dw_form():
+    """(waves, rows of a strip, strips side by side) of a depthwise 3x3 layer of stride 1 padded by one."""
+    from paper_2303_04769_amd import binding
+
+    class Form(C.Structure):
+        _fields_ = [("waves", C.c_long), ("rows", C.c_int), ("fold", C.c_bool)]
+    f = binding.load()["_ZN5small14dw_dpp_u8_formERKNS_9LayerGeomE"]
+    f.restype = Form
+
+    def call(N, Ci, H, W):
+        form = f((C.c_int * 14)(N, H, W, H, W, Ci, Ci, 16, 16, 3, 3, 1, 1, 1))
+        return form.waves, form.rows, form.fold
+    return call
+
+
+@pytest.mark.parametrize("W", range(1, 8))
+def test_narrow_planes_of_few_images_fill_their_lanes(dw_form, W):
+    """The depthwise kernel puts several planes of up to seven pixels a row side by side on a wave's lanes, of consecutive images or,
+    of one or a few images, strips of the same plane: at least two fifths of the lanes have a pixel, whatever the number of images."""
+    for N in range(1, 40):
+        for Ci in (16, 512, 4096, 16384):
+            H = (1 << 25) // (N * Ci * W) // 9 * 9 + 9                     # (strips of 9 rows: layers that fill the chip)
+            waves = dw_form(N, Ci, H, W)[0]
+            assert 0.4 * waves * (16 // W if W <= 5 else 2) <= N * (Ci // 16) * (H // 9) + Ci // 16, (N, Ci, H)
+
+
+def test_parity_cases_reach_the_depthwise_forms(dw_form):
+    from test_gpu_u8 import FOLDED_DW_CASES
+    forms = [dw_form(*shape) + (shape[3] <= 5,) for shape in FOLDED_DW_CASES]
+    assert all(f[2] for f in forms)
+    assert {(f[1], f[3]) for f in forms} == {(rows, narrow) for rows in (3, 5, 7, 9) for narrow in (False, True)}
+    for shape in [(17, 16, 3100, 1), (9, 512, 300, 1), (2, 1024, 300, 6), (1, 512, 300, 8), (1, 128, 40, 4), (1, 32, 3, 1)]:
+        assert not dw_form(*shape)[2], shape
