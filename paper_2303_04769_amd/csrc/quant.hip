@@ -70,7 +70,7 @@ __device__ __forceinline__ void store_tiles_form(const QConvArgs &a, const intx4
                 // wrap-around arithmetic: the true sum fits 32 bits, the partial terms need not
                 const unsigned v = (unsigned)acc[wm][wn][r] - (unsigned)zb * (unsigned)acc_s[wm][r] -
                                    (unsigned)za * (unsigned)acc_w[wn][r] + kab;
-                packed |= (unsigned)(FORM ? requant_code<FORM == 2>((int)v, a.q, addend) : requant((int)v, a.q)) << (8 * r);
+                packed |= (unsigned)(FORM ? requant_code<FORM == 2>((int)v, a.q, addend) : requant_above((int)v, a.q)) << (8 * r);
             }
             unsigned *o = reinterpret_cast<unsigned *>(a.out + (((size_t)n * a.nCob + cob0 + wn) * a.HoWo + pix) * 16 + g * 4);
             *o = packed;
@@ -632,13 +632,15 @@ __global__ void __launch_bounds__(256) window_u8(QWindowArgs a, size_t total)
         }
     }
     unsigned packed = 0;
+    if (a.mode == 0) {
+        if constexpr (VEC == 4) packed = requant_word(acc, a.q);
+        else packed = (unsigned)requant(acc[0], a.q);
+    } else {
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) {
-        int y;
-        if (a.mode == 0) y = requant(acc[v], a.q);
-        else if (a.mode == 1) y = acc[v];
-        else y = cnt > 0 ? (acc[v] + cnt / 2) / cnt : 0;
-        packed |= (unsigned)y << (8 * v);
+        for (int v = 0; v < VEC; ++v) {
+            const int y = a.mode == 1 ? acc[v] : cnt > 0 ? (acc[v] + cnt / 2) / cnt : 0;
+            packed |= (unsigned)y << (8 * v);
+        }
     }
     unsigned char *o = a.out + i * VEC;
     if (VEC == 4) *reinterpret_cast<unsigned *>(o) = packed;
@@ -696,15 +698,14 @@ __global__ void __launch_bounds__(256) dw3x3_u8(QDw3Args a)
                 const unsigned v = img[((ih0 + ky) * a.W + iw0 + kx) * 4 & m];
                 x[ky * 3 + kx] = ((v ^ zx4) & (unsigned)m) ^ zx4;
             }
-        unsigned packed = 0;
+        int acc[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            int acc = -a.q.zx * wsum[c];
+            acc[c] = -a.q.zx * wsum[c];
 #pragma unroll
-            for (int t = 0; t < 9; ++t) acc += (int)((x[t] >> (8 * c)) & 255u) * wq[t][c];
-            packed |= (unsigned)requant(acc, a.q) << (8 * c);
+            for (int t = 0; t < 9; ++t) acc[c] += (int)((x[t] >> (8 * c)) & 255u) * wq[t][c];
         }
-        dst[(size_t)pix * 4] = packed;
+        dst[(size_t)pix * 4] = requant_word(acc, a.q);
     }
 }
 

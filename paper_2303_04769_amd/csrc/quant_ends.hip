@@ -143,7 +143,7 @@ __global__ void __launch_bounds__(256) conv_first_u8(FirstU8Args a)
 #pragma unroll
             for (int kd = 0; kd < KD; ++kd) dot = dot4(x[kd], wl[co * KD + kd], dot);
             const int acc = (int)dot - a.q.zx * sw[co] + base;
-            packed[co / 4] |= (unsigned)(FORM ? requant_code<FORM == 2>(acc, a.q, addend) : requant(acc, a.q)) << (8 * (co % 4));
+            packed[co / 4] |= (unsigned)(FORM ? requant_code<FORM == 2>(acc, a.q, addend) : requant_above(acc, a.q)) << (8 * (co % 4));
         }
     };
     if (a.q.mult32 >= 0) codes(std::integral_constant<int, 2>());

@@ -347,10 +347,9 @@ __device__ __forceinline__ int requant_code(int acc, const QuantParams &q, long 
     return clamp_code((int)(((long)acc * (long)mult + addend) >> 32), q.lo, q.hi);
 }
 
-// For any layer.
-__device__ __forceinline__ int requant(int acc, const QuantParams &q)
+// For layers with q.mult32 < 0, whatever the scale.
+__device__ __forceinline__ int requant_above(int acc, const QuantParams &q)
 {
-    if (q.mult32 >= 0) return requant_code<true>(acc, q, requant_addend<true>(q));
     if (q.amax > 0) {
         const int c = acc < -q.amax ? -q.amax : (acc > q.amax ? q.amax : acc);
         long v = (long)c * (long)q.mult;
@@ -365,6 +364,27 @@ __device__ __forceinline__ int requant(int acc, const QuantParams &q)
     v = v < q.lo ? q.lo : v;
     v = v > q.hi ? q.hi : v;
     return (int)v;
+}
+
+// For any layer: a sum, and four sums into a word of codes. (The form is chosen once for the word. Chosen at each of its codes, the
+// forms' code four times over: depthwise 5x5 stride 2, 4 images of 16 channels 58x38 7.98 us, here 7.70; 3x3 stride 2, 2 images of 96
+// 11x63 4.12 / 3.91.)
+__device__ __forceinline__ int requant(int acc, const QuantParams &q)
+{
+    return q.mult32 >= 0 ? requant_code<true>(acc, q, requant_addend<true>(q)) : requant_above(acc, q);
+}
+__device__ __forceinline__ unsigned requant_word(const int (&acc)[4], const QuantParams &q)
+{
+    unsigned y[4];
+    if (q.mult32 >= 0) {
+        const long addend = requant_addend<true>(q);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) y[c] = (unsigned)requant_code<true>(acc[c], q, addend);
+    } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) y[c] = (unsigned)requant_above(acc[c], q);
+    }
+    return y[0] | y[1] << 8 | y[2] << 16 | y[3] << 24;
 }
 
 // layout change of uint8 tensors (layout_u8.hip): plain -> blocked, or blocked -> plain with unpack

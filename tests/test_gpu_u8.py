@@ -766,6 +766,21 @@ def test_requantization_on_both_sides_of_a_half(mult, shift):
             _same(Q.unpack(g.check(), ref.shape, 16), ref, f"dw stride {s}, {mult} / 2^{shift}, {zx}, {zw}")
 
 
+@pytest.mark.parametrize("mult,shift", HALF_SCALES + [((1 << 31) - 1, 0), (0, 7)])
+def test_window_requantization(mult, shift):
+    """The depthwise kernels that choose the form of the requantization per word of codes, or per code (blocks that are no
+    multiple of four channels), for scales of every form. Exact."""
+    r = _rng(36)
+    q = Q.Quant(zx=11, zw=247, zy=77, mult=mult, shift=shift, lo=3, hi=250)
+    for C, Cb, k, s in ((32, 16, 5, 2), (32, 16, 3, 2), (6, 3, 5, 1), (8, 4, 3, 1)):
+        x, w, pad = WL.u8_codes(r, (3, C, 9, 11)), WL.u8_codes(r, (C, 1, k, k)), (k // 2,) * 4
+        x[0], w[:2] = 255, np.array([0, 255], dtype=np.uint8).reshape(2, 1, 1, 1)
+        ref = Q.dwconv2d(x, w, s, pad, q)
+        g = Guarded8(ref.size)
+        S.small_dwconv2d_u8(dev8(Q.pack(x, Cb)), dev8(Q.pack_dw_filter(w, Cb)), g.t, 3, C, 9, 11, k, k, s, pad, Cb, q)
+        _same(Q.unpack(g.check(), ref.shape, Cb), ref, f"dw {C}/{Cb} {k}x{k} stride {s}, {mult} / 2^{shift}")
+
+
 @pytest.mark.parametrize("mult,shift", [(1 << 30, 31), (3, 2), ((1 << 30) - 1, 31)])
 def test_network_resident_scales_of_a_half_and_more(mult, shift):
     """Layers of an image-resident run at such scales, others below beside them."""
