@@ -1,4 +1,5 @@
 """The extension in front of the ctypes binding: takes the plain calls, leaves everything else, refuses what ctypes' path refuses."""
+import inspect
 import runpy
 import sysconfig
 
@@ -58,7 +59,7 @@ def _forms(name, args):
             yield "a padding of five", [a + (1,) if j == k else b for j, b in enumerate(args)]
         if isinstance(a, B.small_quant):
             yield "a record of another type", [object() if j == k else b for j, b in enumerate(args)]
-    yield "a parameter", [torch.nn.Buffer(args[0]) if hasattr(torch.nn, "Buffer") else args[0].as_subclass(type("T", (torch.Tensor,), {}))] + args[1:]
+    yield "a tensor of a subclass", [args[0].as_subclass(type("T", (torch.Tensor,), {}))] + args[1:]
 
 
 @pytest.mark.parametrize("name", sorted(CALLS))
@@ -73,8 +74,7 @@ def test_only_plain_calls_are_taken(name):
         getattr(S, "small_" + name)(*args)
     assert fast(*args, object()) is None and fast(*args) is None and fast(*args, None, None) is None
     for what, other in _forms(name, args):
-        if what != "a parameter" or type(other[0]) not in (torch.Tensor, torch.nn.Parameter):
-            assert fast(*other, None) is None, what
+        assert fast(*other, None) is None, what
 
 
 @pytest.mark.parametrize("why", ["no compiler", "a file that does not load"])
@@ -151,23 +151,28 @@ def test_no_half_written_file_is_in_place(monkeypatch, tmp_path, fails):
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", sorted(CALLS))
 def test_both_routes_agree(name):
-    """The extension, the ctypes path (a stream given) and the keyword form: the same bytes; a type or stride it does not take is
-    refused; an error of the library has the same code on both routes; a side stream is taken as the current one."""
+    """The extension, the ctypes path (a stream given) and keywords: the same bytes; on a side stream that is still to write the
+    call's input, the call waits for it; a type or stride it does not take is refused; an error of the library has the same code on
+    both routes."""
     args, out = _arguments(name, "cuda:0")
     call = getattr(S, "small_" + name)
     want = None
-    for route in ("extension", "ctypes", "side"):
+    for route in ("extension", "ctypes", "keywords") + 4 * ("side",):      # (a stream may share the default one's hardware queue)
         args[out] = torch.zeros_like(args[out])
         if route == "extension":
             assert getattr(B._fast(), name)(*args, None) == 0
         elif route == "ctypes":
             call(*args, stream=torch.cuda.current_stream())
+        elif route == "keywords":
+            call(**dict(zip(inspect.signature(call).parameters, args)))
         else:
-            side = torch.cuda.Stream()
-            side.wait_stream(torch.cuda.current_stream())
+            data, side = args[0].clone(), torch.cuda.Stream()
+            args[0].zero_()
+            torch.cuda.synchronize()
             with torch.cuda.stream(side):
+                torch.cuda._sleep(10_000_000)            # some milliseconds: a call on another stream reads zeros
+                args[0].copy_(data)
                 call(*args)
-            torch.cuda.current_stream().wait_stream(side)
         torch.cuda.synchronize()
         got = args[out].cpu()
         want = got if want is None else want

@@ -693,9 +693,10 @@ def test_depthwise_lane_shift_strips(case):
 ])
 def test_depthwise_matrix_forms(shape, zw):
     """Every strip length with every number of planes per band, the last image group not full, with the products by the
-    filter's zero point left out (128), once and twice (0, whose 128 is no signed byte): exact."""
+    filter's zero point left out (128), once and twice (0, whose 128 is no signed byte), for scales on both sides of a half: exact."""
     N, C, H, W = shape
     test_depthwise_lane_shift((N, C, H, W, (zw * 7 + H) % 256, zw))
+    _dw_scale_above_a_half(shape, 130, zw)
 
 
 FOLDED_DW_CASES = [  # N, C, H, W: strips of a plane side by side
@@ -741,6 +742,7 @@ def test_depthwise_extreme_scales(mult, shift):
     _same(Q.unpack(g.check(), ref.shape, 16), ref, f"dw u8 scale {mult} / 2^{shift}")
 
 
+POINTWISE_AT_A_HALF = (16, 64, 48, 31, 61)         # N, Ci, Co, H, W
 HALF_SCALES = [((1 << 30) - 1, 31), (1 << 30, 31), ((1 << 30) + 1, 31), (1, 1), (1, 2), (2, 2), ((1 << 29) - 1, 30), ((1 << 31) - 1, 31), (12345, 31)]
 
 
@@ -752,7 +754,7 @@ def test_requantization_on_both_sides_of_a_half(mult, shift):
     for zx, zw in ((0, 255), (255, 255), (131, 120)):
         q = Q.Quant(zx=zx, zw=zw, zy=77, mult=mult, shift=shift, lo=3, hi=250)
         for N, Ci, Co, H, W, k, s, sums, Cib, Cob in ((3, 64, 32, 11, 9, 3, 1, True, 16, 16), (2, 32, 16, 8, 8, 3, 1, False, 16, 16),
-                                                      (9, 64, 48, 31, 61, 1, 1, True, 16, 16), (2, 3, 16, 9, 9, 3, 1, False, 3, 16)):
+                                                      POINTWISE_AT_A_HALF + (1, 1, True, 16, 16), (2, 3, 16, 9, 9, 3, 1, False, 3, 16)):
             x, w = WL.u8_codes(r, (N, Ci, H, W)), WL.u8_codes(r, (Co, Ci, k, k))
             x[0], w[:8] = 255, np.where(np.arange(8) % 2, 255, 0).astype(np.uint8).reshape(8, 1, 1, 1)
             pad = (k // 2,) * 4
@@ -764,6 +766,24 @@ def test_requantization_on_both_sides_of_a_half(mult, shift):
             g = Guarded8(ref.size)
             S.small_dwconv2d_u8(dev8(Q.pack(x, 16)), dev8(Q.pack_dw_filter(w, 16)), g.t, 3, 32, 9, 20, 3, 3, s, (1, 1, 1, 1), 16, q)
             _same(Q.unpack(g.check(), ref.shape, 16), ref, f"dw stride {s}, {mult} / 2^{shift}, {zx}, {zw}")
+
+
+STREAMED_AT_A_HALF = [  # N, Ci, Co, H, W, k, zx, zw
+    (257, 16, 64, 29, 23, 1, 7, 140), (65, 256, 176, 31, 31, 1, 3, 128), (65, 64, 80, 31, 29, 3, 140, 119), (745, 16, 16, 16, 25, 5, 128, 128),
+]
+
+
+@pytest.mark.parametrize("case", STREAMED_AT_A_HALF)
+def test_requantization_above_a_half_streamed(case):
+    """Pointwise layers and tiles whose output is stored non-temporally, for a scale of a half and a little."""
+    N, Ci, Co, H, W, k, zx, zw = case
+    r = _rng(37)
+    x, w, pad = WL.u8_codes(r, (N, Ci, H, W)), WL.u8_codes(r, (Co, Ci, k, k)), (k // 2,) * 4
+    w[:8] = np.where(np.arange(8) % 2, 255, 0).astype(np.uint8).reshape(8, 1, 1, 1)
+    q = Q.Quant(zx=zx, zw=zw, zy=77, mult=(1 << 30) + 1, shift=31, lo=3, hi=250)
+    got = _conv(x, w, 1, pad, q, 16, 16, with_sums=True)
+    for n in (0, N // 2, N - 1):
+        _same(got[n:n + 1], Q.conv2d(x[n:n + 1], w, 1, pad, q), f"conv u8 {case} image {n}")
 
 
 @pytest.mark.parametrize("mult,shift", HALF_SCALES + [((1 << 31) - 1, 0), (0, 7)])

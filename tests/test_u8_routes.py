@@ -82,6 +82,26 @@ def test_streamed_tiles(tile_form, tiles):
         assert tiles(*layer) and tile_form(*layer)[:2] == (tile, True), tile
 
 
+def test_parity_cases_reach_the_pointwise_walk(tiles, tile_form):
+    """Every row of the walk's own test, the row of the test of scales, and the streamed rows of scales above a half."""
+    from paper_2303_04769_amd import binding
+    from test_gpu_u8 import POINTWISE_AT_A_HALF, STREAMED_AT_A_HALF, test_conv_pointwise_walk, test_conv_pointwise_walk_streamed
+    f = binding.load()["_ZN5small19conv_u8_pw_eligibleERKNS_9LayerGeomERKNS_11QuantParamsEPKiPKv"]
+    f.restype = C.c_bool
+    quant = (C.c_int * 9)(100, 128, 128, (1 << 30) + 1, 31, 0, 255, 1025, -1)
+
+    def walk(N, Ci, Co, H, W, s=1):
+        geom = (C.c_int * 14)(N, H, W, (H - 1) // s + 1, (W - 1) // s + 1, Ci, Co, 16, 16, 1, 1, s, 0, 0)
+        return f(geom, quant, C.c_void_p(0x1000), C.c_void_p(0x1000))
+    rows = [r[:6] for r in test_conv_pointwise_walk.pytestmark[0].args[1]] + [r[:5] for r in test_conv_pointwise_walk_streamed.pytestmark[0].args[1]]
+    for row in rows + [POINTWISE_AT_A_HALF]:
+        assert walk(*row), row
+    assert not walk(9, *POINTWISE_AT_A_HALF[1:])
+    for N, Ci, Co, H, W, k, zx, zw in STREAMED_AT_A_HALF:
+        layer = (N, Ci, Co, H, W, k, k, 1, (k // 2,) * 4)
+        assert walk(N, Ci, Co, H, W) and N * Co * H * W >= 10 << 20 if k == 1 else tiles(*layer) and tile_form(*layer)[1], layer
+
+
 @pytest.fixture(scope="module")
 def dw_form():
     """(waves, rows of a strip, strips side by side) of a depthwise 3x3 layer of stride 1 padded by one."""
