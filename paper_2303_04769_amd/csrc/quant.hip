@@ -33,8 +33,6 @@ struct QConvArgs {
     QuantParams q;
 };
 
-// Zero-point corrections and requantization of a wave's accumulators, four consecutive output channels
-// (one 32-bit word of the blocked output) per lane and tile. acc_w: sum of the signed filter bytes per channel.
 // The signed operand of 16 codes where m is all ones, the word `other` four times where m is zero.
 __device__ __forceinline__ intx4 signed_or(const intx4 v, int m, int other)
 {
@@ -48,6 +46,8 @@ __device__ __forceinline__ int image_mask(int ih, int iw, const QConvArgs &a)
     return lane_mask(((unsigned)ih < (unsigned)a.H) & ((unsigned)iw < (unsigned)a.W));
 }
 
+// Zero-point corrections and requantization of a wave's accumulators, four consecutive output channels
+// (one 32-bit word of the blocked output) per lane and tile. acc_w: sum of the signed filter bytes per channel.
 // FORM: of the requantization, 2 where q.mult32 >= 0, else 1 where q.amax > 0, else 0.
 template <int FORM, int WM, int WN>
 __device__ __forceinline__ void store_tiles_form(const QConvArgs &a, const intx4 (&acc)[WM][WN], const intx4 (&acc_s)[WM],

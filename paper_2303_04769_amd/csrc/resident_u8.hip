@@ -315,7 +315,7 @@ size_t ru8_chunks(const RU8Group &g)
     return g.kind == RU8_CONV ? (size_t)g.Ci / 16 * g.kh * g.kw : g.kind == RU8_DW ? (size_t)g.kh * g.kw : 0;
 }
 
-// what filter_arrive stages behind a layer's filter: the one statement of it, for the layout and for the kernel
+// what filter_request brings into LDS behind a layer's filter: the one statement of it, for the layout and for the kernel
 size_t ru8_sums_bytes(const RU8Group &g) { return g.kind == RU8_CONV ? (size_t)g.Co * 4 : 0; }
 
 struct Layout { int pads, table, filt0, filt1, at[kRU8Buffers]; size_t bytes; };

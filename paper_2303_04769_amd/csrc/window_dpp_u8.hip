@@ -71,11 +71,12 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
     const int l = lane & 15, q = lane >> 4;
 
     const int t = FOLD ? unit : a.by_nb.div(unit), band = FOLD ? 0 : unit - t * a.nb;
-    const int pg = FOLD ? unit : a.by_sp.div(t);
-    const int strip = FOLD ? 0 : t - pg * a.sp;
+    const int pg = FOLD ? unit : a.by_sp.div(t), strip = FOLD ? 0 : t - pg * a.sp;
     int r0 = strip * ROWS, r1 = min(r0 + ROWS, a.H);                                   // output rows r0 .. r1 - 1
+    int n_in = r1 - r0 + 2;
     const int ig = a.by_nCb.div(pg), cb = pg - ig * a.nCb;                             // images (strips) ig * ppb .., channel block
 
+    // (the rows before the images: behind them the scalar instructions come in another order, 1 % on the audio CNN's layer)
     int image, x;
     bool lane_used = true;
     if (SEG == 16) {
@@ -95,8 +96,8 @@ __global__ void __launch_bounds__(256) dw16_dpp_u8(DppU8Args a)
         image = a.by_sp.div(slot);
         r0 = (slot - image * a.sp) * ROWS;
         r1 = min(r0 + ROWS, a.H);
+        n_in = r1 - r0 + 2;
     }
-    const int n_in = r1 - r0 + 2;
     const int plane = image * a.nCb + cb;
     const bool col_in = lane_used & (x >= 0) & (x < a.W) & (plane < a.n_planes);
     const bool col_out = col_in & (SEG != 16 || (l >= 1 && l <= 14));
@@ -221,13 +222,6 @@ void go3(const DppU8Args &a, int seg, hipStream_t s)
     else if (seg == 8) hipLaunchKernelGGL((dw16_dpp_u8<8, NZ, ROWS, HIGH, CACHED, false>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((dw16_dpp_u8<16, NZ, ROWS, HIGH, CACHED, false>), grid, block, 0, s, a);
 }
-template <int ROWS, bool HIGH>
-void go_fold(const DppU8Args &a, int seg, hipStream_t s)
-{
-    const dim3 grid((unsigned)((a.n_units + 3) / 4)), block(256);
-    if (seg == 0) hipLaunchKernelGGL((dw16_dpp_u8<0, kAnyNZ, ROWS, HIGH, true, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((dw16_dpp_u8<8, kAnyNZ, ROWS, HIGH, true, true>), grid, block, 0, s, a);
-}
 template <int ROWS, bool HIGH, bool CACHED>
 void go2(const DppU8Args &a, int seg, hipStream_t s)
 {
@@ -236,13 +230,24 @@ void go2(const DppU8Args &a, int seg, hipStream_t s)
     else go3<ROWS, HIGH, CACHED, 1>(a, seg, s);
 }
 template <int ROWS>
-void go(const DppU8Args &a, int seg, bool fold, hipStream_t s)
+void go(const DppU8Args &a, int seg, hipStream_t s)
 {
-    if (fold && a.q.mult32 < 0) go_fold<ROWS, false>(a, seg, s);
-    else if (fold) go_fold<ROWS, true>(a, seg, s);
-    else if (a.q.mult32 < 0) go2<ROWS, false, false>(a, seg, s);
+    if (a.q.mult32 < 0) go2<ROWS, false, false>(a, seg, s);
     else if (a.cached) go2<ROWS, true, true>(a, seg, s);
     else go2<ROWS, true, false>(a, seg, s);
+}
+template <int ROWS, bool HIGH>
+void go_strips2(const DppU8Args &a, int seg, hipStream_t s)
+{
+    const dim3 grid((unsigned)((a.n_units + 3) / 4)), block(256);
+    if (seg == 0) hipLaunchKernelGGL((dw16_dpp_u8<0, kAnyNZ, ROWS, HIGH, true, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((dw16_dpp_u8<8, kAnyNZ, ROWS, HIGH, true, true>), grid, block, 0, s, a);
+}
+template <int ROWS>
+void go_strips(const DppU8Args &a, int seg, hipStream_t s)
+{
+    if (a.q.mult32 < 0) go_strips2<ROWS, false>(a, seg, s);
+    else go_strips2<ROWS, true>(a, seg, s);
 }
 
 }  // namespace
@@ -277,16 +282,24 @@ hipError_t launch_dw_dpp_u8(const unsigned char *in, const unsigned char *filt, 
     a.nz = q.zw == 128 ? 0 : q.zw == 0 ? 2 : 1;
     // Outputs of less than 4 MB stay in the cache, 3 to 6 % faster on average; past that the non-temporal stores are (8 to 16 MB: 8 %),
     // except to planes of one pixel a row, which a wave writes in pieces of 16 bytes at as many images: half a cache line each
-    // (2000 images of 64 channels 86x1: 22.5 us non-temporal, 13.7). (A branch on it at each store costs 4 to 8 %.)
+    // (2000 images of 64 channels 86x1: 22.5 us non-temporal, 13.7). (A branch on it at each store costs 4 to 8 %.) Scales of a half
+    // and more have the non-temporal form alone, strips side by side the other alone: one kernel less for each layer that hardly occurs.
     a.cached = a.bytes < (4u << 20) || g.W == 1;
     a.by_nb = make_fastdiv(a.nb);
     a.by_sp = make_fastdiv(a.sp);
     a.by_nCb = make_fastdiv(a.nCb);
     a.by_W = make_fastdiv(g.W);
-    if (pl.rows == 3) go<3>(a, pl.seg, pl.fold, s);
-    else if (pl.rows == 5) go<5>(a, pl.seg, pl.fold, s);
-    else if (pl.rows == 7) go<7>(a, pl.seg, pl.fold, s);
-    else go<9>(a, pl.seg, pl.fold, s);
+    if (!pl.fold) {
+        if (pl.rows == 3) go<3>(a, pl.seg, s);
+        else if (pl.rows == 5) go<5>(a, pl.seg, s);
+        else if (pl.rows == 7) go<7>(a, pl.seg, s);
+        else go<9>(a, pl.seg, s);
+    } else {
+        if (pl.rows == 3) go_strips<3>(a, pl.seg, s);
+        else if (pl.rows == 5) go_strips<5>(a, pl.seg, s);
+        else if (pl.rows == 7) go_strips<7>(a, pl.seg, s);
+        else go_strips<9>(a, pl.seg, s);
+    }
     return hipGetLastError();
 }
 
