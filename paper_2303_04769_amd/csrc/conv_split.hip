@@ -19,11 +19,11 @@ struct SplitArgs {
     const float *in, *filt, *res, *bn;
     float *out;
     int H, W, HoWo, Wo, M;
-    int nCib, nCob, taps, kw, stride, pt, pl, steps;
+    int nCib, nCob, taps, kw, stride, pt, pl, steps, run;  // steps; of a wave
     int n_groups;                      // pixel groups of 16
     int epilogue;
     unsigned in_bytes, filt_bytes;
-    FastDiv dHoWo, dWo, dTaps, dKw, dGroups;
+    FastDiv dHoWo, dWo, dCib, dKw, dGroups;
 };
 
 template <int WAVES, int WM, int WN>
@@ -36,8 +36,6 @@ __global__ void __launch_bounds__(64 * WAVES) conv16_split(SplitArgs a)
     // pixel groups fastest: the workgroups that read one output block's filter meet in one L2
     const int wg = (int)xcd_contiguous(blockIdx.x, gridDim.x);
     const int ct = quotient(a.dGroups, wg), grp = wg - ct * a.n_groups, cob0 = ct * WN;
-    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.in), 0, a.in_bytes, kRawBuffer);
-    const __amdgpu_buffer_rsrc_t flt = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.filt), 0, a.filt_bytes, kRawBuffer);
     const int HW = a.H * a.W;
     int ih0[WM], iw0[WM], org[WM];                             // window origin; this lane's quad at tap (0, 0) of block 0
 #pragma unroll
@@ -55,25 +53,44 @@ __global__ void __launch_bounds__(64 * WAVES) conv16_split(SplitArgs a)
     for (int j = 0; j < WN; ++j)
         f_lane[j] = cob0 + j < a.nCob ? (unsigned)((cob0 + j) * a.steps) * 1024u + (unsigned)(q * 64 + p) * 4u : kBeyond;
 
+    // This wave's steps are a run of them, the input block innermost: from one to the next only the scalar offsets of the loads change,
+    // and the lanes' offsets, of which the tap's place in the image is part, where the run comes to another tap. Behind the run's
+    // end the descriptors have no size (and the scalar offsets are zero, for the hardware takes them off the size): such loads read zero.
+    const int first = wave * a.run, last = min(first + a.run, a.steps);
     floatx4 x[kAhead][WM];
     float w[kAhead][WN][4];
-    auto request = [&](int s, floatx4 (&xs)[WM], float (&ws)[WN][4]) __attribute__((always_inline)) {
-        const int sc = s < a.steps ? s : 0;
-        const int cib = quotient(a.dTaps, sc), tap = sc - cib * a.taps, y = quotient(a.dKw, tap), z = tap - y * a.kw;    // wave-uniform
+    int tap = quotient(a.dCib, first), cib = first - tap * a.nCib, s_next = first;
+    unsigned at[WM];
+    auto lanes = [&]() __attribute__((always_inline)) {
+        const int y = quotient(a.dKw, tap), z = tap - y * a.kw;
 #pragma unroll
         for (int i = 0; i < WM; ++i) {
-            const bool inside = ((unsigned)(ih0[i] + y) < (unsigned)a.H) & ((unsigned)(iw0[i] + z) < (unsigned)a.W) & (s < a.steps);
-            const unsigned at = (unsigned)(org[i] + (cib * HW + y * a.W + z) * 64);
-            xs[i] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(src, inside ? at : kBeyond, 0, 0));
+            const bool inside = ((unsigned)(ih0[i] + y) < (unsigned)a.H) & ((unsigned)(iw0[i] + z) < (unsigned)a.W);
+            at[i] = inside ? (unsigned)(org[i] + (y * a.W + z) * 64) : kBeyond;
         }
+    };
+    lanes();
+    auto request = [&](floatx4 (&xs)[WM], float (&ws)[WN][4]) __attribute__((always_inline)) {
+        const bool more = s_next < last;
+        const int x_block = more ? cib * HW * 64 : 0, w_block = more ? (cib * a.taps + tap) * 1024 : 0;
+        const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.in), 0, more ? a.in_bytes : 0u, kRawBuffer);
+        const __amdgpu_buffer_rsrc_t flt = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.filt), 0, more ? a.filt_bytes : 0u, kRawBuffer);
+#pragma unroll
+        for (int i = 0; i < WM; ++i) xs[i] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(src, at[i], x_block, 0));
 #pragma unroll
         for (int j = 0; j < WN; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                ws[j][r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(flt, s < a.steps ? f_lane[j] + (unsigned)sc * 1024u + 64u * r : kBeyond, 0, 0));
+                ws[j][r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(flt, f_lane[j] + 64u * r, w_block, 0));
+        ++s_next;
+        if (++cib == a.nCib) {
+            cib = 0;
+            ++tap;
+            lanes();
+        }
     };
 #pragma unroll
-    for (int i = 0; i < kAhead; ++i) request(wave + i * WAVES, x[i], w[i]);
+    for (int i = 0; i < kAhead; ++i) request(x[i], w[i]);
     floatx4 acc[WM][WN][CH];
 #pragma unroll
     for (int i = 0; i < WM; ++i)
@@ -81,7 +98,7 @@ __global__ void __launch_bounds__(64 * WAVES) conv16_split(SplitArgs a)
         for (int j = 0; j < WN; ++j)
 #pragma unroll
             for (int c = 0; c < CH; ++c) acc[i][j][c] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int s = wave; s < a.steps; s += kAhead * WAVES) {
+    for (int s = first; s < last; s += kAhead) {
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) {
             // (steps past the end multiply zeros by zeros)
@@ -92,7 +109,7 @@ __global__ void __launch_bounds__(64 * WAVES) conv16_split(SplitArgs a)
 #pragma unroll
                     for (int j = 0; j < WN; ++j)
                         acc[i][j][r % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[k][j][r], x[k][i][r], acc[i][j][r % CH], 0, 0, 0);
-            request(s + (k + kAhead) * WAVES, x[k], w[k]);
+            request(x[k], w[k]);
         }
     }
 #pragma unroll
@@ -188,11 +205,12 @@ hipError_t launch_conv_split(const float *in, const float *filt, float *out, con
     a.nCib = g.Ci / 16; a.nCob = g.Co / 16; a.taps = g.kh * g.kw; a.kw = g.kw;
     a.stride = g.stride; a.pt = g.pt; a.pl = g.pl; a.steps = a.nCib * a.taps;
     const int v = pick_variant(g);
+    a.run = (a.steps + kVariants[v].waves - 1) / kVariants[v].waves;
     a.n_groups = (a.M + 16 * kVariants[v].wm - 1) / (16 * kVariants[v].wm);
     a.epilogue = epilogue;
     a.in_bytes = (unsigned)((size_t)g.N * g.Ci * g.H * g.W * 4);
     a.filt_bytes = (unsigned)((size_t)g.Co * g.Ci * a.taps * 4);
-    a.dHoWo = make_fastdiv(a.HoWo); a.dWo = make_fastdiv(a.Wo); a.dTaps = make_fastdiv(a.taps); a.dKw = make_fastdiv(a.kw);
+    a.dHoWo = make_fastdiv(a.HoWo); a.dWo = make_fastdiv(a.Wo); a.dCib = make_fastdiv(a.nCib); a.dKw = make_fastdiv(a.kw);
     a.dGroups = make_fastdiv(a.n_groups);
     switch (v) {
         case 0: return run<16, 1, 1>(a, s);
