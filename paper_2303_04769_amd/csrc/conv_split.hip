@@ -13,7 +13,9 @@
 namespace small {
 namespace {
 
-constexpr int kAhead = 4;              // steps of operands in flight per wave
+// Steps of operands in flight per wave. A wave's run is filled up to a multiple of it with steps of zeros: with 4, 6 and 9 the layers
+// below took 1.04, 1.12 and 1.22 of the time (512 channels 3x3 6x6, one image, 18 steps a wave 9.3 / 9.3 / 9.9 us against 8.6).
+constexpr int kAhead = 3;
 
 struct SplitArgs {
     const float *in, *filt, *res, *bn;
