@@ -620,6 +620,7 @@ const char *conv_kernel_name(const LayerGeom &g)
         if (g.Cib == 8 && g.kh == 1 && g.kw == 1) return "conv_small<8,1,1>";
         return "conv_small<0,0,0>";
     }
+    if (conv_split3_wide_eligible(g)) return conv_split3_wide_kernel_name();
     if (conv_split3_eligible(g)) return conv_split3_kernel_name();
     if (conv_split_eligible(g)) return conv_split_kernel_name(g);
     if (conv_pw_eligible(g)) return conv_pw_kernel_name(g);
@@ -718,6 +719,7 @@ hipError_t launch_conv(const float *in, const float *filt, float *out, const flo
         hipLaunchKernelGGL(conv_direct, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a, g.Cib, g.Cob, total);
         return hipGetLastError();
     }
+    if (conv_split3_wide_eligible(g)) return launch_conv_split3_wide(in, filt, out, a.res, g, epilogue, s, bn);
     if (conv_split3_eligible(g)) return launch_conv_split3(in, filt, out, a.res, g, epilogue, s, bn);
     if (conv_split_eligible(g)) return launch_conv_split(in, filt, out, a.res, g, epilogue, s, bn);
     if (conv_pw_eligible(g)) return launch_conv_pw(in, filt, out, a.res, g, epilogue, s, bn);

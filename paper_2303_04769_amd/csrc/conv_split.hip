@@ -184,9 +184,9 @@ bool conv_split_eligible(const LayerGeom &g)
         // few / many tiles: 4 steps 0.97 up to one tile a unit, 1.1 to 1.7 beyond (16 -> 32 channels 1x2 48x48 263 images 69 / 26 us,
         // 16 -> 16 1x3 14x14 9633 images 190 / 58); 8 steps 0.78 to 0.96 / 0.93 to 1.24; 9 to 11 steps 0.70 to 1.0 / 1.04 to 1.33;
         // 12 to 15 0.54 to 1.08 / 0.97 to 1.21; from 16 on 0.11 to 1.0, with many tiles 0.7 to 1.1 unless the last round of
-        // steps (2 waves, kAhead each) or of output blocks (two a tile) is too empty: 18 steps 0.93 to 1.23.
+        // steps (2 waves of 4, as they were then) or of output blocks (two a tile) is too empty: 18 steps 0.93 to 1.23.
         const double most = steps < 4 ? 0 : steps < 8 ? 1 : steps < 9 ? 2.5 : steps < 12 ? (g.Co == 16 ? 8 : 5.5) : 20;
-        const long nCob = g.Co / 16, done = (steps + 2 * kAhead - 1) / (2 * kAhead) * (2 * kAhead) * ((nCob + 1) / 2 * 2);
+        const long nCob = g.Co / 16, done = (steps + 7) / 8 * 8 * ((nCob + 1) / 2 * 2);
         return tiles <= most * cus || (steps >= 16 && 100 * steps * nCob >= 78 * done);
     }
     // Against the tiles of conv_same.hip (their us / here): up to one tile per compute unit from 7 steps on (189 tiles of 7

@@ -488,6 +488,32 @@ def test_conv2d_three_part_products_scattered_infinities(case):
         assert (np.abs(got[ok].astype(np.float64) - ref[ok]) <= (Ci * kh * kw + 1) * 2.0 ** -23 * size[ok]).all()
 
 
+WIDE_CASES = [  # N, Ci, Co, H, W, kh, kw, pad: 256-pixel tiles, a wave 64 x 64, workgroups that walk over tiles
+    (46, 96, 48, 33, 33, 3, 3, (1, 1, 1, 1)),        # fewer tiles than compute units; three chunks; three output blocks of four
+    (94, 64, 96, 103, 9, 3, 3, (1, 1, 1, 1)),        # two to three tiles a workgroup, which end inside images; six output blocks
+    (40, 96, 64, 27, 51, 3, 3, (1, 0, 2, 0)),        # uneven padding: 26 x 51 outputs, the last strip shorter
+    (900, 64, 64, 56, 7, 3, 3, (1, 1, 1, 1)),        # narrow images
+]
+
+
+@pytest.mark.parametrize("case", WIDE_CASES)
+@pytest.mark.parametrize("scale", [1.0, 1e-36, 1e30])
+def test_conv2d_three_part_wide_tiles(case, scale):
+    N, Ci, Co, H, W, kh, kw, pad = case
+    assert S.small_conv2d_kernel(N, Ci, Co, H, W, kh, kw, 1, pad, 16, 16).startswith("conv16_split3_wide"), case
+    test_conv2d_three_part_products(case, scale)
+
+
+@pytest.mark.parametrize("case", WIDE_CASES)
+def test_conv2d_three_part_wide_tiles_scattered_infinities(case):
+    test_conv2d_three_part_products_scattered_infinities(case)
+
+
+@pytest.mark.parametrize("kind", sorted(SPARSE_FILTERS))
+def test_conv2d_three_part_wide_tiles_precision(kind):
+    test_conv2d_three_part_products_precision(kind, 20, 64, 64, 64, 47, 3)
+
+
 def test_conv_identity_filter_is_exact():
     rng = np.random.default_rng(5)
     x = rng.standard_normal((2, 32, 10, 12)).astype(np.float32)

@@ -574,6 +574,37 @@ def test_pointwise_stream_epilogues(C, N, H, W):
     assert_close(_run(net, x, ws, S.SMALL_RUN_RESIDENT_OFF), ref, C, f"pointwise stream with epilogues, C={C}")
 
 
+def test_three_part_wide_tiles_epilogues():
+    """ReLU, and a residual add (+ ReLU) onto another tensor, in the store phase of the kernel whose workgroups walk over
+    tiles; a value whose
+    parts overflow makes some waves compute their tiles again, behind the others."""
+    from workloads.nets import Layer, Network, IN, OUT
+    N, C, H, W, p = 90, 64, 40, 31, (1, 1, 1, 1)
+    net = Network("three_part_wide_epilogues", C, H, W)
+    net.wshapes = [((C, C, 3, 3), 9 * C), ((C, C, 3, 3), 9 * C)]
+    net.layers = [
+        Layer("conv", C, C, H, W, 3, 3, 1, p, src=IN, dst=0, w=0),
+        Layer("relu", C, C, H, W, src=0, dst=0),
+        Layer("conv", C, C, H, W, 3, 3, 1, p, src=0, dst=1, w=1),
+        Layer("add", C, C, H, W, src=1, src2=0, dst=1),
+        Layer("relu", C, C, H, W, src=1, dst=1),
+        Layer("maxpool", C, C, H, W, 1, 1, 1, (0, 0, 0, 0), src=1, dst=OUT),
+    ]
+    assert S.small_conv2d_kernel(N, C, C, H, W, 3, 3, 1, p, 16, 16).startswith("conv16_split3_wide")
+    x, ws = WL.network_tensors(net, N, 6300)
+    x[7, 5, 20, 11] = 1e31
+    got = _run(net, x, ws, S.SMALL_RUN_RESIDENT_OFF)
+    idx = [0, 6, 7, 8, N - 1]
+    a = O.relu(O.conv2d(x[idx], ws[0], 1, p))
+    ref = O.relu(O.add(O.conv2d(a, ws[1], 1, p), a))
+    assert np.abs(ref[2]).max() > 1e30
+    assert_close(got[7], ref[2], 9 * C, "the image with a large value")
+    far = np.ones((H, W), bool)
+    far[17:24, 8:15] = False                       # its reach after two 3x3 layers, and one pixel more
+    assert_close(got[7][:, far], ref[2][:, far], 9 * C, "the rest of it")
+    assert_close(got[[0, 6, 8, N - 1]], ref[[0, 1, 3, 4]], 9 * C, "three-part wide tiles with epilogues")
+
+
 def _run_both(net, x, ws):
     """Blocked outputs of small_pack + small_network_run and of small_network_run_plain on the same input."""
     N = x.shape[0]
