@@ -14,7 +14,7 @@ LIB = os.path.join(HERE, "libsmall_hip.so")
 # for which Python and which torch it was built, so that no other one loads it.
 FASTCALL = os.path.join(HERE, f"_fastcall.{sysconfig.get_config_var('SOABI')}.torch-{torch.__version__}.so")
 PROBE_LIB = os.path.join(HERE, "libsmall_probe.so")       # the benchmark's matrix-rate probe, a library of its own
-SOURCES = ["elementwise.hip", "window.hip", "window_rows.hip", "window_dpp.hip", "window_dpp_u8.hip", "pool_dpp_u8.hip", "quant_ends.hip", "pool_dpp.hip", "conv.hip", "conv_same.hip", "conv_pw.hip", "conv_split.hip", "conv_split3.hip", "conv_split3_wide.hip", "dwpw.hip", "dwpw_run.hip", "chain.hip", "resident.hip", "quant.hip", "conv_u8_tile.hip", "conv_u8_pw.hip", "layout_u8.hip", "resident_u8.hip", "table2.hip", "small_api.hip"]
+SOURCES = ["elementwise.hip", "window.hip", "window_rows.hip", "window_dpp.hip", "window_dpp_u8.hip", "pool_dpp_u8.hip", "quant_ends.hip", "pool_dpp.hip", "conv.hip", "conv_same.hip", "conv_pw.hip", "conv_split.hip", "conv_split3.hip", "conv_split3_wide.hip", "dwpw.hip", "dwpw_run.hip", "dwpw_team.hip", "chain.hip", "resident.hip", "quant.hip", "conv_u8_tile.hip", "conv_u8_pw.hip", "layout_u8.hip", "resident_u8.hip", "table2.hip", "small_api.hip"]
 # packed fp32 VALU ops are switched off for every device translation unit
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc", "-Wall", "-Wno-unused-function", "-Wno-pass-failed",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

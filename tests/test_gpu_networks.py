@@ -1076,3 +1076,111 @@ def test_depthwise_pointwise_runs(case):
     ref = O.run_network(net, x, ws)
     got = _run(net, x, ws, S.SMALL_RUN_RESIDENT_OFF)
     assert_close(got, ref.reshape(got.shape), C, f"dwpw run {case}")
+
+
+# ------------------------------------------------------------------ such runs on few images: a team of workgroups each
+
+def _team_net(C0, H, W, spec, up=4, head=0):
+    """A ReLU into a buffer of up x up times the run's input (where a team's workgroups exchange their results), a max pooling,
+    then pairs [depthwise 3x3 (+ReLU)] -> [1x1 conv (+ReLU)] by (Cout, stride, padding, ReLUs) in two buffers in turn (the last
+    result without a head in a third), closed by a max pooling into OUT or by average + fully connected layer with `head` outputs."""
+    from workloads.nets import Layer, Network, IN, OUT
+    z = (0, 0, 0, 0)
+    net = Network("dwpw_team", C0, H * up, W * up)
+    net.layers.append(Layer("relu", C0, C0, H * up, W * up, src=IN, dst=0))
+    net.layers.append(Layer("maxpool", C0, C0, H * up, W * up, up, up, up, z, src=0, dst=1))
+    C, k, t = C0, 0, 1
+    for Co, s, pad, (r1, r2) in spec:
+        t = 1 if head or k + 2 < 2 * len(spec) else 2
+        L = Layer("dw", C, C, H, W, 3, 3, s, pad, src=1, dst=0, w=k)
+        H, W = L.Ho, L.Wo
+        net.wshapes += [((C, 1, 3, 3), 9), ((Co, C, 1, 1), C)]
+        net.layers.append(L)
+        if r1:
+            net.layers.append(Layer("relu", C, C, H, W, src=0, dst=0))
+        net.layers.append(Layer("conv", C, Co, H, W, 1, 1, 1, z, src=0, dst=t, w=k + 1))
+        if r2:
+            net.layers.append(Layer("relu", Co, Co, H, W, src=t, dst=t))
+        C, k = Co, k + 2
+    if head:
+        net.layers.append(Layer("avgpool", C, C, H, W, H, W, 1, z, src=1, dst=2))
+        net.wshapes.append(((head, C, 1, 1), C))
+        net.layers.append(Layer("dense", C, head, 1, 1, 1, 1, 1, z, src=2, dst=OUT, w=k, Cob=head))
+    else:
+        net.layers.append(Layer("maxpool", C, C, H, W, 1, 1, 1, z, src=t, dst=OUT))
+    return net
+
+
+_P1, _S2, _BOTH = (1, 1, 1, 1), (0, 1, 0, 1), (1, 1)
+_DSEP = [(32, 1, _P1, _BOTH), (64, 2, _S2, _BOTH), (64, 1, _P1, _BOTH), (128, 2, _S2, _BOTH), (128, 1, _P1, _BOTH),
+         (256, 2, _P1, _BOTH), (256, 1, _P1, _BOTH)]
+TEAM_CASES = [  # C0, H, W, N, [(Cout, stride, padding, ReLUs)], outputs of a head or 0, whether a team takes it
+    (32, 12, 12, 1, _DSEP, 2, True),                        # the depthwise-separable CNN's: 16 workgroups
+    (32, 12, 12, 2, _DSEP, 0, True),                        # as many images as 256 compute units are used for
+    (32, 12, 12, 3, _DSEP, 2, False),                       # and one more
+    (16, 16, 16, 5, [(16, 1, _P1, (1, 0)), (16, 2, _S2, (0, 1)), (48, 1, _P1, _BOTH)], 0, True),   # 16 pixel groups, one input block
+    (48, 5, 7, 4, [(80, 2, _P1, _BOTH), (112, 1, _P1, _BOTH), (48, 1, _P1, (0, 0))], 16, True),    # 3, 5, 7 blocks; 16 outputs
+    (32, 1, 1, 16, [(32, 1, _P1, _BOTH), (16, 1, _P1, _BOTH)], 3, True),                           # one pixel
+    (64, 7, 5, 3, [(64, 3, (1, 0, 2, 1), _BOTH), (32, 1, _P1, _BOTH)], 0, True),                   # stride 3, uneven padding
+    (96, 4, 4, 2, [(96, 1, (2, 2, 2, 2), _BOTH), (160, 1, (2, 2, 0, 0), _BOTH), (32, 2, _P1, _BOTH)], 5, True),  # 1, 3, 3, 1 groups
+    (240, 4, 4, 1, [(240, 1, _P1, (0, 0)), (240, 1, (1, 2, 1, 2), _BOTH), (16, 2, _P1, _BOTH)], 0, True),        # 4 x 2 items a wave
+]
+
+
+@pytest.mark.parametrize("case", TEAM_CASES)
+def test_depthwise_pointwise_runs_by_a_team(case):
+    """The result for every image against the oracle's layer-by-layer chain, from a first call, a repeated one on other values
+    and replays of a captured one; the exchange area starts with the first depthwise layer's result where a team takes the run
+    (and holds the first ReLU's where not)."""
+    C0, H, W, N, spec, head, team = case
+    net = _team_net(C0, H, W, spec, head=head)
+    pn = None
+    for seed in (1, 2):
+        x, ws = WL.network_tensors(net, N, 9300 + C0 + N)
+        x = np.ascontiguousarray(x * np.float32(1.5 * seed - 2))          # other inputs under the same filters
+        if pn is None:
+            pn = S.PackedNetwork(net, ws, DEV)
+            xb, out = pn.pack_input(dev(x)), Guarded(pn.out_elems(N))
+            pn.workspace(N)[0].fill_(3.0)
+        else:
+            xb.copy_(pn.pack_input(dev(x)))
+        ref = O.run_network(net, x, ws)
+        K = max(C0, max(c for c, *_ in spec))
+        pn.run(xb, out.t, N)
+        got = out.check().copy()
+        L = net.layers[-1]
+        assert_close(O.unpack(got, (N, L.Co, L.Ho, L.Wo), L.Cob).reshape(ref.shape), ref, K, f"team {case}")
+        assert np.abs(ref).max() > 1e-3
+        first = O.dwconv2d(O.pool2d(np.maximum(x, 0), (4, 4), 4, (0, 0, 0, 0), "max"), ws[0], spec[0][1], spec[0][2])
+        first = O.pack(O.relu(first) if spec[0][3][0] else first, 16).reshape(N, -1)
+        per_image = sum(L.Co * L.Ho * L.Wo for L in net.layers if L.op == "dw") + (256 if head else 0)
+        slot0 = pn.workspace(N)[0].cpu().numpy()
+        there = all(np.allclose(slot0[n * per_image:][:first[n].size], first[n], rtol=1e-4, atol=1e-5) for n in range(N))
+        assert there == team
+    graph = pn.capture(xb, out.t, N)
+    for k in range(3):
+        pn.workspace(N)[0].fill_(float(k))
+        out.t.zero_()
+        graph.replay()
+        assert np.array_equal(out.check(), got)
+
+
+def test_depthwise_pointwise_run_by_a_team_on_nans():
+    """NaNs of every kind, the one that stands for "not there yet" in the exchange area among them, arrive as NaNs, at the
+    outputs whose sums they are part of and at no others."""
+    plain = (0, 0)
+    net = _team_net(32, 6, 6, [(32, 1, _P1, plain), (48, 1, _P1, plain)], up=4)
+    net.layers[0].op = "add"                                # no ReLU in front: it would drop the NaNs
+    net.layers[0].src2 = net.layers[0].src
+    x, ws = WL.network_tensors(net, 2, 9400)
+    net.layers[1].op = net.layers[-1].op = "avgpool"        # a maximum drops them as well
+    bits = np.array([0xffffffff, 0x7fffffff, 0x7fc00000, 0xffc00001], np.uint32).view(np.float32)
+    for k, v in enumerate(bits):
+        x[1, 8 * k + 1, 0, 0] = v
+    pn = S.PackedNetwork(net, ws, DEV)
+    out = Guarded(pn.out_elems(2))
+    pn.run(pn.pack_input(dev(x)), out.t, 2)
+    got = O.unpack(out.check(), (2, 48, 6, 6), 16)
+    assert np.isfinite(got[0]).all()
+    nan = np.isnan(got[1])
+    assert nan[:, :3, :3].all() and not nan[:, 3:, :].any() and not nan[:, :, 3:].any()
