@@ -395,17 +395,20 @@ void launch_mfma(const ConvArgs &a, hipStream_t s)
 // leave 4 or more of them resident per compute unit, which hides each other's prologue, barrier and
 // store phases. 1x1 (little work per pixel): 32 pixels x 64 channels, or 32 x 32 for narrow layers.
 // 3x3: the candidate with the least work on the busiest compute unit (workgroups are spread evenly,
-// so that is ceil(workgroups / compute units) x tile area), 64 x 32 preferred on near-ties for its operand reuse.
+// so that is ceil(workgroups / compute units) x tile area), 64 x 32 preferred on near-ties for its operand reuse. Stride 2, where a
+// step stages two input entries per pixel, has 64 x 48 as well: us with 64x32 / 64x16 / 32x32 / 64x48 for 48 -> 96 channels 45x37, 50
+// images, 24.0 / 25.5 / 24.8 / 21.9 (cost 10240 / 9861 / 9953 / 9216), 48 channels 45x62, 159 images, 65.8 / 62.2 / 74.4 / 49.8; not
+// where its workgroups go round less evenly: 160 -> 48 channels 77x90, 20 images, 68.7 / 52.7 / 63.9 / 65.0 (10240 / 7669 / 9953 / 9216).
 int pick_tile(const LayerGeom &g)
 {
     const long M = (long)g.N * g.Ho * g.Wo;
     const bool pointwise = g.kh == 1 && g.kw == 1;
     if (pointwise) return g.Co >= 64 ? SAME_32x64 : g.Co >= 32 ? SAME_32x32 : SAME_64x16;
     struct Cand { int tile, tm, tn; double penalty; };
-    static const Cand wide[] = {{SAME_64x32, 64, 32, 1.0}, {SAME_64x16, 64, 16, 1.07}, {SAME_32x32, 32, 32, 1.08}};
+    static const Cand wide[] = {{SAME_64x32, 64, 32, 1.0}, {SAME_64x16, 64, 16, 1.07}, {SAME_32x32, 32, 32, 1.08}, {SAME_64x48, 64, 48, 1.0}};
     static const Cand narrow[] = {{SAME_128x16, 128, 16, 1.0}, {SAME_64x16, 64, 16, 1.05}};
     const Cand *cands = g.Co >= 32 ? wide : narrow;
-    const int n = g.Co >= 32 ? 3 : 2;
+    const int n = g.Co < 32 ? 2 : conv_same_eligible(g) && g.stride == 2 && g.Co >= 48 ? 4 : 3;
     const long cus = device_cus();
     int best = cands[0].tile;
     double best_cost = 0;
@@ -584,8 +587,7 @@ bool is_dense(const LayerGeom &g)
     return g.Ho == 1 && g.Wo == 1 && g.kh == g.H && g.kw == g.W && g.pt == 0 && g.pl == 0;
 }
 
-const char *const kTileWaves[] = {"2,2,4,4", "1,4,4,2", "2,2,4,2", "2,2,2,2", "4,1,2,2", "4,1,1,2", "4,1,2,1", "4,1,1,1",
-                                  "2,2,1,2", "2,2,1,1", "4,1,4,1"};
+const char *const kTileWaves[] = {"4,1,1,2", "4,1,2,1", "4,1,1,1", "2,2,1,2", "2,2,1,1", "4,1,1,3"};
 
 }  // namespace
 

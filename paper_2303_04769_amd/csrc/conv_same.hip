@@ -79,10 +79,21 @@ __device__ __forceinline__ floatx4 epi4(floatx4 v, int epi, const float *res, co
     return v;
 }
 
+// the sums of a tile: instruction r of a filter slab adds to sum r % CH
+template <int CH>
+__device__ __forceinline__ floatx4 total(const floatx4 (&acc)[CH])
+{
+    if constexpr (CH == 4) return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    else return acc[0];
+}
+
 constexpr int gcd_(int a, int b) { return b == 0 ? a : gcd_(b, a % b); }
 
 // KS: square filter size (1 or 3). NA: Ci blocks staged per reduction step (1 for 3x3). ES: staged entries
-// per output pixel step (1: stride 1, or any stride with a 1x1 filter; 2: 3x3 filter with stride 2).
+// per output pixel step (1: stride 1, or any stride with a 1x1 filter; 2: 3x3 filter with stride 2, a pixel's entries are its taps 0
+// and 1 and its tap 2 is the next pixel's tap 0; kBorrowBefore: two as well, its taps 1 and 2, behind one entry for the tile's first tap
+// 0, and its tap 0 is the tap 2 of the pixel before).
+constexpr int kBorrowBefore = 3;
 template <int WAVES_M, int WAVES_N, int WM, int WN, int KS, int NA, int STAGES, int ES = 1>
 struct SameCfg {
     static constexpr int NW = WAVES_M * WAVES_N;
@@ -90,7 +101,7 @@ struct SameCfg {
     static constexpr int TM = WAVES_M * WM * 16;
     static constexpr int TN = WAVES_N * WN * 16;
     static constexpr int NSUB = TN / 16;
-    static constexpr int ENT = ES * (TM - 1) + KS;           // staged input pixels per plane
+    static constexpr int ENT = (ES == kBorrowBefore ? 2 : ES) * (TM - 1) + KS;           // staged input pixels per plane
     static constexpr int ENTP = (ENT + 15) / 16 * 16;        // rounded up to whole wave instructions
     static constexpr int NS = NA * KS;                       // filter slabs per step
     static constexpr int A_BYTES = NA * ENTP * 64;
@@ -99,18 +110,24 @@ struct SameCfg {
     static constexpr int STAGE_BYTES = ZERO_REL + 16;
     static constexpr int NAI = NA * ENTP / 16, NBI = NS * NSUB;   // wave instructions per step
     static constexpr int LPS = (NAI + NBI + NW - 1) / NW;         // ... per wave
+    static constexpr int EPP = ES == kBorrowBefore ? 2 : ES;
+    static constexpr int BEFORE = ES == kBorrowBefore ? 1 : 0;
+    // Sums per tile. Four where the other choice is a kernel that splits the reduction over waves (conv_split.hip), whose error that
+    // is (48 -> 96 channels 45x36, 50 images, against 64 bits: 2.6e-7 there with two sums, 1.9e-7 with four); they cost some 5 %
+    // (64 channels 57x57, 30 images, 22.9 -> 24.2 us).
+    static constexpr int CH = ES == kBorrowBefore ? 4 : 1;
     static constexpr int UNROLL = STAGES * KS / gcd_(STAGES, KS); // steps after which (ring slot, filter row) repeat
     static constexpr size_t LDS_BYTES = (size_t)STAGES * STAGE_BYTES;
     static_assert((STAGES - 2) * LPS < 64, "too many loads in flight for vmcnt");
     static_assert(KS == 1 || NA == 1, "several planes per step only for 1x1 filters");
-    static_assert(ES == 1 || (ES == 2 && KS == 3), "two entries per pixel only for the strided 3x3 filter");
+    static_assert(ES == 1 || KS == 3, "two entries per pixel only for the strided 3x3 filter");
 };
 
 template <int WAVES_M, int WAVES_N, int WM, int WN, int KS, int NA, int STAGES, int ES>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_same(SameArgs a)
 {
     using C = SameCfg<WAVES_M, WAVES_N, WM, WN, KS, NA, STAGES, ES>;
-    constexpr int NW = C::NW, TM = C::TM, NSUB = C::NSUB, ENT = C::ENT, ENTP = C::ENTP, LPS = C::LPS, NS = C::NS;
+    constexpr int NW = C::NW, TM = C::TM, NSUB = C::NSUB, ENT = C::ENT, ENTP = C::ENTP, LPS = C::LPS, NS = C::NS, CH = C::CH;
 
     extern __shared__ floatx4 lds[];
     const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)lds;
@@ -147,8 +164,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_same(SameArgs a
             const int e = chunk * 16 + (lane >> 2);
             const int quad = (lane & 3) ^ ((e >> 1) & 3);
             // Source pixel of entry e for filter row 0. Stride-1 3x3: entries are consecutive input pixels
-            // (the flat order of input and output pixels is the same). Otherwise entry e belongs to output
-            // pixel e / ES and holds its tap e % ES (the last entry: tap KS - 1 of the last pixel).
+            // (the flat order of input and output pixels is the same). Otherwise, 1x1: entry e is output pixel e's;
+            // stride 2: tap x of pixel i is read at entry 2i + x, which it shares with a neighbour (see kBorrowBefore).
             int n, hb, wb;
             if constexpr (KS == 3 && ES == 1) {
                 const int fb = m0 + e - a.pl;
@@ -159,7 +176,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_same(SameArgs a
                 hb = a.dWo.div(pix);
                 wb = pix - hb * a.Wo;
             } else {
-                const int pxe = min(e / ES, TM - 1), xe = min(e - pxe * ES, KS - 1);
+                const int pxe = min(max(e - C::BEFORE, 0) / C::EPP, TM - 1), xe = min(e - pxe * C::EPP, KS - 1);
                 const int mo = min(m0 + pxe, a.M - 1);
                 n = a.dHWo.div(mo);
                 const int pix = mo - n * a.HWo;
@@ -212,7 +229,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_same(SameArgs a
         for (int t = 0; t < KS; ++t) {
             row_ok[t] = (unsigned)(oh * a.stride + t - a.pt) < (unsigned)a.H;
             col_ok[t] = (unsigned)(ow * a.stride + t - a.pl) < (unsigned)a.W;
-            const int e = px * ES + t;
+            const int e = px * C::EPP + t;
             real[t] = (unsigned)((e * 4 + (lq ^ ((e >> 1) & 3))) * 16);
         }
 #pragma unroll
@@ -223,11 +240,13 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_same(SameArgs a
     }
     const unsigned b_addr = (unsigned)(C::A_BYTES + wave_n * WN * 1024 + lane * 4);
 
-    floatx4 acc[WM][WN];
+    floatx4 acc[WM][WN][CH];
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
-        for (int j = 0; j < WN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) acc[i][j][c] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     // ---- reduction
     const int nsteps = (a.nCib / NA) * KS;
@@ -301,7 +320,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_same(SameArgs a
                         for (int i = 0; i < WM; ++i)
 #pragma unroll
                             for (int j = 0; j < WN; ++j)
-                                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[sl & 1][j][r], fa[sl & 1][i][r], acc[i][j], 0, 0, 0);
+                                acc[i][j][r % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[sl & 1][j][r], fa[sl & 1][i][r], acc[i][j][r % CH], 0, 0, 0);
                     }
                 }
             };
@@ -323,7 +342,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_same(SameArgs a
         for (int i = 0; i < WM; ++i) {
             if (!o_ok[i]) continue;
             *reinterpret_cast<floatx4 *>(out_c + cb + o_off[i]) =
-                epi4(acc[i][j], a.epilogue, reinterpret_cast<const float *>(res_c + cb + o_off[i]), bn_c, a.nCob * 16);
+                epi4(total(acc[i][j]), a.epilogue, reinterpret_cast<const float *>(res_c + cb + o_off[i]), bn_c, a.nCob * 16);
         }
     }
 }
@@ -341,7 +360,7 @@ template <int WAVES_M, int WAVES_N, int WM, int WN, int KS, int NA, int STAGES, 
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_img(SameArgs a)
 {
     using C = SameCfg<WAVES_M, WAVES_N, WM, WN, KS, NA, STAGES, ES>;
-    constexpr int NW = C::NW, TM = C::TM, NSUB = C::NSUB, ENT = C::ENT, ENTP = C::ENTP, LPS = C::LPS, NS = C::NS;
+    constexpr int NW = C::NW, TM = C::TM, NSUB = C::NSUB, ENT = C::ENT, ENTP = C::ENTP, LPS = C::LPS, NS = C::NS, CH = C::CH;
 
     extern __shared__ floatx4 lds[];
     const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)lds;
@@ -388,7 +407,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_img(SameArgs a)
                 hb = a.dWo.div(pix);
                 wb = pix - hb * a.Wo;
             } else {
-                const int pxe = min(e / ES, TM - 1), xe = min(e - pxe * ES, KS - 1);
+                const int pxe = min(max(e - C::BEFORE, 0) / C::EPP, TM - 1), xe = min(e - pxe * C::EPP, KS - 1);
                 const int pix = min(m0 + pxe, a.HWo - 1);
                 const int oh = a.dWo.div(pix), ow = pix - oh * a.Wo;
                 hb = oh * a.stride;
@@ -436,7 +455,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_img(SameArgs a)
         for (int t = 0; t < KS; ++t) {
             row_ok[t] = (unsigned)(oh * a.stride + t - a.pt) < (unsigned)a.H;
             col_ok[t] = (unsigned)(ow * a.stride + t - a.pl) < (unsigned)a.W;
-            const int e = px * ES + t;
+            const int e = px * C::EPP + t;
             real[t] = (unsigned)((e * 4 + (lq ^ ((e >> 1) & 3))) * 16);
         }
 #pragma unroll
@@ -493,11 +512,13 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_img(SameArgs a)
             fa[i] = *reinterpret_cast<const floatx4 *>(lds_c + p_addr[i][y][x] + slot * C::STAGE_BYTES + dc * (ENTP * 64));
     };
 
-    floatx4 acc[WM][WN];
+    floatx4 acc[WM][WN][CH];
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
-        for (int j = 0; j < WN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) acc[i][j][c] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     int n = grp, c_step = 0;                               // image and step being computed
     for (;;) {
@@ -536,7 +557,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_img(SameArgs a)
                         for (int i = 0; i < WM; ++i)
 #pragma unroll
                             for (int j = 0; j < WN; ++j)
-                                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[sl & 1][j][r], fa[sl & 1][i][r], acc[i][j], 0, 0, 0);
+                                acc[i][j][r % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[sl & 1][j][r], fa[sl & 1][i][r], acc[i][j][r % CH], 0, 0, 0);
                     }
                 }
             };
@@ -555,7 +576,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_img(SameArgs a)
                         for (int i = 0; i < WM; ++i) {
                             if (o_ok[i])
                                 *reinterpret_cast<floatx4 *>(out_c + cb + o_off[i]) =
-                                    epi4(acc[i][j], a.epilogue, reinterpret_cast<const float *>(res_c + cb + o_off[i]), bn_c,
+                                    epi4(total(acc[i][j]), a.epilogue, reinterpret_cast<const float *>(res_c + cb + o_off[i]), bn_c,
                                          a.nCob * 16);
                         }
                     }
@@ -563,7 +584,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) conv16_img(SameArgs a)
 #pragma unroll
                 for (int i = 0; i < WM; ++i)
 #pragma unroll
-                    for (int j = 0; j < WN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    for (int j = 0; j < WN; ++j)
+#pragma unroll
+                        for (int c = 0; c < CH; ++c) acc[i][j][c] = floatx4{0.f, 0.f, 0.f, 0.f};
                 c_step = 0;
                 n += a.n_groups;
                 if (n >= a.N) return;                          // uniform: every wave of the workgroup leaves here
@@ -647,16 +670,11 @@ template <class F>
 auto with_tile(int tile, F &&f)
 {
     switch (tile) {
-        case SAME_128x128: return f.template operator()<2, 2, 4, 4>();
-        case SAME_64x128: return f.template operator()<1, 4, 4, 2>();
-        case SAME_128x64: return f.template operator()<2, 2, 4, 2>();
-        case SAME_64x64: return f.template operator()<2, 2, 2, 2>();
-        case SAME_128x32: return f.template operator()<4, 1, 2, 2>();
         case SAME_64x32: return f.template operator()<4, 1, 1, 2>();
         case SAME_128x16: return f.template operator()<4, 1, 2, 1>();
         case SAME_32x64: return f.template operator()<2, 2, 1, 2>();
         case SAME_32x32: return f.template operator()<2, 2, 1, 1>();
-        case SAME_256x16: return f.template operator()<4, 1, 4, 1>();
+        case SAME_64x48: return f.template operator()<4, 1, 1, 3>();
         default: return f.template operator()<4, 1, 1, 1>();
     }
 }
@@ -678,6 +696,9 @@ struct PlanTile {
 
 }  // namespace
 
+// 3x3 with stride 2: the last pixel of a row has a tap 2 inside the image, which no next pixel's tap 0 stands for
+static bool before(const LayerGeom &g) { return 2 * (g.Wo - 1) + 2 - g.pl < g.W; }
+
 bool conv_same_eligible(const LayerGeom &g)
 {
     // the last pixel's byte offset must fit the 32-bit per-lane offset of the load and store instructions
@@ -689,9 +710,16 @@ bool conv_same_eligible(const LayerGeom &g)
         return g.pt == 0 && g.pl == 0 && g.stride >= 1 && (g.Ho - 1) * g.stride < g.H && (g.Wo - 1) * g.stride < g.W;
     if (g.kw != 3 || g.pl >= 3 || g.pt >= 3) return false;
     if (g.stride == 1) return g.Ho == g.H && g.Wo == g.W;                   // output pixels in input order
-    // stride 2: taps 0, 1 of a pixel are its own staged entries, tap 2 is the next pixel's tap 0, which is
-    // only right if a row's last pixel has no tap 2 inside the image
-    return g.stride == 2 && 2 * (g.Wo - 1) + 2 - g.pl >= g.W;
+    // stride 2: neighbouring pixels share an entry, tap 2 of one and tap 0 of the next, which is only right if a row's last pixel has
+    // no tap 2 inside the image or its first one no tap 0
+    if (g.stride != 2) return false;
+    if (!before(g)) return true;
+    // In the second case, rows of even length padded by one, the reduction split over waves (conv_split.hip) is the other choice, and
+    // the better one up to 24 tiles of 16 x 16 per compute unit, where it splits by four and more: us here / there 10.3 / 9.1 (20 images of
+    // 64 channels 50x20, 13 tiles a unit); beyond, 21.1 / 26.9 (50 of 48 -> 96 45x36, 30), 66.6 / 83.9 (64 of 144 92x12, 39), 79.4 /
+    // 88.5 (64 of 64 -> 128 56x56, 98), and where the gather kernel (conv.hip) took the layer 52.7 / 87.8 (20 of 160 -> 48 77x90,
+    // 26), 49.4 / 75.9 (159 of 48 45x62, 83). Reductions of one input block stay there (100 of 16 -> 32 70x70: 18.1 / 19.0).
+    return g.pl >= 1 && g.Ci >= 32 && ((long)g.N * g.Ho * g.Wo + 15) / 16 * (g.Co / 16) > 24L * device_cus();
 }
 
 int conv_same_planes(const LayerGeom &g)
@@ -708,6 +736,7 @@ template <template <int, int, int> class F, class... Args>
 auto with_shape(const LayerGeom &g, int tile, Args &&...args)
 {
     if (g.kw == 3) {
+        if (g.stride == 2 && before(g)) return with_tile(tile, F<3, 1, kBorrowBefore>{args...});
         if (g.stride == 2) return with_tile(tile, F<3, 1, 2>{args...});
         return with_tile(tile, F<3, 1, 1>{args...});
     }

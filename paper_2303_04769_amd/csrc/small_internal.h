@@ -212,9 +212,8 @@ hipError_t launch_resident(const ResGroup *g, int n, const float *in, float *out
 const char *conv_kernel_name(const LayerGeom &g);
 
 // Workgroup tiles (output pixels x output channels) of the matrix-core convolutions.
-enum : int { SAME_128x128, SAME_64x128, SAME_128x64, SAME_64x64, SAME_128x32, SAME_64x32, SAME_128x16, SAME_64x16,
-              SAME_32x64, SAME_32x32, SAME_256x16, SAME_NUM_TILES };
-bool conv_same_eligible(const LayerGeom &g);     // stride 1, output size == input size, kw in {1, 3}, 16-blocks
+enum : int { SAME_64x32, SAME_128x16, SAME_64x16, SAME_32x64, SAME_32x32, SAME_64x48 };
+bool conv_same_eligible(const LayerGeom &g);     // 16-blocks; 3x3 with stride 1, output size == input size, or with stride 2; unpadded 1x1
 int conv_same_planes(const LayerGeom &g);        // Ci blocks staged per reduction step (1x1 filters)
 // images each workgroup walks in the image-aligned persistent variant, 0 = flat variant (host arithmetic only)
 int conv_same_images_per_workgroup(const LayerGeom &g, int tile);

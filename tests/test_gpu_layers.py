@@ -161,6 +161,32 @@ def test_conv2d_same_tiles(case):
     assert_close(run_conv(x, w, s, pad), O.conv2d(x, w, s, pad), Ci * k * k, f"conv tile {case}")
 
 
+STRIDED_CASES = [  # N, Ci, Co, H, W, pad, kernel: 3x3 with stride 2, tiles of three output blocks, and images whose rows' last tap is inside
+    (50, 16, 96, 45, 37, (1, 1, 1, 1), "conv16_same<4,1,1,3,3,1,2>"),          # 64 x 48; tap 0 of a row's first pixel outside, tap 2 of its last
+    (124, 16, 80, 17, 11, (1, 1, 1, 1), "conv16_same<4,1,1,3,3,1,2>"),         # five output blocks under tiles of three
+    (31, 16, 48, 44, 32, (0, 1, 0, 1), "conv16_same<4,1,1,3,3,1,2>"),          # padded on the right only
+    (50, 32, 96, 45, 36, (1, 1, 1, 1), "conv16_same<4,1,1,2,3,1,2>"),          # tap 2 of a row's last pixel inside; tiles across images
+    (159, 32, 48, 45, 62, (1, 1, 1, 1), "conv16_same<4,1,1,3,3,1,2>"),         # ... 64 x 48
+    (150, 32, 80, 32, 30, (1, 1, 1, 0), "conv16_img<4,1,1,1,3,1,2>"),          # ... 64 x 16, tiles end with the image
+    (161, 32, 96, 16, 35, (0, 1, 1, 0), "conv16_same<4,1,1,3,3,1,2>"),         # ... padded on the left only, rows from the image's first
+    (110, 32, 48, 33, 64, (2, 1, 2, 1), "conv16_same<4,1,1,3,3,1,2>"),         # ... padded by two: taps 0 and 1 outside
+    (300, 32, 16, 44, 38, (1, 1, 1, 1), "conv16_same<4,1,2,1,3,1,2>"),         # ... one output block
+    (130, 32, 48, 32, 32, (1, 1, 1, 1), "conv16_same<4,1,1,1,3,1,2>"),         # ... just over 24 tiles per compute unit
+    (64, 48, 64, 32, 32, (1, 1, 1, 1), "conv16_split<4,2,2>"),                 # ... and below
+    (150, 16, 96, 45, 36, (1, 1, 1, 1), "conv16_mfma<4,1,1,2>"),               # ... one input block
+]
+
+
+@pytest.mark.parametrize("case", STRIDED_CASES)
+def test_conv2d_strided(case):
+    N, Ci, Co, H, W, pad, kernel = case
+    assert S.small_conv2d_kernel(N, Ci, Co, H, W, 3, 3, 2, pad, 16, 16) == kernel, case
+    rng = np.random.default_rng(8800 + N + W)
+    x = (rng.random((N, Ci, H, W), dtype=np.float32) * 2 - 1).astype(np.float32)
+    w = (rng.random((Co, Ci, 3, 3), dtype=np.float32) * 2 - 1).astype(np.float32)
+    assert_close(run_conv(x, w, 2, pad), O.conv2d(x, w, 2, pad), Ci * 9, f"strided {case}")
+
+
 PERSISTENT_CASES = [  # N, Ci, Co, H, W, k: enough images that a workgroup walks several of them
     (131, 16, 16, 32, 32, 3),      # 16 tiles per image, last image group ragged
     (160, 16, 16, 30, 30, 3),      # image size not a multiple of the tile: masked lanes in each image's last tile
