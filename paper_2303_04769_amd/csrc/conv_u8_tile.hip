@@ -391,8 +391,8 @@ Plan plan_tile(const LayerGeom &g)
 }
 
 // Where the register-only kernels of quant.hip stay the better ones: reductions of at most 20 chunks, which their short form
-// holds in registers whole (16 channels 32 x 32 x 100 images 5.3 us there, 6.6 here; 32 channels 16 x 16 x 100 4.0 / 4.9), and
-// where the two models below say so. They are fitted to 3300 measured pairs of layer and tile (us, before both
+// holds in registers whole (16 channels 32 x 32 x 100 images 5.3 us there, 6.6 here; 32 channels 16 x 16 x 100 4.0 / 4.9) unless they
+// are large (large_short), and where the two models below say so. They are fitted to 3300 measured pairs of layer and tile (us, before both
 // sides lost 3 to 12 % of their time by a shorter requantization; 3 to 8 % root mean square for
 // the tiles, 7 to 13 for the kernels there), w being the workgroups of the fullest compute unit:
 //   here   3.0 + a w + phases (b + c w) + chunks (d + e w)       a phase: kTG steps; a chunk: input brought in and two barriers
@@ -412,11 +412,29 @@ constexpr Rate kHere[kNumTiles] = {{2.88, 0.43, 0.38, 0.34, 0.51}, {2.56, 0.47, 
 constexpr Rate kThere[2][3] = {{{0.74, 0.34, 0.093, 0.016, 0}, {1.10, 0.36, 0.110, 0.013, 0}, {1.97, 0.55, 0.091, 0.042, 0}},
                                {{0.39, 0.086, 0.085, 0.054, 0}, {0.64, 0.062, 0.120, 0.043, 0}, {1.34, 0.060, 0.168, 0.052, 0}}};
 
+// Short reductions, 3x3 windows on 16 or 32 channels, that are better here all the same: there a workgroup has one, two or four
+// output blocks, by what divides their number, and reads its window, makes it signed and looks at the edge once more for each such
+// group, so the more groups and pixels the more that costs. By pixels x groups of the layer in thousands per compute unit, 210 random
+// layers of up to 2 M pixels, us here / there. Three, five, ... blocks (groups of one) on 32 channels: 8.5 / 7.7 at 0.78, 8.1 / 10.1 at
+// 1.16 (184 images, 112 channels out, 41x21 stride 2), 14.9 / 20.2 at 2.6, 33.9 / 54.1 at 8.4; on 16 channels 7.9 / 7.1 at 0.92, 10.4 /
+// 11.4 at 2.0, 15.9 / 21.8 at 4.0. On 32 channels with stride 1 also groups of four (16.5 / 15.8 at 0.85, 16.7 / 18.0 at 0.96), groups of two
+// (11.7 / 11.3 at 0.9, 13.3 / 14.7 at 1.5) and a single block (14.8 / 15.3 at 2.2); with stride 2 those are not (15.6 / 12.9 at 1.2, two
+// blocks), and on 16 channels groups of two and four take 1.0 to 1.2 times as long here. 70 fresh layers: 34 taken, 0.60 to 0.97 of
+// the time.
+bool large_short(const LayerGeom &g, long cus)
+{
+    const int nCob = g.Co / 16, group = nCob % 4 == 0 ? 4 : nCob % 2 == 0 ? 2 : 1;
+    if (g.kh != 3 || g.kw != 3) return false;
+    const long passes = (long)g.N * g.Ho * g.Wo * (nCob / group);
+    if (group == 1 && nCob > 1) return passes >= (g.Ci == 32 ? 940 : 1950) * cus;
+    return g.Ci == 32 && g.stride == 1 && passes >= (group == 4 ? 900 : group == 2 ? 1500 : 1950) * cus;
+}
+
 bool better_in_registers(const LayerGeom &g, const Plan &pl)
 {
     const int nCib = g.Ci / 16, nCob = g.Co / 16, taps = g.kh * g.kw;
-    if (nCib * taps <= 20) return true;
     const long cus = device_cus();
+    if (nCib * taps <= 20) return !large_short(g, cus);
     // workgroups of the fullest compute unit; many are as good as spread evenly
     auto fullest = [&](long wgs) { return wgs < 4 * cus ? (double)((wgs + cus - 1) / cus) : (double)wgs / cus; };
     const Tile &k = kTiles[pl.tile];

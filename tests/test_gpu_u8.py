@@ -152,6 +152,14 @@ TILE_CASES = [  # N, Ci, Co, H, W, kh, kw, stride, pad, zx, zw: windows through 
     (1, 368, 240, 1, 1, 3, 3, 1, (1, 1, 1, 1), 5, 250),        # one pixel on a number of blocks that is no multiple of four
     (2, 80, 80, 6, 5, 2, 7, 1, (1, 0, 3, 6), 77, 140),         # ... a wide window
 ]
+SHORT_TILE_CASES = [  # N, Ci, Co, H, W, stride, zx, zw: 3x3 on one or two input blocks, large enough for the LDS tiles
+    (66, 32, 80, 58, 13, 1, 17, 140),         # five output blocks
+    (100, 32, 208, 27, 28, 2, 128, 128),      # thirteen, stride 2
+    (90, 16, 144, 29, 22, 1, 128, 99),        # nine, a single input block
+    (72, 32, 256, 29, 28, 1, 200, 128),       # groups of four
+    (490, 32, 32, 28, 28, 1, 0, 131),         # a group of two
+    (700, 32, 16, 27, 27, 1, 90, 255),        # one block
+]
 TILE_CASES_ELSEWHERE = [TILE_CASES[7], TILE_CASES[8]]          # the register kernels are faster there
 
 
@@ -167,6 +175,18 @@ def test_conv_tiles(case):
     ref = Q.conv2d(x, w, s, pad, q)
     _same(_conv(x, w, s, pad, q, 16, 16, with_sums=True), ref, f"conv u8 tiles {case}")
     assert len(np.unique(ref)) > 8
+
+
+@pytest.mark.parametrize("case", SHORT_TILE_CASES)
+def test_conv_tiles_short_reductions(case):
+    """Large layers of a short reduction; the first and the last images recomputed."""
+    N, Ci, Co, H, W, s, zx, zw = case
+    r = _rng(23)
+    x, w = WL.u8_codes(r, (N, Ci, H, W)), WL.u8_codes(r, (Co, Ci, 3, 3))
+    q = _quant(Ci * 9, zx, zw)
+    got = _conv(x, w, s, (1, 1, 1, 1), q, 16, 16, with_sums=True)
+    part = np.r_[0:3, N - 3:N]
+    _same(got[part], Q.conv2d(x[part], w, s, (1, 1, 1, 1), q), f"conv u8 short {case}")
 
 
 @pytest.mark.parametrize("N,Ci,Co,H,W,k", [(64, 48, 64, 40, 40, 3), (64, 48, 32, 40, 41, 3), (90, 96, 144, 20, 21, 3), (30, 80, 16, 60, 61, 3)])

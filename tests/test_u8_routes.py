@@ -53,6 +53,17 @@ def test_tile_kernel_where_it_is_faster(tiles):
         assert not tiles(*layer), layer
 
 
+def test_tile_kernel_on_short_reductions(tiles):
+    """Large layers of nine or eighteen chunks, those of the parity test, and layers on the other side of each line."""
+    from test_gpu_u8 import SHORT_TILE_CASES
+    for N, Ci, Co, H, W, s, *_ in SHORT_TILE_CASES:
+        assert tiles(N, Ci, Co, H, W, 3, 3, s, P1), (N, Ci, Co)
+    for N, Ci, Co, H, W, s in [(60, 32, 80, 58, 13, 1), (80, 32, 208, 27, 28, 2), (80, 16, 144, 29, 22, 1), (60, 32, 256, 29, 28, 1),
+                               (480, 32, 32, 28, 28, 1), (490, 32, 32, 56, 56, 2), (650, 32, 16, 27, 27, 1), (700, 16, 32, 27, 27, 1)]:
+        assert not tiles(N, Ci, Co, H, W, 3, 3, s, P1), (N, Ci, Co)
+    assert not tiles(90, 16, 144, 29, 22, 3, 1, 1, (1, 1, 0, 0)) and not tiles(66, 32, 80, 58, 13, 3, 3, 1, P1, sums=None)
+
+
 def test_tile_kernel_conditions(tiles):
     layer = (64, 128, 128, 28, 28, 3, 3, 1, P1)
     assert not tiles(*layer, out=0x1008) and not tiles(*layer, amax=0) and not tiles(*layer, sums=None)
