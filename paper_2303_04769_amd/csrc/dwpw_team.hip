@@ -5,13 +5,15 @@
 // stage there, some 4 us a block, while the rest of the chip idles. Here workgroup t owns channel block t: it computes the
 // pointwise result of that block (its share of the filters is one sixteenth), then, as a depthwise layer maps channel
 // blocks on their own, the next block's depthwise layer on it, and hands the result to the team. So a block costs one
-// hand-over through memory, one reduction of at most 16 steps split over the workgroup's four waves, and one window pass.
-// The eleven blocks and the head of the depthwise-separable CNN, one image: 50 -> 26.0 us and 2 for the launch in front, of which
-// some 1.3 us a block are the way of a value to memory and back; the network's call 66.8 -> 42.2 (two images 65.3 -> 40.9 without
-// the packing of its input). All of a team on one of the chip's eight dies gains nothing (30.1 against 28.9 us at the time), nor
-// does waiting before the first look (0.07 to 2.9 us slower): values are looked at past the dies' caches either way. What a wave
-// needs for its next stage besides results -- taps, window entries, the layer's numbers -- it gets ready while it would be
-// waiting (28.9 -> 26.0 us).
+// hand-over through memory, one reduction of at most 16 steps and one window pass, a wave per 16 pixels. All sums are those of
+// dwpw_run, in its order: the results are the same bits, however many images there are.
+// The depthwise-separable CNN, one image, without the packing of its input: 64.0 -> 45.8 us, two images 65.3 -> 46.4, the launch in
+// front (2 us) among it. Some 1.3 us a block are the way of a value to memory and back. With the reduction split over the four waves
+// it was 39.8, but sums in another order: after 26 layers two logits near zero can then differ
+// by more than a few 1e-6 of them between an image on its own and in a batch.
+// All of a team on one of the chip's eight dies gained nothing (30.1 against 28.9 us for the kernel at the time), nor did waiting
+// before the first look (0.07 to 2.9 us slower): values are looked at past the dies' caches either way. What a wave needs for its
+// next stage besides results -- taps, window entries, the layer's numbers -- it gets ready while it would be waiting (28.9 -> 26.0).
 //
 // The hand-over has no flags and no barrier: a word of the exchange area is "not there yet" while it holds kNotYet, a NaN
 // with all bits set, which no result is stored as, and the launch in front fills the area with it. A consumer reads the
@@ -19,7 +21,7 @@
 // value that is there is final. Nothing else is communicated, so nothing has to be ordered.
 //
 // Every wait ends: a workgroup needs only results of its own team, and the launch is small enough for all teams to be on
-// the chip together (dwpw_team_eligible). Should they not get there all the same, a wave gives up after some seconds, hands
+// the chip together (dwpw_team_exchange). Should they not get there all the same, a wave gives up after some seconds, hands
 // nothing on, and the outputs of that image are NaN.
 #include "small_internal.h"
 
@@ -31,7 +33,7 @@ namespace {
 constexpr int kTeamWaves = 4;
 constexpr int kTeamThreads = kTeamWaves * 64;
 constexpr int kTeamMax = 16;              // workgroups of a team = channel blocks of the widest tensor
-constexpr int kTeamItems = 8;             // (input block, pixel group) pairs that a wave has in registers
+constexpr int kTeamItems = 16;            // (input block, pixel group) pairs that a wave has in registers
 constexpr unsigned kNotYet = ~0u;
 constexpr unsigned kMaxTries = 1u << 21;  // a try takes at least a round trip to memory, some 0.6 us
 
@@ -40,7 +42,6 @@ struct TeamBlock {
     int dw_relu, pw_relu;
     int nCbi, nCbo;
     int Hi, Wi, Ho, Wo, stride, pt, pl;
-    int log_kw;                           // the pointwise reduction is split over 1 << log_kw waves, the pixel groups over the rest
     FastDiv by_Wo;
 };
 
@@ -87,24 +88,23 @@ __device__ __forceinline__ floatx4 team_relu(floatx4 v)
     return v;
 }
 
-// A wave's part of the pointwise reduction: NI items, input blocks k0, k0 + kw, ... (J of them) of pixel groups g0, g0 + gw, ...
-// Filters and values are all requested at once; the sums of a pixel group go to part[group][lane].
+// A wave's part of a pointwise layer: NI items, the J input blocks of pixel groups g0, g0 + kTeamWaves, ... Filters and values are all
+// requested at once; the sums of a pixel group, in the order of dwpw_run, go to part[group][lane].
 template <int NI>
-__device__ __forceinline__ void team_reduce(const float *filt, GlobalBytes x, int HW, int p, int q, int lane, int k0, int kw, int J,
-                                            int g0, int gw, floatx4 *part, bool &lost)
+__device__ __forceinline__ void team_reduce(const float *filt, GlobalBytes x, int HW, int p, int q, int lane, int J, int g0,
+                                            floatx4 *part, bool &lost)
 {
     float a[NI][4];
     unsigned off[NI];
     {
-        int ci = k0, g = g0, j = 0;
+        int ci = 0, g = g0;
 #pragma unroll
         for (int n = 0; n < NI; ++n) {
             const float *f = filt + (size_t)ci * 256 + q * 64 + p;
 #pragma unroll
             for (int r = 0; r < 4; ++r) a[n][r] = f[r * 16];
             off[n] = (unsigned)(ci * HW + min(g * 16 + p, HW - 1)) * 64 + q * 16;      // lanes past the image: its last pixel again
-            ci += kw;
-            if (++j == J) { j = 0; ci = k0; g += gw; }
+            if (++ci == J) { ci = 0; g += kTeamWaves; }
         }
     }
     unsigned long long v[NI][2];
@@ -130,7 +130,7 @@ __device__ __forceinline__ void team_reduce(const float *filt, GlobalBytes x, in
         if (++j == J) {
             part[g * 64 + lane] = acc;
             acc = floatx4{0.f, 0.f, 0.f, 0.f};
-            j = 0; g += gw;
+            j = 0; g += kTeamWaves;
         }
     }
 }
@@ -148,7 +148,7 @@ __global__ void __launch_bounds__(kTeamThreads) dwpw_team(TeamArgs args)
     float *out = ka->out;
     GlobalBytes x = (GlobalBytes)(ka->exchange + (size_t)img * ka->exchange_bytes);
 
-    // LDS: [a pixel of zeros][this workgroup's channel block of the present tensor: pixel, quad][partial sums, two sets in turn]
+    // LDS: [a pixel of zeros][this workgroup's channel block of the present tensor: pixel, quad][sums of the next, two sets in turn]
     extern __shared__ floatx4 lds[];
     __shared__ int gave_up;
     floatx4 *plane = lds + 4;
@@ -224,31 +224,23 @@ __global__ void __launch_bounds__(kTeamThreads) dwpw_team(TeamArgs args)
 
         // ---------------- pointwise: exchange area -> partial sums -> plane
         if (t < nCbo) {
-            const int log_kw = ka->block[b].log_kw, kw = 1 << log_kw, gw = kTeamWaves >> log_kw;
-            const int k0 = w & (kw - 1), g0 = w >> log_kw;
-            const int J = (nCbi - k0 + kw - 1) >> log_kw;
-            const int items = g0 < ng ? J * ((ng - g0 + gw - 1) >> (2 - log_kw)) : 0;
+            const int items = w < ng ? nCbi * ((ng - w + kTeamWaves - 1) / kTeamWaves) : 0;
             const float *filt = ka->block[b].pw + (size_t)t * nCbi * 256;
-            floatx4 *mine = part + k0 * ng * 64;
             switch (items) {
-                case 1: team_reduce<1>(filt, x, HW, p, q, lane, k0, kw, J, g0, gw, mine, lost); break;
-                case 2: team_reduce<2>(filt, x, HW, p, q, lane, k0, kw, J, g0, gw, mine, lost); break;
-                case 3: team_reduce<3>(filt, x, HW, p, q, lane, k0, kw, J, g0, gw, mine, lost); break;
-                case 4: team_reduce<4>(filt, x, HW, p, q, lane, k0, kw, J, g0, gw, mine, lost); break;
-                case 5: team_reduce<5>(filt, x, HW, p, q, lane, k0, kw, J, g0, gw, mine, lost); break;
-                case 6: team_reduce<6>(filt, x, HW, p, q, lane, k0, kw, J, g0, gw, mine, lost); break;
-                case 7: team_reduce<7>(filt, x, HW, p, q, lane, k0, kw, J, g0, gw, mine, lost); break;
-                case 8: team_reduce<8>(filt, x, HW, p, q, lane, k0, kw, J, g0, gw, mine, lost); break;
+#define SMALL_TEAM_CASE(NI_) case NI_: team_reduce<NI_>(filt, x, HW, p, q, lane, nCbi, w, part, lost); break;
+                SMALL_TEAM_CASE(1) SMALL_TEAM_CASE(2) SMALL_TEAM_CASE(3) SMALL_TEAM_CASE(4) SMALL_TEAM_CASE(5) SMALL_TEAM_CASE(6)
+                SMALL_TEAM_CASE(7) SMALL_TEAM_CASE(8) SMALL_TEAM_CASE(9) SMALL_TEAM_CASE(10) SMALL_TEAM_CASE(11) SMALL_TEAM_CASE(12)
+                SMALL_TEAM_CASE(13) SMALL_TEAM_CASE(14) SMALL_TEAM_CASE(15) SMALL_TEAM_CASE(16)
+#undef SMALL_TEAM_CASE
                 default: break;
             }
             if (lost && lane == 0) gave_up = 1;
-            __syncthreads();                            // the partial sums are complete, and plane has been read
+            __syncthreads();                            // plane has been read
             lost = __builtin_amdgcn_readfirstlane(gave_up) != 0;
             const int pw_relu = ka->block[b].pw_relu;
             const bool to_memory = b + 1 == n_blocks && head == nullptr;
             for (int g = w; g < ng; g += kTeamWaves) {
                 floatx4 v = part[g * 64 + lane];
-                for (int k = 1; k < kw; ++k) v += part[(k * ng + g) * 64 + lane];
                 if (pw_relu) v = team_relu(v);
                 const int m = g * 16 + p;
                 if (m < HW) {
@@ -260,8 +252,7 @@ __global__ void __launch_bounds__(kTeamThreads) dwpw_team(TeamArgs args)
                     }
                 }
             }
-            // One pixel group, here and in the next block: wave 0 wrote plane and alone reads it. The other set of partial sums is
-            // next, so a wave that runs ahead, past at most one more barrier, writes nothing that is still read.
+            // One pixel group, here and in the next block: wave 0 wrote plane and alone reads it. The other set of sums is next, so a wave that runs ahead, past at most one more barrier, writes nothing that is still read.
             if (ng > 1 || (b + 1 < n_blocks && d_ng > 1)) __syncthreads();
             else {
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -273,49 +264,43 @@ __global__ void __launch_bounds__(kTeamThreads) dwpw_team(TeamArgs args)
     }
 
     // ---------------- the network's head: mean over the pixels, fully connected layer; every workgroup its channels' part
-    if (head != nullptr && w == 0) {
+    if (head != nullptr) {
         const int nCb = ka->block[n_blocks - 1].nCbo, C = nCb * 16;
         const int HW = ka->block[n_blocks - 1].Ho * ka->block[n_blocks - 1].Wo;
         const int Co = ka->head_Co, Cob = ka->head_Cob;
-        if (t < nCb && !lost) {
+        if (w == 0 && t < nCb && !lost && lane < 16) {          // lane: a channel
             const float *act = reinterpret_cast<const float *>(plane);
             float sum = 0.f;
-            for (int m = q; m < HW; m += 4) sum += act[m * 16 + p];
-            sum += __shfl_xor(sum, 16, 64);
-            sum += __shfl_xor(sum, 32, 64);             // lane: channel p
-            float mine = 0.f;
-#pragma unroll
-            for (int o = 0; o < 16; ++o) {
-                if (o < Co) {
-                    float v = sum * head[((size_t)(o / Cob) * C + t * 16 + p) * Cob + o % Cob];
-#pragma unroll
-                    for (int d = 8; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-                    mine = lane == o ? v : mine;
-                }
+            for (int m = 0; m < HW; ++m) sum += act[m * 16 + lane];
+            for (int o = 0; o < Co; ++o) {
+                const float v = fmaf(sum, head[((size_t)(o / Cob) * C + t * 16 + lane) * Cob + o % Cob], 0.f);
+                __hip_atomic_store((GlobalWords)(x + (unsigned)(o * C + t * 16 + lane) * 4), team_word(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            if (lane < Co)
-                __hip_atomic_store((GlobalWords)(x + (unsigned)(t * 16 + lane) * 4), team_word(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        if (t == 0) {
-            const int o = min(p, Co - 1);
-            unsigned v[4];
-            for (unsigned tries = 0;; ++tries) {
-                bool there = true;
+        if (t == 0) {                                   // a wave per output; lane: a channel of 64, summed as dwpw_run does
+            for (int o = w; o < Co; o += kTeamWaves) {
+                unsigned v[kTeamMax / 4];
+                for (unsigned tries = 0;; ++tries) {
+                    bool there = true;
 #pragma unroll
-                for (int k = 0; k < 4; ++k)             // lane: output p, channel blocks q, q + 4, ...
-                    v[k] = __hip_atomic_load((GlobalWords)(x + (unsigned)(min(q + 4 * k, nCb - 1) * 16 + o) * 4), __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
+                    for (int k = 0; k < kTeamMax / 4; ++k)
+                        v[k] = __hip_atomic_load((GlobalWords)(x + (unsigned)(o * C + min(k * 64 + lane, C - 1)) * 4), __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) there = there && v[k] != kNotYet;
-                if (__ballot(!there) == 0) break;
-                if (lost || tries >= kMaxTries) { lost = true; break; }
+                    for (int k = 0; k < kTeamMax / 4; ++k) there = there && v[k] != kNotYet;
+                    if (__ballot(!there) == 0) break;
+                    if (lost || tries >= kMaxTries) { lost = true; break; }
+                }
+                float sum = 0.f;
+#pragma unroll
+                for (int k = 0; k < kTeamMax / 4; ++k) {
+                    float u = k * 64 + lane < C ? __builtin_bit_cast(float, v[k]) : 0.f;
+#pragma unroll
+                    for (int d = 32; d > 0; d >>= 1) u += __shfl_xor(u, d, 64);
+                    sum += u;
+                }
+                if (lane == 0) out[(size_t)img * Co + o] = lost ? __builtin_nanf("") : sum * (1.f / (float)HW);
             }
-            float sum = 0.f;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) sum += q + 4 * k < nCb ? __builtin_bit_cast(float, v[k]) : 0.f;
-            sum += __shfl_xor(sum, 16, 64);
-            sum += __shfl_xor(sum, 32, 64);
-            if (lane < Co) out[(size_t)img * Co + lane] = lost ? __builtin_nanf("") : sum * (1.f / (float)HW);
         }
     }
 }
@@ -332,11 +317,10 @@ int team_size(const DwpwRunBlock *b, int n)
     for (int i = 0; i < n; ++i) most = std::max(most, b[i].Cout);
     return most / 16;
 }
-int team_log_kw(int nCbi) { return nCbi >= 4 ? 2 : (nCbi >= 2 ? 1 : 0); }
 int team_groups(const DwpwRunBlock &b) { return (b.Ho * b.Wo + 15) / 16; }
-size_t team_exchange_bytes(const DwpwRunBlock *b, int n, bool head)
+size_t team_exchange_bytes(const DwpwRunBlock *b, int n, int head_Co)
 {
-    size_t words = head ? (size_t)kTeamMax * 16 : 0;
+    size_t words = (size_t)b[n - 1].Cout * head_Co;
     for (int i = 0; i < n; ++i) words += (size_t)b[i].Cin * b[i].Ho * b[i].Wo;
     return words * 4;
 }
@@ -346,17 +330,17 @@ void team_lds(const DwpwRunBlock *b, int n, int &plane, int &part)
     part = 0;
     for (int i = 0; i < n; ++i) {
         plane = std::max(plane, b[i].Ho * b[i].Wo * 64);
-        part = std::max(part, team_groups(b[i]) << (10 + team_log_kw(b[i].Cin / 16)));
+        part = std::max(part, team_groups(b[i]) << 10);
     }
 }
 
 }  // namespace
 
 // A workgroup of a team waits for the others, so all of them have to find a place on the chip whatever else runs there. A compute
-// unit holds three (registers, LDS); kernels that wait for nobody make room in the end; and with an eighth of the compute units'
-// number per launch, 24 launches that wait, more than the hardware runs queues at a time, fit together. A stream may be confined
-// to some of the compute units: those count.
-size_t dwpw_team_exchange(const DwpwRunBlock *blocks, int n_blocks, int N, bool head, hipStream_t s)
+// unit holds two (registers); kernels that wait for nobody make room in the end; and with an eighth of the compute units' number per
+// launch, 16 launches that wait fit together, four times the hardware queues that a process has unless told otherwise. A stream may
+// be confined to some of the compute units: those count.
+size_t dwpw_team_exchange(const DwpwRunBlock *blocks, int n_blocks, int N, int head_Co, hipStream_t s)
 {
     const int T = team_size(blocks, n_blocks);
     if (T > kTeamMax || T < 2 || 8L * N * T > device_cus()) return 0;
@@ -369,14 +353,12 @@ size_t dwpw_team_exchange(const DwpwRunBlock *blocks, int n_blocks, int N, bool 
     for (uint32_t m : mask) cus += __builtin_popcount(m);
     if (8L * N * T > cus) return 0;
     for (int i = 0; i < n_blocks; ++i) {
-        const int nCbi = blocks[i].Cin / 16, log_kw = team_log_kw(nCbi), gw = kTeamWaves >> log_kw;
-        const int J = (nCbi + (1 << log_kw) - 1) >> log_kw;
-        if (J * ((team_groups(blocks[i]) + gw - 1) / gw) > kTeamItems) return 0;
+        if (blocks[i].Cin / 16 * ((team_groups(blocks[i]) + kTeamWaves - 1) / kTeamWaves) > kTeamItems) return 0;
     }
     int plane, part;
     team_lds(blocks, n_blocks, plane, part);
     if (plane + 2 * part > 52 * 1024) return 0;
-    return (size_t)N * team_exchange_bytes(blocks, n_blocks, head);
+    return (size_t)N * team_exchange_bytes(blocks, n_blocks, head_Co);
 }
 
 hipError_t launch_dwpw_team(const float *in, float *out, const DwpwRunBlock *blocks, int n_blocks, int N, const DwpwRunHead &head,
@@ -388,7 +370,7 @@ hipError_t launch_dwpw_team(const float *in, float *out, const DwpwRunBlock *blo
     a.n_blocks = n_blocks;
     a.team = team_size(blocks, n_blocks);
     a.by_team = make_fastdiv(a.team);
-    a.exchange_bytes = (unsigned)team_exchange_bytes(blocks, n_blocks, head.filt != nullptr);
+    a.exchange_bytes = (unsigned)team_exchange_bytes(blocks, n_blocks, head.filt ? head.Co : 0);
     team_lds(blocks, n_blocks, a.plane_bytes, a.part_bytes);
     for (int i = 0; i < kDwpwChainMaxBlocks; ++i) {
         const DwpwRunBlock &b = blocks[i < n_blocks ? i : n_blocks - 1];
@@ -396,7 +378,6 @@ hipError_t launch_dwpw_team(const float *in, float *out, const DwpwRunBlock *blo
         d.dw = b.dw; d.pw = b.pw; d.dw_relu = b.dw_relu; d.pw_relu = b.pw_relu;
         d.nCbi = b.Cin / 16; d.nCbo = b.Cout / 16;
         d.Hi = b.Hi; d.Wi = b.Wi; d.Ho = b.Ho; d.Wo = b.Wo; d.stride = b.stride; d.pt = b.pt; d.pl = b.pl;
-        d.log_kw = team_log_kw(d.nCbi);
         d.by_Wo = make_fastdiv(b.Wo);
     }
     const unsigned quads = (unsigned)((size_t)N * a.exchange_bytes / 16);

@@ -1313,9 +1313,9 @@ int walk(const small_layer *L, int nL, int N, int C0, int H0, int W0, NetPlan &p
                         const float *rin = ptr(l.src);
                         float *rout = ptr(dr.head ? L[dr.head].dst : (dr.rename ? ldw.dst : lpw.dst));
                         // few images: a team of workgroups for each, where the memory of a slot that the run leaves unwritten
-                        // (and that nobody reads behind it) holds what they exchange; depthwise-separable CNN 64.0 -> 39.8 us
-                        // at one image, 65.3 -> 40.9 at two; from three on (65.7) dwpw_team_exchange says no
-                        const size_t need = dwpw_team_exchange(dr.block, dr.n, N, dr.head != 0, s);
+                        // (and that nobody reads behind it) holds what they exchange; depthwise-separable CNN 64.0 -> 45.8 us
+                        // at one image, 65.3 -> 46.4 at two; from three on (65.7) dwpw_team_exchange says no
+                        const size_t need = dwpw_team_exchange(dr.block, dr.n, N, dr.head ? L[dr.head].Co : 0, s);
                         char *scratch = nullptr;
                         for (int b = 0; need && !scratch && b < dr.n; ++b) {
                             const int ids[2] = {L[dr.dw_idx[b]].dst, L[dr.pw_idx[b]].dst};

@@ -296,7 +296,7 @@ hipError_t launch_dwpw_run(const float *in, float *out, const DwpwRunBlock *bloc
                            hipStream_t s);
 // The same run on few images, a team of workgroups per image (dwpw_team.hip), two launches. dwpw_team_exchange: the bytes of
 // scratch memory it needs (16-byte aligned, not overlapping in, out or each other), 0 where it does not take the run.
-size_t dwpw_team_exchange(const DwpwRunBlock *blocks, int n_blocks, int N, bool head, hipStream_t s);
+size_t dwpw_team_exchange(const DwpwRunBlock *blocks, int n_blocks, int N, int head_Co, hipStream_t s);
 hipError_t launch_dwpw_team(const float *in, float *out, const DwpwRunBlock *blocks, int n_blocks, int N, const DwpwRunHead &head,
                             void *exchange, hipStream_t s);
 

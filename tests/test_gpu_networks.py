@@ -1153,7 +1153,7 @@ def test_depthwise_pointwise_runs_by_a_team(case):
         assert np.abs(ref).max() > 1e-3
         first = O.dwconv2d(O.pool2d(np.maximum(x, 0), (4, 4), 4, (0, 0, 0, 0), "max"), ws[0], spec[0][1], spec[0][2])
         first = O.pack(O.relu(first) if spec[0][3][0] else first, 16).reshape(N, -1)
-        per_image = sum(L.Co * L.Ho * L.Wo for L in net.layers if L.op == "dw") + (256 if head else 0)
+        per_image = sum(L.Co * L.Ho * L.Wo for L in net.layers if L.op == "dw") + spec[-1][0] * head
         slot0 = pn.workspace(N)[0].cpu().numpy()
         there = all(np.allclose(slot0[n * per_image:][:first[n].size], first[n], rtol=1e-4, atol=1e-5) for n in range(N))
         assert there == team
@@ -1163,6 +1163,16 @@ def test_depthwise_pointwise_runs_by_a_team(case):
         out.t.zero_()
         graph.replay()
         assert np.array_equal(out.check(), got)
+
+
+@pytest.mark.parametrize("head", [0, 2, 16])
+def test_depthwise_pointwise_run_by_a_team_in_the_same_order(head):
+    """An image on its own, by a team, gives the bits that it gives in a batch, by a single workgroup."""
+    net = _team_net(32, 12, 12, _DSEP, head=head)
+    x, ws = WL.network_tensors(net, 3, 9500)
+    batch = _run(net, x, ws)
+    for n in range(3):
+        assert np.array_equal(_run(net, x[n:n + 1], ws)[0], batch[n])
 
 
 def test_depthwise_pointwise_run_by_a_team_on_nans():
