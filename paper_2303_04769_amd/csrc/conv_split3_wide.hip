@@ -20,6 +20,8 @@
 // 23 x 23, 13 images 95 / 67, 160 channels 24 x 24, 29 images 68 / 46.
 #include "small_internal.h"
 
+#include <algorithm>
+
 namespace small {
 namespace {
 
@@ -266,7 +268,7 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
             }
         }
     };
-    unsigned long long bad = 0;                                // rounds of tiles whose sums here are not finite; bit 63: some later one's
+    unsigned long long bad = 0;                                // rounds of tiles whose sums here are not finite (kMaxRounds bits)
     int round = 0;
 
     // the chunk behind the current one: of this tile or the first of the next
@@ -366,7 +368,7 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
                     most = __builtin_elementwise_maximum(most, __builtin_elementwise_maximum(__builtin_fabsf(acc[wm][wn].x), __builtin_fabsf(acc[wm][wn].y)));
                     most = __builtin_elementwise_maximum(most, __builtin_elementwise_maximum(__builtin_fabsf(acc[wm][wn].z), __builtin_fabsf(acc[wm][wn].w)));
                 }
-            if (__ballot(!(most < __builtin_inff()))) bad |= 1ull << min(round, 63);
+            if (__ballot(!(most < __builtin_inff()))) bad |= 1ull << round;
             else put(tile, acc);
             ++round;
             if (!ok2) break;
@@ -384,7 +386,7 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
     // pixels, filter values [4g + r][p]), or, with such a value in the filter, plain fp32: a tap outside the image does not count,
     // whatever its weight (an infinite one times the zero read there would).
     for (int t = (int)xcd_contiguous(blockIdx.x, gridDim.x), rnd = 0; bad && t < a.n_tiles; t += (int)gridDim.x, ++rnd) {
-        if (!(bad >> min(rnd, 63) & 1)) continue;
+        if (!(bad >> rnd & 1)) continue;
         const int steps = a.nCib * kTaps, mt = quotient(a.dCt, t), m0 = mt * TM + wave_m * WM * 16;
         const int cob_w = (t - mt * a.n_cot) * NCT + wave_n * WN;
         int ih0[WM], iw0[WM], at0[WM];
@@ -468,6 +470,10 @@ constexpr int kWM = 4, kWN = 4, kWVM = 4, kWVN = 1, kEntries = 384;
 constexpr int kTM = 16 * kWM * kWVM, kNCT = kWN * kWVN;
 constexpr size_t kLds = (size_t)2 * kNCT * 3 * 1024 + (size_t)20 * (kEntries + 1) * 16;
 constexpr int kStrip = 16;             // output columns of a strip, at most
+// Tiles that a workgroup walks over, at most: one bit of `bad` for each. A tile that is not finite must be computed again on its own,
+// not with others that are stored already, for its result may stand in the residual's place. Layers of more rounds get a second,
+// third, ... set of workgroups, which start where others end (64 channels 56x56, 1400 images: 34 + 34 rounds instead of 67).
+constexpr int kMaxRounds = 64;
 
 struct WidePlan { bool ok; int strips, Ws; long tiles; };
 
@@ -529,8 +535,8 @@ hipError_t launch_conv_split3_wide(const float *in, const float *filt, float *ou
     a.in_bytes = (unsigned)((size_t)g.N * g.Ci * g.H * g.W * 4); a.filt_bytes = (unsigned)((size_t)g.Co * g.Ci * 36);
     a.dHoWs = make_fastdiv(a.HoWs); a.dWs = make_fastdiv(a.Ws); a.dWv = make_fastdiv(a.Wv); a.dHv = make_fastdiv(a.Hv);
     a.dStrips = make_fastdiv(a.strips); a.dCt = make_fastdiv(a.n_cot);
-    const long cus = device_cus();
-    hipLaunchKernelGGL((conv16_split3_wide<kWM, kWN, kWVM, kWVN, kEntries>), dim3((unsigned)(pl.tiles < cus ? pl.tiles : cus)), dim3(256), kLds, s, a);
+    const long cus = device_cus(), sets = (pl.tiles + kMaxRounds * cus - 1) / (kMaxRounds * cus);
+    hipLaunchKernelGGL((conv16_split3_wide<kWM, kWN, kWVM, kWVN, kEntries>), dim3((unsigned)std::min(pl.tiles, sets * cus)), dim3(256), kLds, s, a);
     return hipGetLastError();
 }
 

@@ -605,6 +605,50 @@ def test_three_part_wide_tiles_epilogues():
     assert_close(got[[0, 6, 8, N - 1]], ref[[0, 1, 3, 4]], 9 * C, "three-part wide tiles with epilogues")
 
 
+def test_three_part_wide_tiles_many_rounds():
+    """So many tiles that a workgroup walks over more than 63 if there is one for each compute unit, the sum in the residual's place:
+    values whose parts overflow, in the first and in some of the last images, make waves compute tiles again, and the residual is added
+    once to every tile all the same, those that the same waves had stored before among them."""
+    from workloads.nets import Layer, Network, IN, OUT
+    N, Ci, Co, H, p, z = 1400, 32, 64, 56, (1, 1, 1, 1), (0, 0, 0, 0)
+    net = Network("three_part_wide_rounds", Ci, H, H)
+    net.wshapes = [((Co, Ci, 1, 1), Ci), ((Co, Ci, 3, 3), 9 * Ci)]
+    net.layers = [
+        Layer("conv", Ci, Co, H, H, 1, 1, 1, z, src=IN, dst=0, w=0),
+        Layer("conv", Ci, Co, H, H, 3, 3, 1, p, src=IN, dst=1, w=1),
+        Layer("add", Co, Co, H, H, src=1, src2=0, dst=0),
+        Layer("maxpool", Co, Co, H, H, 1, 1, 1, z, src=0, dst=OUT),
+    ]
+    assert S.small_conv2d_kernel(N, Ci, Co, H, H, 3, 3, 1, p, 16, 16).startswith("conv16_split3_wide")
+    assert N * H * H > 64 * 256 * 256
+    _, ws = WL.network_tensors(net, 1, 6400)
+    pn = S.PackedNetwork(net, ws, DEV)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(6401)
+    x = torch.rand(N, Ci // 16, H, H, 16, generator=g, device=DEV) * 2 - 1
+    large = [0, 1330, 1365, 1399]
+    outs = []
+    for k in range(2):
+        if k:
+            x[large, 1, 20, 11, 5] = 1e31
+        out = torch.empty(pn.out_elems(N), dtype=torch.float32, device=DEV)
+        pn.run_opt(x.reshape(-1), out, N, S.SMALL_RUN_RESIDENT_OFF)
+        outs.append(out.reshape(N, Co // 16, H, H, 16))
+    plain = x[[0, 700, 1365]].cpu().numpy().transpose(0, 1, 4, 2, 3).reshape(3, Ci, H, H)
+    ref = O.add(O.conv2d(plain, ws[1], 1, p), O.conv2d(plain, ws[0], 1, z))
+    got = outs[1][[0, 700, 1365]].cpu().numpy().transpose(0, 1, 4, 2, 3).reshape(ref.shape)
+    for n in range(3):
+        assert_close(got[n], ref[n], 9 * Ci, "image with a large value" if n != 1 else "image without")
+    assert np.abs(ref[0]).max() > 1e30 and np.abs(ref[2]).max() > 1e30
+    near = torch.zeros(N, 1, H, H, 1, dtype=torch.bool, device=DEV)
+    near[large, :, 19:22, 10:13] = True
+    diff = ((outs[1] - outs[0]).abs().masked_fill_(near, 0.0)).amax(dim=(1, 2, 3, 4)).cpu().numpy()
+    # two roundings of sums of 9 Ci products each, and of the residual's, to the largest of the values
+    bound = (9 * Ci + Ci + 2) * 2.0 ** -23 * float(outs[0].abs().max())
+    worst = float(diff.max())
+    assert worst <= bound, (int(diff.argmax()), worst)
+
+
 def _run_both(net, x, ws):
     """Blocked outputs of small_pack + small_network_run and of small_network_run_plain on the same input."""
     N = x.shape[0]
