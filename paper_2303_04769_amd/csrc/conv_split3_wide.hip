@@ -77,6 +77,15 @@ __device__ __forceinline__ void split_piece(Pair &s)
     }
 }
 
+// The compiler does not see matrix instructions in the asm statements and puts in no wait states round them: what writes their operands
+// or reads their results stands on the other side of one of these, whose operands keep it there. 1: two wait states, from a vector
+// instruction to a matrix instruction; 15: sixteen, from a result to its use, which needs at most eleven.
+template <int STATES>
+__device__ __forceinline__ void wait_states(floatx4 (&u)[4], floatx4 (&v)[4])
+{
+    asm volatile("s_nop %8" : "+a"(u[0]), "+a"(u[1]), "+a"(u[2]), "+a"(u[3]), "+a"(v[0]), "+a"(v[1]), "+a"(v[2]), "+a"(v[3]) : "n"(STATES));
+}
+
 template <int WM, int WN, int WVM, int WVN, int ENTRIES>
 __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
 {
@@ -222,9 +231,11 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
     floatx4 acc[WM][WN], low[WM][WN];
     auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int wm = 0; wm < WM; ++wm)
+        for (int wm = 0; wm < WM; ++wm) {
 #pragma unroll
             for (int wn = 0; wn < WN; ++wn) acc[wm][wn] = low[wm][wn] = floatx4{0.f, 0.f, 0.f, 0.f};
+            wait_states<1>(acc[wm], low[wm]);
+        }
     };
     clear();
 
@@ -357,7 +368,9 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
         par ^= 1;
         bpar ^= 1;
         if (t2 != tile) {
-            asm volatile("s_nop 15\n\ts_nop 15");
+            wait_states<15>(acc[0], low[0]);
+#pragma unroll
+            for (int wm = 1; wm < WM; ++wm) wait_states<0>(acc[wm], low[wm]);      // (behind it, as volatile statements stay in order)
             float most = 0.f;                                  // the largest magnitude, or NaN
 #pragma unroll
             for (int wm = 0; wm < WM; ++wm)
@@ -379,6 +392,8 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
         ch = ch2; t2 = t3; ch2 = ch3; lanes = lanes2; block = block2;
         each<3>([&](auto s) { fb[0][s.value] = b_get(0, 0, s.value, bpar); });
         each<WN>([&](auto wn) { each<3>([&](auto s) { fa[0][wn.value][s.value] = fa[1][wn.value][s.value]; }); });
+#pragma unroll
+        for (int wn = 0; wn < WN; ++wn) asm volatile("s_nop 1" : "+a"(fa[0][wn][0]), "+a"(fa[0][wn][1]), "+a"(fa[0][wn][2]));
     }
 
     // ---- the tiles whose sums were not all finite: some value there, or a sum, is not finite or not so at the scale of the parts.
