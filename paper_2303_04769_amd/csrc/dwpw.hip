@@ -303,6 +303,13 @@ __global__ void __launch_bounds__(OWN ? 512 : 256) dwpw16_img(DwPwArgs a)
         cb = 0;
 
         // ---- STORE phase of this tile
+        // (the compiler does not see the matrix instructions in the statements above: the ten wait states from the last one's result to
+        // its use stand in one that the results pass through, the others' statements behind it)
+#pragma unroll
+        for (int j = WN - 1; j >= 0; --j) {
+            if (j == WN - 1) asm volatile("s_nop 10" : "+v"(acc[j]));
+            else asm volatile("" : "+v"(acc[j]));
+        }
 #pragma unroll
         for (int j = 0; j < WN; ++j) {
             const int cob = cob0 + j;

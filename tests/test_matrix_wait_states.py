@@ -12,7 +12,7 @@ from paper_2303_04769_amd import build
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 RESULT = 11          # wait states from an instruction of eight passes (16x16x32 bf16, 16x16x4 fp32) to another kind's use of its result
-SOURCES = {"conv_split3_wide.hip": 864}          # and how many such instructions there are at least
+SOURCES = {"conv_split3_wide.hip": 864, "dwpw.hip": 350}          # and how many such instructions there are at least
 OPERAND = 2          # from a vector instruction's result to a matrix instruction that reads it
 
 
@@ -101,3 +101,8 @@ def test_wait_states(source, number, tmp_path):
                    stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
     n, found = faults(open(out).read())
     assert n >= number and not found, found[:5]
+
+
+def test_every_file_with_such_instructions_is_read():
+    files = [f for f in os.listdir(build.CSRC) if re.search(r'asm[^;]*"v_mfma', open(os.path.join(build.CSRC, f)).read())]
+    assert sorted(files) == sorted(SOURCES)
