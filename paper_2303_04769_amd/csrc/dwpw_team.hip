@@ -20,9 +20,12 @@
 // values it needs, each in agent scope (which goes past the L2s, of which the chip has eight), until none is kNotYet; a
 // value that is there is final. Nothing else is communicated, so nothing has to be ordered.
 //
-// Every wait ends: a workgroup needs only results of its own team, and the launch is small enough for all teams to be on
-// the chip together (dwpw_team_exchange). Should they not get there all the same, a wave gives up after some seconds, hands
-// nothing on, and the outputs of that image are NaN.
+// Every wait ends: a workgroup needs only results of its own team, and the launch is small enough for all teams to be on the chip
+// together where one process with its four hardware queues uses it (dwpw_team_exchange). Nothing guarantees that -- several
+// processes share a device, a captured run can be replayed on a stream of a few compute units -- so a workgroup that has looked for
+// some milliseconds does the whole image by itself, the parts of all of the team in turn, and hands everything on on the way. The
+// words and the outputs it stores are the bits that the others store there, so it does not matter who comes first, and one that
+// finds its place late finds all it needs.
 #include "small_internal.h"
 
 #include <algorithm>
@@ -35,7 +38,7 @@ constexpr int kTeamThreads = kTeamWaves * 64;
 constexpr int kTeamMax = 16;              // workgroups of a team = channel blocks of the widest tensor
 constexpr int kTeamItems = 16;            // (input block, pixel group) pairs that a wave has in registers
 constexpr unsigned kNotYet = ~0u;
-constexpr unsigned kMaxTries = 1u << 21;  // a try takes at least a round trip to memory, some 0.6 us
+constexpr unsigned kOwnTries = 1u << 21;  // for what is known to come: a workgroup's own stores
 
 struct TeamBlock {
     const float *dw, *pw;
@@ -51,6 +54,7 @@ struct TeamArgs {
     char *exchange;
     unsigned exchange_bytes;              // per image
     int n_blocks, team, plane_bytes, part_bytes;
+    unsigned tries;                       // looks at values that are not there yet, before a wave gives up
     FastDiv by_team;
     const float *head;                    // as in dwpw_run.hip
     int head_Co, head_Cob;
@@ -77,9 +81,9 @@ __device__ __forceinline__ void team_store(GlobalBytes p, floatx4 v)
     __hip_atomic_store((GlobalPairs)p, (unsigned long long)y << 32 | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store((GlobalPairs)(p + 8), (unsigned long long)u << 32 | z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ bool team_there(unsigned long long v)
+__device__ __forceinline__ unsigned team_most(unsigned m, unsigned long long v)
 {
-    return (unsigned)v != kNotYet && (unsigned)(v >> 32) != kNotYet;
+    return max(max(m, (unsigned)v), (unsigned)(v >> 32));
 }
 __device__ __forceinline__ floatx4 team_relu(floatx4 v)
 {
@@ -92,7 +96,7 @@ __device__ __forceinline__ floatx4 team_relu(floatx4 v)
 // requested at once; the sums of a pixel group, in the order of dwpw_run, go to part[group][lane].
 template <int NI>
 __device__ __forceinline__ void team_reduce(const float *filt, GlobalBytes x, int HW, int p, int q, int lane, int J, int g0,
-                                            floatx4 *part, bool &lost)
+                                            floatx4 *part, TeamKernArgs ka, bool &lost)
 {
     float a[NI][4];
     unsigned off[NI];
@@ -114,11 +118,11 @@ __device__ __forceinline__ void team_reduce(const float *filt, GlobalBytes x, in
             v[n][0] = team_load(x + off[n]);
             v[n][1] = team_load(x + off[n] + 8);
         }
-        bool there = true;
+        unsigned most = 0;                // kNotYet is the largest word (and a maximum of three is one instruction, without branches)
 #pragma unroll
-        for (int n = 0; n < NI; ++n) there = there && team_there(v[n][0]) && team_there(v[n][1]);
-        if (__ballot(!there) == 0) break;
-        if (lost || tries >= kMaxTries) { lost = true; break; }
+        for (int n = 0; n < NI; ++n) most = team_most(team_most(most, v[n][0]), v[n][1]);
+        if (__ballot(most == kNotYet) == 0) break;
+        if (tries >= ka->tries) { lost = true; break; }
     }
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
     int g = g0, j = 0;
@@ -133,6 +137,123 @@ __device__ __forceinline__ void team_reduce(const float *filt, GlobalBytes x, in
             j = 0; g += kTeamWaves;
         }
     }
+}
+
+// The head, a channel block's part of it: the sum over the pixels by the weights, to the exchange area. Lane: a channel.
+__device__ __forceinline__ void team_head_part(TeamKernArgs ka, const float *head, GlobalBytes x, const floatx4 *plane, int c, int w, int lane)
+{
+    if (w != 0 || lane >= 16) return;
+    const int last = ka->n_blocks - 1, C = ka->block[last].nCbo * 16, HW = ka->block[last].Ho * ka->block[last].Wo;
+    const int Co = ka->head_Co, Cob = ka->head_Cob;
+    const float *act = reinterpret_cast<const float *>(plane);
+    float sum = 0.f;
+    for (int m = 0; m < HW; ++m) sum += act[m * 16 + lane];
+    for (int o = 0; o < Co; ++o) {
+        const float v = fmaf(sum, head[((size_t)(o / Cob) * C + c * 16 + lane) * Cob + o % Cob], 0.f);
+        __hip_atomic_store((GlobalWords)(x + (unsigned)(o * C + c * 16 + lane) * 4), team_word(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// ... and the outputs, a wave per output; lane: a channel of 64, summed as dwpw_run does.
+__device__ __forceinline__ void team_head_sum(TeamKernArgs ka, float *out, int img, GlobalBytes x, int w, int lane, unsigned most, bool &lost)
+{
+    const int last = ka->n_blocks - 1, C = ka->block[last].nCbo * 16, HW = ka->block[last].Ho * ka->block[last].Wo, Co = ka->head_Co;
+    for (int o = w; o < Co; o += kTeamWaves) {
+        unsigned v[kTeamMax / 4];
+        for (unsigned tries = 0;; ++tries) {
+            unsigned most_word = 0;
+#pragma unroll
+            for (int k = 0; k < kTeamMax / 4; ++k)
+                v[k] = __hip_atomic_load((GlobalWords)(x + (unsigned)(o * C + min(k * 64 + lane, C - 1)) * 4), __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int k = 0; k < kTeamMax / 4; ++k) most_word = max(most_word, v[k]);
+            if (__ballot(most_word == kNotYet) == 0) break;
+            if (lost || tries >= most) { lost = true; break; }
+        }
+        float sum = 0.f;
+#pragma unroll
+        for (int k = 0; k < kTeamMax / 4; ++k) {
+            float u = k * 64 + lane < C ? __builtin_bit_cast(float, v[k]) : 0.f;
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) u += __shfl_xor(u, d, 64);
+            sum += u;
+        }
+        if (lane == 0) out[(size_t)img * Co + o] = sum * (1.f / (float)HW);
+    }
+}
+
+// A workgroup that has given up its team: the parts of all of the team one after the other, from the run's input on, and every output.
+// Waits for nothing but its own stores. Not inlined, so that the kernel's registers are those of its usual way.
+__device__ __attribute__((noinline)) void team_alone(TeamKernArgs ka, int img, floatx4 *lds)
+{
+    const int lane = threadIdx.x & 63, p = lane & 15, q = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int n_blocks = ka->n_blocks;
+    const float *head = ka->head;
+    floatx4 *plane = lds + 4;
+    GlobalBytes x = (GlobalBytes)(ka->exchange + (size_t)img * ka->exchange_bytes);       // what the pointwise layer reads
+    for (int b = 0; b <= n_blocks; ++b) {
+        // block b's input, a channel block at a time: to plane, then what the block's depthwise layer makes of it
+        const int last = max(b - 1, 0), J = ka->block[last].nCbi;
+        const int HW = ka->block[last].Ho * ka->block[last].Wo;
+        GlobalBytes behind = x + (b ? (unsigned)(J * HW) * 64 : 0u);
+        const int n_c = b ? ka->block[last].nCbo : J;
+        for (int c = 0; c < n_c; ++c) {
+            __syncthreads();                                    // plane has been read
+            if (b == 0) {
+                const int quads = ka->block[0].Hi * ka->block[0].Wi * 4;
+                const floatx4 *src = reinterpret_cast<const floatx4 *>(ka->in) + ((size_t)img * n_c + c) * quads;
+                for (int k = threadIdx.x; k < quads; k += kTeamThreads) plane[k] = src[k];
+            }
+            for (int g = w; b > 0 && g * 16 < HW; g += kTeamWaves) {
+                const int m = g * 16 + p;
+                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+                for (int ci = 0; ci < J; ++ci) {
+                    const float *f = ka->block[last].pw + ((size_t)c * J + ci) * 256 + q * 64 + p;
+                    const GlobalBytes from = x + ((unsigned)(ci * HW + min(m, HW - 1)) * 64 + q * 16);
+                    unsigned long long u = 0, v = 0;
+                    for (unsigned tries = 0; tries < kOwnTries; ++tries) {
+                        u = team_load(from);
+                        v = team_load(from + 8);
+                        if (__ballot(team_most(team_most(0, u), v) == kNotYet) == 0) break;
+                    }
+                    const unsigned y[4] = {(unsigned)u, (unsigned)(u >> 32), (unsigned)v, (unsigned)(v >> 32)};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(f[r * 16], __builtin_bit_cast(float, y[r]), acc, 0, 0, 0);
+                }
+                if (ka->block[last].pw_relu) acc = team_relu(acc);
+                if (m < HW) {
+                    if (b == n_blocks && head == nullptr) reinterpret_cast<floatx4 *>(ka->out)[((size_t)img * n_c + c) * HW * 4 + m * 4 + q] = acc;
+                    else plane[m * 4 + q] = acc;
+                }
+            }
+            __syncthreads();
+            if (b < n_blocks) {
+                const floatx4 *taps = reinterpret_cast<const floatx4 *>(ka->block[b].dw + (size_t)c * 144) + q;
+                const int Hi = ka->block[b].Hi, Wi = ka->block[b].Wi, Wo = ka->block[b].Wo, d_HW = ka->block[b].Ho * Wo;
+                for (int m = w * 16 + p; m < d_HW; m += kTeamWaves * 16) {
+                    const int oy = m / Wo, ox = m - oy * Wo;
+                    const int iy0 = oy * ka->block[b].stride - ka->block[b].pt, ix0 = ox * ka->block[b].stride - ka->block[b].pl;
+                    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+                    for (int k = 0; k < 9; ++k) {               // (taps outside the image multiply zeros, as in the kernel)
+                        const int iy = iy0 + k / 3, ix = ix0 + k % 3;
+                        const bool on = (unsigned)iy < (unsigned)Hi && (unsigned)ix < (unsigned)Wi;
+                        const floatx4 v = plane[(on ? iy * Wi + ix : -1) * 4 + q], u = taps[k * 4];
+                        acc.x = fmaf(v.x, u.x, acc.x); acc.y = fmaf(v.y, u.y, acc.y);
+                        acc.z = fmaf(v.z, u.z, acc.z); acc.w = fmaf(v.w, u.w, acc.w);
+                    }
+                    if (ka->block[b].dw_relu) acc = team_relu(acc);
+                    team_store(behind + (unsigned)(c * d_HW + m) * 64 + q * 16, acc);
+                }
+            } else if (head != nullptr) {
+                team_head_part(ka, head, behind, plane, c, w, lane);
+            }
+        }
+        x = behind;
+    }
+    bool lost = false;
+    if (head != nullptr) team_head_sum(ka, ka->out, img, x, w, lane, kOwnTries, lost);
 }
 
 __global__ void __launch_bounds__(kTeamThreads) dwpw_team(TeamArgs args)
@@ -150,7 +271,7 @@ __global__ void __launch_bounds__(kTeamThreads) dwpw_team(TeamArgs args)
 
     // LDS: [a pixel of zeros][this workgroup's channel block of the present tensor: pixel, quad][sums of the next, two sets in turn]
     extern __shared__ floatx4 lds[];
-    __shared__ int gave_up;
+    __shared__ int gave_up[2];            // with the sets of sums, in turn: a wave ahead of the others, past at most one barrier, sets the other
     floatx4 *plane = lds + 4;
     const int part_set = ka->part_bytes >> 4;
     floatx4 *const part0 = plane + (ka->plane_bytes >> 4);
@@ -187,7 +308,7 @@ __global__ void __launch_bounds__(kTeamThreads) dwpw_team(TeamArgs args)
         d_by_Wo.magic = ka->block[b].by_Wo.magic; d_by_Wo.shift = ka->block[b].by_Wo.shift; d_by_Wo.d = ka->block[b].by_Wo.d;
         window(w);
     };
-    if (threadIdx.x == 0) gave_up = 0;
+    if (threadIdx.x < 2) gave_up[threadIdx.x] = 0;
     if (threadIdx.x < 4) lds[threadIdx.x] = floatx4{0.f, 0.f, 0.f, 0.f};
     if (t < ka->block[0].nCbi) {
         const int quads = ka->block[0].Hi * ka->block[0].Wi * 4;
@@ -203,7 +324,7 @@ __global__ void __launch_bounds__(kTeamThreads) dwpw_team(TeamArgs args)
         const int ng = (HW + 15) >> 4;
 
         // ---------------- depthwise: plane -> exchange area, pixel groups round the waves
-        if (t < nCbi && !lost) {
+        if (t < nCbi) {
             for (int g = w; g < d_ng; g += kTeamWaves) {
                 if (g != w) window(g);
                 floatx4 v[9];
@@ -227,16 +348,18 @@ __global__ void __launch_bounds__(kTeamThreads) dwpw_team(TeamArgs args)
             const int items = w < ng ? nCbi * ((ng - w + kTeamWaves - 1) / kTeamWaves) : 0;
             const float *filt = ka->block[b].pw + (size_t)t * nCbi * 256;
             switch (items) {
-#define SMALL_TEAM_CASE(NI_) case NI_: team_reduce<NI_>(filt, x, HW, p, q, lane, nCbi, w, part, lost); break;
+#define SMALL_TEAM_CASE(NI_) case NI_: team_reduce<NI_>(filt, x, HW, p, q, lane, nCbi, w, part, ka, lost); break;
                 SMALL_TEAM_CASE(1) SMALL_TEAM_CASE(2) SMALL_TEAM_CASE(3) SMALL_TEAM_CASE(4) SMALL_TEAM_CASE(5) SMALL_TEAM_CASE(6)
                 SMALL_TEAM_CASE(7) SMALL_TEAM_CASE(8) SMALL_TEAM_CASE(9) SMALL_TEAM_CASE(10) SMALL_TEAM_CASE(11) SMALL_TEAM_CASE(12)
                 SMALL_TEAM_CASE(13) SMALL_TEAM_CASE(14) SMALL_TEAM_CASE(15) SMALL_TEAM_CASE(16)
 #undef SMALL_TEAM_CASE
                 default: break;
             }
-            if (lost && lane == 0) gave_up = 1;
+            int *const flag = gave_up + (part != part0);
+            if (lost && lane == 0) *flag = 1;
             __syncthreads();                            // plane has been read
-            lost = __builtin_amdgcn_readfirstlane(gave_up) != 0;
+            lost = __builtin_amdgcn_readfirstlane(*flag) != 0;
+            if (lost) break;
             const int pw_relu = ka->block[b].pw_relu;
             const bool to_memory = b + 1 == n_blocks && head == nullptr;
             for (int g = w; g < ng; g += kTeamWaves) {
@@ -244,12 +367,8 @@ __global__ void __launch_bounds__(kTeamThreads) dwpw_team(TeamArgs args)
                 if (pw_relu) v = team_relu(v);
                 const int m = g * 16 + p;
                 if (m < HW) {
-                    if (to_memory) {
-                        const float nan = __builtin_nanf("");
-                        reinterpret_cast<floatx4 *>(out)[((size_t)img * nCbo + t) * HW * 4 + m * 4 + q] = lost ? floatx4{nan, nan, nan, nan} : v;
-                    } else {
-                        plane[m * 4 + q] = v;
-                    }
+                    if (to_memory) reinterpret_cast<floatx4 *>(out)[((size_t)img * nCbo + t) * HW * 4 + m * 4 + q] = v;
+                    else plane[m * 4 + q] = v;
                 }
             }
             // One pixel group, here and in the next block: wave 0 wrote plane and alone reads it. The other set of sums is next, so a wave that runs ahead, past at most one more barrier, writes nothing that is still read.
@@ -264,45 +383,18 @@ __global__ void __launch_bounds__(kTeamThreads) dwpw_team(TeamArgs args)
     }
 
     // ---------------- the network's head: mean over the pixels, fully connected layer; every workgroup its channels' part
-    if (head != nullptr) {
-        const int nCb = ka->block[n_blocks - 1].nCbo, C = nCb * 16;
-        const int HW = ka->block[n_blocks - 1].Ho * ka->block[n_blocks - 1].Wo;
-        const int Co = ka->head_Co, Cob = ka->head_Cob;
-        if (w == 0 && t < nCb && !lost && lane < 16) {          // lane: a channel
-            const float *act = reinterpret_cast<const float *>(plane);
-            float sum = 0.f;
-            for (int m = 0; m < HW; ++m) sum += act[m * 16 + lane];
-            for (int o = 0; o < Co; ++o) {
-                const float v = fmaf(sum, head[((size_t)(o / Cob) * C + t * 16 + lane) * Cob + o % Cob], 0.f);
-                __hip_atomic_store((GlobalWords)(x + (unsigned)(o * C + t * 16 + lane) * 4), team_word(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        if (t == 0) {                                   // a wave per output; lane: a channel of 64, summed as dwpw_run does
-            for (int o = w; o < Co; o += kTeamWaves) {
-                unsigned v[kTeamMax / 4];
-                for (unsigned tries = 0;; ++tries) {
-                    bool there = true;
-#pragma unroll
-                    for (int k = 0; k < kTeamMax / 4; ++k)
-                        v[k] = __hip_atomic_load((GlobalWords)(x + (unsigned)(o * C + min(k * 64 + lane, C - 1)) * 4), __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-                    for (int k = 0; k < kTeamMax / 4; ++k) there = there && v[k] != kNotYet;
-                    if (__ballot(!there) == 0) break;
-                    if (lost || tries >= kMaxTries) { lost = true; break; }
-                }
-                float sum = 0.f;
-#pragma unroll
-                for (int k = 0; k < kTeamMax / 4; ++k) {
-                    float u = k * 64 + lane < C ? __builtin_bit_cast(float, v[k]) : 0.f;
-#pragma unroll
-                    for (int d = 32; d > 0; d >>= 1) u += __shfl_xor(u, d, 64);
-                    sum += u;
-                }
-                if (lane == 0) out[(size_t)img * Co + o] = lost ? __builtin_nanf("") : sum * (1.f / (float)HW);
-            }
+    if (head != nullptr && !lost) {
+        const int last = n_blocks - 1;
+        if (t < ka->block[last].nCbo) team_head_part(ka, head, x, plane, t, w, lane);
+        if (t == 0) {
+            team_head_sum(ka, out, img, x, w, lane, ka->tries, lost);
+            int *const flag = gave_up + (part != part0);
+            if (lost && lane == 0) *flag = 1;
+            __syncthreads();
+            lost = __builtin_amdgcn_readfirstlane(*flag) != 0;
         }
     }
+    if (lost) team_alone(ka, img, lds);
 }
 
 __global__ void __launch_bounds__(kTeamThreads) team_clear(uint4 *p, unsigned n)
@@ -336,8 +428,8 @@ void team_lds(const DwpwRunBlock *b, int n, int &plane, int &part)
 
 }  // namespace
 
-// A workgroup of a team waits for the others, so all of them have to find a place on the chip whatever else runs there. A compute
-// unit holds two (registers); kernels that wait for nobody make room in the end; and with an eighth of the compute units' number per
+// A workgroup of a team waits for the others, and where they find no place on the chip beside it, it has waited in vain. A compute unit
+// holds two (registers); kernels that wait for nobody make room in the end; and with an eighth of the compute units' number per
 // launch, 16 launches that wait fit together, four times the hardware queues that a process has unless told otherwise. A stream may
 // be confined to some of the compute units: those count.
 size_t dwpw_team_exchange(const DwpwRunBlock *blocks, int n_blocks, int N, int head_Co, hipStream_t s)
@@ -362,9 +454,10 @@ size_t dwpw_team_exchange(const DwpwRunBlock *blocks, int n_blocks, int N, int h
 }
 
 hipError_t launch_dwpw_team(const float *in, float *out, const DwpwRunBlock *blocks, int n_blocks, int N, const DwpwRunHead &head,
-                            void *exchange, hipStream_t s)
+                            void *exchange, hipStream_t s, unsigned tries, int absent)
 {
     TeamArgs a;
+    a.tries = tries;
     a.in = in; a.out = out; a.exchange = (char *)exchange;
     a.head = head.filt; a.head_Co = head.Co; a.head_Cob = head.Cob;
     a.n_blocks = n_blocks;
@@ -382,7 +475,7 @@ hipError_t launch_dwpw_team(const float *in, float *out, const DwpwRunBlock *blo
     }
     const unsigned quads = (unsigned)((size_t)N * a.exchange_bytes / 16);
     hipLaunchKernelGGL(team_clear, dim3((quads + kTeamThreads - 1) / kTeamThreads), dim3(kTeamThreads), 0, s, (uint4 *)exchange, quads);
-    hipLaunchKernelGGL(dwpw_team, dim3((unsigned)(N * a.team)), dim3(kTeamThreads), 64 + (size_t)a.plane_bytes + 2 * (size_t)a.part_bytes, s, a);
+    hipLaunchKernelGGL(dwpw_team, dim3((unsigned)(N * a.team - absent)), dim3(kTeamThreads), 64 + (size_t)a.plane_bytes + 2 * (size_t)a.part_bytes, s, a);
     return hipGetLastError();
 }
 

@@ -297,8 +297,11 @@ hipError_t launch_dwpw_run(const float *in, float *out, const DwpwRunBlock *bloc
 // The same run on few images, a team of workgroups per image (dwpw_team.hip), two launches. dwpw_team_exchange: the bytes of
 // scratch memory it needs (16-byte aligned, not overlapping in, out or each other), 0 where it does not take the run.
 size_t dwpw_team_exchange(const DwpwRunBlock *blocks, int n_blocks, int N, int head_Co, hipStream_t s);
+// tries: after how many looks at values that do not come a workgroup does without its team; absent: workgroups of the last image that are
+// not launched, as if they found no place (tests).
+constexpr unsigned kDwpwTeamTries = 1u << 13;      // a look takes at least a round trip to memory, some 0.6 us
 hipError_t launch_dwpw_team(const float *in, float *out, const DwpwRunBlock *blocks, int n_blocks, int N, const DwpwRunHead &head,
-                            void *exchange, hipStream_t s);
+                            void *exchange, hipStream_t s, unsigned tries = kDwpwTeamTries, int absent = 0);
 
 // Remaining Table 2 layers (table2.hip): y = x * scale[c] + shift[c]; nearest-neighbour upsampling by integer
 // factors; group convolution (geometry in g with g.Ci = all input channels, g.Co = G * K, g.Cib the activation block).

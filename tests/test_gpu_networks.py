@@ -1238,3 +1238,61 @@ def test_depthwise_pointwise_run_by_a_team_on_nans():
     assert np.isfinite(got[0]).all()
     nan = np.isnan(got[1])
     assert nan[:, :3, :3].all() and not nan[:, 3:, :].any() and not nan[:, :, 3:].any()
+
+
+_ALONE = [  # C0, H, W, [(Cout, stride, padding, ReLUs)], outputs of a head or 0; the first workgroup waits for others in each
+    (32, 12, 12, _DSEP, 2),
+    (32, 12, 12, _DSEP, 0),
+    (48, 8, 8, [(16, 1, _P1, (1, 0)), (16, 2, _S2, (0, 1)), (48, 1, _P1, _BOTH)], 0),              # two of three have nothing to do in between
+    (48, 5, 7, [(80, 2, _P1, _BOTH), (112, 1, _P1, _BOTH), (48, 1, _P1, (0, 0))], 16),
+    (96, 4, 4, [(96, 1, (2, 2, 2, 2), _BOTH), (160, 1, (2, 2, 0, 0), _BOTH), (32, 2, _P1, _BOTH)], 5),
+    (240, 4, 4, [(240, 1, _P1, (0, 0)), (16, 2, _P1, _BOTH)], 0),
+]
+
+
+@pytest.mark.parametrize("case", _ALONE)
+def test_depthwise_pointwise_run_by_a_team_whose_members_do_not_come(case):
+    """A workgroup whose team does not get there does the image by itself: the launches called with few looks before it does, and with
+    all workgroups of an image but the first left out. The same bits as by dwpw_run, every time."""
+    import ctypes as C
+
+    class Block(C.Structure):
+        _fields_ = [("dw", C.c_void_p), ("pw", C.c_void_p)] + [(n, C.c_int) for n in "dw_relu pw_relu Cin Cout Hi Wi Ho Wo stride pt pl".split()]
+
+    class Head(C.Structure):
+        _fields_ = [("filt", C.c_void_p), ("Co", C.c_int), ("Cob", C.c_int)]
+    lib = S.binding.load()
+    run = lib["_ZN5small15launch_dwpw_runEPKfPfPKNS_12DwpwRunBlockEiiRKNS_11DwpwRunHeadEP12ihipStream_t"]
+    team = lib["_ZN5small16launch_dwpw_teamEPKfPfPKNS_12DwpwRunBlockEiiRKNS_11DwpwRunHeadEPvP12ihipStream_tji"]
+    need = lib["_ZN5small18dwpw_team_exchangeEPKNS_12DwpwRunBlockEiiiP12ihipStream_t"]
+    need.restype = C.c_size_t
+    C0, H, W, spec, head = case
+    g = torch.Generator(device=DEV)
+    g.manual_seed(9600 + C0)
+    keep, blocks = [], (Block * len(spec))()
+
+    def normal(n, fan_in):
+        keep.append(torch.randn(n, generator=g, device=DEV) * (2.0 / fan_in) ** 0.5)
+        return keep[-1].data_ptr()
+    Ci, h, w = C0, H, W
+    for b, (Co, s, (t, bo, l, r), relus) in zip(blocks, spec):
+        b.dw, b.pw = normal(Ci * 9, 9), normal(Ci * Co, Ci)
+        b.dw_relu, b.pw_relu, b.Cin, b.Cout, b.Hi, b.Wi, b.stride, b.pt, b.pl = *relus, Ci, Co, h, w, s, t, l
+        h, w = (h + t + bo - 3) // s + 1, (w + l + r - 3) // s + 1
+        b.Ho, b.Wo, Ci = h, w, Co
+    top = Head(normal(Ci * head, Ci), head, head) if head else Head(None, 0, 0)
+    members = max([C0] + [b.Cout for b in blocks]) // 16
+    n_out = head or Ci * h * w
+    stream = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    for N, tries, absent in [(1, 1 << 13, 0), (1, 0, 0), (1, 64, members - 1), (1, 64, 1), (2, 0, 0), (2, 64, members - 1), (2, 3, members // 2)]:
+        x = torch.rand(N * C0 * H * W, generator=g, device=DEV)
+        size = need(blocks, len(spec), N, head, stream)
+        assert size > 0
+        area = Guarded(size // 4)
+        ref, out = Guarded(N * n_out), Guarded(N * n_out)
+        assert run(C.c_void_p(x.data_ptr()), C.c_void_p(ref.t.data_ptr()), blocks, len(spec), N, C.byref(top), stream) == 0
+        assert team(C.c_void_p(x.data_ptr()), C.c_void_p(out.t.data_ptr()), blocks, len(spec), N, C.byref(top), C.c_void_p(area.t.data_ptr()),
+                    stream, C.c_uint(tries), absent) == 0
+        assert np.isfinite(ref.check()).all() and np.abs(ref.check()).max() > 1e-3
+        assert_bits(out.check(), ref.check(), f"{case} N={N} tries={tries} absent={absent}")
+        area.check()
