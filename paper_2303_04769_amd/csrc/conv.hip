@@ -622,7 +622,7 @@ const char *conv_kernel_name(const LayerGeom &g)
         if (g.Cib == 8 && g.kh == 1 && g.kw == 1) return "conv_small<8,1,1>";
         return "conv_small<0,0,0>";
     }
-    if (conv_split3_wide_eligible(g)) return conv_split3_wide_kernel_name();
+    if (conv_split3_wide_eligible(g)) return conv_split3_wide_kernel_name(g);
     if (conv_split3_eligible(g)) return conv_split3_kernel_name();
     if (conv_split_eligible(g)) return conv_split_kernel_name(g);
     if (conv_pw_eligible(g)) return conv_pw_kernel_name(g);

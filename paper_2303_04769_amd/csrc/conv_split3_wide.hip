@@ -1,5 +1,5 @@
 // fp32 convolution on the bf16 matrix cores, each value as the sum of three bf16 ones (conv_split3.hip says which products, at which
-// scale, and with what error; the sums are the same, in the same order): 3x3 windows at stride 1, an even number of input blocks,
+// scale, and with what error; here two more of them where the fp32 instruction is the other choice, see products()): 3x3 windows at stride 1, an even number of input blocks,
 // layers of about half a 256-pixel x 64-channel tile per compute unit or more.
 //
 // Bound: the matrix cores' power. conv16_split3 spends 3570 cycles of a compute unit on what is 1536 cycles of matrix instructions:
@@ -16,8 +16,8 @@
 // the accumulators are tied operands of an asm statement, and empty asm statements keep the pieces from being moved together.
 // 1536 cycles of matrix instructions take some 2000 here, and the clock falls from 2.2 to 2.05 GHz: fewer cycles (2300 to 2000 a step)
 // brought nothing any more at the largest layers. us, conv16_split3 / here: 64 channels 56 x 56, 256 images 341 / 286 (207 TFLOP/s of
-// fp32 work), 128 channels 28 x 28, 64 images 95.9 / 84.8, 32 images 50.2 / 42.8; with the fp32 instruction / here: 224 -> 384 channels
-// 23 x 23, 13 images 95 / 67, 160 channels 24 x 24, 29 images 68 / 46.
+// fp32 work), 128 channels 28 x 28, 64 images 95.9 / 84.8, 32 images 50.2 / 42.8; with the fp32 instruction / here: 160 channels
+// 24 x 24, 27 images 62 / 56 (eight products), 192 channels 106 x 14, 10 images 89 / 66.
 #include "small_internal.h"
 
 #include <algorithm>
@@ -86,7 +86,7 @@ __device__ __forceinline__ void wait_states(floatx4 (&u)[4], floatx4 (&v)[4])
     asm volatile("s_nop %8" : "+a"(u[0]), "+a"(u[1]), "+a"(u[2]), "+a"(u[3]), "+a"(v[0]), "+a"(v[1]), "+a"(v[2]), "+a"(v[3]) : "n"(STATES));
 }
 
-template <int WM, int WN, int WVM, int WVN, int ENTRIES>
+template <int WM, int WN, int WVM, int WVN, int ENTRIES, int PRODUCTS>
 __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
 {
     constexpr int TM = 16 * WM * WVM, NCT = WN * WVN, FI = NCT / 4, R = ENTRIES / 64, EC = ENTRIES + 1;     // (an entry more: planes four banks apart)
@@ -327,36 +327,34 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
             };
             each<WM>([&](auto W) {
                 constexpr int wm = W.value;
-                each<6 * WN>([&](auto TN) {
-                    constexpr int t = TN.value / WN, wn = TN.value % WN, i = wm * 6 * WN + TN.value;
-                    constexpr int pa[6] = {0, 1, 0, 1, 2, 0}, pb[6] = {0, 0, 1, 1, 0, 2};
+                each<PRODUCTS * WN>([&](auto TN) {
+                    constexpr int t = TN.value / WN, wn = TN.value % WN;
+                    constexpr int pa[8] = {0, 1, 0, 1, 2, 0, 1, 2}, pb[8] = {0, 0, 1, 1, 0, 2, 2, 1};
                     floatx4 &c = t == 0 ? acc[wm][wn] : low[wm][wn];
                     const bf16x8 x = s == kTaps - 1 && pb[t] == 2 ? fl[wm] : fb[wm & 1][pb[t]];
                     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "a"(fa[cur][wn][pa[t]]), "v"(x));
                     // every fourth gap reads an operand, of the next pixels or of the next step's filter, and requests some of the
                     // filter of step s + 3; the others take turns at the filter's and the input's splitting
-                    if constexpr (i % 4 == 0) {
-                        constexpr int r = i / 4, b = r % 6;
-                        if constexpr (b < 3) {
+                    if constexpr (wn == 0) {
+                        if constexpr (t < 3) {
                             if constexpr (wm + 1 < WM) {
-                                if constexpr (s < kTaps - 1 || b < 2) fb[(wm + 1) & 1][b] = b_get(wm + 1, s, b, bpar);
+                                if constexpr (s < kTaps - 1 || t < 2) fb[(wm + 1) & 1][t] = b_get(wm + 1, s, t, bpar);
                             } else if constexpr (s < kTaps - 1) {
-                                if constexpr (s < kTaps - 2 || b < 2) fb[0][b] = b_get(0, s + 1, b, bpar);
+                                if constexpr (s < kTaps - 2 || t < 2) fb[0][t] = b_get(0, s + 1, t, bpar);
                             }
-                        } else {
-                            constexpr int n = wm * 3 + b - 3;
+                        } else if constexpr (t < 6) {
+                            constexpr int n = wm * 3 + t - 3;
                             if constexpr (n < 3 * WN) a_get(nxt, my_slot ^ 1, n / 3, n % 3);
                         }
-                        // (values 2q and 2q + 1 are taken in piece 16 q of the gaps between)
-                        constexpr int q = (r - 1) / 6, k = 2 * q + (r - 1) % 6 / 2;
-                        if constexpr (r % 6 == 1 || r % 6 == 3) {
-                            constexpr int ahead = s + 3;
+                        // (values 2q and 2q + 1 are taken in piece 8q of the filter's, before)
+                        if constexpr (t == 1 || t == 3) {
+                            constexpr int k = 2 * wm + t / 2, ahead = s + 3;
                             if constexpr (ahead < kTaps) f_load(k, lanes, block, ahead);
                             else f_load(k, lanes2, block2, ahead - kTaps);
                         }
-                        if constexpr (s == kTaps - 2 && r % 6 == 5) fl[wm] = b_get(wm, s + 1, 2, bpar);
+                        if constexpr (s == kTaps - 2 && t == 5) fl[wm] = b_get(wm, s + 1, 2, bpar);
                     } else {
-                        constexpr int r = i / 4 * 3 + i % 4 - 1;
+                        constexpr int r = (wm * PRODUCTS + t) * (WN - 1) + wn - 1;
                         if constexpr (r % 2 == 0) filter_work(Num<r / 2>{});
                         else input_work(Num<r / 2>{});
                     }
@@ -515,30 +513,47 @@ WidePlan plan_wide(const LayerGeom &g)
 
 }  // namespace
 
-const char *conv_split3_wide_kernel_name() { return "conv16_split3_wide<4,4,4,1>"; }
+// Products of the parts that are taken. Where conv_split3.hip is the other choice, six, as there. Layers that the fp32 instruction would
+// compute keep ml and lm too: without them a product is off by up to 1.9 x 2^-24 of it, which shows in filters of one weight, and
+// with them by the 2^-24 of that instruction (one weight, 2-norm: 2.57e-8 / 2.53e-8, fp32 2.53e-8; dense filters 1.3e-7 either way,
+// fp32 4.2e-7). They cost a fifth: 160 channels 24x24, 27 images, 46.8 / 55.6 us, fp32 62.0.
+static int products(const LayerGeom &g) { return conv_split3_eligible(g) ? 6 : 8; }
 
-// Where it beats the others: times in us of both sides. Here, by rounds of tiles (120 random layers, 4 % root mean square): 6.9 a chunk
-// and 2.8 a tile, 1.7 more a chunk when all compute units work, and 6 once. The others: 2 and the layer's work at 172 TFLOP/s where
-// conv16_split3 would take it, at 122 elsewhere, which their best layers reach. Of the 118 layers 32 are taken, at 0.87 of their time on
-// average, none slower, and 11 that would gain 5 % or more are not.
+const char *conv_split3_wide_kernel_name(const LayerGeom &g)
+{
+    return products(g) == 6 ? "conv16_split3_wide<4,4,4,1,384,6>" : "conv16_split3_wide<4,4,4,1,384,8>";
+}
+
+// Where it beats the others: times in us of both sides, here by rounds of tiles. With six products (120 random layers, 4 % root mean
+// square): 6.9 a chunk and 2.8 a tile, 1.7 more a chunk when all compute units work, and 6 once, against 2 and the layer's work at
+// 172 TFLOP/s, which the best layers of conv16_split3 reach. With eight (140 random layers, 2.1 %): 8.9, 2.5, 0.7 and 6.2, against 2 and
+// the work at 125 TFLOP/s, which the best ones on the fp32 instruction reach: of the 140 it takes 37, at 0.87 of their time, and leaves 12
+// that would gain 5 % or more; 60 others that it takes 0.74 to 1.00 of theirs.
 bool conv_split3_wide_eligible(const LayerGeom &g)
 {
     const WidePlan pl = plan_wide(g);
     if (!pl.ok) return false;
     const long cus = device_cus(), rounds = (pl.tiles + cus - 1) / cus;
     const double chunks = g.Ci / 32, fill = pl.tiles < cus ? (double)pl.tiles / cus : 1.0;
-    const double here = rounds * (6.88 * chunks + 2.75 + 1.73 * fill * chunks) + 5.94;
     const double mflop = 18e-6 * g.N * g.Ho * g.Wo * (double)g.Ci * g.Co;
-    return here < 2.0 + mflop / (conv_split3_eligible(g) ? 172.0 : 122.0);
+    if (products(g) == 6) return rounds * (6.88 * chunks + 2.75 + 1.73 * fill * chunks) + 5.94 < 2.0 + mflop / 172.0;
+    return rounds * (8.93 * chunks + 2.50 + 0.73 * fill * chunks) + 6.22 < 2.0 + mflop / 125.0;
+}
+
+template <int PRODUCTS>
+static hipError_t run_wide(const WideArgs &a, unsigned groups, hipStream_t s)
+{
+    const auto kernel = conv16_split3_wide<kWM, kWN, kWVM, kWVN, kEntries, PRODUCTS>;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(256), kLds, s, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_conv_split3_wide(const float *in, const float *filt, float *out, const float *res, const LayerGeom &g, int epilogue,
                                    hipStream_t s, const float *bn)
 {
     const WidePlan pl = plan_wide(g);
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(conv16_split3_wide<kWM, kWN, kWVM, kWVN, kEntries>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
-    if (attr != hipSuccess) return attr;
     if (!pl.ok) return hipErrorInvalidValue;
     WideArgs a;
     a.in = in; a.filt = filt; a.out = out; a.res = res; a.bn = bn; a.epilogue = epilogue;
@@ -551,8 +566,8 @@ hipError_t launch_conv_split3_wide(const float *in, const float *filt, float *ou
     a.dHoWs = make_fastdiv(a.HoWs); a.dWs = make_fastdiv(a.Ws); a.dWv = make_fastdiv(a.Wv); a.dHv = make_fastdiv(a.Hv);
     a.dStrips = make_fastdiv(a.strips); a.dCt = make_fastdiv(a.n_cot);
     const long cus = device_cus(), sets = (pl.tiles + kMaxRounds * cus - 1) / (kMaxRounds * cus);
-    hipLaunchKernelGGL((conv16_split3_wide<kWM, kWN, kWVM, kWVN, kEntries>), dim3((unsigned)std::min(pl.tiles, sets * cus)), dim3(256), kLds, s, a);
-    return hipGetLastError();
+    const unsigned groups = (unsigned)std::min(pl.tiles, sets * cus);
+    return products(g) == 6 ? run_wide<6>(a, groups, s) : run_wide<8>(a, groups, s);
 }
 
 }  // namespace small

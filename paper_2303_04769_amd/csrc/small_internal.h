@@ -249,7 +249,7 @@ bool conv_split3_eligible(const LayerGeom &g);
 const char *conv_split3_kernel_name();
 // ... 3x3 at stride 1 on an even number of input blocks, larger tiles, workgroups that walk over them (conv_split3_wide.hip)
 bool conv_split3_wide_eligible(const LayerGeom &g);
-const char *conv_split3_wide_kernel_name();
+const char *conv_split3_wide_kernel_name(const LayerGeom &g);
 hipError_t launch_conv_split3_wide(const float *in, const float *filt, float *out, const float *res, const LayerGeom &g, int epilogue,
                                    hipStream_t s, const float *bn = nullptr);
 hipError_t launch_conv_split3(const float *in, const float *filt, float *out, const float *res, const LayerGeom &g, int epilogue,

@@ -515,7 +515,7 @@ def test_conv2d_three_part_products_scattered_infinities(case):
 
 
 WIDE_CASES = [  # N, Ci, Co, H, W, kh, kw, pad: 256-pixel tiles, a wave 64 x 64, workgroups that walk over tiles
-    (46, 96, 48, 33, 33, 3, 3, (1, 1, 1, 1)),        # fewer tiles than compute units; three chunks; three output blocks of four
+    (60, 96, 48, 27, 33, 3, 3, (1, 1, 1, 1)),        # fewer tiles than compute units; three chunks; three output blocks of four
     (94, 64, 96, 103, 9, 3, 3, (1, 1, 1, 1)),        # two to three tiles a workgroup, which end inside images; six output blocks
     (40, 96, 64, 27, 51, 3, 3, (1, 0, 2, 0)),        # uneven padding: 26 x 51 outputs, the last strip shorter
     (900, 64, 64, 56, 7, 3, 3, (1, 1, 1, 1)),        # narrow images
@@ -538,6 +538,26 @@ def test_conv2d_three_part_wide_tiles_scattered_infinities(case):
 @pytest.mark.parametrize("kind", sorted(SPARSE_FILTERS))
 def test_conv2d_three_part_wide_tiles_precision(kind):
     test_conv2d_three_part_products_precision(kind, 20, 64, 64, 64, 47, 3)
+
+
+EIGHT_PRODUCTS = {  # as SPARSE_FILTERS, where the other choice is the fp32 instruction: no more than its errors
+    # The final rounding, 1; seven of the small products' sum inside matrix instructions, which round to within a unit of the last place
+    # and not to half of one: 7 x 2 x 2^-7 at most, 0.11 (fp32 1.0, 2.53e-8).
+    "one": (1.11, 2.6e-8),
+    # And the large products' one, 2 by the same, the small ones' twice: 3.25 (2.24 seen; fp32 1.94, 3.1e-8).
+    "two": (3.25, 3.0e-8),
+    "box": (None, 8e-8),
+    "rectified": (None, 2.6e-7),
+}
+
+
+@pytest.mark.parametrize("kind", sorted(EIGHT_PRODUCTS))
+@pytest.mark.parametrize("N,Ci,Co,H,W", [(27, 160, 160, 24, 24), (10, 192, 96, 69, 42)])
+def test_conv2d_three_part_wide_tiles_precision_of_fp32(kind, N, Ci, Co, H, W, monkeypatch):
+    """Layers that the fp32 instruction would compute otherwise keep its precision, whatever the filter."""
+    assert S.small_conv2d_kernel(N, Ci, Co, H, W, 3, 3, 1, (1, 1, 1, 1), 16, 16) == "conv16_split3_wide<4,4,4,1,384,8>"
+    monkeypatch.setitem(SPARSE_FILTERS, kind, EIGHT_PRODUCTS[kind])
+    test_conv2d_three_part_products_precision(kind, N, Ci, Co, H, W, 3)
 
 
 def test_conv_identity_filter_is_exact():
