@@ -598,7 +598,7 @@ int group_conv_same_tile(const LayerGeom &g, int F_C, int S_C, int K)
     one.Ci = F_C;
     one.Co = K;
     // (byte offsets are those of the whole tensors)
-    if (!conv_same_eligible(one) || !((size_t)g.N * g.Ci * g.H * g.W < ((size_t)1 << 30)) ||
+    if (!conv_same_can(one) || !((size_t)g.N * g.Ci * g.H * g.W < ((size_t)1 << 30)) ||
         !((size_t)g.N * g.Co * g.Ho * g.Wo < ((size_t)1 << 30)))
         return -1;
     // the tile's output channels must not straddle groups

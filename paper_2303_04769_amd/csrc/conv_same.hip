@@ -699,7 +699,7 @@ struct PlanTile {
 // 3x3 with stride 2: the last pixel of a row has a tap 2 inside the image, which no next pixel's tap 0 stands for
 static bool before(const LayerGeom &g) { return 2 * (g.Wo - 1) + 2 - g.pl < g.W; }
 
-bool conv_same_eligible(const LayerGeom &g)
+bool conv_same_can(const LayerGeom &g)
 {
     // the last pixel's byte offset must fit the 32-bit per-lane offset of the load and store instructions
     const bool small_enough = (size_t)g.N * g.Ci * g.H * g.W < ((size_t)1 << 30) &&
@@ -712,14 +712,19 @@ bool conv_same_eligible(const LayerGeom &g)
     if (g.stride == 1) return g.Ho == g.H && g.Wo == g.W;                   // output pixels in input order
     // stride 2: neighbouring pixels share an entry, tap 2 of one and tap 0 of the next, which is only right if a row's last pixel has
     // no tap 2 inside the image or its first one no tap 0
-    if (g.stride != 2) return false;
-    if (!before(g)) return true;
-    // In the second case, rows of even length padded by one, the reduction split over waves (conv_split.hip) is the other choice, and
+    return g.stride == 2 && (!before(g) || g.pl >= 1);
+}
+
+bool conv_same_eligible(const LayerGeom &g)
+{
+    if (!conv_same_can(g)) return false;
+    if (g.kw != 3 || g.stride != 2 || !before(g)) return true;
+    // Rows of even length padded by one: the reduction split over waves (conv_split.hip) is the other choice, and
     // the better one up to 24 tiles of 16 x 16 per compute unit, where it splits by four and more: us here / there 10.3 / 9.1 (20 images of
     // 64 channels 50x20, 13 tiles a unit); beyond, 21.1 / 26.9 (50 of 48 -> 96 45x36, 30), 66.6 / 83.9 (64 of 144 92x12, 39), 79.4 /
     // 88.5 (64 of 64 -> 128 56x56, 98), and where the gather kernel (conv.hip) took the layer 52.7 / 87.8 (20 of 160 -> 48 77x90,
     // 26), 49.4 / 75.9 (159 of 48 45x62, 83). Reductions of one input block stay there (100 of 16 -> 32 70x70: 18.1 / 19.0).
-    return g.pl >= 1 && g.Ci >= 32 && ((long)g.N * g.Ho * g.Wo + 15) / 16 * (g.Co / 16) > 24L * device_cus();
+    return g.Ci >= 32 && ((long)g.N * g.Ho * g.Wo + 15) / 16 * (g.Co / 16) > 24L * device_cus();
 }
 
 int conv_same_planes(const LayerGeom &g)

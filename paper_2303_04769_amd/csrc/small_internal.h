@@ -213,7 +213,8 @@ const char *conv_kernel_name(const LayerGeom &g);
 
 // Workgroup tiles (output pixels x output channels) of the matrix-core convolutions.
 enum : int { SAME_64x32, SAME_128x16, SAME_64x16, SAME_32x64, SAME_32x32, SAME_64x48 };
-bool conv_same_eligible(const LayerGeom &g);     // 16-blocks; 3x3 with stride 1, output size == input size, or with stride 2; unpadded 1x1
+bool conv_same_can(const LayerGeom &g);          // 16-blocks; 3x3 with stride 1, output size == input size, or with stride 2; unpadded 1x1
+bool conv_same_eligible(const LayerGeom &g);     // ... and not better done by the kernels that launch_conv has besides
 int conv_same_planes(const LayerGeom &g);        // Ci blocks staged per reduction step (1x1 filters)
 // images each workgroup walks in the image-aligned persistent variant, 0 = flat variant (host arithmetic only)
 int conv_same_images_per_workgroup(const LayerGeom &g, int tile);
@@ -223,7 +224,7 @@ int conv_same_images_per_workgroup(const LayerGeom &g, int tile);
 hipError_t launch_conv_same(const float *in, const float *filt, float *out, const float *res, const LayerGeom &g,
                             int tile, int epilogue, hipStream_t s, int F_C = 0, int S_C = 0, int K = 0,
                             const float *bn = nullptr);
-// tile (SAME_*) for a group convolution that launch_conv_same takes, or -1: geometry of conv_same_eligible, channel
+// tile (SAME_*) for a group convolution that launch_conv_same takes, or -1: geometry of conv_same_can, channel
 // counts as above
 int group_conv_same_tile(const LayerGeom &g, int F_C, int S_C, int K);
 

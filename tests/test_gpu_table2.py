@@ -65,6 +65,12 @@ GROUP_CASES = [  # N, Ci, F_C, S_C, K, H, W, k, stride, pad, Cib, F_Cb, Cob
     (40, 64, 32, 32, 32, 16, 16, 3, 1, (1, 1, 1, 1), 16, 16, 16),  # many images: the image-aligned persistent variant
     (5, 128, 32, 32, 48, 10, 10, 3, 2, (0, 1, 0, 1), 16, 16, 16),  # stride 2, four groups of three output blocks
     (8, 256, 32, 32, 32, 28, 28, 3, 1, (1, 1, 1, 1), 16, 16, 16),  # the sweep's group convolution on eight images
+    # stride 2, even widths padded on the left: neighbouring pixels share the entry of the first one's last tap
+    (3, 64, 32, 32, 32, 10, 8, 3, 2, (1, 1, 1, 1), 16, 16, 16),
+    (2, 48, 16, 16, 16, 9, 12, 3, 2, (1, 1, 1, 1), 16, 16, 16),    # one input block a group
+    (5, 96, 48, 48, 48, 7, 7, 3, 2, (1, 0, 2, 1), 16, 16, 16),     # padded by two on the left
+    (4, 64, 32, 16, 16, 6, 2, 3, 2, (0, 1, 1, 0), 16, 16, 16),     # overlapping groups, one output column
+    (130, 64, 32, 32, 32, 32, 32, 3, 2, (1, 1, 1, 1), 16, 16, 16), # many images
 ]
 
 
