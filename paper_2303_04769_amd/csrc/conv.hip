@@ -629,7 +629,7 @@ const char *conv_kernel_name(const LayerGeom &g)
     const int tile = pick_tile(g);
     if (conv_same_eligible(g))
         snprintf(name, sizeof(name), "%s<%s,%d,%d,%d>", conv_same_images_per_workgroup(g, tile) ? "conv16_img" : "conv16_same",
-                 kTileWaves[tile], g.kw, conv_same_planes(g), (g.kw == 3 && g.stride == 2) ? 2 : 1);
+                 kTileWaves[tile], g.kw, conv_same_planes(g), conv_same_entries(g));
     else
         snprintf(name, sizeof(name), "conv16_mfma<%s>", kTileWaves[tile]);
     return name;

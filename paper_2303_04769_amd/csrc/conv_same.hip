@@ -727,6 +727,8 @@ bool conv_same_eligible(const LayerGeom &g)
     return g.Ci >= 32 && ((long)g.N * g.Ho * g.Wo + 15) / 16 * (g.Co / 16) > 24L * device_cus();
 }
 
+int conv_same_entries(const LayerGeom &g) { return g.kw != 3 || g.stride != 2 ? 1 : before(g) ? kBorrowBefore : 2; }
+
 int conv_same_planes(const LayerGeom &g)
 {
     if (g.kw != 1) return 1;
@@ -741,9 +743,11 @@ template <template <int, int, int> class F, class... Args>
 auto with_shape(const LayerGeom &g, int tile, Args &&...args)
 {
     if (g.kw == 3) {
-        if (g.stride == 2 && before(g)) return with_tile(tile, F<3, 1, kBorrowBefore>{args...});
-        if (g.stride == 2) return with_tile(tile, F<3, 1, 2>{args...});
-        return with_tile(tile, F<3, 1, 1>{args...});
+        switch (conv_same_entries(g)) {
+            case kBorrowBefore: return with_tile(tile, F<3, 1, kBorrowBefore>{args...});
+            case 2: return with_tile(tile, F<3, 1, 2>{args...});
+            default: return with_tile(tile, F<3, 1, 1>{args...});
+        }
     }
     if (conv_same_planes(g) == 2) return with_tile(tile, F<1, 2, 1>{args...});
     return with_tile(tile, F<1, 1, 1>{args...});

@@ -216,6 +216,7 @@ enum : int { SAME_64x32, SAME_128x16, SAME_64x16, SAME_32x64, SAME_32x32, SAME_6
 bool conv_same_can(const LayerGeom &g);          // 16-blocks; 3x3 with stride 1, output size == input size, or with stride 2; unpadded 1x1
 bool conv_same_eligible(const LayerGeom &g);     // ... and not better done by the kernels that launch_conv has besides
 int conv_same_planes(const LayerGeom &g);        // Ci blocks staged per reduction step (1x1 filters)
+int conv_same_entries(const LayerGeom &g);       // how the kernel stages the entries of a pixel (conv_same.hip, SameCfg)
 // images each workgroup walks in the image-aligned persistent variant, 0 = flat variant (host arithmetic only)
 int conv_same_images_per_workgroup(const LayerGeom &g, int tile);
 // F_C > 0: a group convolution (partial-channel reduction) on the same kernels: g.Ci, g.Co are all input / output
