@@ -170,7 +170,7 @@ STRIDED_CASES = [  # N, Ci, Co, H, W, pad, kernel: 3x3 with stride 2, tiles of t
     (150, 32, 80, 32, 30, (1, 1, 1, 0), "conv16_img<4,1,1,1,3,1,3>"),          # ... 64 x 16, tiles end with the image
     (161, 32, 96, 16, 35, (0, 1, 1, 0), "conv16_same<4,1,1,3,3,1,3>"),         # ... padded on the left only, rows from the image's first
     (110, 32, 48, 33, 64, (2, 1, 2, 1), "conv16_same<4,1,1,3,3,1,2>"),         # padded by two: taps 0 and 1 outside, tap 2 of the last too
-    (110, 32, 48, 33, 63, (2, 1, 2, 1), "conv16_same<4,1,1,3,3,1,3>"),         # ... padded by two: taps 0 and 1 outside
+    (113, 32, 48, 33, 63, (2, 1, 2, 1), "conv16_same<4,1,1,3,3,1,3>"),         # ... padded by two: taps 0 and 1 outside
     (300, 32, 16, 44, 38, (1, 1, 1, 1), "conv16_same<4,1,2,1,3,1,3>"),         # ... one output block
     (130, 32, 48, 32, 32, (1, 1, 1, 1), "conv16_same<4,1,1,1,3,1,3>"),         # ... just over 24 tiles per compute unit
     (64, 48, 64, 32, 32, (1, 1, 1, 1), "conv16_split<4,2,2>"),                 # ... and below
