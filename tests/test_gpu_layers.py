@@ -533,11 +533,14 @@ def test_conv2d_three_part_wide_tiles(case, scale):
 
 @pytest.mark.parametrize("case", WIDE_CASES)
 def test_conv2d_three_part_wide_tiles_scattered_infinities(case):
+    N, Ci, Co, H, W, kh, kw, pad = case
+    assert S.small_conv2d_kernel(N, Ci, Co, H, W, kh, kw, 1, pad, 16, 16).startswith("conv16_split3_wide"), case
     test_conv2d_three_part_products_scattered_infinities(case)
 
 
 @pytest.mark.parametrize("kind", sorted(SPARSE_FILTERS))
 def test_conv2d_three_part_wide_tiles_precision(kind):
+    assert S.small_conv2d_kernel(20, 64, 64, 64, 47, 3, 3, 1, (1, 1, 1, 1), 16, 16) == "conv16_split3_wide<4,4,4,1,384,6>"
     test_conv2d_three_part_products_precision(kind, 20, 64, 64, 64, 47, 3)
 
 

@@ -163,6 +163,64 @@ def test_residual_block_with_batch_normalization(N, C, H, W):
     assert_close(got, O.run_network(net, x, ws), C * 9, "the same with image-resident runs forced on")
 
 
+@pytest.mark.parametrize("N,C,H,W,kernel", [(90, 64, 40, 31, "conv16_split3_wide<4,4,4,1,384,6>"), (27, 160, 24, 24, "conv16_split3_wide<4,4,4,1,384,8>")])
+def test_batch_normalization_behind_wide_tiles(N, C, H, W, kernel):
+    """The same block on the kernel whose workgroups walk over tiles; a value whose parts overflow makes some waves compute a tile again,
+    with the same epilogue."""
+    from workloads.nets import Layer, Network, IN, OUT
+    net = Network("bn_wide", C, H, W)
+    p1, z = (1, 1, 1, 1), (0, 0, 0, 0)
+    net.wshapes = [((C, C, 3, 3), C * 9), ((2, C), 1)]
+    net.layers = [
+        Layer("conv", C, C, H, W, 3, 3, 1, p1, src=IN, dst=0, w=0),
+        Layer("bn", C, C, H, W, src=0, dst=0, w=1),
+        Layer("add", C, C, H, W, src=0, src2=IN, dst=0),
+        Layer("relu", C, C, H, W, src=0, dst=0),
+        Layer("maxpool", C, C, H, W, 1, 1, 1, z, src=0, dst=OUT),
+    ]
+    assert S.small_conv2d_kernel(N, C, C, H, W, 3, 3, 1, p1, 16, 16) == kernel
+    x, ws = _tensors(net, N, 7150 + C, [(1, C)])
+    x[N // 2, 3, 10, 11] = 1e31
+    got, pn = _run_table(net, x, ws, S.SMALL_RUN_RESIDENT_OFF)
+    assert pn.launches_at(N, S.SMALL_RUN_RESIDENT_OFF) == [0, 4]
+    idx = np.r_[0, 1, N // 2 - 1, N // 2 + 1, N - 1]
+    assert_close(got[idx], O.run_network(net, x[idx], ws).reshape(got[idx].shape), C * 9, f"normalization behind {kernel}")
+    large = [N // 2]
+    ref = O.run_network(net, x[large], ws).reshape(got[large].shape)
+    assert np.abs(ref).max() > 1e30
+    far = np.ones((H, W), bool)
+    far[9:12, 10:13] = False
+    assert_close(got[large][:, :, far], ref[:, :, far], C * 9, "the image with a large value, outside its reach")
+    assert_close(got[large], ref, C * 9, "that image")
+
+
+@pytest.mark.parametrize("N,Ci,Co,H,W,kernel", [(50, 32, 96, 45, 36, "conv16_same<4,1,1,2,3,1,3>"), (150, 32, 80, 32, 30, "conv16_img<4,1,1,1,3,1,3>"),
+                                                (50, 48, 96, 45, 37, "conv16_same<4,1,1,3,3,1,2>"), (64, 48, 64, 32, 32, "conv16_split<4,2,2>")])
+def test_batch_normalization_behind_strided_tiles(N, Ci, Co, H, W, kernel):
+    """3x3 with stride 2, norm, add, ReLU. The tiles have that epilogue, in either staging form; the split reduction gets it only for layers
+    that the tiles prefer, so the last one's normalization is a launch of its own."""
+    from workloads.nets import Layer, Network, IN, OUT
+    p1, z = (1, 1, 1, 1), (0, 0, 0, 0)
+    net = Network("bn_strided", Ci, H, W)
+    net.wshapes = [((Co, Ci, 3, 3), Ci * 9), ((2, Co), 1), ((Co, Ci, 3, 3), Ci * 9), ((2, Co), 1)]
+    Ho, Wo = (H + 1) // 2, (W + 1) // 2
+    net.layers = [
+        Layer("conv", Ci, Co, H, W, 3, 3, 2, p1, src=IN, dst=0, w=0),
+        Layer("bn", Co, Co, Ho, Wo, src=0, dst=0, w=1),
+        Layer("conv", Ci, Co, H, W, 3, 3, 2, p1, src=IN, dst=1, w=2),
+        Layer("bn", Co, Co, Ho, Wo, src=1, dst=1, w=3),
+        Layer("add", Co, Co, Ho, Wo, src=1, src2=0, dst=1),
+        Layer("relu", Co, Co, Ho, Wo, src=1, dst=1),
+        Layer("maxpool", Co, Co, Ho, Wo, 1, 1, 1, z, src=1, dst=OUT),
+    ]
+    assert S.small_conv2d_kernel(N, Ci, Co, H, W, 3, 3, 2, p1, 16, 16) == kernel
+    x, ws = _tensors(net, N, 7180 + Co, [(1, Co), (3, Co)])
+    got, pn = _run_table(net, x, ws)
+    folded = "split" not in kernel
+    assert (pn.launches_at(N) == [0, 2, 6]) == folded, pn.launches_at(N)
+    assert_close(got, O.run_network(net, x, ws).reshape(got.shape), Ci * 9, f"normalization behind {kernel}")
+
+
 def test_batch_normalization_after_kernels_without_that_epilogue():
     """A first layer on 3 channels (its kernel has no normalization epilogue) and a 5 x 5 convolution (the generic
     matrix-core kernel): the runner takes the fusion back and launches conv, norm (+ ReLU) as the table lists them;
