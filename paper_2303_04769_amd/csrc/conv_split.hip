@@ -4,18 +4,13 @@
 // Bound: streaming the filter (every value is used for a handful of pixels only) and, per workgroup, a chain of matrix
 // instructions. The tiled kernels give a layer of few pixels to a few workgroups that walk the whole reduction one step
 // after the other -- 512 channels on one 6 x 6 image are 16 workgroups of 96 steps on a chip of 256 compute units. Here a
-// wave owns WM x WN tiles of 16 output pixels x 16 output channels and takes every WAVES-th reduction step, a step being
-// one (input block, tap): the waves of a workgroup read neighbouring kilobytes of the filter, each keeps kAhead steps of
-// operands in flight in registers (no LDS and no barrier in the loop), and the partial sums meet in LDS at the end, in a
-// fixed order. A tap outside the image is an offset beyond the buffer descriptor, which reads zero.
+// wave owns WM x WN tiles of 16 output pixels x 16 output channels and takes a run of reduction steps, a step being one (input
+// block, tap), the WAVES-th part of them. It keeps AHEAD steps of operands in flight in registers (no LDS and no barrier in the
+// loop), and the partial sums meet in LDS at the end, in a fixed order. A tap outside the image is an offset beyond the buffer descriptor, which reads zero.
 #include "small_internal.h"
 
 namespace small {
 namespace {
-
-// Steps of operands in flight per wave. A wave's run is filled up to a multiple of it with steps of zeros: with 4, 6 and 9 the layers
-// below took 1.04, 1.12 and 1.22 of the time (512 channels 3x3 6x6, one image, 18 steps a wave 9.3 / 9.3 / 9.9 us against 8.6).
-constexpr int kAhead = 3;
 
 struct SplitArgs {
     const float *in, *filt, *res, *bn;
@@ -25,14 +20,14 @@ struct SplitArgs {
     int n_groups;                      // pixel groups of 16
     int epilogue;
     unsigned in_bytes, filt_bytes;
-    FastDiv dHoWo, dWo, dCib, dKw, dGroups;
+    FastDiv dHoWo, dWo, dCib, dTaps, dKw, dGroups;
 };
 
-template <int WAVES, int WM, int WN>
+template <int WAVES, int WM, int WN, bool TAPS_INSIDE, int AHEAD>
 __global__ void __launch_bounds__(64 * WAVES) conv16_split(SplitArgs a)
 {
     // CH sums per tile, matrix instruction r into sum r % CH: shorter chains round less often. A wave's run of steps meets the image's
-    // border in whole stretches of zeros, so the other runs' sums are longer than if the steps were dealt out in turn; error against
+    // border in whole stretches of zeros (blocks innermost), so the other runs' sums are longer than if the steps were dealt out in turn; error against
     // 64 bits, 512 channels 3x3 6x6 one image / 7x7 four images: steps in turn 2.12e-7 / 4.02e-7, runs 2.21e-7 / 4.15e-7 with two sums
     // / one, 1.65e-7 / 2.97e-7 with four / two (+0.06 us).
     constexpr int T = WM * WN, CH = T == 1 ? 4 : 2;
@@ -59,13 +54,13 @@ __global__ void __launch_bounds__(64 * WAVES) conv16_split(SplitArgs a)
     for (int j = 0; j < WN; ++j)
         f_lane[j] = cob0 + j < a.nCob ? (unsigned)((cob0 + j) * a.steps) * 1024u + (unsigned)(q * 64 + p) * 4u : kBeyond;
 
-    // This wave's steps are a run of them, the input block innermost: from one to the next only the scalar offsets of the loads change,
-    // and the lanes' offsets, of which the tap's place in the image is part, where the run comes to another tap. Behind the run's
-    // end the descriptors have no size (and the scalar offsets are zero, for the hardware takes them off the size): such loads read zero.
+    // This wave's run: from a block to the next only the scalar offsets of the loads change, from a tap to the next the lanes' offsets
+    // too, of which the tap's place in the image is part. Behind the run's end the descriptors have no size (and the scalar offsets are zero, for the hardware takes them off the size): such loads read zero.
     const int first = wave * a.run, last = min(first + a.run, a.steps);
-    floatx4 x[kAhead][WM];
-    float w[kAhead][WN][4];
-    int tap = quotient(a.dCib, first), cib = first - tap * a.nCib, s_next = first;
+    floatx4 x[AHEAD][WM];
+    float w[AHEAD][WN][4];
+    int outer = quotient(TAPS_INSIDE ? a.dTaps : a.dCib, first), inner = first - outer * (TAPS_INSIDE ? a.taps : a.nCib), s_next = first;
+    int &tap = TAPS_INSIDE ? inner : outer, &cib = TAPS_INSIDE ? outer : inner;
     unsigned at[WM];
     auto lanes = [&]() __attribute__((always_inline)) {
         const int y = quotient(a.dKw, tap), z = tap - y * a.kw;
@@ -89,14 +84,15 @@ __global__ void __launch_bounds__(64 * WAVES) conv16_split(SplitArgs a)
             for (int r = 0; r < 4; ++r)
                 ws[j][r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(flt, f_lane[j] + 64u * r, w_block, 0));
         ++s_next;
-        if (++cib == a.nCib) {
-            cib = 0;
-            ++tap;
-            lanes();
+        const bool turn = ++inner == (TAPS_INSIDE ? a.taps : a.nCib);
+        if (turn) {
+            inner = 0;
+            ++outer;
         }
+        if (TAPS_INSIDE || turn) lanes();
     };
 #pragma unroll
-    for (int i = 0; i < kAhead; ++i) request(x[i], w[i]);
+    for (int i = 0; i < AHEAD; ++i) request(x[i], w[i]);
     floatx4 acc[WM][WN][CH];
 #pragma unroll
     for (int i = 0; i < WM; ++i)
@@ -104,9 +100,9 @@ __global__ void __launch_bounds__(64 * WAVES) conv16_split(SplitArgs a)
         for (int j = 0; j < WN; ++j)
 #pragma unroll
             for (int c = 0; c < CH; ++c) acc[i][j][c] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int s = first; s < last; s += kAhead) {
+    for (int s = first; s < last; s += AHEAD) {
 #pragma unroll
-        for (int k = 0; k < kAhead; ++k) {
+        for (int k = 0; k < AHEAD; ++k) {
             // (steps past the end multiply zeros by zeros)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -149,9 +145,10 @@ __global__ void __launch_bounds__(64 * WAVES) conv16_split(SplitArgs a)
     }
 }
 
-struct Variant { int waves, wm, wn; const char *name; };
-constexpr Variant kVariants[] = {{16, 1, 1, "conv16_split<16,1,1>"}, {8, 1, 1, "conv16_split<8,1,1>"}, {4, 1, 1, "conv16_split<4,1,1>"},
-                                 {4, 2, 1, "conv16_split<4,2,1>"},   {4, 2, 2, "conv16_split<4,2,2>"}, {2, 2, 2, "conv16_split<2,2,2>"}};
+struct Variant { int waves, wm, wn; const char *name, *name_taps; };
+constexpr Variant kVariants[] = {{16, 1, 1, "conv16_split<16,1,1>", "conv16_split<16,1,1,taps>"}, {8, 1, 1, "conv16_split<8,1,1>", "conv16_split<8,1,1,taps>"},
+                                 {4, 1, 1, "conv16_split<4,1,1>", "conv16_split<4,1,1,taps>"},    {4, 2, 1, "conv16_split<4,2,1>", "conv16_split<4,2,1,taps>"},
+                                 {4, 2, 2, "conv16_split<4,2,2>", "conv16_split<4,2,2,taps>"},    {2, 2, 2, "conv16_split<2,2,2>", "conv16_split<2,2,2,taps>"}};
 
 long split_steps(const LayerGeom &g) { return (long)(g.Ci / 16) * g.kh * g.kw; }
 long split_tiles(const LayerGeom &g) { return ((long)g.N * g.Ho * g.Wo + 15) / 16 * (g.Co / 16); }
@@ -170,11 +167,35 @@ int pick_variant(const LayerGeom &g)
     return tiles <= 24 * cus ? 4 : 5;
 }
 
+// Which of block and tap a wave's run has innermost. The block: from step to step only scalar offsets change, which is up to 1.4
+// times as fast where the data comes from the caches. But a pixel of a block is 64 bytes, half a cache line, and its neighbour, the
+// next tap's, is then read a whole round of blocks later, from memory again once the layer's data is more than the caches hold:
+// with the tap innermost it is 0.6 to 0.9 of the time there. The line: the input's bytes times the output blocks (how often they are
+// read), 150 MB, or for strides above one, whose taps share less, input and filter, 14 MB. us, block / tap innermost (steps dealt
+// out in turn before there were runs): 464 images of 384 channels 3x3 stride 2 7x7 202 / 127 (141), 27 of 464 -> 96 5x5 stride 2
+// 49x13 185 / 133 (129), 60 of 192 -> 112 2x2 stride 2 27x80 111 / 74 (80), 136 of 128 3x3 stride 2 10x56 66 / 48 (51); below it 62
+// of 384 -> 48 5x5 6x6 26 / 36 (42), 5 of 128 -> 16 3x3 7x47 4.1 / 5.6 (6.3). 2300 random layers of 6 us and more take 0.83 of the
+// time with the steps dealt out; 4 are more than 4 % slower, none more than 9, and with the block innermost everywhere up to 63.
+// (One output block, <4,2,1>: the block up to the first line, 80 -> 16 channels 3x1 stride 2 63x12, 125 images 6.3 / 7.1.)
+bool taps_inside(const LayerGeom &g, int variant)
+{
+    const double in = (double)g.N * g.Ci * g.H * g.W * 4, filt = (double)g.Co * g.Ci * g.kh * g.kw * 4;
+    return g.kh * g.kw > 1 && (in * (g.Co / 16) > 150e6 || (g.stride > 1 && variant != 3 && in + filt > 14e6));
+}
+
+// A run is filled up with steps of zeros to a multiple of the steps in flight. Three are enough (with four the layers took 1.04 of the
+// time on average, with 6 and 9 1.12 and 1.22: 512 channels 3x3 6x6, one image, 18 steps a wave 8.6 / 9.3 / 9.3 / 9.9 us), but runs
+// of 4, 8 and 16 steps come out even with four: two by two tiles 0.85, 0.95 and 0.95 of the time (64 channels 2x2 41x41, 7 images 10.1
+// / 8.6), with the tap innermost 0.93, 1.09 and 1.05; waves with a tile of their own have more of them in flight and gain nothing.
 template <int WAVES, int WM, int WN>
-hipError_t run(const SplitArgs &a, hipStream_t s)
+hipError_t run(const SplitArgs &a, bool taps, hipStream_t s)
 {
     const dim3 grid((unsigned)(a.n_groups * ((a.nCob + WN - 1) / WN)));
-    hipLaunchKernelGGL((conv16_split<WAVES, WM, WN>), grid, dim3(64 * WAVES), 0, s, a);
+    constexpr int kEven = WM * WN == 4 ? 4 : 3;
+    if (taps && a.run == 4) hipLaunchKernelGGL((conv16_split<WAVES, WM, WN, true, kEven>), grid, dim3(64 * WAVES), 0, s, a);
+    else if (taps) hipLaunchKernelGGL((conv16_split<WAVES, WM, WN, true, 3>), grid, dim3(64 * WAVES), 0, s, a);
+    else if (a.run == 4 || a.run == 8 || a.run == 16) hipLaunchKernelGGL((conv16_split<WAVES, WM, WN, false, kEven>), grid, dim3(64 * WAVES), 0, s, a);
+    else hipLaunchKernelGGL((conv16_split<WAVES, WM, WN, false, 3>), grid, dim3(64 * WAVES), 0, s, a);
     return hipGetLastError();
 }
 
@@ -192,7 +213,8 @@ bool conv_split_eligible(const LayerGeom &g)
         // few / many tiles: 4 steps 0.97 up to one tile a unit, 1.1 to 1.7 beyond (16 -> 32 channels 1x2 48x48 263 images 69 / 26 us,
         // 16 -> 16 1x3 14x14 9633 images 190 / 58); 8 steps 0.78 to 0.96 / 0.93 to 1.24; 9 to 11 steps 0.70 to 1.0 / 1.04 to 1.33;
         // 12 to 15 0.54 to 1.08 / 0.97 to 1.21; from 16 on 0.11 to 1.0, with many tiles 0.7 to 1.1 unless the last round of
-        // steps (2 waves of 4, as they were then) or of output blocks (two a tile) is too empty: 18 steps 0.93 to 1.23.
+        // steps (2 waves of 4, as the kernel was then; a run is filled up to three steps now, and the line has not been drawn again:
+        // 40 images of 32 channels 40x40, unpadded, stay below it though 18 steps waste nothing) or of output blocks (two a tile) is too empty: 18 steps 0.93 to 1.23.
         const double most = steps < 4 ? 0 : steps < 8 ? 1 : steps < 9 ? 2.5 : steps < 12 ? (g.Co == 16 ? 8 : 5.5) : 20;
         const long nCob = g.Co / 16, done = (steps + 7) / 8 * 8 * ((nCob + 1) / 2 * 2);
         return tiles <= most * cus || (steps >= 16 && 100 * steps * nCob >= 78 * done);
@@ -204,7 +226,11 @@ bool conv_split_eligible(const LayerGeom &g)
     return tiles <= cus ? steps >= 7 : tiles <= 2 * cus ? steps >= 32 : tiles <= 4 * cus && steps >= 200;
 }
 
-const char *conv_split_kernel_name(const LayerGeom &g) { return kVariants[pick_variant(g)].name; }
+const char *conv_split_kernel_name(const LayerGeom &g)
+{
+    const int v = pick_variant(g);
+    return taps_inside(g, v) ? kVariants[v].name_taps : kVariants[v].name;
+}
 
 hipError_t launch_conv_split(const float *in, const float *filt, float *out, const float *res, const LayerGeom &g, int epilogue,
                              hipStream_t s, const float *bn)
@@ -215,20 +241,21 @@ hipError_t launch_conv_split(const float *in, const float *filt, float *out, con
     a.nCib = g.Ci / 16; a.nCob = g.Co / 16; a.taps = g.kh * g.kw; a.kw = g.kw;
     a.stride = g.stride; a.pt = g.pt; a.pl = g.pl; a.steps = a.nCib * a.taps;
     const int v = pick_variant(g);
+    const bool taps = taps_inside(g, v);
     a.run = (a.steps + kVariants[v].waves - 1) / kVariants[v].waves;
     a.n_groups = (a.M + 16 * kVariants[v].wm - 1) / (16 * kVariants[v].wm);
     a.epilogue = epilogue;
     a.in_bytes = (unsigned)((size_t)g.N * g.Ci * g.H * g.W * 4);
     a.filt_bytes = (unsigned)((size_t)g.Co * g.Ci * a.taps * 4);
-    a.dHoWo = make_fastdiv(a.HoWo); a.dWo = make_fastdiv(a.Wo); a.dCib = make_fastdiv(a.nCib); a.dKw = make_fastdiv(a.kw);
+    a.dHoWo = make_fastdiv(a.HoWo); a.dWo = make_fastdiv(a.Wo); a.dCib = make_fastdiv(a.nCib); a.dTaps = make_fastdiv(a.taps); a.dKw = make_fastdiv(a.kw);
     a.dGroups = make_fastdiv(a.n_groups);
     switch (v) {
-        case 0: return run<16, 1, 1>(a, s);
-        case 1: return run<8, 1, 1>(a, s);
-        case 2: return run<4, 1, 1>(a, s);
-        case 3: return run<4, 2, 1>(a, s);
-        case 4: return run<4, 2, 2>(a, s);
-        default: return run<2, 2, 2>(a, s);
+        case 0: return run<16, 1, 1>(a, taps, s);
+        case 1: return run<8, 1, 1>(a, taps, s);
+        case 2: return run<4, 1, 1>(a, taps, s);
+        case 3: return run<4, 2, 1>(a, taps, s);
+        case 4: return run<4, 2, 2>(a, taps, s);
+        default: return run<2, 2, 2>(a, taps, s);
     }
 }
 

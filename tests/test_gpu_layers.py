@@ -317,6 +317,17 @@ SPLIT_CASES = [  # N, Ci, Co, H, W, kh, kw, stride, pad, kernel: the reduction s
     (20, 16, 16, 68, 68, 3, 3, 2, (1, 1, 1, 1), "4,2,1"),      # one output block, many pixels
     (12, 32, 48, 70, 70, 3, 3, 2, (1, 1, 1, 1), "4,2,2"),      # three output blocks: the last workgroup has one
     (31, 16, 112, 59, 60, 4, 4, 2, (1, 1, 1, 1), "2,2,2"),     # seven output blocks; pixels end inside a group
+    (7, 64, 48, 41, 41, 2, 2, 1, (1, 1, 1, 1), "4,2,2"),       # runs of four steps, four in flight; three output blocks
+    (94, 128, 80, 14, 14, 2, 2, 1, (1, 1, 1, 1), "2,2,2"),     # ... of sixteen
+    # taps innermost: a large input, strided, or many output blocks on it
+    (23, 368, 16, 33, 25, 3, 3, 2, (1, 1, 1, 1), "16,1,1,taps"),    # 207 steps, 13 a wave: runs start inside a block
+    (25, 208, 16, 31, 27, 3, 3, 2, (1, 1, 1, 1), "8,1,1,taps"),     # 117 steps, 15 a wave; the last has 12
+    (31, 208, 112, 29, 23, 3, 2, 3, (0, 2, 1, 1), "4,1,1,taps"),    # stride 3, uneven padding; a window without a middle
+    (45, 96, 80, 32, 27, 2, 3, 2, (1, 0, 0, 2), "4,2,2,taps"),      # five output blocks, 36 steps
+    (212, 64, 64, 42, 7, 2, 2, 2, (1, 1, 1, 1), "4,2,2,taps"),      # runs of four steps, four in flight
+    (140, 112, 96, 27, 17, 1, 3, 2, (0, 0, 1, 1), "2,2,2,taps"),    # 21 steps on two waves: eleven and ten
+    (50, 256, 272, 14, 13, 1, 2, 1, (0, 0, 0, 0), "2,2,2,taps"),    # stride 1, seventeen output blocks
+    (150, 160, 16, 40, 41, 3, 3, 3, (0, 0, 0, 0), "4,2,1,taps"),    # one output block
 ]
 
 
