@@ -399,7 +399,9 @@ void launch_mfma(const ConvArgs &a, hipStream_t s)
 // step stages two input entries per pixel, has 64 x 48 as well: us with 64x32 / 64x16 / 32x32 / 64x48 for 48 -> 96 channels 45x37, 50
 // images, 24.0 / 25.5 / 24.8 / 21.9 (cost 10240 / 9861 / 9953 / 9216), 48 channels 45x62, 159 images, 65.8 / 62.2 / 74.4 / 49.8; not
 // where its workgroups go round less evenly: 160 -> 48 channels 77x90, 20 images, 68.7 / 52.7 / 63.9 / 65.0 (10240 / 7669 / 9953 / 9216).
-int pick_tile(const LayerGeom &g)
+// And not where they are no more than the compute units, one round that a layer's work is little of: 64 x 16 tiles, which come in two
+// rounds then, measured 1.01 to 1.06 times as fast (59 images of 272 -> 432 channels 9x7 36.8 / 38.8 us), from two rounds on 0.9.
+int pick_tile(const LayerGeom &g, bool strided)
 {
     const long M = (long)g.N * g.Ho * g.Wo;
     const bool pointwise = g.kh == 1 && g.kw == 1;
@@ -408,17 +410,19 @@ int pick_tile(const LayerGeom &g)
     static const Cand wide[] = {{SAME_64x32, 64, 32, 1.0}, {SAME_64x16, 64, 16, 1.07}, {SAME_32x32, 32, 32, 1.08}, {SAME_64x48, 64, 48, 1.0}};
     static const Cand narrow[] = {{SAME_128x16, 128, 16, 1.0}, {SAME_64x16, 64, 16, 1.05}};
     const Cand *cands = g.Co >= 32 ? wide : narrow;
-    const int n = g.Co < 32 ? 2 : conv_same_eligible(g) && g.stride == 2 && g.Co >= 48 ? 4 : 3;
+    const int n = g.Co < 32 ? 2 : strided && g.Co >= 48 ? 4 : 3;
     const long cus = device_cus();
     int best = cands[0].tile;
     double best_cost = 0;
     for (int i = 0; i < n; ++i) {
         const long wgs = ((M + cands[i].tm - 1) / cands[i].tm) * ((g.Co + cands[i].tn - 1) / cands[i].tn);
         const double cost = (double)((wgs + cus - 1) / cus) * cands[i].tm * cands[i].tn * cands[i].penalty;
+        if (cands[i].tile == SAME_64x48 && wgs <= cus) continue;
         if (i == 0 || cost < best_cost) { best = cands[i].tile; best_cost = cost; }
     }
     return best;
 }
+int pick_tile(const LayerGeom &g) { return pick_tile(g, g.kw == 3 && g.stride == 2 && conv_same_eligible(g)); }
 
 // ---------------------------------------------------------------------------------------------
 // First layers on the matrix cores: one input block of fewer than 16 channels (Ci = 1, 3, ...) and a short
@@ -590,6 +594,8 @@ bool is_dense(const LayerGeom &g)
 const char *const kTileWaves[] = {"4,1,1,2", "4,1,2,1", "4,1,1,1", "2,2,1,2", "2,2,1,1", "4,1,1,3"};
 
 }  // namespace
+
+int conv_strided_tile(const LayerGeom &g) { return pick_tile(g, true); }
 
 int group_conv_same_tile(const LayerGeom &g, int F_C, int S_C, int K)
 {

@@ -715,18 +715,6 @@ bool conv_same_can(const LayerGeom &g)
     return g.stride == 2 && (!before(g) || g.pl >= 1);
 }
 
-bool conv_same_eligible(const LayerGeom &g)
-{
-    if (!conv_same_can(g)) return false;
-    if (g.kw != 3 || g.stride != 2 || !before(g)) return true;
-    // Rows of even length padded by one: the reduction split over waves (conv_split.hip) is the other choice, and
-    // the better one up to 24 tiles of 16 x 16 per compute unit, where it splits by four and more: us here / there 10.3 / 9.1 (20 images of
-    // 64 channels 50x20, 13 tiles a unit); beyond, 21.1 / 26.9 (50 of 48 -> 96 45x36, 30), 66.6 / 83.9 (64 of 144 92x12, 39), 79.4 /
-    // 88.5 (64 of 64 -> 128 56x56, 98), and where the gather kernel (conv.hip) took the layer 52.7 / 87.8 (20 of 160 -> 48 77x90,
-    // 26), 49.4 / 75.9 (159 of 48 45x62, 83). Reductions of one input block stay there (100 of 16 -> 32 70x70: 18.1 / 19.0).
-    return g.Ci >= 32 && ((long)g.N * g.Ho * g.Wo + 15) / 16 * (g.Co / 16) > 24L * device_cus();
-}
-
 int conv_same_entries(const LayerGeom &g) { return g.kw != 3 || g.stride != 2 ? 1 : before(g) ? kBorrowBefore : 2; }
 
 int conv_same_planes(const LayerGeom &g)
@@ -786,6 +774,22 @@ hipError_t launch_conv_same(const float *in, const float *filt, float *out, cons
 int conv_same_images_per_workgroup(const LayerGeom &g, int tile)
 {
     return with_shape<PlanTile>(g, tile, g.N, g.Ho * g.Wo, g.Ci / 16, g.Co / 16);
+}
+
+bool conv_same_eligible(const LayerGeom &g)
+{
+    if (!conv_same_can(g)) return false;
+    if (g.kw != 3 || g.stride != 2 || !before(g)) return true;
+    // Rows of even length padded by one: the reduction split over waves (conv_split.hip) is the other choice, and
+    // the better one up to 24 tiles of 16 x 16 per compute unit, where it splits by four and more: us here / there 10.3 / 9.1 (20 images of
+    // 64 channels 50x20, 13 tiles a unit); beyond, 21.1 / 26.9 (50 of 48 -> 96 45x36, 30), 66.6 / 83.9 (64 of 144 92x12, 39), 79.4 /
+    // 88.5 (64 of 64 -> 128 56x56, 98), and where the gather kernel (conv.hip) took the layer 52.7 / 87.8 (20 of 160 -> 48 77x90,
+    // 26), 49.4 / 75.9 (159 of 48 45x62, 83). Reductions of one input block stay there (100 of 16 -> 32 70x70: 18.1 / 19.0). So do
+    // layers that the split reduction takes and whose tiles of one or two output blocks would end with the image: 48 of 368 -> 240 50x50 530 / 446, 21 of 64 -> 128 47x68
+    // 37.3 / 31.7; of 43 such ones 0.98 of the time there, of 150 others 1.06.
+    if (g.Ci < 32 || ((long)g.N * g.Ho * g.Wo + 15) / 16 * (g.Co / 16) <= 24L * device_cus()) return false;
+    const int tile = conv_strided_tile(g);
+    return tile == SAME_64x48 || conv_same_images_per_workgroup(g, tile) == 0 || !conv_split_beats_gather(g);
 }
 
 }  // namespace small

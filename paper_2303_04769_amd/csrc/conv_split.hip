@@ -201,24 +201,33 @@ hipError_t run(const SplitArgs &a, bool taps, hipStream_t s)
 
 }  // namespace
 
+static bool conv_split_can(const LayerGeom &g)
+{
+    return g.Cib == 16 && g.Cob == 16 && (long)g.N * g.Ho * g.Wo < (1L << 30) && split_tiles(g) < (1L << 30) && split_steps(g) < (1L << 20) &&
+           (size_t)g.N * g.Ci * g.H * g.W * 4 < kBeyond && (size_t)g.Co * g.Ci * g.kh * g.kw * 4 < kBeyond;
+}
+
+bool conv_split_beats_gather(const LayerGeom &g)
+{
+    if (!conv_split_can(g)) return false;
+    const long steps = split_steps(g), tiles = split_tiles(g), cus = device_cus();
+    // Against the gather kernel of conv.hip, which spends a barrier per step but stages each input value once for a tile: the
+    // shorter the reduction, the fewer tiles per compute unit until it wins. 500 random layers, time here over time there, for
+    // few / many tiles: 4 steps 0.97 up to one tile a unit, 1.1 to 1.7 beyond (16 -> 32 channels 1x2 48x48 263 images 69 / 26 us,
+    // 16 -> 16 1x3 14x14 9633 images 190 / 58); 8 steps 0.78 to 0.96 / 0.93 to 1.24; 9 to 11 steps 0.70 to 1.0 / 1.04 to 1.33;
+    // 12 to 15 0.54 to 1.08 / 0.97 to 1.21; from 16 on 0.11 to 1.0, with many tiles 0.7 to 1.1 unless the last round of
+    // steps (2 waves of 4, as the kernel was then; a run is filled up to three steps now, and the line has not been drawn again:
+    // 40 images of 32 channels 40x40, unpadded, stay below it though 18 steps waste nothing) or of output blocks (two a tile) is too empty: 18 steps 0.93 to 1.23.
+    const double most = steps < 4 ? 0 : steps < 8 ? 1 : steps < 9 ? 2.5 : steps < 12 ? (g.Co == 16 ? 8 : 5.5) : 20;
+    const long nCob = g.Co / 16, done = (steps + 7) / 8 * 8 * ((nCob + 1) / 2 * 2);
+    return tiles <= most * cus || (steps >= 16 && 100 * steps * nCob >= 78 * done);
+}
+
 bool conv_split_eligible(const LayerGeom &g)
 {
-    const long M = (long)g.N * g.Ho * g.Wo, steps = split_steps(g), tiles = split_tiles(g), cus = device_cus();
-    if (g.Cib != 16 || g.Cob != 16 || M >= (1L << 30) || tiles >= (1L << 30) || steps >= (1L << 20) ||
-        (size_t)g.N * g.Ci * g.H * g.W * 4 >= kBeyond || (size_t)g.Co * g.Ci * g.kh * g.kw * 4 >= kBeyond)
-        return false;
-    if (!conv_same_eligible(g)) {
-        // Against the gather kernel of conv.hip, which spends a barrier per step but stages each input value once for a tile: the
-        // shorter the reduction, the fewer tiles per compute unit until it wins. 500 random layers, time here over time there, for
-        // few / many tiles: 4 steps 0.97 up to one tile a unit, 1.1 to 1.7 beyond (16 -> 32 channels 1x2 48x48 263 images 69 / 26 us,
-        // 16 -> 16 1x3 14x14 9633 images 190 / 58); 8 steps 0.78 to 0.96 / 0.93 to 1.24; 9 to 11 steps 0.70 to 1.0 / 1.04 to 1.33;
-        // 12 to 15 0.54 to 1.08 / 0.97 to 1.21; from 16 on 0.11 to 1.0, with many tiles 0.7 to 1.1 unless the last round of
-        // steps (2 waves of 4, as the kernel was then; a run is filled up to three steps now, and the line has not been drawn again:
-        // 40 images of 32 channels 40x40, unpadded, stay below it though 18 steps waste nothing) or of output blocks (two a tile) is too empty: 18 steps 0.93 to 1.23.
-        const double most = steps < 4 ? 0 : steps < 8 ? 1 : steps < 9 ? 2.5 : steps < 12 ? (g.Co == 16 ? 8 : 5.5) : 20;
-        const long nCob = g.Co / 16, done = (steps + 7) / 8 * 8 * ((nCob + 1) / 2 * 2);
-        return tiles <= most * cus || (steps >= 16 && 100 * steps * nCob >= 78 * done);
-    }
+    if (!conv_same_eligible(g)) return conv_split_beats_gather(g);
+    if (!conv_split_can(g)) return false;
+    const long steps = split_steps(g), tiles = split_tiles(g), cus = device_cus();
     // Against the tiles of conv_same.hip (their us / here): up to one tile per compute unit from 7 steps on (189 tiles of 7
     // steps 3.9 / 3.1, 96 of 288 36.0 / 10.4; but 51 of 6 3.4 / 3.8), up to two for reductions of 32 (510 of 45 7.7 / 5.0; but 288
     // of 18 4.6 / 4.5), up to four for 200 (999 of 243 45.7 / 24.7; but 912 of 144 19.5 / 21.5); above that they win (2090 of 45 13.3 / 12.8, 4032 of

@@ -214,6 +214,7 @@ const char *conv_kernel_name(const LayerGeom &g);
 // Workgroup tiles (output pixels x output channels) of the matrix-core convolutions.
 enum : int { SAME_64x32, SAME_128x16, SAME_64x16, SAME_32x64, SAME_32x32, SAME_64x48 };
 bool conv_same_can(const LayerGeom &g);          // 16-blocks; 3x3 with stride 1, output size == input size, or with stride 2; unpadded 1x1
+int conv_strided_tile(const LayerGeom &g);       // the tile (SAME_*) of a 3x3 layer with stride 2, if conv_same.hip takes it
 bool conv_same_eligible(const LayerGeom &g);     // ... and not better done by the kernels that launch_conv has besides
 int conv_same_planes(const LayerGeom &g);        // Ci blocks staged per reduction step (1x1 filters)
 int conv_same_entries(const LayerGeom &g);       // how the kernel stages the entries of a pixel (conv_same.hip, SameCfg)
@@ -240,6 +241,7 @@ hipError_t launch_conv_pw(const float *in, const float *filt, float *out, const 
 // The reduction split over the waves of a workgroup (conv_split.hip): few output pixels and a long reduction, and windows,
 // strides and paddings that conv_same_eligible refuses. 16-channel blocks, 16-byte aligned pointers, input and filter below
 // 2 GiB.
+bool conv_split_beats_gather(const LayerGeom &g);      // can take the layer and is faster than the gather kernel of conv.hip
 bool conv_split_eligible(const LayerGeom &g);
 const char *conv_split_kernel_name(const LayerGeom &g);
 hipError_t launch_conv_split(const float *in, const float *filt, float *out, const float *res, const LayerGeom &g, int epilogue,

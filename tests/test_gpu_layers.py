@@ -163,8 +163,9 @@ def test_conv2d_same_tiles(case):
 
 STRIDED_CASES = [  # N, Ci, Co, H, W, pad, kernel: 3x3 with stride 2, tiles of three output blocks, and images whose rows' last tap is inside
     (50, 16, 96, 45, 37, (1, 1, 1, 1), "conv16_same<4,1,1,3,3,1,2>"),          # 64 x 48; tap 0 of a row's first pixel outside, tap 2 of its last
-    (124, 16, 80, 17, 11, (1, 1, 1, 1), "conv16_same<4,1,1,3,3,1,2>"),         # five output blocks under tiles of three
-    (31, 16, 48, 44, 32, (0, 1, 0, 1), "conv16_same<4,1,1,3,3,1,2>"),          # padded on the right only
+    (176, 16, 224, 17, 11, (1, 1, 1, 1), "conv16_same<4,1,1,3,3,1,2>"),        # fourteen output blocks under tiles of three
+    (124, 16, 80, 17, 11, (1, 1, 1, 1), "conv16_same<4,1,1,1,3,1,2>"),         # no more such tiles than compute units: smaller ones
+    (78, 16, 48, 44, 32, (0, 1, 0, 1), "conv16_same<4,1,1,3,3,1,2>"),          # padded on the right only
     (50, 32, 96, 45, 36, (1, 1, 1, 1), "conv16_same<4,1,1,2,3,1,3>"),          # tap 2 of a row's last pixel inside; tiles across images
     (159, 32, 48, 45, 62, (1, 1, 1, 1), "conv16_same<4,1,1,3,3,1,3>"),         # ... 64 x 48
     (150, 32, 80, 32, 30, (1, 1, 1, 0), "conv16_img<4,1,1,1,3,1,3>"),          # ... 64 x 16, tiles end with the image
@@ -174,6 +175,7 @@ STRIDED_CASES = [  # N, Ci, Co, H, W, pad, kernel: 3x3 with stride 2, tiles of t
     (300, 32, 16, 44, 38, (1, 1, 1, 1), "conv16_same<4,1,2,1,3,1,3>"),         # ... one output block
     (130, 32, 48, 32, 32, (1, 1, 1, 1), "conv16_same<4,1,1,1,3,1,3>"),         # ... just over 24 tiles per compute unit
     (64, 48, 64, 32, 32, (1, 1, 1, 1), "conv16_split<4,2,2>"),                 # ... and below
+    (71, 96, 96, 43, 44, (1, 1, 1, 1), "conv16_split<2,2,2,taps>"),            # ... tiles of one block that would end with the image
     (150, 16, 96, 45, 36, (1, 1, 1, 1), "conv16_mfma<4,1,1,2>"),               # ... one input block
 ]
 
