@@ -419,22 +419,24 @@ constexpr Rate kThere[2][3] = {{{0.74, 0.34, 0.093, 0.016, 0}, {1.10, 0.36, 0.11
 // 1.16 (184 images, 112 channels out, 41x21 stride 2), 14.9 / 20.2 at 2.6, 33.9 / 54.1 at 8.4; on 16 channels 7.9 / 7.1 at 0.92, 10.4 /
 // 11.4 at 2.0, 15.9 / 21.8 at 4.0. On 32 channels with stride 1 also groups of four (16.5 / 15.8 at 0.85, 16.7 / 18.0 at 0.96), groups of two
 // (11.7 / 11.3 at 0.9, 13.3 / 14.7 at 1.5) and a single block (14.8 / 15.3 at 2.2); with stride 2 those are not (15.6 / 12.9 at 1.2, two
-// blocks), and on 16 channels groups of two and four take 1.0 to 1.2 times as long here. 70 fresh layers: 34 taken, 0.60 to 0.97 of
-// the time.
-bool large_short(const LayerGeom &g, long cus)
+// blocks), and on 16 channels groups of two and four take 1.0 to 1.2 times as long here. Nor are groups of two whose filter has another
+// zero point than 128, where the tiles sum up the codes with matrix instructions: 0.95 to 1.07 of the time there (32 channels 43x104, 106
+// images 19.1 / 17.8), 0.86 to 0.97 without. 440 random layers that changed: 0.78 of the time, none of the taken ones more than 4 % longer.
+bool large_short(const LayerGeom &g, bool plain_filter, long cus)
 {
     const int nCob = g.Co / 16, group = nCob % 4 == 0 ? 4 : nCob % 2 == 0 ? 2 : 1;
     if (g.kh != 3 || g.kw != 3) return false;
     const long passes = (long)g.N * g.Ho * g.Wo * (nCob / group);
     if (group == 1 && nCob > 1) return passes >= (g.Ci == 32 ? 940 : 1950) * cus;
-    return g.Ci == 32 && g.stride == 1 && passes >= (group == 4 ? 900 : group == 2 ? 1500 : 1950) * cus;
+    if (g.Ci != 32 || g.stride != 1 || (group == 2 && !plain_filter)) return false;
+    return passes >= (group == 4 ? 900 : group == 2 ? 1500 : 1950) * cus;
 }
 
-bool better_in_registers(const LayerGeom &g, const Plan &pl)
+bool better_in_registers(const LayerGeom &g, const Plan &pl, bool plain_filter)
 {
     const int nCib = g.Ci / 16, nCob = g.Co / 16, taps = g.kh * g.kw;
     const long cus = device_cus();
-    if (nCib * taps <= 20) return !large_short(g, cus);
+    if (nCib * taps <= 20) return !large_short(g, plain_filter, cus);
     // workgroups of the fullest compute unit; many are as good as spread evenly
     auto fullest = [&](long wgs) { return wgs < 4 * cus ? (double)((wgs + cus - 1) / cus) : (double)wgs / cus; };
     const Tile &k = kTiles[pl.tile];
@@ -464,7 +466,7 @@ bool conv_u8_tile_eligible(const LayerGeom &g, const QuantParams &q, const int *
 {
     if (((uintptr_t)out & 15u) != 0 || q.amax <= 0 || (!filt_sums && q.zx != 128)) return false;
     const Plan pl = plan_tile(g);
-    return pl.tile >= 0 && !better_in_registers(g, pl);
+    return pl.tile >= 0 && !better_in_registers(g, pl, q.zw == 128);
 }
 
 TileForm conv_u8_tile_form(const LayerGeom &g)
