@@ -1,6 +1,8 @@
-// fp32 convolution on the bf16 matrix cores, each value as the sum of three bf16 ones (conv_split3.hip says which products, at which
-// scale, and with what error; here two more of them where the fp32 instruction is the other choice, see products()): 3x3 windows at stride 1, an even number of input blocks,
-// layers of about half a 256-pixel x 64-channel tile per compute unit or more.
+// fp32 convolution on the bf16 matrix cores, each value as the sum of three bf16 ones: 3x3 windows at stride 1, an even number of input
+// blocks, layers of about half a 256-pixel x 64-channel tile per compute unit or more. conv_split3.hip says which products, at which
+// scale, and with what error; here two more of them where the fp32 instruction is the other choice (products()). A matrix
+// instruction's 32 products are of another 32 channels than there (lane group g holds channels 4g .. 4g + 3 of two blocks, there
+// eight of one), so results differ in the last bits (1.7e-7 of the result, 2-norm); their error is the same.
 //
 // Bound: the matrix cores' power. conv16_split3 spends 3570 cycles of a compute unit on what is 1536 cycles of matrix instructions:
 // its waves own 32 pixels x 64 channels, whose operands take LDS 94 of its 128 bytes a cycle, and its two workgroups meet at two
@@ -14,10 +16,10 @@
 //   third parts, which have one, in the last step, whose own are in registers by then). One barrier a step.
 // The workgroup stays and walks over tiles, so that the pipeline runs on across them. The instructions are pinned where they stand:
 // the accumulators are tied operands of an asm statement, and empty asm statements keep the pieces from being moved together.
-// 1536 cycles of matrix instructions take some 2000 here, and the clock falls from 2.2 to 2.05 GHz: fewer cycles (2300 to 2000 a step)
-// brought nothing any more at the largest layers. us, conv16_split3 / here: 64 channels 56 x 56, 256 images 341 / 286 (207 TFLOP/s of
-// fp32 work), 128 channels 28 x 28, 64 images 95.9 / 84.8, 32 images 50.2 / 42.8; with the fp32 instruction / here: 160 channels
-// 24 x 24, 27 images 62 / 56 (eight products), 192 channels 106 x 14, 10 images 89 / 66.
+// 1536 cycles of matrix instructions take some 2000 here, and the clock falls from 2.2 to 2.05 GHz and less, by the device: fewer cycles
+// (2300 to 2000 a step) brought nothing any more at the largest layers. us, conv16_split3 / here, several devices: 64 channels 56 x 56, 256
+// images 339 to 343 / 305 to 316 (188 to 194 TFLOP/s of fp32 work), 128 channels 28 x 28, 64 images 96 / 79 to 82, 32 images 50 /
+// 40; with the fp32 instruction / here (eight products): 160 channels 24 x 24, 27 images 62 / 56, 192 channels 106 x 14, 10 images 90 / 65.
 #include "small_internal.h"
 
 #include <algorithm>
@@ -38,8 +40,8 @@ struct WideArgs {
     float *out;
     int H, W, HoWo, Wo;
     int Ws, strips, HoWs, M;           // as in conv_u8_tile.hip: columns of a strip, strips per image, pixels of a strip, of all
-    int nCib, nCob, pt, pl, stride;
-    int Hv, Wv, WsS, nCibH, n_chunks, n_cot, n_tiles, epilogue;
+    int nCib, nCob, pt, pl;
+    int Hv, Wv, nCibH, n_chunks, n_cot, n_tiles, epilogue;
     unsigned in_bytes, filt_bytes;
     FastDiv dHoWs, dWs, dWv, dHv, dStrips, dCt;
 };
@@ -86,20 +88,25 @@ __device__ __forceinline__ void wait_states(floatx4 (&u)[4], floatx4 (&v)[4])
     asm volatile("s_nop %8" : "+a"(u[0]), "+a"(u[1]), "+a"(u[2]), "+a"(u[3]), "+a"(v[0]), "+a"(v[1]), "+a"(v[2]), "+a"(v[3]) : "n"(STATES));
 }
 
-template <int WM, int WN, int WVM, int WVN, int ENTRIES, int PRODUCTS>
+// A workgroup's tile is kTM pixels by kNCT output blocks, a wave's part of it WM x WN groups of 16.
+constexpr int WM = 4, WN = 4, kWavesM = 4, kWavesN = 1;
+constexpr int kTM = 16 * WM * kWavesM, kNCT = WN * kWavesN;
+constexpr int kEntries = 384;          // staged input entries of a tile, at most
+
+template <int PRODUCTS>
 __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
 {
-    constexpr int TM = 16 * WM * WVM, NCT = WN * WVN, FI = NCT / 4, R = ENTRIES / 64, EC = ENTRIES + 1;     // (an entry more: planes four banks apart)
-    static_assert(WVM * WVN == 4 && NCT % 4 == 0 && FI == 1 && ENTRIES % 64 == 0 && R == 6, "four waves, a block of the filter each; six parts of a chunk's input");
+    constexpr int R = kEntries / 64, EC = kEntries + 1;        // (an entry more: planes four banks apart)
+    static_assert(kWavesM * kWavesN == 4 && kNCT == 4 && kEntries % 64 == 0 && R == 6, "a block of the filter for each wave; six parts of a chunk's input");
     constexpr int PLANE = EC * 16, PART_B = 4 * PLANE;         // bytes
 
     extern __shared__ uintx4 lds[];
     uintx4 *const A = lds;                                     // two of [block][part][lane]
-    char *const B = reinterpret_cast<char *>(lds + 2 * NCT * 3 * 64);      // [quad][entry]: l; then two times h, m
+    char *const B = reinterpret_cast<char *>(lds + 2 * kNCT * 3 * 64);      // [quad][entry]: l; then two times h, m
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int p = lane & 15, g = lane >> 4;
-    const int wave_m = wave % WVM, wave_n = wave / WVM;
+    const int wave_m = wave % kWavesM, wave_n = wave / kWavesM;
     const int sp = (tid >> 4) & 3, se = (tid & 15) + 16 * (tid >> 6);      // staged: quad sp, entries se + 64 k
     const unsigned plane_bytes = (unsigned)(a.H * a.W) * 64u;
 
@@ -111,12 +118,12 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
     auto aim = [&](int t) __attribute__((always_inline)) {
         ok_aim = t < a.n_tiles;
         t = min(t, a.n_tiles - 1);
-        const int mt = quotient(a.dCt, t), m0 = mt * TM;
-        cob_aim = (t - mt * a.n_cot) * NCT;
+        const int mt = quotient(a.dCt, t), m0 = mt * kTM;
+        cob_aim = (t - mt * a.n_cot) * kNCT;
         const int n0 = quotient(a.dHoWs, m0);
-        vr0_aim = n0 * a.Hv + quotient(a.dWs, m0 - n0 * a.HoWs) * a.stride;
-        const int m1 = min(m0 + TM, a.M) - 1;
-        const int n1 = quotient(a.dHoWs, m1), vr1 = n1 * a.Hv + quotient(a.dWs, m1 - n1 * a.HoWs) * a.stride + 2;
+        vr0_aim = n0 * a.Hv + quotient(a.dWs, m0 - n0 * a.HoWs);
+        const int m1 = min(m0 + kTM, a.M) - 1;
+        const int n1 = quotient(a.dHoWs, m1), vr1 = n1 * a.Hv + quotient(a.dWs, m1 - n1 * a.HoWs) + 2;
         nE_aim = ok_aim ? (vr1 - vr0_aim + 1) * a.Wv : 0;
     };
     // where entry se + 64 k of that tile lies, in ten pieces
@@ -139,7 +146,7 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
         } else if constexpr (piece == 5) {
             p_ix = p_ns - p_n * a.strips;
         } else if constexpr (piece == 6) {
-            p_ix = col[k] + p_ix * a.WsS;
+            p_ix = col[k] + p_ix * a.Ws;
         } else if constexpr (piece == 7) {
             at[k] = (unsigned)(p_n * a.nCibH + p_iy);
         } else if constexpr (piece == 8) {
@@ -170,7 +177,7 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
     uintx4 *const a_write = A + wave * 3 * 64 + lane;
     const uintx4 *const a_read = A + wave_n * WN * 3 * 64 + lane;
     int par = 0;                                               // slot of the chunk's step 0
-    constexpr int SLOT = NCT * 3 * 64;
+    constexpr int SLOT = kNCT * 3 * 64;
     auto f_write = [&](int slot, int s) __attribute__((always_inline)) {
         a_write[slot * SLOT + s * 64] = uintx4{fp[0].part[s], fp[1].part[s], fp[2].part[s], fp[3].part[s]};
     };
@@ -217,12 +224,12 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
 
     const char *base[WM];
     auto rebase = [&]() __attribute__((always_inline)) {
-        const int m0 = quotient(a.dCt, tile) * TM;
+        const int m0 = quotient(a.dCt, tile) * kTM;
 #pragma unroll
         for (int wm = 0; wm < WM; ++wm) {
             const int m = min(m0 + (wave_m * WM + wm) * 16 + p, a.M - 1);
             const int n = quotient(a.dHoWs, m), rem = m - n * a.HoWs, oh = quotient(a.dWs, rem);
-            base[wm] = B + g * PLANE + ((n * a.Hv + oh * a.stride - vr0) * a.Wv + (rem - oh * a.Ws) * a.stride) * 16;
+            base[wm] = B + g * PLANE + ((n * a.Hv + oh - vr0) * a.Wv + (rem - oh * a.Ws)) * 16;
         }
     };
     rebase();
@@ -251,7 +258,7 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
 
     // ---- results of this wave's part of tile t
     auto put = [&](int t, const floatx4 (&v)[WM][WN]) __attribute__((always_inline)) {
-        const int mt = quotient(a.dCt, t), m0 = mt * TM + wave_m * WM * 16, cob_w = (t - mt * a.n_cot) * NCT + wave_n * WN;
+        const int mt = quotient(a.dCt, t), m0 = mt * kTM + wave_m * WM * 16, cob_w = (t - mt * a.n_cot) * kNCT + wave_n * WN;
 #pragma unroll
         for (int wm = 0; wm < WM; ++wm) {
             const int m = m0 + wm * 16 + p;
@@ -293,7 +300,7 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
     aim(t2);
     for (;;) {
         const int cob2 = cob_aim, vr2 = vr0_aim, ok2 = ok_aim;
-            const unsigned lanes2 = f_lanes(cob2, ok2), block2 = f_block(cob2, ch2), chunk2 = 2 * ch2 * plane_bytes;
+        const unsigned lanes2 = f_lanes(cob2, ok2), block2 = f_block(cob2, ch2), chunk2 = 2 * ch2 * plane_bytes;
         int t3 = t2, ch3 = ch2;
         behind(t3, ch3);
 
@@ -400,8 +407,8 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
     // whatever its weight (an infinite one times the zero read there would).
     for (int t = (int)xcd_contiguous(blockIdx.x, gridDim.x), rnd = 0; bad && t < a.n_tiles; t += (int)gridDim.x, ++rnd) {
         if (!(bad >> rnd & 1)) continue;
-        const int steps = a.nCib * kTaps, mt = quotient(a.dCt, t), m0 = mt * TM + wave_m * WM * 16;
-        const int cob_w = (t - mt * a.n_cot) * NCT + wave_n * WN;
+        const int steps = a.nCib * kTaps, mt = quotient(a.dCt, t), m0 = mt * kTM + wave_m * WM * 16;
+        const int cob_w = (t - mt * a.n_cot) * kNCT + wave_n * WN;
         int ih0[WM], iw0[WM], at0[WM];
         floatx4 v[WM][WN];
 #pragma unroll
@@ -409,8 +416,8 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
             const int m = min(m0 + wm * 16 + p, a.M - 1);
             const int ns = quotient(a.dHoWs, m), rem = m - ns * a.HoWs, oh = quotient(a.dWs, rem);
             const int n = quotient(a.dStrips, ns), ow = rem - oh * a.Ws + (ns - n * a.strips) * a.Ws;
-            ih0[wm] = oh * a.stride - a.pt;
-            iw0[wm] = ow * a.stride - a.pl;
+            ih0[wm] = oh - a.pt;
+            iw0[wm] = ow - a.pl;
             at0[wm] = n * a.nCib * a.H * a.W + ih0[wm] * a.W + iw0[wm];
 #pragma unroll
             for (int wn = 0; wn < WN; ++wn) v[wm][wn] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -479,8 +486,6 @@ __global__ void __launch_bounds__(256, 1) conv16_split3_wide(WideArgs a)
     }
 }
 
-constexpr int kWM = 4, kWN = 4, kWVM = 4, kWVN = 1, kEntries = 384;
-constexpr int kTM = 16 * kWM * kWVM, kNCT = kWN * kWVN;
 constexpr size_t kLds = (size_t)2 * kNCT * 3 * 1024 + (size_t)20 * (kEntries + 1) * 16;
 constexpr int kStrip = 16;             // output columns of a strip, at most
 // Tiles that a workgroup walks over, at most: one bit of `bad` for each. A tile that is not finite must be computed again on its own,
@@ -494,7 +499,7 @@ WidePlan plan_wide(const LayerGeom &g)
 {
     WidePlan o;
     o.ok = false;
-    const int nCib = g.Ci / 16, Hv = (g.Ho - 1) * g.stride + 3;
+    const int nCib = g.Ci / 16, Hv = g.Ho + 2;
     if (g.Cib != 16 || g.Cob != 16 || g.kh != 3 || g.kw != 3 || g.stride != 1 || nCib % 2 || (size_t)g.N * g.Ci * g.H * g.W * 4 >= kBeyond ||
         (size_t)g.Co * g.Ci * 36 >= kBeyond)
         return o;
@@ -514,14 +519,14 @@ WidePlan plan_wide(const LayerGeom &g)
 }  // namespace
 
 // Products of the parts that are taken. Where conv_split3.hip is the other choice, six, as there. Layers that the fp32 instruction would
-// compute keep ml and lm too: without them a product is off by up to 1.9 x 2^-24 of it, which shows in filters of one weight, and
-// with them by the 2^-24 of that instruction (one weight, 2-norm: 2.57e-8 / 2.53e-8, fp32 2.53e-8; dense filters 1.3e-7 either way,
-// fp32 4.2e-7). They cost a fifth: 160 channels 24x24, 27 images, 46.8 / 55.6 us, fp32 62.0.
+// compute keep ml and lm too: without them a product is off by up to 1.9 x 2^-24 of it, which shows in filters of one weight, and with
+// them by the 2^-24 of that instruction. 160 channels 24x24, 27 images, six / eight / fp32: one weight, 2-norm 2.60e-8 / 2.53e-8 / 2.53e-8,
+// worst 1.56 / 1.00 / 1.00 x 2^-24; dense filters 2.2e-7 / 2.2e-7 / 6.7e-7. They cost a fifth: 46.8 / 55.6 / 62.3 us.
 static int products(const LayerGeom &g) { return conv_split3_eligible(g) ? 6 : 8; }
 
 const char *conv_split3_wide_kernel_name(const LayerGeom &g)
 {
-    return products(g) == 6 ? "conv16_split3_wide<4,4,4,1,384,6>" : "conv16_split3_wide<4,4,4,1,384,8>";
+    return products(g) == 6 ? "conv16_split3_wide<6>" : "conv16_split3_wide<8>";
 }
 
 // Where it beats the others: times in us of both sides, here by rounds of tiles. With six products (120 random layers, 4 % root mean
@@ -543,7 +548,7 @@ bool conv_split3_wide_eligible(const LayerGeom &g)
 template <int PRODUCTS>
 static hipError_t run_wide(const WideArgs &a, unsigned groups, hipStream_t s)
 {
-    const auto kernel = conv16_split3_wide<kWM, kWN, kWVM, kWVN, kEntries, PRODUCTS>;
+    const auto kernel = conv16_split3_wide<PRODUCTS>;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(256), kLds, s, a);
@@ -559,8 +564,8 @@ hipError_t launch_conv_split3_wide(const float *in, const float *filt, float *ou
     a.in = in; a.filt = filt; a.out = out; a.res = res; a.bn = bn; a.epilogue = epilogue;
     a.H = g.H; a.W = g.W; a.Wo = g.Wo; a.HoWo = g.Ho * g.Wo;
     a.Ws = pl.Ws; a.strips = pl.strips; a.HoWs = g.Ho * pl.Ws; a.M = g.N * pl.strips * a.HoWs;
-    a.nCib = g.Ci / 16; a.nCob = g.Co / 16; a.pt = g.pt; a.pl = g.pl; a.stride = g.stride;
-    a.Hv = (g.Ho - 1) * g.stride + 3; a.Wv = (pl.Ws - 1) * g.stride + 3; a.WsS = pl.Ws * g.stride; a.nCibH = a.nCib * g.H;
+    a.nCib = g.Ci / 16; a.nCob = g.Co / 16; a.pt = g.pt; a.pl = g.pl;
+    a.Hv = g.Ho + 2; a.Wv = pl.Ws + 2; a.nCibH = a.nCib * g.H;
     a.n_chunks = (a.nCib + 1) / 2; a.n_cot = (a.nCob + kNCT - 1) / kNCT; a.n_tiles = (int)pl.tiles;
     a.in_bytes = (unsigned)((size_t)g.N * g.Ci * g.H * g.W * 4); a.filt_bytes = (unsigned)((size_t)g.Co * g.Ci * 36);
     a.dHoWs = make_fastdiv(a.HoWs); a.dWs = make_fastdiv(a.Ws); a.dWv = make_fastdiv(a.Wv); a.dHv = make_fastdiv(a.Hv);

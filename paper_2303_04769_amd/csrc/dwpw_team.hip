@@ -382,7 +382,8 @@ __global__ void __launch_bounds__(kTeamThreads) dwpw_team(TeamArgs args)
                     else plane[m * 4 + q] = v;
                 }
             }
-            // One pixel group, here and in the next block: wave 0 wrote plane and alone reads it. The other set of sums is next, so a wave that runs ahead, past at most one more barrier, writes nothing that is still read.
+            // One pixel group, here and in the next block: wave 0 wrote plane and alone reads it. The other set of sums is next, so
+            // a wave that runs ahead, past at most one more barrier, writes nothing that is still read.
             if (ng > 1 || (b + 1 < n_blocks && d_ng > 1)) __syncthreads();
             else {
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

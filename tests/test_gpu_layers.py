@@ -553,7 +553,7 @@ def test_conv2d_three_part_wide_tiles_scattered_infinities(case):
 
 @pytest.mark.parametrize("kind", sorted(SPARSE_FILTERS))
 def test_conv2d_three_part_wide_tiles_precision(kind):
-    assert S.small_conv2d_kernel(20, 64, 64, 64, 47, 3, 3, 1, (1, 1, 1, 1), 16, 16) == "conv16_split3_wide<4,4,4,1,384,6>"
+    assert S.small_conv2d_kernel(20, 64, 64, 64, 47, 3, 3, 1, (1, 1, 1, 1), 16, 16) == "conv16_split3_wide<6>"
     test_conv2d_three_part_products_precision(kind, 20, 64, 64, 64, 47, 3)
 
 
@@ -572,7 +572,7 @@ EIGHT_PRODUCTS = {  # as SPARSE_FILTERS, where the other choice is the fp32 inst
 @pytest.mark.parametrize("N,Ci,Co,H,W", [(27, 160, 160, 24, 24), (10, 192, 96, 69, 42)])
 def test_conv2d_three_part_wide_tiles_precision_of_fp32(kind, N, Ci, Co, H, W, monkeypatch):
     """Layers that the fp32 instruction would compute otherwise keep its precision, whatever the filter."""
-    assert S.small_conv2d_kernel(N, Ci, Co, H, W, 3, 3, 1, (1, 1, 1, 1), 16, 16) == "conv16_split3_wide<4,4,4,1,384,8>"
+    assert S.small_conv2d_kernel(N, Ci, Co, H, W, 3, 3, 1, (1, 1, 1, 1), 16, 16) == "conv16_split3_wide<8>"
     monkeypatch.setitem(SPARSE_FILTERS, kind, EIGHT_PRODUCTS[kind])
     test_conv2d_three_part_products_precision(kind, N, Ci, Co, H, W, 3)
 

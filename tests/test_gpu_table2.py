@@ -163,7 +163,7 @@ def test_residual_block_with_batch_normalization(N, C, H, W):
     assert_close(got, O.run_network(net, x, ws), C * 9, "the same with image-resident runs forced on")
 
 
-@pytest.mark.parametrize("N,C,H,W,kernel", [(90, 64, 40, 31, "conv16_split3_wide<4,4,4,1,384,6>"), (27, 160, 24, 24, "conv16_split3_wide<4,4,4,1,384,8>")])
+@pytest.mark.parametrize("N,C,H,W,kernel", [(90, 64, 40, 31, "conv16_split3_wide<6>"), (27, 160, 24, 24, "conv16_split3_wide<8>")])
 def test_batch_normalization_behind_wide_tiles(N, C, H, W, kernel):
     """The same block on the kernel whose workgroups walk over tiles; a value whose parts overflow makes some waves compute a tile again,
     with the same epilogue."""
