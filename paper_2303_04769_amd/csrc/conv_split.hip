@@ -6,7 +6,8 @@
 // after the other -- 512 channels on one 6 x 6 image are 16 workgroups of 96 steps on a chip of 256 compute units. Here a
 // wave owns WM x WN tiles of 16 output pixels x 16 output channels and takes a run of reduction steps, a step being one (input
 // block, tap), the WAVES-th part of them. It keeps AHEAD steps of operands in flight in registers (no LDS and no barrier in the
-// loop), and the partial sums meet in LDS at the end, in a fixed order. A tap outside the image is an offset beyond the buffer descriptor, which reads zero.
+// loop), and the partial sums meet in LDS at the end, in a fixed order. A tap outside the image is an offset beyond the buffer
+// descriptor, which reads zero.
 #include "small_internal.h"
 
 namespace small {
@@ -26,8 +27,8 @@ struct SplitArgs {
 template <int WAVES, int WM, int WN, bool TAPS_INSIDE, int AHEAD>
 __global__ void __launch_bounds__(64 * WAVES) conv16_split(SplitArgs a)
 {
-    // CH sums per tile, matrix instruction r into sum r % CH: shorter chains round less often. A wave's run of steps meets the image's
-    // border in whole stretches of zeros (blocks innermost), so the other runs' sums are longer than if the steps were dealt out in turn; error against
+    // CH sums per tile, matrix instruction r into sum r % CH: shorter chains round less often. With blocks innermost a wave's run meets
+    // the image's border in whole stretches of zeros, so the other runs' sums are longer than if the steps were dealt out in turn; error against
     // 64 bits, 512 channels 3x3 6x6 one image / 7x7 four images: steps in turn 2.12e-7 / 4.02e-7, runs 2.21e-7 / 4.15e-7 with two sums
     // / one, 1.65e-7 / 2.97e-7 with four / two (+0.06 us).
     constexpr int T = WM * WN, CH = T == 1 ? 4 : 2;
@@ -55,7 +56,8 @@ __global__ void __launch_bounds__(64 * WAVES) conv16_split(SplitArgs a)
         f_lane[j] = cob0 + j < a.nCob ? (unsigned)((cob0 + j) * a.steps) * 1024u + (unsigned)(q * 64 + p) * 4u : kBeyond;
 
     // This wave's run: from a block to the next only the scalar offsets of the loads change, from a tap to the next the lanes' offsets
-    // too, of which the tap's place in the image is part. Behind the run's end the descriptors have no size (and the scalar offsets are zero, for the hardware takes them off the size): such loads read zero.
+    // too, of which the tap's place in the image is part. Behind the run's end the descriptors have no size (and the scalar offsets are
+    // zero, for the hardware takes them off the size): such loads read zero.
     const int first = wave * a.run, last = min(first + a.run, a.steps);
     floatx4 x[AHEAD][WM];
     float w[AHEAD][WN][4];
@@ -155,7 +157,7 @@ long split_tiles(const LayerGeom &g) { return ((long)g.N * g.Ho * g.Wo + 15) / 1
 
 // Up to about five 16 x 16 tiles per compute unit every tile is a workgroup of its own, split the more ways the longer its
 // reduction and the fewer the workgroups; beyond, waves own more tiles (operands serve two of them) and split less. Sweep
-// over random layers, us: 96 tiles of 288 steps 10.4 / 15.9 / 11.9 with 16 / 8 / 4 waves; 90 tiles of 125 steps 7.8 / 7.2 /
+// over random layers when steps were dealt out in turn, which took 1.2 of the time, us: 96 tiles of 288 steps 10.4 / 15.9 / 11.9 with 16 / 8 / 4 waves; 90 tiles of 125 steps 7.8 / 7.2 /
 // 7.3; 999 tiles of 243 steps 28.1 / 25.9 / 24.7; 3006 tiles of 25 steps 15.6 with <4,1,1>, 11.3 with <4,2,2>; 13128 tiles of
 // 25 steps 44.5, 35.3, and 33.7 with <2,2,2>.
 int pick_variant(const LayerGeom &g)
@@ -216,8 +218,9 @@ bool conv_split_beats_gather(const LayerGeom &g)
     // few / many tiles: 4 steps 0.97 up to one tile a unit, 1.1 to 1.7 beyond (16 -> 32 channels 1x2 48x48 263 images 69 / 26 us,
     // 16 -> 16 1x3 14x14 9633 images 190 / 58); 8 steps 0.78 to 0.96 / 0.93 to 1.24; 9 to 11 steps 0.70 to 1.0 / 1.04 to 1.33;
     // 12 to 15 0.54 to 1.08 / 0.97 to 1.21; from 16 on 0.11 to 1.0, with many tiles 0.7 to 1.1 unless the last round of
-    // steps (2 waves of 4, as the kernel was then; a run is filled up to three steps now, and the line has not been drawn again:
-    // 40 images of 32 channels 40x40, unpadded, stay below it though 18 steps waste nothing) or of output blocks (two a tile) is too empty: 18 steps 0.93 to 1.23.
+    // steps (2 waves of 4, as the kernel was then) or of output blocks (two a tile) is too empty: 18 steps 0.93 to 1.23. (A run is filled
+    // up to three steps now and the kernel takes 0.8 of the time; these lines have not been drawn again: 40 images of 32 channels
+    // 40x40, unpadded, stay with the gather kernel though their 18 steps waste nothing any more.)
     const double most = steps < 4 ? 0 : steps < 8 ? 1 : steps < 9 ? 2.5 : steps < 12 ? (g.Co == 16 ? 8 : 5.5) : 20;
     const long nCob = g.Co / 16, done = (steps + 7) / 8 * 8 * ((nCob + 1) / 2 * 2);
     return tiles <= most * cus || (steps >= 16 && 100 * steps * nCob >= 78 * done);
@@ -228,7 +231,7 @@ bool conv_split_eligible(const LayerGeom &g)
     if (!conv_same_eligible(g)) return conv_split_beats_gather(g);
     if (!conv_split_can(g)) return false;
     const long steps = split_steps(g), tiles = split_tiles(g), cus = device_cus();
-    // Against the tiles of conv_same.hip (their us / here): up to one tile per compute unit from 7 steps on (189 tiles of 7
+    // Against the tiles of conv_same.hip (their us / here, which was 1.2 times as slow then): up to one tile per compute unit from 7 steps on (189 tiles of 7
     // steps 3.9 / 3.1, 96 of 288 36.0 / 10.4; but 51 of 6 3.4 / 3.8), up to two for reductions of 32 (510 of 45 7.7 / 5.0; but 288
     // of 18 4.6 / 4.5), up to four for 200 (999 of 243 45.7 / 24.7; but 912 of 144 19.5 / 21.5); above that they win (2090 of 45 13.3 / 12.8, 4032 of
     // 63 21.3 / 25.5).

@@ -531,7 +531,9 @@ const char *conv_split3_wide_kernel_name(const LayerGeom &g)
 
 // Where it beats the others: times in us of both sides, here by rounds of tiles. With six products (120 random layers, 4 % root mean
 // square): 6.9 a chunk and 2.8 a tile, 1.7 more a chunk when all compute units work, and 6 once, against 2 and the layer's work at
-// 172 TFLOP/s, which the best layers of conv16_split3 reach. With eight (140 random layers, 2.1 %): 8.9, 2.5, 0.7 and 6.2, against 2 and
+// 178 TFLOP/s, which conv16_split3 reaches with one layer in ten. (Near the line this kernel is ahead by some 5 % where both run in turns
+// and no more where each runs for itself, for it draws the clocks down further: 64 channels 56x56, 64 images 94.5 / 88 and 92.9 / 93.5. Of
+// 220 random layers 133 are taken, at 0.82 to 0.97 of the time in turns.) With eight (140 random layers, 2.1 %): 8.9, 2.5, 0.7 and 6.2, against 2 and
 // the work at 125 TFLOP/s, which the best ones on the fp32 instruction reach: of the 140 it takes 37, at 0.87 of their time, and leaves 12
 // that would gain 5 % or more; 60 others that it takes 0.74 to 1.00 of theirs.
 bool conv_split3_wide_eligible(const LayerGeom &g)
@@ -541,7 +543,7 @@ bool conv_split3_wide_eligible(const LayerGeom &g)
     const long cus = device_cus(), rounds = (pl.tiles + cus - 1) / cus;
     const double chunks = g.Ci / 32, fill = pl.tiles < cus ? (double)pl.tiles / cus : 1.0;
     const double mflop = 18e-6 * g.N * g.Ho * g.Wo * (double)g.Ci * g.Co;
-    if (products(g) == 6) return rounds * (6.88 * chunks + 2.75 + 1.73 * fill * chunks) + 5.94 < 2.0 + mflop / 172.0;
+    if (products(g) == 6) return rounds * (6.88 * chunks + 2.75 + 1.73 * fill * chunks) + 5.94 < 2.0 + mflop / 178.0;
     return rounds * (8.93 * chunks + 2.50 + 0.73 * fill * chunks) + 6.22 < 2.0 + mflop / 125.0;
 }
 

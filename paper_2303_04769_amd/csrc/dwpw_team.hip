@@ -7,10 +7,11 @@
 // blocks on their own, the next block's depthwise layer on it, and hands the result to the team. So a block costs one
 // hand-over through memory, one reduction of at most 16 steps and one window pass, a wave per 16 pixels. All sums are those of
 // dwpw_run, in its order: the results are the same bits, however many images there are.
-// The depthwise-separable CNN, one image, without the packing of its input: 64.0 -> 45.8 us, two images 65.3 -> 46.4, the launch in
-// front (2 us) among it. Some 1.3 us a block are the way of a value to memory and back. With the reduction split over the four waves
-// it was 39.8, but sums in another order: after 26 layers two logits near zero can then differ
-// by more than a few 1e-6 of them between an image on its own and in a batch.
+// The depthwise-separable CNN, one image, without the packing of its input: 64.3 -> 42.9 us, two images 64.4 -> 43.8, the launch in
+// front (2 us) among it; the kernel 29. Some 1.3 us a block are the way of a value to memory and back. Whether all values that a wave
+// waits for are there is the maximum of their words: asked one by one, a branch each, it cost 239 spilled scalar registers and 2.4 us.
+// With the reduction split over the four waves it was faster by 6 (at the time), but sums in another order: after 26 layers two logits
+// near zero can then differ by more than a few 1e-6 of them between an image on its own and in a batch.
 // All of a team on one of the chip's eight dies gained nothing (30.1 against 28.9 us for the kernel at the time), nor did waiting
 // before the first look (0.07 to 2.9 us slower): values are looked at past the dies' caches either way. What a wave needs for its
 // next stage besides results -- taps, window entries, the layer's numbers -- it gets ready while it would be waiting (28.9 -> 26.0).

@@ -1313,8 +1313,8 @@ int walk(const small_layer *L, int nL, int N, int C0, int H0, int W0, NetPlan &p
                         const float *rin = ptr(l.src);
                         float *rout = ptr(dr.head ? L[dr.head].dst : (dr.rename ? ldw.dst : lpw.dst));
                         // few images: a team of workgroups for each, where the memory of a slot that the run leaves unwritten
-                        // (and that nobody reads behind it) holds what they exchange; depthwise-separable CNN 64.0 -> 45.8 us
-                        // at one image, 65.3 -> 46.4 at two; from three on (65.7) dwpw_team_exchange says no
+                        // (and that nobody reads behind it) holds what they exchange; depthwise-separable CNN 64.3 -> 42.9 us
+                        // at one image, 64.4 -> 43.8 at two; from three on (64.8) dwpw_team_exchange says no
                         const size_t need = dwpw_team_exchange(dr.block, dr.n, N, dr.head ? L[dr.head].Co : 0, s);
                         char *scratch = nullptr;
                         for (int b = 0; need && !scratch && b < dr.n; ++b) {
